@@ -29,7 +29,7 @@ sys.path.insert(0, ROOT)
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 HBM_PEAK_GBS = 8000.0
 # simulation kernels, in launch order, between the library's measurement boundaries
-SIM_KERNELS = ["k_static", "k_sim<2>", "k_sim<1>", "k_sim<8>", "k_afab", "k_sim_mat<2>"]
+SIM_KERNELS = ["k_sched", "k_sim<2>", "k_sim<1>", "k_sim<8>", "k_afab", "k_sim_mat<2>"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_nemotron-h-like-52L-P8-M64.json")
 
 
@@ -54,21 +54,11 @@ def algorithmic_work(recs, P, M):
     return 2 * E + N, 5 * E + 2 * N
 
 
-def static_class_mask(recs, P, v_max):
-    """Candidates that the library evaluates with a static round schedule: no moves, not AFAB,
-    v = 1, or v = 2 with looped, blocked or V-shape stage pairs (the structure classes)."""
-    pol, v, npert = recs[:, 0], recs[:, 1], recs[:, 2]
-    s_max = P * v_max
-    dev = recs[:, 3 + s_max:3 + 2 * s_max].astype(np.int64)
-    ok = (pol != 0) & (npert == 0)
-    st = ok & (v == 1)
-    if v_max >= 2:
-        i = np.arange(P)
-        lp = (dev[:, i] == dev[:, i + P]).all(axis=1)
-        bl = (dev[:, 2 * i] == dev[:, 2 * i + 1]).all(axis=1)
-        vs = (dev[:, i] == dev[:, 2 * P - 1 - i]).all(axis=1)
-        st |= ok & (v == 2) & (lp | bl | vs)
-    return st
+def scheduled_mask(recs):
+    """Candidates that the library evaluates from precomputed entries (k_sched): no moves, not
+    AFAB (the structure classes' round schedules and the MERGE orders' stage rows together cover
+    every generated queue)."""
+    return (recs[:, 0] != 0) & (recs[:, 2] == 0)
 
 
 def cpu_model():
@@ -484,7 +474,7 @@ def main():
     int64_c, lane_c = algorithmic_work(recs_np, w.P, w.M)
     v, pol = recs_np[:, 1], recs_np[:, 0]
     # candidates each simulation kernel handles (no moves in this workload)
-    stat = static_class_mask(recs_np, w.P, w.v_max)
+    stat = scheduled_mask(recs_np)
     sets = [stat, (v == 2) & (pol != 0) & ~stat, (v == 1) & (pol != 0) & ~stat,
             (v >= 3) & (pol != 0), pol == 0, np.zeros(n, dtype=bool)]
     # the dominant kernel: the one that takes longest

@@ -7,9 +7,12 @@
 //               sentinel of invalid candidates, count candidates per work bin.
 //   k_plan      start position of each bin.
 //   k_scatter   candidate indices grouped by bin (counting sort).
-//   k_sim       persistent waves; each takes a chunk of CPW candidates of one INTER or MERGE
-//               bin and simulates them together, queues generated in registers (the hot
-//               kernel); finish tables with ring rows.
+//   k_sched     persistent waves; each takes a chunk of CPW candidates of one bin and runs them
+//               together from precomputed entries (the hot kernel): the round schedules of the
+//               structure classes, the stage rows of the MERGE orders.
+//   k_sim       the INTER and MERGE candidates that no schedule covers (blocking transfers; a
+//               scratch array too small for the tables): queues generated in registers or read
+//               from queue tables, readiness tested; finish tables with ring rows.
 //   k_afab      AFAB candidates, one lane each: a pass over the stage rows in chain order.
 //   k_sim_mat   candidates with perturbations: queues materialised in global memory, moved,
 //               then simulated.
@@ -22,6 +25,7 @@
 #include <map>
 #include <mutex>
 #include <utility>
+#include <vector>
 
 #include "../../include/octo.h"
 #include "octo_device.hpp"
@@ -42,9 +46,9 @@ constexpr int CTL_WIDE = 171;     // perturbed candidates whose queue window pas
 constexpr int CTL_WORK_WIDE = 172;// chunk counter of k_sim_mat40 over the wide list
 constexpr int CTL_TOTAL = 173;    // valid records (all bins; set by k_plan)
 constexpr int CTL_START = 176;    // [NBINS] first index position of each bin
-constexpr int CTL_WORK_V = 241;   // chunk counters of the v = 3..8 k_sim launches (6), then of
+constexpr int CTL_WORK_V = 256;   // chunk counters of the v = 3..8 k_sim launches (6), then of
                                   // their rendezvous GPipe launches (6)
-constexpr int CTL_WORDS = 256;
+constexpr int CTL_WORDS = 320;
 static_assert(CTL_START + NBINS <= CTL_WORK_V && CTL_WORK_V + 12 <= CTL_WORDS, "control words");
 static_assert(NBINS <= 80, "bin arrays of the control block hold 80 bins");
 // rounds a materialised queue is read ahead of its use (GenMatK; rows of at least 8 entries)
@@ -90,13 +94,17 @@ struct SimArgs {
   int64_t qt_merge[2];     // [split], v = 2, one row per stage pair s0 < s1
   int64_t qt_end;          // the table's final terminators
   int strm_off;            // LDS byte offset of the per-lane stream table
-  // static round schedules (null: every candidate takes the generated-queue kernels): rows of
-  // st_rowlen entries, P + 1 rows per class (one per role, then a row of sc_nop), st_cls
-  // entries apart; smeta [NSC][4] = {valid, rounds, slots, 0}
+  // static round schedules of the structure classes (null: their candidates take the
+  // generated-queue kernels): P + 1 rows per class at sc_offset; smeta [NSC][4] = {valid, rounds,
+  // slots, rounds until every device has started}
   const uint32_t* stab;
   const int32_t* smeta;
-  int64_t st_cls;
-  int st_rowlen;
+  // k_sched over MERGE bins: the stage rows of v = sr_v (null: none), S + 1 rows of sr_rowlen[split]
+  // entries from sr_off[split], of which sr_steps[split] are steps
+  const uint32_t* srow;
+  int sr_v;
+  int64_t sr_off[2];
+  int sr_rowlen[2], sr_steps[2];
 };
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (WAVE - 1)); }
@@ -1147,290 +1155,444 @@ __device__ __forceinline__ uint64_t wave_or(uint64_t x) {
   return x;
 }
 
-// Node id of op (kind, s, m) among the 3 S M ops of a structure.
+// Node id of a forward or backward (kind, s, m) of a structure.
 __device__ __forceinline__ int sc_node(int S, int M, int kind, int s, int m) {
   return (kind * S + s) * M + m;
 }
 
-// LDS bytes of k_static_build for (P, M): node rounds (int16) and slots (uint8) of the largest
-// structure (v = 2, split), then every device's op list (uint32 per op).
-__host__ __device__ inline size_t sc_build_lds(int P, int M) {
-  const size_t nn = (size_t)3 * 2 * P * M;
-  const size_t a = (nn * 2 + 15) / 16 * 16, b = (nn + 15) / 16 * 16;
-  return a + b + (size_t)P * 6 * M * 4;
-}
+// LDS bytes of k_static_build for S stages: a done flag and a slot per forward and backward.
+__host__ __device__ inline size_t sc_build_lds(int S, int M) { return (size_t)4 * S * M; }
 
 // One workgroup (one wave, lane = canonical device) per structure class: run the lockstep rounds
 // of the class's structure once, costs aside — each round every device takes its next op if the
-// op's producer ran in an earlier round — recording the round of each op; give every finish
-// time that another device reads a slot for the rounds it is live (from its producer's round to
-// its reader's: every such value has exactly one reader), lowest free slot first, a slot freed
-// in a round being free for that round's writers (reads precede writes); then write every
-// device's row of round entries. smeta[class] = {valid, rounds, slots used}; a class is invalid
-// (its candidates take the generated-queue kernels) when its rounds pass nr_cap or it needs more
-// than sc_neg(sc_slots(P)) slots. v = 2 classes need P v_max >= 2 P.
+// op's producer ran in an earlier round — noting the op of each round in the device's row; then,
+// in round order, give every finish time that another device reads a slot for the rounds it is
+// live (from its producer's round to its reader's: every such value has exactly one reader),
+// lowest free slot first, a slot freed in a round being free for that round's writers (reads
+// precede writes), and rewrite the row as schedule entries. smeta[class] = {valid, rounds, slots
+// used, rounds until every device has started}; a class is invalid (its candidates take the
+// generated-queue kernels) when its rounds pass the cap or it needs more than
+// sc_neg(sc_slots(P, v)) slots.
 __global__ void __launch_bounds__(WAVE) k_static_build(int P, int M, int v_max,
                                                        const uint32_t* __restrict__ mtab,
                                                        uint32_t* __restrict__ stab,
-                                                       int32_t* __restrict__ smeta,
-                                                       int64_t cls_stride, int rowlen,
-                                                       int nr_cap) {
+                                                       int32_t* __restrict__ smeta) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int cls = blockIdx.x;
   int v, gen, split, pat;
   sc_decode(cls, &v, &gen, &split, &pat);
-  uint32_t* rows = stab + cls * cls_stride;
+  const int rowlen = sc_rowlen(P, M, v), nr_cap = sc_round_cap(P, M, v);
   const int c = lane_id();
-  const int ns = sc_slots(P), neg = sc_neg(ns), dummy = sc_dummy(ns);
+  const int ns = sc_slots(P, v), neg = sc_neg(ns), dummy = sc_dummy(ns);
   const uint32_t nop = sc_nop(ns);
-  if (v > v_max) {
-    for (int i = c; i < (P + 1) * rowlen; i += WAVE) rows[i] = nop;
-    if (c == 0) smeta[4 * cls] = 0, smeta[4 * cls + 1] = 0, smeta[4 * cls + 2] = 0;
+  if (v > v_max || (gen == GEN_INTER && v >= 2 && M % P != 0)) {
+    if (c < 4) smeta[4 * cls + c] = 0;
     return;
   }
+  uint32_t* rows = stab + sc_offset(P, M, cls);
   const int S = P * v, q = (split ? 3 : 2) * v * M;
-  const int nn = 3 * 2 * P * M;
-  int16_t* rnd = reinterpret_cast<int16_t*>(smem);
-  uint8_t* slot = smem + ((size_t)nn * 2 + 15) / 16 * 16;
-  uint32_t* ops = reinterpret_cast<uint32_t*>(slot + ((size_t)nn + 15) / 16 * 16);
-  for (int i = c; i < nn; i += WAVE) rnd[i] = -1, slot[i] = (uint8_t)dummy;
+  const int nn = 2 * S * M;
+  uint8_t* done = smem;
+  uint8_t* slot = smem + nn;
+  for (int i = c; i < nn; i += WAVE) done[i] = 0, slot[i] = (uint8_t)dummy;
   __syncthreads();
   const bool lane = c < P;
-  int st0 = 0, st1 = 0;
-  if (lane) sc_stages(pat, P, c, &st0, &st1);
+  uint32_t* row = rows + (int64_t)(lane ? c : 0) * rowlen;
   GenInter gi;
   GenMerge<2> gm;
   if (gen == GEN_INTER) {
-    gi.init(P, v, M, lane ? st0 : 0, split, split ? (lane ? st0 : 0) : 0);
+    gi.init(P, v, M, lane ? c : 0, split, split ? (lane ? c : 0) : 0);
   } else {
     gm.init(mtab + merge_offset(P, M, 2, split), (split ? 3 : 2) * M, lane ? 2 : 0,
-            [&](int k) { return k == 0 ? st0 : st1; });
+            [&](int k) { return sc_stage(pat, P, c, k); });
   }
-  // pass 1: the lockstep rounds
-  int pos = 0, round = 0;
+  // pass 1: the lockstep rounds; the op of each round as 1 << 31 | kind << 14 | k << 11 | m
+  int pos = 0, round = 0, first = 0;
   for (;;) {
     const int kind = gen == GEN_INTER ? gi.kind : gm.kind;
     const int k = gen == GEN_INTER ? gi.k : gm.k;
     const int m = gen == GEN_INTER ? gi.m : gm.m;
-    const int s = k == 0 ? st0 : st1;
+    const int s = sc_stage(pat, P, c, k);
     const bool has = lane && pos < q;
     int prod = -1;
     if (kind == KF) prod = s > 0 ? sc_node(S, M, KF, s - 1, m) : -1;
     else if (kind == KB) prod = s < S - 1 ? sc_node(S, M, KB, s + 1, m) : sc_node(S, M, KF, s, m);
     else prod = sc_node(S, M, KB, s, m);
-    const bool ready = has && (prod < 0 || rnd[prod] >= 0);
+    const bool ready = has && (prod < 0 || done[prod]);
     if (__ballot(ready) == 0 || round >= nr_cap) break;
     __asm__ volatile("" ::: "memory");
-    if (ready) {
-      rnd[sc_node(S, M, kind, s, m)] = (int16_t)round;
-      ops[c * q + pos] = (uint32_t)round << 16 | (uint32_t)kind << 14 | (uint32_t)k << 11 |
-                         (uint32_t)m;
-      ++pos;
-    }
+    if (ready && kind != KW) done[sc_node(S, M, kind, s, m)] = 1;
+    if (lane)
+      row[round] = ready ? 1u << 31 | (uint32_t)kind << 14 | (uint32_t)k << 11 | (uint32_t)m : 0u;
+    first = __ballot(lane && pos == 0) ? round + 1 : first;
+    pos += ready ? 1 : 0;
     if (gen == GEN_INTER) gi.advance(ready);
     else gm.advance(ready);
     __asm__ volatile("" ::: "memory");
     ++round;
   }
   const int nrounds = round;
-  bool valid = __ballot(lane && pos != q) == 0 && nrounds <= nr_cap;
-  // pass 2: slots of the cross-device finish times, in round order
-  uint64_t freem = (1ull << neg) - 1;  // slots 0 .. neg - 1
-  uint64_t used = 0;
-  int p2 = 0;
-  for (int r = 0; valid && r < nrounds; ++r) {
-    const uint32_t o = lane && p2 < q ? ops[c * q + p2] : 0xFFFFFFFFu;
-    const bool act = lane && p2 < q && (int)(o >> 16) == r;
-    const int kind = (o >> 14) & 3, k = (o >> 11) & 7, m = o & 0x7FF;
-    const int s = k == 0 ? st0 : st1;
-    // the op's input from another device: its one reader is this op, so the slot frees now
-    int pin = -1;
-    if (act && kind == KF && s > 0 && sc_device(pat, P, s - 1) != c) pin = sc_node(S, M, KF, s - 1, m);
-    if (act && kind == KB && s < S - 1 && sc_device(pat, P, s + 1) != c)
-      pin = sc_node(S, M, KB, s + 1, m);
-    freem |= wave_or(pin >= 0 ? 1ull << slot[pin] : 0);
-    // its output to another device needs a slot
-    const bool out = act && ((kind == KF && s < S - 1 && sc_device(pat, P, s + 1) != c) ||
-                             (kind == KB && s > 0 && sc_device(pat, P, s - 1) != c));
-    const uint64_t wm = __ballot(out);
-    if (__popcll(wm) > __popcll(freem)) {
-      valid = false;
-      break;
-    }
-    int sl = dummy;
-    if (out) {
-      uint64_t x = freem;
-      const int rank = __popcll(wm & ((1ull << c) - 1));
-      for (int i = 0; i < rank; ++i) x &= x - 1;
-      sl = __ffsll((unsigned long long)x) - 1;
-      slot[sc_node(S, M, kind, s, m)] = (uint8_t)sl;
-    }
-    const uint64_t took = wave_or(out ? 1ull << sl : 0);
-    freem &= ~took;
-    used |= took;
-    p2 += act ? 1 : 0;
+  bool valid = __ballot(lane && pos != q) == 0;
+  // pass 2: slots of the cross-device finish times, in round order, and the entries
+  uint64_t freem[SC_SLOTS_MAX / 64], used[SC_SLOTS_MAX / 64];
+#pragma unroll
+  for (int i = 0; i < SC_SLOTS_MAX / 64; ++i) {
+    const int n = neg - 64 * i;  // slots 0 .. neg - 1 are free
+    freem[i] = n >= 64 ? ~0ull : n > 0 ? (1ull << n) - 1 : 0;
+    used[i] = 0;
   }
-  __syncthreads();
-  // pass 3: the rows (role c; row P is all nop)
-  for (int i = c; i < rowlen; i += WAVE) rows[(int64_t)P * rowlen + i] = nop;
-  if (lane) {
-    uint32_t* row = rows + (int64_t)c * rowlen;
-    int p3 = 0;
-    for (int r = 0; r < rowlen; ++r) {
-      uint32_t e = nop;
-      const uint32_t o = valid && p3 < q ? ops[c * q + p3] : 0xFFFFFFFFu;
-      if (valid && p3 < q && (int)(o >> 16) == r) {
-        const int kind = (o >> 14) & 3, k = (o >> 11) & 7, m = o & 0x7FF;
-        const int s = k == 0 ? st0 : st1;
-        int rd = neg;
-        if (kind == KF && s > 0 && sc_device(pat, P, s - 1) != c)
-          rd = slot[sc_node(S, M, KF, s - 1, m)];
-        if (kind == KB && s < S - 1 && sc_device(pat, P, s + 1) != c)
-          rd = slot[sc_node(S, M, KB, s + 1, m)];
-        const int wr = kind == KW ? dummy : slot[sc_node(S, M, kind, s, m)];
-        e = sc_entry(rd, kind * v + k, wr);
-        ++p3;
+  for (int r0 = 0; valid && r0 < nrounds; r0 += 8) {
+    uint32_t code[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) code[u] = lane && r0 + u < nrounds ? row[r0 + u] : 0u;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t o = code[u];
+      const bool act = (o >> 31) != 0 && valid;
+      const int kind = (o >> 14) & 3, k = (o >> 11) & 7, m = o & 0x7FF;
+      const int s = sc_stage(pat, P, c, k);
+      // the op's input from another device: its one reader is this op, so the slot frees now
+      int pin = -1;
+      if (act && kind == KF && s > 0 && sc_device(pat, P, s - 1) != c)
+        pin = sc_node(S, M, KF, s - 1, m);
+      if (act && kind == KB && s < S - 1 && sc_device(pat, P, s + 1) != c)
+        pin = sc_node(S, M, KB, s + 1, m);
+      const int rd = pin >= 0 ? slot[pin] : neg;
+      // its output to another device needs a slot
+      const bool out = act && ((kind == KF && s < S - 1 && sc_device(pat, P, s + 1) != c) ||
+                               (kind == KB && s > 0 && sc_device(pat, P, s - 1) != c));
+      const uint64_t wm = __ballot(out);
+      int rank = __popcll(wm & ((1ull << c) - 1)), need = __popcll(wm), sl = dummy;
+#pragma unroll
+      for (int i = 0; i < SC_SLOTS_MAX / 64; ++i) {
+        freem[i] |= wave_or(pin >= 0 && (rd >> 6) == i ? 1ull << (rd & 63) : 0);
+        const int nf = __popcll(freem[i]);
+        uint64_t take = 0;
+        if (out && sl == dummy && rank < nf) {
+          uint64_t x = freem[i];
+          for (int j = 0; j < rank; ++j) x &= x - 1;
+          const int bit = __ffsll((unsigned long long)x) - 1;
+          sl = 64 * i + bit;
+          take = 1ull << bit;
+        }
+        rank -= nf;
+        need -= nf;
+        take = wave_or(take);
+        freem[i] &= ~take;
+        used[i] |= take;
       }
-      row[r] = e;
+      valid = valid && need <= 0;
+      if (out) slot[sc_node(S, M, kind, s, m)] = (uint8_t)sl;
+      __asm__ volatile("" ::: "memory");
+      if (lane && r0 + u < nrounds)
+        row[r0 + u] = act ? sc_entry(rd, k * 4 + kind, kind == KW ? dummy : sl) : nop;
     }
   }
+  if (lane)
+    for (int i = nrounds; i < rowlen; ++i) row[i] = nop;
+  for (int i = c; i < rowlen; i += WAVE) rows[(int64_t)P * rowlen + i] = nop;
   if (c == 0) {
     smeta[4 * cls] = valid ? 1 : 0;
     smeta[4 * cls + 1] = valid ? nrounds : 0;
-    smeta[4 * cls + 2] = __popcll(used);
-    smeta[4 * cls + 3] = 0;
+    smeta[4 * cls + 2] = 0;
+#pragma unroll
+    for (int i = 0; i < SC_SLOTS_MAX / 64; ++i) smeta[4 * cls + 2] += __popcll(used[i]);
+    smeta[4 * cls + 3] = first;
   }
 }
 
-// Static-schedule evaluation: persistent waves take chunks of CPW candidates of one class bin;
-// each lane runs its role's row of the class's schedule with its candidate's costs. Per round:
-// read the slot its op reads and its stream's {input weight, duration}, start = max(device
-// clock, slot + weight), finish = start + duration, write the finish to the slot its op writes.
-// LDS: one 512-byte row per stream ({weight, duration} as two uint32 per lane; stream
-// SC_NOP_STREAM is zero) from offset 0, so that a stream address is (entry & mask) | lane
-// offset; then each group's ns = sc_slots(P) slots (64-bit, 8 ns bytes per group), then the
-// staged records. The groups of a wave run one class, so in a round they read and write the same
-// slot numbers: slot k of group g lives at k ^ (9g mod ns), which spreads the groups' accesses
-// over the LDS banks (without it every group hits the same banks; of the XOR steps 4g, 5g, 7g,
-// 9g and 13g, 9g measured fastest on the P = 8, M = 64 batch, 3 % ahead of 4g). A candidate
-// whose weights or durations pass 32 bits goes to the 64-bit redo list.
+// The stage rows of v in [2, v_max] (octo_device.hpp): block (x, s) writes row s of the table of
+// v = 2 + x / 2, split x & 1 from that stage's row of the MERGE table (row S: all sc_nop).
+struct SrGeom {
+  int64_t off[9][2];            // first entry, by v and split
+  int rowlen[9][2], steps[9][2];  // entries per row; steps (largest ideal start + 1)
+};
+__global__ void k_stage_rows(int P, int M, SrGeom g, const uint32_t* __restrict__ mtab,
+                             uint32_t* __restrict__ out) {
+  const int v = 2 + (int)(blockIdx.x >> 1), split = (int)(blockIdx.x & 1), s = (int)blockIdx.y;
+  const int S = P * v, rowlen = g.rowlen[v][split];
+  if (s > S) return;
+  uint32_t* row = out + g.off[v][split] + (int64_t)s * rowlen;
+  const uint32_t nop = sc_nop(sr_slots(S));
+  for (int i = threadIdx.x; i < rowlen; i += blockDim.x) row[i] = nop;
+  __syncthreads();
+  if (s == S) return;
+  const int n = (split ? 3 : 2) * M;
+  const uint32_t* src = mtab + merge_offset(P, M, v, split) + (int64_t)s * n;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const uint32_t e = src[i];
+    row[e >> 16] = sr_entry(S, s, (int)(e >> 12) & 3, (int)(e & 0x7FF));
+  }
+}
+
+// Scheduled evaluation: persistent waves take chunks of CPW candidates of one bin; each lane runs
+// its device's ops from precomputed entries with its candidate's costs, with no readiness test.
+// NR = 1: the bins of the structure classes, one row per lane (its role's row of the class's
+// round schedule). NR >= 2: the MERGE bins of v <= NR, one stage row per chunk of the lane, its
+// entries of one step taken in stage order. Per entry: read the slot its op reads and its
+// stream's {input weight, duration}, start = max(device clock, slot + weight), finish = start +
+// duration, write the finish to the slot its op writes. What the variants add per entry: XM the
+// activation bytes held and their peak; XB the first op's start (only in the first steps, until
+// every device has started); XC the overlap of communication nodes (their number and time follow
+// from the placement alone); XS the output's transfer queued on its link, whose free time is kept
+// per lane and destination, and the slot then holds the arrival.
+// LDS: rows of 64 stream records (8 bytes {weight, duration}; 16 for XM, XC and XS), four rows per
+// chunk (the fourth, SC_NOP's, is zero), from offset 0, so that a stream's address is a bit field
+// of the entry | lane offset; then each group's slots (64-bit, 8 ns bytes per group); XS: the
+// links' free times; then the staged records. The groups of a wave run one schedule, so in a step
+// they read and write the same slot numbers: slot k of group g lives at k ^ (9g mod ns), which
+// spreads the groups' accesses over the LDS banks (without it every group hits the same banks; of
+// the XOR steps 4g, 5g, 7g, 9g and 13g, 9g measured fastest on the P = 8, M = 64 batch, 3 % ahead
+// of 4g). A candidate whose weights or durations pass 32 bits goes to the 64-bit redo list.
 typedef __attribute__((address_space(3))) int64_t lds_i64;
 typedef __attribute__((address_space(3))) uint64_t lds_u64;
-__global__ void __launch_bounds__(WAVE) k_static(SimArgs a, int sbase, int rbase) {
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+template <int X>
+constexpr int SREC = X == XM || X == XC || X == XS ? 16 : 8;  // bytes of a stream record
+
+template <int X>
+struct SchedLane {
+  int64_t clock;
+  int64_t mem, peak;  // XM
+  int64_t fs;         // XB
+  int64_t tov;        // XC: overlap time, ...
+  int nov;            // ... overlappable nodes,
+  uint32_t pd, pc;    // ... the last op's duration and its output's transfer time
+};
+
+// One entry; sg: group slot base | salt, sb: the lane's stream base (of the entry's chunk).
+template <int X, bool FIRST>
+__device__ __forceinline__ void sched_step(SchedLane<X>& s, uint32_t en, uint32_t sg, uint32_t sb) {
+  constexpr int LG = SREC<X> == 16 ? 10 : 9;
+  const uint32_t ra = (en & 0x7F8u) ^ sg;
+  const uint32_t sa = (((en >> 11) & 31u) << LG) + sb;
+  const uint32_t wa = (en >> 16) ^ sg;
+  const int64_t x = *reinterpret_cast<const lds_i64*>((uintptr_t)ra);
+  uint32_t w, du, e2 = 0, e3 = 0;
+  if constexpr (SREC<X> == 16) {
+    const u32x4 sr = *reinterpret_cast<const lds_u32x4*>((uintptr_t)sa);
+    w = sr.x, du = sr.y, e2 = sr.z, e3 = sr.w;
+  } else {
+    const uint64_t sr = *reinterpret_cast<const lds_u64*>((uintptr_t)sa);
+    w = (uint32_t)sr, du = (uint32_t)(sr >> 32);
+  }
+  if constexpr (X == XS) {  // the record is {link cell, duration, output transfer, 0}
+    const int64_t st = x > s.clock ? x : s.clock;
+    s.clock = st + (int64_t)du;
+    const int64_t lf = *reinterpret_cast<const lds_i64*>((uintptr_t)w);
+    const int64_t arr = (s.clock > lf ? s.clock : lf) + (int64_t)e2;
+    *reinterpret_cast<lds_i64*>((uintptr_t)w) = arr;
+    *reinterpret_cast<lds_i64*>((uintptr_t)wa) = arr;
+    return;
+  }
+  const int64_t tin = x + (int64_t)w;
+  const int64_t st = tin > s.clock ? tin : s.clock;
+  if constexpr (X == XB && FIRST)
+    s.fs = s.fs < 0 && (en & (SC_NOP << 11)) != (SC_NOP << 11) ? st : s.fs;
+  if constexpr (X == XC) {
+    // a receive overlaps the op before the consumer when the transfer [x, tin] and that op
+    // [clock - pd, clock] share a positive length; a send overlaps this op [st, st + du] when the
+    // previous op's output [clock, clock + pc] does (an output that stays has pc = 0)
+    const bool rov = w != 0 && s.pd != 0 && x < s.clock && tin > s.clock - (int64_t)s.pd;
+    const bool sov = du != 0 && st < s.clock + (int64_t)s.pc;
+    s.nov += (rov ? 1 : 0) + (sov ? 1 : 0);
+    const uint32_t ro = s.pd < w ? s.pd : w, so = du < s.pc ? du : s.pc;
+    s.tov += (int64_t)(rov ? ro : 0u) + (int64_t)(sov ? so : 0u);
+    const bool nop = (en & (SC_NOP << 11)) == (SC_NOP << 11);
+    s.pd = nop ? s.pd : du;
+    s.pc = nop ? s.pc : e2;
+  }
+  s.clock = st + (int64_t)du;
+  if constexpr (X == XM) {
+    s.mem += (int64_t)((uint64_t)e2 | (uint64_t)e3 << 32);
+    s.peak = s.mem > s.peak ? s.mem : s.peak;
+  }
+  *reinterpret_cast<lds_i64*>((uintptr_t)wa) = s.clock;
+}
+
+// Steps [b0, b1) (multiples of 4 D) over the lane's NR rows: blocks of four steps, their entries
+// loaded D blocks ahead (a row is L2-resident, so a load takes far longer than one block of
+// steps). q holds the next D blocks on entry and exit; nr <= NR rows are in use.
+template <int NR, int D, int X, bool FIRST>
+__device__ __forceinline__ void sched_run(SchedLane<X>& s, uint4 (&q)[D][NR],
+                                          const uint4* const (&row)[NR], int nr, int b0, int b1,
+                                          uint32_t sg, uint32_t sb) {
+  for (int b = b0; b < b1; b += 4 * D) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int c = 0; c < NR; ++c) {
+          if (NR > 4 && c >= nr) break;
+          const uint32_t en = t == 0 ? q[j][c].x : t == 1 ? q[j][c].y : t == 2 ? q[j][c].z : q[j][c].w;
+          sched_step<X, FIRST>(s, en, sg, sb + (uint32_t)c * (4u * WAVE * SREC<X>));
+        }
+#pragma unroll
+      for (int c = 0; c < NR; ++c) {
+        if (NR > 4 && c >= nr) break;
+        q[j][c] = row[c][(b >> 2) + j + D];
+      }
+    }
+  }
+}
+
+template <int NR, int VC, int X>
+__global__ void __launch_bounds__(WAVE) k_sched(SimArgs a, int sbase, int lbase, int rbase) {
   extern __shared__ __align__(4096) uint8_t st_smem[];
   const int G = a.G, P = a.pr.P, M = a.pr.M;
   const int g = lane_id() / G;
   const int d = lane_id() % G;
   const int gg = g < a.CPW ? g : 0;
   const uint32_t lb = (uint32_t)(uintptr_t)st_smem;  // LDS address of the array (4096-aligned)
-  // group base | salt: slot addresses are (slot * 8) ^ sg
-  const int ns = sc_slots(P);
-  const uint32_t sg = (lb + (uint32_t)sbase + (uint32_t)(gg * ns) * 8u) |
-                      (((uint32_t)gg * 72u) & (uint32_t)(8 * ns - 8));
-  const uint32_t sb = lb + (uint32_t)lane_id() * 8u;
+  const uint32_t sb = lb + (uint32_t)lane_id() * SREC<X>;
+  const uint32_t lcell = lb + (uint32_t)lbase + (uint32_t)lane_id() * 8u;  // XS: link cells
   uint8_t* rec = st_smem + rbase + gg * a.rec_stride;
-  // the class bins' counts, first positions and chunk ranges, one class per lane
+  // the bins' counts, first positions and chunk ranges, one bin per lane
+  constexpr int C0 = NR == 1 && VC > 2 ? NSC2 : 0;  // first class of this launch
+  constexpr int NB = NR > 1 ? 2 : VC > 2 ? NSC - NSC2 : NSC2;
   const int ci = lane_id();
-  const int cnt_i = ci < NSC ? a.ctl[CTL_COUNTS + BIN_STATIC + ci] : 0;
-  const int start_i = ci < NSC ? a.ctl[CTL_START + BIN_STATIC + ci] : 0;
+  const int bin_i = NR == 1 ? BIN_STATIC + C0 + ci : bin_of(a.sr_v, GEN_MERGE, ci == 0 ? 1 : 0);
+  const int cnt_i = ci < NB ? a.ctl[CTL_COUNTS + bin_i] : 0;
+  const int start_i = ci < NB ? a.ctl[CTL_START + bin_i] : 0;
   const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
-  int end_i = nch_i;  // inclusive prefix: chunks of classes 0..ci
+  int end_i = nch_i;  // inclusive prefix: chunks of bins 0..ci
   for (int off = 1; off < 16; off <<= 1) {
     const int y = __shfl_up(end_i, off, WAVE);
     end_i += ci >= off ? y : 0;
   }
   // chunks by grid stride, not by an atomic work counter: thousands of waves taking chunks of
-  // a few hundred rounds would serialise on one counter's atomics. Chunks are in class order,
+  // a few hundred rounds would serialise on one counter's atomics. Chunks are in bin order,
   // so each sweep of the grid hands every wave chunks of about one cost.
   for (int ch = (int)blockIdx.x;; ch += (int)gridDim.x) {
-    // the class whose chunk range holds ch: the number of classes that end at or before it
-    const int cls = __popcll(__ballot(ci < NSC && end_i <= ch));
-    if (cls >= NSC) break;
-    const int cnt = __shfl(cnt_i, cls, WAVE);
-    const int pos0 = __shfl(start_i, cls, WAVE);
-    const int entry0 = (ch - (__shfl(end_i, cls, WAVE) - __shfl(nch_i, cls, WAVE))) * a.CPW;
-    int v, gen, split, pat;
-    sc_decode(cls, &v, &gen, &split, &pat);
+    // the bin whose chunk range holds ch: the number of bins that end at or before it
+    const int ib = __popcll(__ballot(ci < NB && end_i <= ch));
+    if (ib >= NB) break;
+    const int cnt = __shfl(cnt_i, ib, WAVE);
+    const int pos0 = __shfl(start_i, ib, WAVE);
+    const int entry0 = (ch - (__shfl(end_i, ib, WAVE) - __shfl(nch_i, ib, WAVE))) * a.CPW;
+    const int cls = C0 + ib;
+    int v = a.sr_v, gen = GEN_MERGE, split = ib == 0 ? 1 : 0, pat = 0;
+    if constexpr (NR == 1) sc_decode(cls, &v, &gen, &split, &pat);
+    const int ns = NR == 1 ? sc_slots(P, v) : sr_slots(P * v);
+    // group base | salt: slot addresses are (slot * 8) ^ sg
+    const uint32_t sg = (lb + (uint32_t)sbase + (uint32_t)(gg * ns) * 8u) |
+                        (((uint32_t)gg * 72u) & (uint32_t)(8 * ns - 8));
     const int e = entry0 + g;
     const int64_t cand = (g < a.CPW && e < cnt) ? (int64_t)a.idx[pos0 + e] : -1;
     const bool mine = cand >= 0 && d < P;
     if (cand >= 0) stage_record(rec, a.cands + cand * a.pr.stride, a.rec_bytes, d, G);
     __asm__ volatile("" ::: "memory");
-    Chunks<2> c;
-    int64_t busy = 0;
+    Chunks<VC> c;
+    int64_t busy = 0, stat = 0;
     bool fits = true;
-    int role = P;
     if (mine) {
-      busy = setup_chunks<2>(c, a.pr, rec, a.pre, a.link, d, v, split, make_ring(M, M));
-      role = sc_role(pat, c.st[0]);
+      busy = setup_chunks<VC>(c, a.pr, rec, a.pre, a.link, d, v, split, make_ring(M, M),
+                              X == XM ? a.pre_mem : nullptr, &stat, X);
     } else {
-      zero_chunks<2>(c);
+      zero_chunks<VC>(c);
     }
+    CommTally tot;
+    tot.reset();
 #pragma unroll
-    for (int kind = 0; kind < 3; ++kind)
+    for (int k = 0; k < VC; ++k) {
+      if (k >= v) break;
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
+      for (int kind = 0; kind < 4; ++kind) {
         const int64_t w = kind == KF ? c.wF[k] : kind == KB ? c.wB[k] : 0;
-        const int64_t du = kind == KF ? c.dF[k] : kind == KB ? c.dB[k] : c.dW[k];
+        const int64_t du = kind == KF ? c.dF[k] : kind == KB ? c.dB[k] : kind == KW ? c.dW[k] : 0;
+        const int64_t co = kind == KF ? c.cF[k] : kind == KB ? c.cB[k] : 0;
         fits = fits && (uint64_t)w <= 0xFFFFFFFFull && (uint64_t)du <= 0xFFFFFFFFull;
-        if (k < v)
-          *reinterpret_cast<lds_u64*>((uintptr_t)(sb + (uint32_t)(kind * v + k) * 512u)) =
-              ((uint64_t)du << 32) | (uint32_t)w;
+        if constexpr (X == XC || X == XS) fits = fits && (uint64_t)co <= 0xFFFFFFFFull;
+        const uint32_t at = sb + (uint32_t)(k * 4 + kind) * (WAVE * SREC<X>);
+        if constexpr (SREC<X> == 16) {
+          u32x4 r;
+          r.x = (uint32_t)w, r.y = (uint32_t)du, r.z = (uint32_t)co, r.w = 0;
+          if constexpr (X == XM) {
+            const int64_t dm = kind == KF ? c.mA[k] : kind == SC_NOP || (kind == KB && split) ? 0 : -c.mA[k];
+            r.z = (uint32_t)dm, r.w = (uint32_t)((uint64_t)dm >> 32);
+          }
+          if constexpr (X == XS) {
+            // the cell of the output's destination: that of the first stream with the same one;
+            // outputs that stay share a cell that never passes the device clock
+            const int dst = kind == KF ? c.dnF[k] : kind == KB ? c.dnB[k] : -1;
+            int cell = 2 * VC;
+            if (dst >= 0) {
+#pragma unroll
+              for (int j = VC - 1; j >= 0; --j) {
+                cell = c.dnB[j] == dst ? 2 * j + 1 : cell;
+                cell = c.dnF[j] == dst ? 2 * j : cell;
+              }
+            }
+            r.x = lcell + (uint32_t)cell * (WAVE * 8u);
+          }
+          *reinterpret_cast<lds_u32x4*>((uintptr_t)at) = r;
+        } else {
+          *reinterpret_cast<lds_u64*>((uintptr_t)at) = ((uint64_t)du << 32) | (uint32_t)w;
+        }
+        if constexpr (X == XC) {
+          const int cx = kind == KF ? c.xF[k] : kind == KB ? c.xB[k] : 0;
+          tot.n += ((cx & CX_IN) ? M : 0) + ((cx & CX_OUT) ? M : 0);
+          tot.t += (w + co) * M;
+        }
       }
-    *reinterpret_cast<lds_u64*>((uintptr_t)(sb + SC_NOP_STREAM * 512u)) = 0;
+    }
+    if constexpr (X == XS) {
+#pragma unroll
+      for (int j = 0; j <= 2 * VC; ++j)
+        *reinterpret_cast<lds_i64*>((uintptr_t)(lcell + (uint32_t)j * (WAVE * 8u))) = 0;
+    }
     if (d == 0)
       *reinterpret_cast<lds_i64*>((uintptr_t)(((uint32_t)sc_neg(ns) * 8u) ^ sg)) =
           -((int64_t)1 << 62);
     uint64_t gbit, lsb;
     group_bits(G, &gbit, &lsb);
     const bool wide = (fold_groups(__ballot(!fits), G, lsb) & gbit) != 0;
-    if (wide) role = P;
-    const int nrounds = a.smeta[4 * cls + 1];
-    const uint4* rowp = reinterpret_cast<const uint4*>(a.stab + cls * a.st_cls +
-                                                       (int64_t)role * a.st_rowlen);
-    __asm__ volatile("" ::: "memory");
-    int64_t clock = 0;
-    auto step = [&](uint32_t en) {
-      const uint32_t ra = (en & 0x1F8u) ^ sg;
-      const uint32_t sa = (en & 0xE00u) | sb;
-      const uint32_t wa = ((en >> 9) & 0x1F8u) ^ sg;
-      const int64_t x = *reinterpret_cast<const lds_i64*>((uintptr_t)ra);
-      const uint64_t sr = *reinterpret_cast<const lds_u64*>((uintptr_t)sa);
-      const int64_t tin = x + (int64_t)(uint32_t)sr;
-      const int64_t st = tin > clock ? tin : clock;
-      clock = st + (int64_t)(sr >> 32);
-      *reinterpret_cast<lds_i64*>((uintptr_t)wa) = clock;
-    };
-    // blocks of four rounds, their entries loaded four blocks ahead (a row is L2-resident, so a
-    // load takes far longer than one block of rounds); a row ends with four blocks of sc_nop,
-    // so every look-ahead stays in it, and the rounds run in whole groups of four blocks (the
-    // rounds past the class's last are sc_nop)
-    uint4 q0 = rowp[0], q1 = rowp[1], q2 = rowp[2], q3 = rowp[3];
-    auto block = [&](const uint4& q) {
-      step(q.x);
-      step(q.y);
-      step(q.z);
-      step(q.w);
-    };
-    for (int b = 0; b < nrounds; b += 16) {
-      const int i = b >> 2;
-      block(q0);
-      q0 = rowp[i + 4];
-      block(q1);
-      q1 = rowp[i + 5];
-      block(q2);
-      q2 = rowp[i + 6];
-      block(q3);
-      q3 = rowp[i + 7];
+    const bool run = mine && !wide;
+    const uint4* row[NR];
+    int nsteps, nfirst;
+    if constexpr (NR == 1) {
+      nsteps = a.smeta[4 * cls + 1], nfirst = a.smeta[4 * cls + 3];
+      const int role = run ? sc_role(pat, c.st[0]) : P;
+      row[0] = reinterpret_cast<const uint4*>(a.stab + sc_offset(P, M, cls) +
+                                              (int64_t)role * sc_rowlen(P, M, v));
+    } else {
+      nsteps = split ? a.sr_steps[1] : a.sr_steps[0];
+      nfirst = P * v;  // a device's first op is its lowest stage's first forward, at that stage
+#pragma unroll
+      for (int k = 0; k < NR; ++k)
+        row[k] = reinterpret_cast<const uint4*>(
+            a.srow + (split ? a.sr_off[1] : a.sr_off[0]) +
+            (int64_t)(run && k < v ? c.st[k] : P * v) * (split ? a.sr_rowlen[1] : a.sr_rowlen[0]));
     }
-    const int64_t ms = group_max(clock, G);
+    __asm__ volatile("" ::: "memory");
+    SchedLane<X> s;
+    s.clock = 0, s.mem = s.peak = 0, s.fs = -1, s.tov = 0, s.nov = 0, s.pd = s.pc = 0;
+    constexpr int D = NR <= 2 ? 4 : 2;
+    uint4 q[D][NR];
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+#pragma unroll
+      for (int k = 0; k < NR; ++k)
+        if (NR <= 4 || k < v) q[j][k] = row[k][j];
+    int b0 = 0;
+    if constexpr (X == XB) {
+      b0 = (nfirst + 4 * D - 1) / (4 * D) * (4 * D);
+      sched_run<NR, D, X, true>(s, q, row, v, 0, b0, sg, sb);
+    }
+    // whole groups of D blocks: the steps past the last are sc_nop
+    sched_run<NR, D, X, false>(s, q, row, v, b0, nsteps, sg, sb);
+    const int64_t ms = group_max(s.clock, G);
+    if constexpr (X == XC) {
+      tot.nov = s.nov, tot.tov = s.tov;
+      tot = group_tally(tot, G);
+    }
     if (mine) {
       if (wide) {
         if (d == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
       } else {
-        CommTally none;
-        none.reset();
-        put_results<XP>(a, cand, d, false, ms, busy, 0, 0, none);
+        put_results<X>(a, cand, d, false, ms, busy, stat, s.peak, tot, s.fs, s.clock);
       }
     }
     __asm__ volatile("" ::: "memory");
@@ -3794,6 +3956,14 @@ using namespace octo;
 
 namespace {
 
+// The schedules' allocation: the class tables, the metadata, the stage rows (none for a v whose
+// ideal pipeline does not keep two slots per link, sr_ok).
+struct StGeom {
+  size_t meta, rows, bytes;  // byte offsets, total
+  SrGeom sr;
+  bool sr_ok[9];
+};
+
 struct Workspace {
   void* base = nullptr;  // per-call scratch (control words, prefix sums, bins, queues)
   size_t bytes = 0;
@@ -3821,12 +3991,15 @@ struct Workspace {
   // reordered coordination: per-slot finish times, receive lists and programs
   void* ord = nullptr;
   size_t ord_bytes = 0;
-  // static round schedules of the structure classes and their metadata, same cache key as mt;
-  // st_ok: the tables exist (false: k_static_build does not fit this problem)
+  // static round schedules of the structure classes, their metadata and the stage rows, same
+  // cache key as mt
   void* st = nullptr;
   size_t st_bytes = 0;
-  bool st_valid = false, st_ok = false;
+  bool st_valid = false;
   int st_P = 0, st_vmax = 0, st_M = 0;
+  // geometry of the schedules for (sg_P, sg_vmax, sg_M)
+  StGeom sg{};
+  int sg_P = 0, sg_vmax = 0, sg_M = 0;
 };
 
 std::mutex g_mu;
@@ -4041,6 +4214,7 @@ struct Setup {
   int m40_ring;  // its rows per stage
   Plan m40f;     // 40-bit full-row plan of its wide pass (CPW 0: does not fit)
   int m40f_grid;
+  bool sched;    // static schedules and stage rows in use (they fit the scratch)
 };
 
 template <int VC>
@@ -4112,48 +4286,98 @@ TabGeom tab_geom(const octo_problem* p, int lds_max, int v, bool wide) {
   return t;
 }
 
-// Geometry of the static round schedules for a problem: rounds a class may take (a lockstep
-// pass takes about a device's op count plus the pipeline depth; twice the largest op count plus
-// four times the stages is a safe cap, a class past it is marked invalid), entries per row (the
-// cap rounded up to whole groups of sixteen rounds, plus sixteen sc_nop entries for the
-// look-ahead of k_static), and the entries per class (P + 1 rows).
-struct StGeom {
-  int nr_cap, rowlen;
-  int64_t cls;
-  size_t bytes;  // tables, then NSC x 4 int32 of metadata
-};
-StGeom st_geom(const octo_problem* p) {
-  StGeom g;
-  g.nr_cap = 2 * 6 * p->M + 4 * 2 * p->P;
-  g.rowlen = (g.nr_cap + 15) / 16 * 16 + 16;
-  g.cls = (int64_t)(p->P + 1) * g.rowlen;
-  g.bytes = align_up((size_t)NSC * g.cls * 4, 256) + NSC * 16;
-  return g;
+// Steps of the ideal stage pipeline of MERGE (largest ideal start + 1) for S stages, or 0 if some
+// link would need more than two slots: every value of micro-batch m must be consumed in an
+// earlier step than the one that produces micro-batch m + 2 of its link (sr_entry). Longest-path
+// times of the unit-cost pipeline, each stage running the interleaved order at v = 1.
+int stage_steps(int S, int M, int split) {
+  std::vector<int> st((size_t)2 * S * M, -1);  // start of F(s, m), then B(s, m)
+  auto at = [&](int kind, int s, int m) -> int& { return st[((size_t)kind * S + s) * M + m]; };
+  const int durB = split ? 1 : 2, n = (split ? 3 : 2) * M;
+  std::vector<GenInter> g(S);
+  std::vector<int> pos(S, 0), clock(S, 0);
+  for (int s = 0; s < S; ++s) g[s].init(S, 1, M, s, split, split ? s : 0);
+  int steps = 0;
+  for (bool go = true; go;) {
+    go = false;
+    for (int s = 0; s < S; ++s)
+      for (; pos[s] < n; ++pos[s], go = true) {
+        const int kind = g[s].kind, m = g[s].m;
+        int in = 0;  // the producer's end
+        if (kind == KF && s > 0) {
+          if (at(KF, s - 1, m) < 0) break;
+          in = at(KF, s - 1, m) + 1;
+        } else if (kind == KB && s < S - 1) {
+          if (at(KB, s + 1, m) < 0) break;
+          in = at(KB, s + 1, m) + durB;
+        }
+        const int t = std::max(clock[s], in);
+        if (kind != KW) at(kind, s, m) = t;
+        clock[s] = t + (kind == KB ? durB : 1);
+        steps = std::max(steps, t + 1);
+        g[s].advance(true);
+      }
+  }
+  for (int s = 0; s < S; ++s)
+    for (int m = 0; m + 2 < M; ++m) {
+      if (s < S - 1 && at(KF, s + 1, m) >= at(KF, s, m + 2)) return 0;
+      if (s > 0 && at(KB, s - 1, m) >= at(KB, s, m + 2)) return 0;
+    }
+  return steps;
 }
 
-// Build the static round schedules (k_static_build) into the workspace when the problem shape
-// changed or the MERGE tables were rebuilt; needs the MERGE tables (v_max >= 2) in place.
-int build_static(const octo_problem* p, Workspace& ws, int lds_max, hipStream_t stream) {
+// Geometry of the static schedules for a problem (cached in the workspace).
+const StGeom& st_geom(const octo_problem* p, Workspace& ws) {
+  if (ws.sg_P == p->P && ws.sg_vmax == p->v_max && ws.sg_M == p->M) return ws.sg;
+  StGeom g{};
+  const int P = p->P, M = p->M;
+  const int last = p->v_max >= 3 ? NSC2 + 2 * (p->v_max - 2) : NSC2;
+  g.meta = align_up((size_t)sc_offset(P, M, last) * 4, 256);
+  g.rows = g.meta + align_up(NSC * 16, 256);
+  int64_t off = 0;
+  for (int v = 2; v <= p->v_max; ++v) {
+    g.sr_ok[v] = true;
+    for (int split = 0; split <= 1; ++split) {
+      const int n = stage_steps(P * v, M, split);
+      if (n == 0) g.sr_ok[v] = false;
+      g.sr.steps[v][split] = n;
+      // whole groups of sixteen steps (every MERGE op's ideal start is below 3 (M + S)), then
+      // sixteen sc_nop entries for the look-ahead of k_sched
+      g.sr.rowlen[v][split] = (int)align_up(std::max(n, 3 * (M + P * v)), 16) + 16;
+      g.sr.off[v][split] = off;
+      off += (int64_t)(P * v + 1) * g.sr.rowlen[v][split];
+    }
+  }
+  g.bytes = g.rows + align_up((size_t)off * 4, 256);
+  ws.sg = g;
+  ws.sg_P = P, ws.sg_vmax = p->v_max, ws.sg_M = M;
+  return ws.sg;
+}
+
+// Build the class schedules (k_static_build) and the stage rows (k_stage_rows) into the workspace
+// when the problem shape changed or the MERGE tables were rebuilt; needs the MERGE tables
+// (v_max >= 2) in place.
+int build_static(const octo_problem* p, Workspace& ws, hipStream_t stream) {
   if (ws.st_valid && ws.st_P == p->P && ws.st_vmax == p->v_max && ws.st_M == p->M) return OCTO_OK;
   ws.st_valid = false;
-  ws.st_ok = false;
-  const size_t lds = sc_build_lds(p->P, p->M);
-  if (p->M > 2047 || (int)lds > lds_max || p->P > WAVE) {
-    ws.st_valid = true;  // no static schedules for this shape
-    ws.st_P = p->P, ws.st_vmax = p->v_max, ws.st_M = p->M;
-    return OCTO_OK;
-  }
-  const StGeom g = st_geom(p);
+  const size_t lds = sc_build_lds(p->P * p->v_max, p->M);
+  const StGeom& g = st_geom(p, ws);
   const int rc = ensure_buf(ws.st, ws.st_bytes, g.bytes, stream);
   if (rc) return rc;
-  uint32_t* tab = static_cast<uint32_t*>(ws.st);
-  int32_t* meta = reinterpret_cast<int32_t*>(static_cast<char*>(ws.st) + g.bytes - NSC * 16);
+  char* base = static_cast<char*>(ws.st);
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_static_build),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(k_static_build, dim3(NSC), dim3(WAVE), lds, stream, p->P, p->M, p->v_max,
-                     static_cast<const uint32_t*>(ws.mt), tab, meta, g.cls, g.rowlen, g.nr_cap);
+                     static_cast<const uint32_t*>(ws.mt), reinterpret_cast<uint32_t*>(base),
+                     reinterpret_cast<int32_t*>(base + g.meta));
   if (hipGetLastError() != hipSuccess) return OCTO_EHIP;
-  ws.st_valid = ws.st_ok = true;
+  if (p->v_max >= 2) {
+    hipLaunchKernelGGL(k_stage_rows, dim3(2 * (p->v_max - 1), p->P * p->v_max + 1), dim3(WAVE), 0,
+                       stream, p->P, p->M, g.sr, static_cast<const uint32_t*>(ws.mt),
+                       reinterpret_cast<uint32_t*>(base + g.rows));
+    if (hipGetLastError() != hipSuccess) return OCTO_EHIP;
+  }
+  ws.st_valid = true;
   ws.st_P = p->P, ws.st_vmax = p->v_max, ws.st_M = p->M;
   return OCTO_OK;
 }
@@ -4241,12 +4465,17 @@ int scratch_regions(const octo_problem* prob, int dev, int64_t n, Setup* su) {
   const size_t mr = prob->v_max >= 2 ? align_up(merge_rows_bytes(prob), 256) : 0;
   int64_t qi[2][2], qm[2], qe;
   const size_t qt = align_up((size_t)qtab_offsets(prob, qi, qm, &qe) * 4, 256);
-  const size_t stb = align_up(st_geom(prob).bytes, 256);
-  const size_t tables = mt + mr + qt + stb;
   // the per-call part without materialised-queue rows, then the rows that fit after it
   const size_t lists = layout(prob, su->big, n, 0).total;
-  if (tables + lists > cap) return OCTO_ESCRATCH;
   const size_t row_bytes = (size_t)prob->P * su->big.qcap * 2;
+  // the static schedules only where they leave a block of each materialised-queue launch its rows
+  // (without them their candidates take the generated-queue kernels, with the same results)
+  size_t stb = st_geom(prob, ws).bytes;
+  const size_t least = (size_t)std::max({su->big.CPW, su->m40.CPW, su->m40f.CPW, 1}) * row_bytes;
+  su->sched = mt + mr + qt + stb + lists + least <= cap;
+  if (!su->sched) stb = 0;
+  const size_t tables = mt + mr + qt + stb;
+  if (tables + lists > cap) return OCTO_ESCRATCH;
   const int64_t slots = (int64_t)((cap - tables - lists) / row_bytes);
   auto narrow = [&](int& grid, int cpw) -> bool {
     if (cpw < 1 || grid < 1) return true;
@@ -4309,6 +4538,7 @@ int prepare(const octo_problem* prob, const int64_t* costs, const int64_t* mem,
              : occupancy_grid(k_sim_mat40<8, XM>, su->m40f.lds_bytes, su->di.cus, &su->m40f_grid);
     if (rc) return rc;
   }
+  su->sched = true;
   if (noalloc && (rc = scratch_regions(prob, dev, n, su))) return rc;
   su->l = layout(prob, su->big, n,
                  std::max<int64_t>({(int64_t)su->mat_grid * su->big.CPW,
@@ -4407,8 +4637,9 @@ SimArgs make_args(const octo_problem* prob, const Plan& pl, const Setup& su, con
   a.strm_off = pl.strm_off;
   a.stab = nullptr;
   a.smeta = nullptr;
-  a.st_cls = 0;
-  a.st_rowlen = 0;
+  a.srow = nullptr;
+  a.sr_v = 0;
+  for (int i = 0; i < 2; ++i) a.sr_off[i] = 0, a.sr_rowlen[i] = 0, a.sr_steps[i] = 0;
   return a;
 }
 
@@ -4421,23 +4652,38 @@ uint64_t bins_of(int v_lo, int v_hi, bool afab) {
   return m;
 }
 
-// Launch k_static over the class bins: CPW = 64 / G candidates per wave; the eight stream rows
-// (4 KiB), each group's sc_slots(P) slots (256 or 512 B), then the staged records: 6.4 KB per
-// wave at P = 8 (with 64-slot blocks, 8.4 KB and 1.28 instead of 1.13 ms per headline call).
-int launch_static(const SimArgs& base, const Setup& su, int64_t n, hipStream_t stream) {
+// Launch k_sched over the class bins (NR = 1; VC = 2: the classes of v <= 2, 8: those of v >= 3) or
+// over the MERGE bins of v (NR >= 2): CPW = 64 / G candidates per wave; the stream rows, each
+// group's slots, the links' free times (XS), then the staged records: 6.4 KB per wave for the
+// plain class schedules at P = 8 (with 64-slot blocks, 8.4 KB and 1.28 instead of 1.13 ms per
+// call on 1,048,576 candidates).
+template <int NR, int VC, int X>
+int launch_sched(const SimArgs& base, const Setup& su, int64_t n, int v, hipStream_t stream) {
   SimArgs a = base;
   a.G = lanes_per_candidate(a.pr.P);
   a.CPW = WAVE / a.G;
-  const int sbase = 8 * 512;
-  const int rbase = sbase + a.CPW * sc_slots(a.pr.P) * 8;
+  const int ns = NR == 1 ? sc_slots(a.pr.P, VC > 2 ? 3 : 2) : sr_slots(a.pr.P * v);
+  const int sbase = (int)align_up((size_t)4 * (NR > 1 ? v : std::min(a.pr.v_max, VC)) * WAVE * SREC<X>,
+                                  (size_t)8 * ns);
+  const int lbase = sbase + a.CPW * ns * 8;
+  const int rbase = lbase + (X == XS ? (2 * VC + 1) * WAVE * 8 : 0);
   const int lds = rbase + a.CPW * a.rec_stride;
-  if (lds > su.di.lds_max) return OCTO_OK;  // cannot happen for P <= 64; leave to k_sim
+  if (lds > su.di.lds_max) return OCTO_EUNSUPPORTED;  // at most 72 KB within the size limits
+  if (NR > 1) {
+    const StGeom& g = su.ws->sg;
+    a.srow = reinterpret_cast<const uint32_t*>(static_cast<const char*>(su.ws->st) + g.rows);
+    a.sr_v = v;
+    for (int i = 0; i < 2; ++i)
+      a.sr_off[i] = g.sr.off[v][i], a.sr_rowlen[i] = g.sr.rowlen[v][i],
+      a.sr_steps[i] = g.sr.steps[v][i];
+  }
   int grid = 0;
-  int rc = occupancy_grid(k_static, lds, su.di.cus, &grid);
+  int rc = occupancy_grid(k_sched<NR, VC, X>, lds, su.di.cus, &grid);
   if (rc) return rc;
   const int64_t need = (n + a.CPW - 1) / a.CPW;
   grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
-  hipLaunchKernelGGL(k_static, dim3(grid), dim3(WAVE), lds, stream, a, sbase, rbase);
+  hipLaunchKernelGGL((k_sched<NR, VC, X>), dim3(grid), dim3(WAVE), lds, stream, a, sbase, lbase,
+                     rbase);
   return launch_ok();
 }
 
@@ -4655,17 +4901,14 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   a.out_comm = cm;
   a.out_bound = bd;
   a.n_live = ex.n_live;
-  // plain evaluations take the static round schedules for the structure classes
-  if (X == XP) {
-    if ((rc = build_static(prob, *su.ws, su.di.lds_max, stream))) return rc;
-    if (su.ws->st_ok) {
-      const StGeom sg = st_geom(prob);
-      a.stab = static_cast<const uint32_t*>(su.ws->st);
-      a.smeta = reinterpret_cast<const int32_t*>(static_cast<const char*>(su.ws->st) +
-                                                 sg.bytes - NSC * 16);
-      a.st_cls = sg.cls;
-      a.st_rowlen = sg.rowlen;
-    }
+  // the static round schedules for the structure classes, the stage rows for the MERGE orders
+  // (asynchronous transfers only: blocking ones change the order of execution)
+  const bool sched = X != XR && su.sched;
+  if (sched) {
+    if ((rc = build_static(prob, *su.ws, stream))) return rc;
+    const char* st = static_cast<const char*>(su.ws->st);
+    a.stab = reinterpret_cast<const uint32_t*>(st);
+    a.smeta = reinterpret_cast<const int32_t*>(st + su.ws->sg.meta);
   }
   if ((rc = classify_sort(prob, su, a, n, stream))) return rc;
   // generated INTER / MERGE queues, one launch per v with finish tables sized for it (ring
@@ -4676,11 +4919,26 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
     return rc;
   const int P = prob->P, M = prob->M;
   if ((rc = record_mark(0, stream))) return rc;
-  if (a.smeta && (rc = launch_static(a, su, n, stream))) return rc;
+  uint64_t taken = 0;  // MERGE bins that the stage rows cover
+  if constexpr (X != XR) {
+    if (sched) {
+      if ((rc = launch_sched<1, 2, X>(a, su, n, 0, stream))) return rc;
+      if (prob->v_max >= 3 && (rc = launch_sched<1, 8, X>(a, su, n, 0, stream))) return rc;
+      for (int v = 2; v <= prob->v_max; ++v) {
+        if (!su.ws->sg.sr_ok[v]) continue;
+        rc = v == 2   ? launch_sched<2, 2, X>(a, su, n, v, stream)
+             : v == 3 ? launch_sched<3, 3, X>(a, su, n, v, stream)
+             : v == 4 ? launch_sched<4, 4, X>(a, su, n, v, stream)
+                      : launch_sched<8, 8, X>(a, su, n, v, stream);
+        if (rc) return rc;
+        taken |= 1ull << bin_of(v, GEN_MERGE, 0) | 1ull << bin_of(v, GEN_MERGE, 1);
+      }
+    }
+  }
   if ((rc = record_mark(1, stream))) return rc;
   if (prob->v_max >= 2 &&
       (rc = launch_sim<2, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
-                             2 * P, 2 * P, bins_of(2, 2, false), CTL_WORK + 1, stream)))
+                             2 * P, 2 * P, bins_of(2, 2, false) & ~taken, CTL_WORK + 1, stream)))
     return rc;
   if ((rc = record_mark(2, stream))) return rc;
   if ((rc = launch_sim<1, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
@@ -4689,7 +4947,7 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   if ((rc = record_mark(3, stream))) return rc;
   for (int v = 3; v <= prob->v_max; ++v)
     if ((rc = launch_sim<8, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm,
-                               bd, P * v, P * v, bins_of(v, v, false), CTL_WORK_V + v - 3,
+                               bd, P * v, P * v, bins_of(v, v, false) & ~taken, CTL_WORK_V + v - 3,
                                stream)))
       return rc;
   if ((rc = record_mark(4, stream))) return rc;

@@ -23,7 +23,7 @@ constexpr int GEN_AFAB = 0, GEN_INTER = 1, GEN_MERGE = 2, GEN_MAT = 3;
 // backward, then fused).
 constexpr int NBIN_GEN = 40;          // (8 - v) * 5 + rank, v = 1..8
 // candidates of a structure class with a static round schedule: bins BIN_STATIC + class
-constexpr int NSC = 9;
+constexpr int NSC = 21;
 constexpr int BIN_STATIC = 40;
 // candidates with perturbations (queues materialised): bins BIN_MAT + mat_sub(v, split), the
 // last ones, by queue length like the generated bins (large v first, split first)
@@ -169,26 +169,30 @@ __device__ __forceinline__ Resolved resolve_record(const Problem& pr, const uint
 // producers finished in earlier rounds, which depends on the structure — which stages share a
 // device, the generator, a split backward — and never on the costs. These classes recur among
 // candidates, so each has one precomputed schedule: v = 1 (any placement: relabelling devices
-// does not change the structure), and v = 2 with the looped {c, c+P}, blocked {2c, 2c+1} or
-// V-shape {c, 2P-1-c} stage pairs. A device's row is picked by its role, the canonical device
-// that hosts the same stages.
+// does not change the structure), v = 2 with the looped {c, c+P}, blocked {2c, 2c+1} or V-shape
+// {c, 2P-1-c} stage pairs, and the interleaved order (looped) at v = 3..8. A device's row is
+// picked by its role, the canonical device that hosts the same stages. Every other MERGE queue
+// takes the stage rows (below).
 //   class: 0 v1 INTER fused, 1 v1 INTER split, 2 looped INTER fused, 3 looped INTER split,
 //          4 looped MERGE fused, 5 blocked MERGE fused, 6 blocked MERGE split,
-//          7 V-shape MERGE fused, 8 V-shape MERGE split
+//          7 V-shape MERGE fused, 8 V-shape MERGE split,
+//          9 + 2 (v - 3) + split: looped INTER at v = 3..8
 // pattern: 0 one stage per device, 1 looped, 2 blocked, 3 V-shape.
 // ------------------------------------------------------------------------------------------
+constexpr int NSC2 = 9;  // classes of v <= 2; the others are those of v = 3..8
 __host__ __device__ __forceinline__ void sc_decode(int c, int* v, int* gen, int* split, int* pat) {
-  *v = c < 2 ? 1 : 2;
-  *gen = (c < 4) ? GEN_INTER : GEN_MERGE;
-  *split = (c == 1 || c == 3 || c == 6 || c == 8) ? 1 : 0;
-  *pat = c < 2 ? 0 : c < 5 ? 1 : c < 7 ? 2 : 3;
+  *v = c < 2 ? 1 : c < NSC2 ? 2 : 3 + (c - NSC2) / 2;
+  *gen = (c < 4 || c >= NSC2) ? GEN_INTER : GEN_MERGE;
+  *split = c >= NSC2 ? (c - NSC2) & 1 : (c == 1 || c == 3 || c == 6 || c == 8) ? 1 : 0;
+  *pat = c < 2 ? 0 : (c < 5 || c >= NSC2) ? 1 : c < 7 ? 2 : 3;
 }
 
-// Class of a valid record (resolved as r), or -1: its queues are generated per candidate.
+// Class of a valid record (resolved as r), or -1.
 __device__ __forceinline__ int static_class(const Problem& pr, const uint8_t* dev,
                                             const Resolved& r) {
-  if (r.n_pert > 0 || r.gen == GEN_AFAB || r.v > 2) return -1;
+  if (r.n_pert > 0 || r.gen == GEN_AFAB) return -1;
   if (r.v == 1) return r.split ? 1 : 0;
+  if (r.v > 2) return r.gen == GEN_INTER ? NSC2 + 2 * (r.v - 3) + (r.split ? 1 : 0) : -1;
   const int P = pr.P;
   bool lp = true, bl = true, vs = true;
 #pragma unroll 4
@@ -204,36 +208,83 @@ __device__ __forceinline__ int static_class(const Problem& pr, const uint8_t* de
   return -1;
 }
 
-// Canonical device of stage s under a pattern, and the role of a device whose lowest stage
-// is s0.
+// Canonical device of stage s under a pattern, the role of a device whose lowest stage is s0,
+// and stage k of canonical device c.
 __host__ __device__ __forceinline__ int sc_device(int pat, int P, int s) {
   return pat == 0 ? s : pat == 1 ? s % P : pat == 2 ? s / 2 : (s < P ? s : 2 * P - 1 - s);
 }
 __host__ __device__ __forceinline__ int sc_role(int pat, int s0) { return pat == 2 ? s0 / 2 : s0; }
-// Stages of canonical device c (the second is unused at v = 1).
-__host__ __device__ __forceinline__ void sc_stages(int pat, int P, int c, int* s0, int* s1) {
-  *s0 = pat == 2 ? 2 * c : c;
-  *s1 = pat == 1 ? c + P : pat == 2 ? 2 * c + 1 : pat == 3 ? 2 * P - 1 - c : c;
+__host__ __device__ __forceinline__ int sc_stage(int pat, int P, int c, int k) {
+  return pat == 0 ? c : pat == 1 ? c + k * P : pat == 2 ? 2 * c + k : (k == 0 ? c : 2 * P - 1 - c);
 }
 
-// Schedule entry of one device in one round: the slot its op reads (a cross-device producer's
+// Schedule entry of one device in one step: the slot its op reads (a cross-device producer's
 // finish time, else the sentinel slot sc_neg, which holds a time far below zero), the stream of
-// its duration and input weight (kind * v + chunk; SC_NOP_STREAM: zero duration), and the slot
-// it writes (its finish time if another device reads it, else the sink slot sc_dummy). Bits:
-// read slot << 3, stream << 9, write slot << 12, so that address = (entry & mask) | base needs
-// one instruction. A round in which the device runs nothing is sc_nop.
-// Slots per candidate: 32 up to P = 8 (the classes there keep at most 16 values live at M = 64,
-// and the smaller LDS block lets more waves run), else 64; the last two are the sentinel and the
-// sink. A class that needs more is left to the generated-queue kernels.
-constexpr int SC_NOP_STREAM = 7;
-__host__ __device__ __forceinline__ int sc_slots(int P) { return P <= 8 ? 32 : 64; }
+// its duration and input weight (chunk * 4 + kind; kind SC_NOP: zero duration), and the slot it
+// writes (its finish time if another device reads it, else the sink slot sc_dummy). Bits: read
+// slot << 3, stream << 11, write slot << 19, so that the slot addresses are the low byte range
+// and the high half-word as they stand. A step in which the device runs nothing is sc_nop.
+constexpr int SC_NOP = 3;
+constexpr int SC_SLOTS_MAX = 256;
+// Slots per candidate of the class schedules (the last two are the sentinel and the sink): 32
+// up to P = 8 at v <= 2 (those classes keep at most 16 values live at M = 64, and the smaller
+// LDS block lets more waves run), else the next power of two from 4 P, twice that at v >= 3. A
+// class that needs more is left to the generated-queue kernels.
+__host__ __device__ __forceinline__ int sc_slots(int P, int v) {
+  const int n = P <= 8 ? 32 : P <= 16 ? 64 : P <= 32 ? 128 : SC_SLOTS_MAX;
+  return v >= 3 && n < SC_SLOTS_MAX ? 2 * n : n;
+}
+// Rounds a class of v may take (a lockstep pass takes about a device's op count plus the pipeline
+// depth; twice the largest op count plus four times the stages is a safe cap, a class past it is
+// invalid) and the entries of a row: the cap in whole groups of sixteen, then sixteen sc_nop
+// entries for the look-ahead of k_sched. The v <= 2 classes share one geometry.
+__host__ __device__ __forceinline__ int sc_round_cap(int P, int M, int v) {
+  v = v < 2 ? 2 : v;
+  return 2 * 3 * v * M + 4 * P * v;
+}
+__host__ __device__ __forceinline__ int sc_rowlen(int P, int M, int v) {
+  return (sc_round_cap(P, M, v) + 15) / 16 * 16 + 16;
+}
+// First entry of class c's P + 1 rows (one per role, then a row of sc_nop).
+__host__ __device__ __forceinline__ int64_t sc_offset(int P, int M, int c) {
+  int64_t o = (int64_t)(c < NSC2 ? c : NSC2) * (P + 1) * sc_rowlen(P, M, 2);
+  for (int i = NSC2; i < c; ++i) o += (int64_t)(P + 1) * sc_rowlen(P, M, 3 + (i - NSC2) / 2);
+  return o;
+}
 __host__ __device__ __forceinline__ int sc_neg(int ns) { return ns - 2; }
 __host__ __device__ __forceinline__ int sc_dummy(int ns) { return ns - 1; }
 __host__ __device__ __forceinline__ uint32_t sc_entry(int rd, int stream, int wr) {
-  return (uint32_t)rd << 3 | (uint32_t)stream << 9 | (uint32_t)wr << 12;
+  return (uint32_t)rd << 3 | (uint32_t)stream << 11 | (uint32_t)wr << 19;
 }
 __host__ __device__ __forceinline__ uint32_t sc_nop(int ns) {
-  return sc_entry(sc_neg(ns), SC_NOP_STREAM, sc_dummy(ns));
+  return sc_entry(sc_neg(ns), SC_NOP, sc_dummy(ns));
+}
+
+// Stage rows: the MERGE order on any placement. Every op has its ideal start (the unit-cost
+// stage pipeline of the MERGE tables), a device runs its ops by (ideal start, stage), and every
+// edge strictly increases the ideal start. So a candidate can be run in steps t = 0, 1, ...: at
+// step t each device takes the ops of its stages that start at t, lowest stage first, with no
+// readiness test, whatever the placement. One row of entries per stage (entry t: the stage's op
+// of ideal start t, or sc_nop; stream = kind, the chunk is the lane's) serves every placement.
+// The value F(s, m) that stage s + 1 reads lives in slot 2 s + (m mod 2), B(s, m) that stage
+// s - 1 reads in 2 (S - 1) + 2 (s - 1) + (m mod 2): in the ideal pipeline m + 2 of a link is
+// never produced before (or in the step when) m is consumed, which the host checks per shape.
+__host__ __device__ __forceinline__ int sr_slots(int S) {
+  int n = 4;
+  while (n < 4 * (S - 1) + 2) n <<= 1;
+  return n;
+}
+__host__ __device__ __forceinline__ uint32_t sr_entry(int S, int s, int kind, int m) {
+  const int ns = sr_slots(S);
+  int rd = sc_neg(ns), wr = sc_dummy(ns);
+  if (kind == KF) {
+    if (s > 0) rd = 2 * (s - 1) + (m & 1);
+    if (s < S - 1) wr = 2 * s + (m & 1);
+  } else if (kind == KB) {
+    if (s < S - 1) rd = 2 * (S - 1) + 2 * s + (m & 1);
+    if (s > 0) wr = 2 * (S - 1) + 2 * (s - 1) + (m & 1);
+  }
+  return sc_entry(rd, kind, wr);
 }
 
 // ------------------------------------------------------------------------------------------

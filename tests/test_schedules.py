@@ -1,0 +1,120 @@
+"""Stage rows: MERGE orders of any placement run step by step from the ideal starts, with two
+finish slots per link and no readiness test. CPU: the rule itself, emulated in Python, against the
+oracle. GPU: every variant that takes the rows or the class schedules, at the edges of their
+ranges (one micro-batch, one device, odd sizes, every v), against the oracle."""
+import os
+
+import numpy as np
+import pytest
+
+from oracle import octoref as R
+from paper_2509_23722_amd import inputs as I
+
+NTHREADS = min(16, os.cpu_count() or 1)
+
+
+def _starts(S, M, split):
+    """{kind: int64 [S, M]} ideal starts of the unit-cost stage pipeline."""
+    return dict(enumerate(R.merge_tau(S, M, split)))
+
+
+@pytest.mark.parametrize("S", [2, 3, 4, 5, 7, 8, 12, 15, 16, 24, 31, 32, 48, 64])
+@pytest.mark.parametrize("split", [0, 1])
+def test_two_slots_per_link(S, split):
+    for M in (1, 2, 3, 5, 8, 17, S, S + 1, 2 * S + 1, 96):
+        t = _starts(S, M, split)
+        if M > 2:
+            assert (t[0][1:, :-2] < t[0][:-1, 2:]).all(), (S, M)
+            assert (t[1][:-1, :-2] < t[1][1:, 2:]).all(), (S, M)
+        # entries of a row: below the length reserved for it
+        assert max(x.max() for x in t.values()) < 3 * (M + S)
+
+
+def _by_steps(rec, P, v_max, M, costs, link):
+    """The stage-row evaluation of one MERGE record: makespan and busy time per device."""
+    r = I.unpack_record(rec, P, v_max, 0)
+    v, split = r["v"], r["policy"] == 3
+    S, L = P * v, len(costs)
+    b, dev = r["b"] + [L], r["dev"]
+    dur = np.array([costs[b[s]:b[s + 1]].sum(axis=0) for s in range(S)])
+    t = _starts(S, M, int(split))
+    kinds = (0, 1, 2) if split else (0, 1)
+    at = [{} for _ in range(S)]
+    for k in kinds:
+        for s in range(S):
+            for m in range(M):
+                at[s][int(t[k][s, m])] = (k, m)
+    slot, clock, busy = {}, [0] * P, [0] * P
+    chunks = [[s for s in range(S) if dev[s] == d] for d in range(P)]
+    for step in range(max(max(a) for a in at) + 1):
+        for d in range(P):
+            for s in chunks[d]:
+                if step not in at[s]:
+                    continue
+                k, m = at[s][step]
+                p = s - 1 if k == 0 else s + 1
+                arrive = 0
+                if k < 2 and 0 <= p < S:
+                    w = 0 if dev[p] == d else link[dev[p]][d]
+                    arrive = slot[(k, p, m % 2)] + w
+                du = dur[s][k] if split or k == 0 else dur[s][1] + dur[s][2]
+                clock[d] = max(clock[d], arrive) + int(du)
+                busy[d] += int(du)
+                if k < 2:
+                    slot[(k, s, m % 2)] = clock[d]
+    return max(clock), busy
+
+
+@pytest.mark.parametrize("P,v_max,M,L", [(1, 2, 1, 4), (1, 8, 5, 20), (2, 2, 7, 9), (3, 3, 4, 14),
+                                         (5, 2, 11, 23), (4, 4, 9, 40), (2, 7, 6, 30)])
+def test_stage_rows_rule(P, v_max, M, L):
+    rng = np.random.default_rng(100 * P + 10 * v_max + M)
+    costs = rng.integers(0, 3000, size=(L, 3)).astype(np.int64)
+    link = rng.integers(0, 800, size=(P, P)).astype(np.int64)
+    recs = I.random_candidates(rng, L, P, v_max, M, 40, policies=(1, 3))
+    prob = R.problem(L, P, v_max, M, recs.shape[1], 0)
+    ms, bub = R.sim_batch(prob, costs, link, recs, nthreads=NTHREADS)
+    done = 0
+    for rec, x, bb in zip(recs, ms, bub):
+        r = I.unpack_record(rec, P, v_max, 0)
+        looped = all(r["dev"][s] == r["dev"][s % P] for s in range(P * r["v"]))
+        if r["v"] < 2 or x < 0 or (r["policy"] == 3 and looped):  # MERGE orders only
+            continue
+        got, busy = _by_steps(rec, P, v_max, M, costs, link)
+        assert got == x and [got - y for y in busy] == bb.tolist()
+        done += 1
+    assert done > 5 or v_max * P == 2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,v_max,M,L", [
+    (1, 2, 1, 5), (1, 8, 3, 16), (2, 2, 1, 7), (2, 3, 9, 11), (3, 2, 15, 13), (6, 4, 6, 40),
+    (8, 2, 5, 31), (8, 8, 8, 64), (5, 6, 10, 60), (9, 7, 18, 90), (16, 2, 33, 47),
+    (17, 3, 7, 70), (32, 2, 32, 101),
+])
+@pytest.mark.parametrize("call", ["plain", "mem", "comm", "serial", "bounds"])
+def test_every_variant(P, v_max, M, L, call):
+    import torch
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(7000 + 100 * P + 10 * v_max + M)
+    print(f"schedules: {call} P={P} v_max={v_max} M={M} L={L}", flush=True)
+    costs = rng.integers(0, 3_000_000, size=(L, 3)).astype(np.int64)
+    link = rng.integers(0, 900_000, size=(P, P)).astype(np.int64)
+    link[rng.random((P, P)) < 0.2] = 0
+    mem = rng.integers(0, 1 << 40, size=(L, 2)).astype(np.int64)
+    recs = I.random_candidates(rng, L, P, v_max, M, 333, policies=(1, 2, 3), invalid_rate=0.05)
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    gp = _lib.problem(L, P, v_max, M, recs.shape[1], 0)
+    rp = R.problem(L, P, v_max, M, recs.shape[1], 0)
+    if call == "mem":
+        g = _lib.sim_batch_mem(gp, t(costs), t(mem), t(link), t(recs))
+        r = R.sim_batch_mem(rp, costs, mem, link, recs, nthreads=NTHREADS)
+    else:
+        name = "sim_batch" if call == "plain" else "sim_batch_" + call
+        g = getattr(_lib, name)(gp, t(costs), t(link), t(recs))
+        r = getattr(R, name)(rp, costs, link, recs, nthreads=NTHREADS)
+    torch.cuda.synchronize()
+    for x, y in zip(g, r):
+        np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
