@@ -1738,27 +1738,39 @@ __device__ __forceinline__ auto group_table(uint8_t* p, int slots) {
     return Table64{reinterpret_cast<int64_t*>(p)};
 }
 
-// The rounds of one evaluation over a materialised queue row of capacity qcap entries: read QK
-// rounds ahead (GenMatK) when the row holds at least eight entries, else one entry ahead;
-// rendezvous transfers take their own rounds (mbox: their mailboxes).
-template <int VMAX, int X, class Tab>
+// Whether a kernel's rounds are the lean ones (relax_lean): 40-bit slots, no variant that needs
+// more per op. Their candidates' weights and durations have to fit 32 bits (lean_fits).
+template <int X, class Tab>
+constexpr bool LEAN = std::is_same<Tab, Table40>::value && (X == XP || X == XB || X == XT);
+template <int VMAX>
+__device__ __forceinline__ bool lean_fits(const Chunks<VMAX>& c, int G, uint64_t gbit, uint64_t lsb) {
+  return (fold_groups(__ballot(!lstreams_fit<VMAX>(c)), G, lsb) & gbit) == 0;
+}
+
+// The rounds of one evaluation over a materialised queue row of capacity qcap entries (a multiple
+// of eight). strm: LDS for the lean rounds' streams (3 VMAX KB at a.strm_off of the kernel's
+// dynamic LDS; unused with REG). Otherwise read QK rounds ahead (GenMatK); rendezvous transfers
+// take their own rounds (mbox: their mailboxes).
+template <int VMAX, int X, bool REG, class Tab>
 __device__ __forceinline__ void rounds_mat(const uint16_t* row, int qcap, const Chunks<VMAX>& c,
-                                           const Ring& ring, Lane& L, const Tab& T, int G,
-                                           uint64_t gbit, uint64_t lsb, bool& dead,
-                                           int64_t* mbox) {
-  if constexpr (X != XR) {
-    if (qcap >= 8) {
-      GenMatK<QK> q;
-      q.init(row, qcap);
-      describe<VMAX>(L, c, ring, q.kind, q.k, q.m);
-      relax_k<VMAX, X>(q, c, ring, L, T, G, gbit, lsb, dead);
-      return;
-    }
+                                           int v, const Ring& ring, Lane& L, const Tab& T, int G,
+                                           uint64_t gbit, uint64_t lsb, bool& dead, int64_t* mbox,
+                                           uint8_t* strm) {
+  if constexpr (LEAN<X, Tab>) {
+    LStreams<VMAX, REG> S;
+    S.init(c, v, T.lg, T.g, strm);
+    relax_lean<VMAX, X, REG>(row, qcap, S, c, ring, L, T, G, gbit, lsb, dead);
+  } else if constexpr (X != XR) {
+    GenMatK<QK> q;
+    q.init(row, qcap);
+    describe<VMAX>(L, c, ring, q.kind, q.k, q.m);
+    relax_k<VMAX, X>(q, c, ring, L, T, G, gbit, lsb, dead);
+  } else {
+    GenMat q;
+    q.init(row, L.nops);
+    describe<VMAX>(L, c, ring, q.kind, q.k, q.m);
+    rounds<VMAX, true, X>(q, c, ring, L, T, G, gbit, lsb, dead, mbox);
   }
-  GenMat q;
-  q.init(row, L.nops);
-  describe<VMAX>(L, c, ring, q.kind, q.k, q.m);
-  rounds<VMAX, true, X>(q, c, ring, L, T, G, gbit, lsb, dead, mbox);
 }
 
 // Move row[from] so that it ends at index to.
@@ -1860,7 +1872,7 @@ __global__ void __launch_bounds__(WAVE) k_sim_mat(SimArgs a) {
       __asm__ volatile("" ::: "memory");
       if constexpr (X == XR) mbox[lane_id()] = RDV_EMPTY;
       bool dead = false;
-      rounds_mat<VMAX, X>(row, a.qcap, c, ring, L, T, G, gbit, lsb, dead, mbox);
+      rounds_mat<VMAX, X, false>(row, a.qcap, c, v, ring, L, T, G, gbit, lsb, dead, mbox, nullptr);
       const int64_t ms = group_max(L.clock, G);
       CommTally tot = L.cm;
       if constexpr (X == XC) tot = group_tally(L.cm, G);
@@ -1942,12 +1954,14 @@ __global__ void __launch_bounds__(WAVE) k_sim_mat40(SimArgs a, int mode) {
     } else {
       zero_chunks<VMAX>(c);
     }
-    // a candidate whose order does not fit the ring goes to the wide list (full rows)
-    const bool on_ring = group_max((int64_t)wl, G) < ring.R;
+    // a candidate whose order does not fit the ring goes to the wide list (full rows), one whose
+    // costs pass 32 bits to the 64-bit redo list
+    const bool fits = !LEAN<X, Table40> || lean_fits<VMAX>(c, G, gbit, lsb);
+    const bool on_ring = group_max((int64_t)wl, G) < ring.R && fits;
     if (!on_ring) {
       L.nops = 0;
       if (mine && d == 0) {
-        if (mode & 2)
+        if ((mode & 2) || !fits)
           a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
         else
           a.wide[atomicAdd(&a.ctl[CTL_WIDE], 1)] = (int32_t)cand;
@@ -1958,7 +1972,8 @@ __global__ void __launch_bounds__(WAVE) k_sim_mat40(SimArgs a, int mode) {
     __asm__ volatile("" ::: "memory");
     if constexpr (X == XR) mbox[lane_id()] = RDV_EMPTY;
     bool dead = false;
-    rounds_mat<VMAX, X>(row, a.qcap, c, ring, L, T, G, gbit, lsb, dead, mbox);
+    rounds_mat<VMAX, X, VMAX <= 2>(row, a.qcap, c, v, ring, L, T, G, gbit, lsb, dead, mbox,
+                        smem + a.strm_off);
     const int64_t ms = group_max(L.clock, G);
     CommTally tot = L.cm;
     if constexpr (X == XC) tot = group_tally(L.cm, G);
@@ -2415,7 +2430,7 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
 // 25.1 ms on 65,536 candidates of the P = 8, M = 64 batch, a few registers spilled); the
 // reordering variant keeps its registers (at three waves it spills and slows by a third).
 template <int VMAX, bool RING, bool REORDER>
-__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(REORDER ? 1 : 3, 8)))
+__global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(REORDER ? 2 : 3, 8)))
 k_ordered(SimArgs a, OrdBufs ob,
                                                   const int32_t* __restrict__ list,
                                                   const int32_t* __restrict__ list_n,
@@ -2478,7 +2493,8 @@ k_ordered(SimArgs a, OrdBufs ob,
     } else {
       zero_chunks<VMAX>(c);
     }
-    const bool on_ring = !RING || group_max((int64_t)wl, G) < ring.R;
+    const bool fits = !RING || lean_fits<VMAX>(c, G, gbit, lsb);
+    const bool on_ring = (!RING || group_max((int64_t)wl, G) < ring.R) && fits;
     const bool run = valid && on_ring;
     const bool mine = run && d < P;
     if (!mine) L.nops = 0;
@@ -2487,7 +2503,8 @@ k_ordered(SimArgs a, OrdBufs ob,
     // A: the asynchronous schedule, finish times recorded
     bool dead = false;
     {
-      rounds_mat<VMAX, XT>(row, a.qcap, c, ring, L, T, G, gbit, lsb, dead, nullptr);
+      rounds_mat<VMAX, XT, false>(row, a.qcap, c, v, ring, L, T, G, gbit, lsb, dead, nullptr,
+                           smem + a.strm_off);
     }
     __syncthreads();  // every lane's finish times visible to the group
     // B: programs
@@ -2606,7 +2623,7 @@ k_ordered(SimArgs a, OrdBufs ob,
     if (has && valid && (!on_ring || top >= Table40::LIMIT)) {
       // too wide for the ring: the full-row 40-bit pass (when one follows); overflow: 64 bits
       if (d == 0) {
-        if (!on_ring && wide_list)
+        if (!on_ring && wide_list && fits)
           a.wide[atomicAdd(&a.ctl[CTL_WIDE], 1)] = (int32_t)cand;
         else
           a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
@@ -2729,7 +2746,7 @@ __device__ __forceinline__ int next_eligible(const uint16_t* row, int n, int p, 
 // (device, from, to), uint16 each, by the lane of that device.
 template <int VMAX, class Tab>
 __device__ AdvOut advance_w(const Tab& T, uint16_t* row, int n, int qcap, const Chunks<VMAX>& c,
-                            const Ring& ring, int S, int M, int P, bool run, int64_t cap,
+                            int v, const Ring& ring, int S, int M, int P, bool run, int64_t cap,
                             int64_t stat, int max_adv, int G, uint64_t gbit, uint64_t lsb,
                             uint16_t* pert) {
   const int d = lane_id() % G;
@@ -2749,7 +2766,7 @@ __device__ AdvOut advance_w(const Tab& T, uint16_t* row, int n, int qcap, const 
       L.clock = 0, L.pos = 0, L.nops = need && d < P ? n : 0, L.mem = L.peak = 0;
       if (need) T.clear(S * ring.R, d, G);
       __asm__ volatile("" ::: "memory");
-      rounds_mat<VMAX, XP>(row, qcap, c, ring, L, T, G, gbit, lsb, dead, nullptr);
+      rounds_mat<VMAX, XP, false>(row, qcap, c, v, ring, L, T, G, gbit, lsb, dead, nullptr, nullptr);
       ms = group_max(L.clock, G);
       o.top = ms > o.top ? ms : o.top;
     }
@@ -2909,7 +2926,8 @@ __global__ void __launch_bounds__(WAVE) k_advance(SimArgs a, const int64_t* __re
         zero_chunks<VMAX>(c);
         busy = stat = 0;
       }
-      if (RING && r.valid && group_max((int64_t)wl, G) >= ring.R) {
+      const bool fits = group_max(lstreams_fit<VMAX>(c) ? 0 : 1, G) == 0;
+      if (RING && r.valid && (group_max((int64_t)wl, G) >= ring.R || !fits)) {
         if (d == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
         continue;
       }
@@ -2934,7 +2952,8 @@ __global__ void __launch_bounds__(WAVE) k_advance(SimArgs a, const int64_t* __re
       L.clock = 0, L.pos = 0, L.nops = need && d < P ? n : 0, L.mem = L.peak = 0;
       if (need) T.clear(S * ring.R, d, G);
       __asm__ volatile("" ::: "memory");
-      rounds_mat<VMAX, XP>(row, a.qcap, c, ring, L, T, G, gbit, lsb, dead, nullptr);
+      rounds_mat<VMAX, XP, false>(row, a.qcap, c, r.valid ? r.v : 1, ring, L, T, G, gbit, lsb, dead,
+                           nullptr, smem + a.strm_off);
       ms = group_max(L.clock, G);
       o.top = need && ms > o.top ? ms : o.top;
     }
@@ -3213,7 +3232,7 @@ __global__ void __launch_bounds__(WAVE) k_tune(TuneArgs t) {
     bool dead = false, fits = true;
     int64_t ms = 0, held = 0;
     if constexpr (MEM) {
-      const AdvOut o = advance_w<VMAX>(T, qrow, run && d < P ? qlen : 0, a.qcap, c, ring, S, M, P,
+      const AdvOut o = advance_w<VMAX>(T, qrow, run && d < P ? qlen : 0, a.qcap, c, v, ring, S, M, P,
                                        run, d < P ? t.cap[d] : 0, stat, t.max_adv, G, gbit, lsb,
                                        nullptr);
       dead = o.dead, fits = o.fits, ms = o.ms, held = o.hi;
@@ -3222,7 +3241,7 @@ __global__ void __launch_bounds__(WAVE) k_tune(TuneArgs t) {
       L.clock = 0, L.pos = 0, L.nops = run && d < P ? qlen : 0, L.mem = L.peak = 0;
       if (run) T.clear(S * M, d, G);
       __asm__ volatile("" ::: "memory");
-      rounds_mat<VMAX, XP>(qrow, a.qcap, c, ring, L, T, G, gbit, lsb, dead, nullptr);
+      rounds_mat<VMAX, XP, false>(qrow, a.qcap, c, v, ring, L, T, G, gbit, lsb, dead, nullptr, nullptr);
       ms = group_max(L.clock, G);
     }
 
@@ -3382,7 +3401,7 @@ __global__ void __launch_bounds__(WAVE) k_tune_ring(TuneArgs t) {
       zero_chunks<VMAX>(c);
     }
     if (t.step == 0) win = group_max((int64_t)wl, G);
-    const bool fits = win < ring.R;
+    const bool fits = win < ring.R && lean_fits<VMAX>(c, G, gbit, lsb);
     const bool run = eval && fits;
     __asm__ volatile("" ::: "memory");
     T.clear_all(a.slots, lane_id(), WAVE);  // every chain's rows fit a.slots
@@ -3390,7 +3409,8 @@ __global__ void __launch_bounds__(WAVE) k_tune_ring(TuneArgs t) {
     Lane L;
     L.clock = 0, L.pos = 0, L.nops = run && d < P ? qlen : 0, L.mem = L.peak = 0;
     bool dead = false;
-    rounds_mat<VMAX, XP>(row, a.qcap, c, ring, L, T, G, gbit, lsb, dead, nullptr);
+    rounds_mat<VMAX, XP, VMAX <= 2>(row, a.qcap, c, v, ring, L, T, G, gbit, lsb, dead, nullptr,
+                         smem + a.strm_off);
     const int64_t ms = group_max(L.clock, G);
 
     if (!has || skip) continue;
@@ -3800,7 +3820,7 @@ __global__ void __launch_bounds__(WAVE) k_alg1_insert(SimArgs a, A1Args b,
     if (valid) T.clear(S * M, d, G);
     __syncthreads();
     bool dead = false;
-    rounds_mat<VMAX, XT>(row, a.qcap, c, ring, L, T, G, gbit, lsb, dead, nullptr);
+    rounds_mat<VMAX, XT, false>(row, a.qcap, c, v, ring, L, T, G, gbit, lsb, dead, nullptr, nullptr);
     __syncthreads();  // every lane's times visible to the group
     // the searched device's queue, decoded by every lane of the group: (1) per position p, when
     // the op could start (its inputs' arrivals) and, for an insertion before p, the end of
@@ -4072,6 +4092,9 @@ int lanes_per_candidate(int P) {
   return G;
 }
 
+// Streams (in 8-byte units) that the lean rounds keep in LDS: a 16-byte record per kind and chunk.
+int lean_streams(const octo_problem* p) { return 2 * 3 * p->v_max; }
+
 // 40-bit-slot plan for generated queues with up to s_cap stages; the staged record shares the
 // table's memory.
 // s_cap stages of R slots (rounded up to 16, so that both slot arrays are 16-byte aligned and
@@ -4096,6 +4119,7 @@ Plan fast_plan(const octo_problem* p, int lds_max, int s_cap, int R, int streams
 // 40-bit ring plan with one table per group (groups that run their own phases gain nothing from
 // interleaving): s_cap stages of R slots, then the staged record.
 Plan ring_plan(const octo_problem* p, int lds_max, int s_cap, int R) {
+  const int strm = lean_streams(p) * WAVE * 8;
   Plan pl;
   pl.G = lanes_per_candidate(p->P);
   pl.slots = (int)align_up((size_t)s_cap * R, 16);
@@ -4103,9 +4127,9 @@ Plan ring_plan(const octo_problem* p, int lds_max, int s_cap, int R) {
   pl.rec_stride = (int)align_up(pl.rec_bytes, 16);
   pl.table_bytes = pl.slots * 5;
   pl.group_bytes = pl.table_bytes + pl.rec_stride;
-  pl.CPW = std::min(WAVE / pl.G, lds_max / pl.group_bytes);
-  pl.lds_bytes = pl.CPW * pl.group_bytes;
-  pl.strm_off = 0;
+  pl.CPW = std::min(WAVE / pl.G, (lds_max - strm) / pl.group_bytes);
+  pl.strm_off = (int)align_up((size_t)std::max(pl.CPW, 0) * pl.group_bytes, 16);
+  pl.lds_bytes = pl.strm_off + strm;
   pl.qcap = queue_cap(p);
   return pl;
 }
@@ -4522,8 +4546,11 @@ int prepare(const octo_problem* prob, const int64_t* costs, const int64_t* mem,
                         : mat_grid_for<8>(su->big, su->di.cus, &su->mat_grid);
   if (rc) return rc;
   su->m40_ring = make_ring(prob->M, 2 * prob->P * prob->v_max).R;
-  su->m40 = fast_plan(prob, su->di.lds_max, prob->P * prob->v_max, su->m40_ring, 0);
-  su->m40f = fast_plan(prob, su->di.lds_max, prob->P * prob->v_max, prob->M, 0);
+  // (up to two chunks the lean rounds' streams are registers, as in k_tune_ring: with 6 KB of
+  // streams the full rows of P = 16, M = 128, v = 2 leave one wave per CU instead of two)
+  const int streams = prob->v_max > 2 ? lean_streams(prob) : 0;
+  su->m40 = fast_plan(prob, su->di.lds_max, prob->P * prob->v_max, su->m40_ring, streams);
+  su->m40f = fast_plan(prob, su->di.lds_max, prob->P * prob->v_max, prob->M, streams);
   su->m40_grid = su->m40f_grid = 0;
   // the memory variant's grid bounds every variant's (as for k_sim_mat)
   if (su->m40.CPW >= 1) {
@@ -5074,7 +5101,10 @@ int tune_step_impl(const octo_problem* prob, const int64_t* layer_costs, const i
     // rings of the smallest power of two >= P v_max rows, the window of the interleaved orders
     // the chains start from; chains with wider windows (or larger times) go to k_tune
     const Ring rr = make_ring(prob->M, prob->P * prob->v_max);
-    const Plan rp = fast_plan(prob, su.di.lds_max, prob->P * prob->v_max, rr.R, 0);
+    // (up to two chunks the lean rounds' streams are registers: with a stream table in LDS only
+    // three 40 KB waves of the P = 32, M = 256, v = 2 chains would fit a CU instead of four)
+    const Plan rp = fast_plan(prob, su.di.lds_max, prob->P * prob->v_max, rr.R,
+                              prob->v_max > 2 ? lean_streams(prob) : 0);
     if (rr.R < prob->M && rp.CPW >= 1) {
       TuneArgs tr = t;
       tr.s = make_args(prob, rp, su, link, nullptr, 0, nullptr, nullptr);

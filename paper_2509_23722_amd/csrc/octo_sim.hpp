@@ -404,6 +404,247 @@ __device__ __forceinline__ void relax_k(GenMatK<K>& gen, const Chunks<VMAX>& c, 
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// Lean rounds over a materialised queue row: the plain times (XP, also XB's first start and XT's
+// recorded finishes) on 40-bit slots, for candidates whose weights and durations fit 32 bits.
+// Slot value: the low array holds the low 32 bits of the finish, the high byte its next five bits
+// and the state bits above them (B 0x20, F 0x40, parity 0x80), so neither side shifts the time.
+// Each (kind, chunk) stream of the lane is four words (LStream) instead of a dozen 64-bit
+// per-chunk arrays; an op's descriptor is its stream's words plus the micro-batch's slot offset.
+// The next op is decoded while the current op's slot read is in flight and taken if it runs.
+// ------------------------------------------------------------------------------------------
+struct LStream {
+  uint32_t base;    // first read slot | first write slot << 16 (interleaved slot indices)
+  uint32_t w, dur;  // input weight, duration
+  uint32_t fl;      // state bits needed (0xE0) | state bits written << 8, parity included (0:
+                    // writes nothing)
+};
+constexpr uint32_t LS_B = ST_B << 5, LS_F = ST_F << 5, LS_PAR = ST_PAR << 5;
+constexpr uint32_t LS_NEVER = 0x100;  // wanted by a lane past its last op: no slot byte has it
+
+template <int VMAX>
+__device__ __forceinline__ LStream lstream(const Chunks<VMAX>& c, int kind, int k, int lg, int g) {
+  LStream x;
+  const int own = c.base[k], off = kind == KF ? c.frow[k] : kind == KB ? c.brow[k] : 0;
+  x.base = (uint32_t)((own + off) << lg | g) | (uint32_t)(own << lg | g) << 16;
+  x.w = (uint32_t)(kind == KF ? c.wF[k] : kind == KB ? c.wB[k] : 0);
+  x.dur = (uint32_t)(kind == KF ? c.dF[k] : kind == KB ? c.dB[k] : c.dW[k]);
+  const uint32_t need = kind == KF   ? (uint32_t)c.fmask[k] << 5
+                        : kind == KB ? (uint32_t)c.bmask[k] << 5
+                                     : LS_B | LS_PAR;
+  x.fl = need | (kind == KF ? LS_F | LS_PAR : kind == KB ? LS_F | LS_B | LS_PAR : 0u) << 8;
+  return x;
+}
+// Whether every weight and duration of the lane's chunks fits the streams.
+template <int VMAX>
+__device__ __forceinline__ bool lstreams_fit(const Chunks<VMAX>& c) {
+  uint64_t x = 0;
+#pragma unroll
+  for (int k = 0; k < VMAX; ++k)
+    x |= (uint64_t)c.wF[k] | (uint64_t)c.wB[k] | (uint64_t)c.dF[k] | (uint64_t)c.dB[k] |
+         (uint64_t)c.dW[k];
+  return (x >> 32) == 0;
+}
+
+// The lane's streams: in LDS (16-byte records, [3 kinds * chunks][64 lanes] at `lds`), or, up to two
+// chunks and where the finish tables leave no LDS (REG), in registers (a select per word and
+// level: 18 instructions more per round).
+template <int VMAX, bool REG>
+struct LStreams {
+  static_assert(!REG || VMAX <= 2, "register streams hold two chunks");
+  LStream f[REG ? VMAX : 1], b[REG ? VMAX : 1], wg[REG ? VMAX : 1];
+  const uint8_t* rec;
+  int vm;
+  __device__ __forceinline__ void init(const Chunks<VMAX>& c, int v, int lg, int g, uint8_t* lds) {
+    if constexpr (REG) {
+#pragma unroll
+      for (int k = 0; k < VMAX; ++k) {
+        f[k] = lstream<VMAX>(c, KF, k, lg, g);
+        b[k] = lstream<VMAX>(c, KB, k, lg, g);
+        wg[k] = lstream<VMAX>(c, KW, k, lg, g);
+      }
+    } else {
+      uint8_t* p = lds + (threadIdx.x & 63) * 16;
+#pragma unroll
+      for (int kind = 0; kind < 3; ++kind)
+#pragma unroll
+        for (int k = 0; k < VMAX; ++k)
+          if (k < v) {
+            const LStream x = lstream<VMAX>(c, kind, k, lg, g);
+            *reinterpret_cast<uint4*>(p + (kind * v + k) * 1024) =
+                make_uint4(x.base, x.w, x.dur, x.fl);
+          }
+      rec = p, vm = v;
+    }
+  }
+  __device__ __forceinline__ LStream get(uint32_t e) const {
+    if constexpr (REG) {
+      const bool c1 = VMAX > 1 && (e & 0x800u) != 0, isB = (e & 0x4000u) != 0,
+                 isW = (e & 0x8000u) != 0;
+      constexpr int o = VMAX > 1 ? 1 : 0;
+      // (values first, selects after: a select between the members themselves would put the
+      // streams in private memory)
+      const LStream f0 = f[0], f1 = f[o], b0 = b[0], b1 = b[o], w0 = wg[0], w1 = wg[o];
+      auto sel = [&](uint32_t pf0, uint32_t pf1, uint32_t pb0, uint32_t pb1, uint32_t pw0,
+                     uint32_t pw1) {
+        const uint32_t y = c1 ? pf1 : pf0, z = c1 ? pb1 : pb0, w = c1 ? pw1 : pw0;
+        const uint32_t q = isB ? z : y;
+        return isW ? w : q;
+      };
+      LStream x;
+      x.base = sel(f0.base, f1.base, b0.base, b1.base, w0.base, w1.base);
+      x.dur = sel(f0.dur, f1.dur, b0.dur, b1.dur, w0.dur, w1.dur);
+      x.w = sel(f0.w, f1.w, b0.w, b1.w, 0u, 0u);
+      x.fl = sel(f0.fl, f1.fl, b0.fl, b1.fl, LS_B | LS_PAR, LS_B | LS_PAR);
+      return x;
+    } else {
+      // entries past the queue's end may hold anything: stay inside the records
+      int i = (int)(e >> 14) * vm + (int)((e >> 11) & 7);
+      i = i < 3 * vm ? i : 0;
+      const uint4 q = *reinterpret_cast<const uint4*>(rec + i * 1024);
+      return LStream{q.x, q.y, q.z, q.w};
+    }
+  }
+};
+
+// Reads a queue row (16-byte aligned, cap a multiple of eight entries) ahead of its use: three
+// spans of eight entries, the last one in flight while the rounds consume the first two; a window
+// of the next four entries, shifted as they are taken and refilled every four rounds (a lane takes
+// at most one entry a round).
+struct LeanQueue {
+  const uint4* row;
+  int qmax, q, pn;  // last span of the row; span of s0; position after the current entry
+  uint4 s0, s1, s2;
+  uint64_t win;
+  __device__ __forceinline__ void init(const uint16_t* r, int cap) {
+    row = reinterpret_cast<const uint4*>(r);
+    qmax = (cap >> 3) - 1;
+    q = 0, pn = 1;
+    s0 = row[0], s1 = row[qmax < 1 ? qmax : 1], s2 = row[qmax < 2 ? qmax : 2];
+    win = 0;
+  }
+  // every eighth round: the spans move up when the first is used up, and the third is requested
+  __device__ __forceinline__ void spans() {
+    const int nq = pn >> 3;
+    const bool up = nq != q;
+    s0.x = up ? s1.x : s0.x, s0.y = up ? s1.y : s0.y, s0.z = up ? s1.z : s0.z, s0.w = up ? s1.w : s0.w;
+    s1.x = up ? s2.x : s1.x, s1.y = up ? s2.y : s1.y, s1.z = up ? s2.z : s1.z, s1.w = up ? s2.w : s1.w;
+    q = nq;
+    const int n2 = nq + 2;
+    s2 = row[n2 < qmax ? n2 : qmax];
+  }
+  // every fourth round: the window from entry pn on (pn - 8 q <= 11)
+  __device__ __forceinline__ void refill() {
+    const int o = pn - 8 * q;
+    const uint64_t d0 = (uint64_t)s0.x | (uint64_t)s0.y << 32, d1 = (uint64_t)s0.z | (uint64_t)s0.w << 32;
+    const uint64_t d2 = (uint64_t)s1.x | (uint64_t)s1.y << 32, d3 = (uint64_t)s1.z | (uint64_t)s1.w << 32;
+    const uint64_t lo = o < 4 ? d0 : o < 8 ? d1 : d2, hi = o < 4 ? d1 : o < 8 ? d2 : d3;
+    const int sh = (o & 3) * 16;
+    win = lo >> sh | (hi << 1) << (63 - sh);
+  }
+};
+
+// The op a lane is at: its slots, what its input slot's byte must show, the bits it writes (0:
+// none), its weight and duration; XT: its node.
+struct LeanOp {
+  uint32_t rd, wr, mask, want, state, w, dur;
+  int nd;
+};
+
+// Decode entry e of a lane; last: there is no such entry (its reads stay at slot 0).
+template <int VMAX, int X, bool REG>
+__device__ __forceinline__ LeanOp lean_decode(uint32_t e, bool last, const LStreams<VMAX, REG>& S,
+                                              const Ring& ring, int lg, const Lane& L,
+                                              const Chunks<VMAX>& ch) {
+  const uint32_t m = e & 0x7FFu;
+  const LStream st = S.get(e);
+  const uint32_t mr = (m & (uint32_t)ring.mask) << lg;
+  const uint32_t parw = ((m >> ring.lg) & 1u) << 7 | LS_B | LS_F;
+  LeanOp o;
+  o.rd = last ? 0u : (st.base & 0xFFFFu) + mr;
+  o.wr = (st.base >> 16) + mr;
+  o.mask = st.fl;  // (compared with a byte: the bits above do not matter)
+  o.want = last ? LS_NEVER : st.fl & parw;
+  o.state = (st.fl >> 8) & parw;
+  o.w = st.w, o.dur = st.dur;
+  o.nd = 0;
+  if constexpr (X == XT) {
+    const int kind = (int)(e >> 14), k = (int)(e >> 11) & (VMAX <= 2 ? 1 : 7);
+    o.nd = (kind * L.tS + pick<VMAX>(ch.st, k)) * L.tM + (int)m;
+  }
+  return o;
+}
+
+// One round; decodes the entry at the window's low end as the next op. Returns whether the lane
+// ran its op.
+template <int VMAX, int X, bool REG>
+__device__ __forceinline__ bool lean_round(LeanQueue& Q, const LStreams<VMAX, REG>& S,
+                                           const Ring& ring, const Table40& T, LeanOp& c, Lane& L,
+                                           const Chunks<VMAX>& ch) {
+  const uint32_t lo = T.lo[c.rd];
+  const uint32_t hi = T.hi[c.rd];
+  LeanOp n = lean_decode<VMAX, X, REG>((uint32_t)Q.win & 0xFFFFu, Q.pn >= L.nops, S, ring, T.lg, L, ch);
+  __asm__ volatile("" : "+v"(n.rd), "+v"(n.wr), "+v"(n.want), "+v"(n.state));
+  const bool ok = (hi & c.mask) == c.want;
+  unsigned cy, cz;
+  const uint32_t tl = __builtin_addc(lo, c.w, 0u, &cy);
+  const uint32_t th = __builtin_addc(hi & 31u, 0u, cy, &cz);
+  const int64_t tin = (int64_t)((uint64_t)tl | (uint64_t)th << 32);
+  const int64_t beg = tin > L.clock ? tin : L.clock;
+  uint32_t fl = __builtin_addc((uint32_t)beg, c.dur, 0u, &cy);
+  uint32_t fh = __builtin_addc((uint32_t)((uint64_t)beg >> 32), 0u, cy, &cz);
+  // (the finish exists before the branch, so that the branch holds the two writes alone)
+  __asm__ volatile("" : "+v"(fl), "+v"(fh));
+  if (ok && c.state) {
+    T.lo[c.wr] = fl;
+    T.hi[c.wr] = (uint8_t)((fh & 31u) | c.state);
+  }
+  const int64_t fin = (int64_t)((uint64_t)fl | (uint64_t)fh << 32);
+  if constexpr (X == XB) L.fs = (ok && L.fs < 0) ? beg : L.fs;
+  if constexpr (X == XT) {
+    if (ok) {
+      L.tb[c.nd] = fin;
+      if (L.ts) L.ts[c.nd] = beg;
+      if (L.tl) L.tl[c.nd] = L.rnd;
+    }
+    L.rnd += 1;
+    c.nd = ok ? n.nd : c.nd;
+  }
+  L.clock = ok ? fin : L.clock;
+  Q.win >>= ok ? 16 : 0;
+  Q.pn += ok ? 1 : 0;
+  c.rd = ok ? n.rd : c.rd, c.wr = ok ? n.wr : c.wr;
+  c.mask = ok ? n.mask : c.mask, c.want = ok ? n.want : c.want, c.state = ok ? n.state : c.state;
+  c.w = ok ? n.w : c.w, c.dur = ok ? n.dur : c.dur;
+  __asm__ volatile("" ::: "memory");
+  return ok;
+}
+
+// The rounds of one evaluation over a queue row of capacity cap (see relax): unrolled eight
+// times, settled when no lane ran an op in the last of eight rounds (a round after one in which
+// no lane moved changes nothing either).
+template <int VMAX, int X, bool REG>
+__device__ __forceinline__ void relax_lean(const uint16_t* row, int cap,
+                                           const LStreams<VMAX, REG>& S, const Chunks<VMAX>& ch,
+                                           const Ring& ring, Lane& L, const Table40& T, int G,
+                                           uint64_t gbit, uint64_t lsb, bool& dead) {
+  LeanQueue Q;
+  Q.init(row, cap);
+  LeanOp c = lean_decode<VMAX, X, REG>(Q.s0.x & 0xFFFFu, L.nops <= 0, S, ring, T.lg, L, ch);
+  for (;;) {
+    Q.spans();
+    Q.refill();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) lean_round<VMAX, X, REG>(Q, S, ring, T, c, L, ch);
+    Q.refill();
+#pragma unroll
+    for (int u = 0; u < 3; ++u) lean_round<VMAX, X, REG>(Q, S, ring, T, c, L, ch);
+    if (__ballot(lean_round<VMAX, X, REG>(Q, S, ring, T, c, L, ch)) == 0) break;
+  }
+  const uint64_t actm = __ballot(c.want != LS_NEVER);
+  if (actm != 0 && (fold_groups(actm, G, lsb) & gbit)) dead = true;
+}
+
 // Blocking rendezvous transfers (XR). Per op a lane takes up to three steps: receive, when the
 // op's input comes from another device — ready once the producer's slot shows it finished; the
 // transfer runs from max(producer's finish, this device's clock) for the link time, this

@@ -118,3 +118,75 @@ def test_every_variant(P, v_max, M, L, call):
     torch.cuda.synchronize()
     for x, y in zip(g, r):
         np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,v_max,M,L", [
+    (1, 1, 1, 2), (1, 2, 1, 4), (2, 1, 4, 5), (2, 2, 2, 6), (1, 3, 3, 7), (3, 1, 5, 7),
+    (3, 2, 3, 9), (2, 3, 4, 13), (5, 2, 5, 17), (4, 1, 33, 9), (8, 2, 40, 21), (4, 4, 16, 30),
+])
+@pytest.mark.parametrize("call", ["plain", "bounds"])
+def test_moved_queues(P, v_max, M, L, call):
+    """Materialised queues read in spans of eight entries (lengths on and around a multiple of
+    eight, one entry to several windows), short and long moves, cyclic orders, and a share of
+    costs past 32 bits (the 64-bit path)."""
+    import torch
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(9000 + 100 * P + 10 * v_max + M)
+    print(f"moved queues: {call} P={P} v_max={v_max} M={M} L={L}", flush=True)
+    costs = rng.integers(0, 3_000_000, size=(L, 3)).astype(np.int64)
+    costs[0] += int(rng.integers(0, 2)) << 33
+    link = rng.integers(0, 900_000, size=(P, P)).astype(np.int64)
+    recs = I.random_candidates(rng, L, P, v_max, M, 257, max_pert=3, pert_rate=0.9)
+    # half of the moves short ones
+    po = I.pert_offset(P, v_max)
+    mv = recs[:, po:po + 18].copy().view(np.uint16).reshape(-1, 3, 3)
+    near = rng.random(mv.shape[:2]) < 0.5
+    qlen = (np.where(recs[:, 0] == 3, 3, 2) * recs[:, 1].astype(int) * M)[:, None]
+    mv[..., 2] = np.where(near, np.minimum(mv[..., 1] + 1, qlen - 1), mv[..., 2])
+    recs[:, po:po + 18] = mv.reshape(len(recs), 9).view(np.uint8)
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    gp = _lib.problem(L, P, v_max, M, recs.shape[1], 3)
+    rp = R.problem(L, P, v_max, M, recs.shape[1], 3)
+    name = "sim_batch" if call == "plain" else "sim_batch_bounds"
+    g = getattr(_lib, name)(gp, t(costs), t(link), t(recs))
+    r = getattr(R, name)(rp, costs, link, recs, nthreads=NTHREADS)
+    torch.cuda.synchronize()
+    for x, y in zip(g, r):
+        np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,v_max,M,L", [(1, 1, 3, 1), (1, 2, 9, 2), (2, 1, 8, 2), (4, 2, 24, 8),
+                                         (4, 2, 24, 9), (8, 1, 33, 11)])
+def test_tuner_skips(P, v_max, M, L):
+    """Chains whose moves mostly change nothing: one stage, as many layers as stages (every
+    boundary move is invalid), two devices, invalid states."""
+    import torch
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(300 + 10 * P + L)
+    print(f"tuner skips: P={P} v_max={v_max} M={M} L={L}", flush=True)
+    costs = rng.integers(1, 3000, size=(L, 3)).astype(np.int64)
+    link = rng.integers(0, 900, size=(P, P)).astype(np.int64)
+    n = 70
+    recs = I.random_candidates(rng, L, P, v_max, M, n, invalid_rate=0.1)
+    gp = _lib.problem(L, P, v_max, M, recs.shape[1], 0)
+    rp = R.problem(L, P, v_max, M, recs.shape[1], 0)
+    chains = np.zeros((n, _lib.chain_stride(gp)), np.uint8)
+    chains[:, :recs.shape[1]] = recs
+    c = torch.from_numpy(chains).cuda()
+    q = torch.zeros((n, P, _lib.queue_capacity(gp)), dtype=torch.int16, device="cuda")
+    cd, ld = torch.from_numpy(costs).cuda(), torch.from_numpy(link).cuda()
+    for step in range(25):
+        _lib.tune_step(gp, cd, ld, c, q, 77, step)
+    torch.cuda.synchronize()
+    ms, acc, bub = (x.numpy() for x in _lib.chain_state(c, gp))
+    r = R.tune(rp, costs, link, recs, 77, 24, nthreads=NTHREADS)
+    np.testing.assert_array_equal(c.cpu().numpy()[:, :recs.shape[1]], r[0])
+    np.testing.assert_array_equal(ms, r[1])
+    np.testing.assert_array_equal(bub, r[2])
+    np.testing.assert_array_equal(acc, r[3])
