@@ -3280,26 +3280,43 @@ __global__ void __launch_bounds__(WAVE) k_tune(TuneArgs t) {
   }
 }
 
-// Chains by queue length, for the ring pass: class (v - 1) * 2 + split from each chain's record
-// header (records whose header is out of range take class 2 * v_max, last); counts into the bin
-// counters, offsets by k_plan, then the chain indices scattered by class.
+// Chains by the length of the step's evaluation, for the ring pass (longest first; the groups of a
+// wave run in lockstep): by v and split from the chain's record header, the chains whose move
+// exchanges two devices' stages after the others (with each device keeping its queue, most of those
+// deadlock within a few rounds: all of 252 on 24 chains of the P = 32, M = 256 workload), and
+// headers out of range last. Chains that this step leaves as they are — an invalid state, a
+// boundary move that empties a stage (68 % of the boundary moves there) — have no class (-1).
+// Counts into the bin counters, offsets by k_plan, then the chain indices scattered by class.
+constexpr int NCLASS = 2 * 2 * 8 + 1;
 __device__ __forceinline__ int chain_class(const TuneArgs& t, int64_t i) {
   const uint8_t* r = t.chains + i * t.chain_stride;
-  const int pol = r[0], v = r[1];
-  return (v >= 1 && v <= t.s.pr.v_max && pol <= POL_ZB) ? (v - 1) * 2 + (pol == POL_ZB)
-                                                          : 2 * t.s.pr.v_max;
+  const int pol = r[0], v = r[1], P = t.s.pr.P, S = P * v;
+  const bool head = v >= 1 && v <= t.s.pr.v_max && pol <= POL_ZB;
+  if (t.step == 0) return head ? mat_sub(v, pol == POL_ZB) : NCLASS - 1;
+  const int64_t cur = *reinterpret_cast<const int64_t*>(r + t.s.pr.stride);
+  if (!head || cur == OCTO_MS_INVALID) return -1;
+  const U4 u = philox4x64_10((uint64_t)i, (uint64_t)t.step, 0, 0, t.seed, 0);
+  const int kind = (int)(u.x[0] % 3);
+  if (kind == 0) {  // as propose()
+    if (S < 2) return -1;
+    const int mi = 1 + (int)(u.x[1] % (uint64_t)(S - 1));
+    const int lo = mi > 1 ? r[4 + mi - 2] : 0;
+    const int hi = mi < S - 1 ? r[4 + mi] : t.s.pr.L;
+    const int nb = r[4 + mi - 1] + ((u.x[2] & 1) ? 1 : -1);
+    if (!(nb > lo && nb < hi)) return -1;
+  }
+  return mat_sub(v, pol == POL_ZB) + (kind == 1 ? 16 : 0);
 }
 
 // Both count per block in LDS first (one LDS atomic per class per wave, one global atomic per
 // class per block): a global atomic per chain on a handful of counters serialises.
-constexpr int NCLASS = 2 * 8 + 1;
 __global__ void k_chain_count(TuneArgs t) {
   __shared__ int hist[NCLASS];
   for (int b = threadIdx.x; b < NCLASS; b += blockDim.x) hist[b] = 0;
   __syncthreads();
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool in = i < t.n_chains;
-  wave_hist_add(hist, in ? chain_class(t, i) : 0, in);
+  const int cls = i < t.n_chains ? chain_class(t, i) : -1;
+  wave_hist_add(hist, cls, cls >= 0);
   __syncthreads();
   for (int b = threadIdx.x; b < NCLASS; b += blockDim.x)
     if (hist[b]) atomicAdd(&t.s.ctl[CTL_COUNTS + b], hist[b]);
@@ -3311,8 +3328,8 @@ __global__ void k_chain_scatter(TuneArgs t, int32_t* __restrict__ list) {
   for (int b = threadIdx.x; b < NCLASS; b += blockDim.x) hist[b] = 0;
   __syncthreads();
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool in = i < t.n_chains;
-  const int cls = in ? chain_class(t, i) : 0;
+  const int cls = i < t.n_chains ? chain_class(t, i) : -1;
+  const bool in = cls >= 0;
   const int local = wave_hist_add(hist, cls, in);
   __syncthreads();
   for (int b = threadIdx.x; b < NCLASS; b += blockDim.x)
