@@ -3470,9 +3470,9 @@ __global__ void __launch_bounds__(WAVE) k_tune_ring(TuneArgs t) {
 
 // Search state per record (int32 words): the phase searched this iteration, flags (bits 0..2:
 // phases whose last search found nothing better; A1_OVER: the search has ended), the first
-// neighbour's position in the batch and the neighbour count; for the insertions: the first
-// placeholder's position, their number and the device searched.
-constexpr int A1_PHASE = 0, A1_FLAGS = 1, A1_BASE = 2, A1_CNT = 3, A1_INSB = 4, A1_NINS = 5,
+// neighbour's position in the batch and the neighbour count; for the moves of the scheduling
+// phase (k_alg1_moves): the first one's position, their number and the device searched.
+constexpr int A1_PHASE = 0, A1_FLAGS = 1, A1_BASE = 2, A1_CNT = 3, A1_BASE2 = 4, A1_CNT2 = 5,
               A1_DR = 6, A1_WORDS = 8;
 constexpr int A1_OVER = 8;
 // Search options (octo_alg1_tune_ex flags)
@@ -3493,8 +3493,10 @@ struct A1Args {
   int flags;               // A1F_*
   uint64_t seed;           // random phases: Philox key (seed, 0)
   int iter;                // this iteration (random phases: Philox counter word 1)
-  int32_t* ins_list;       // records whose insertions k_alg1_insert finds this iteration ...
-  int32_t* ins_n;          // ... and their count
+  int32_t* mv_list;        // records whose moves k_alg1_moves finds this iteration ...
+  int32_t* mv_n;           // ... and their count
+  int32_t* mv_wide;        // those of them whose costs or times need the 64-bit pass ...
+  int32_t* mv_wide_n;      // ... and their count
   uint8_t* nb_rec;         // neighbour records of this iteration, compacted
   const int64_t* nb_ms;    // [batch] their makespan
   const int64_t* nb_bub;   // [batch][P]
@@ -3544,18 +3546,16 @@ __global__ void k_alg1_init(int32_t* __restrict__ st, int64_t* __restrict__ stat
 
 // One neighbour as byte edits of the current record: edited spans [lo, hi) and what goes there.
 struct A1Edit {
-  int kind;  // 0 layer migration, 1 stage exchange, 2 stage dispersion, 3 policy, 4 op swap,
-             // 5 insertion placeholder (the record with its flags byte set: invalid until
-             //   k_alg1_insert writes a move into it)
+  int kind;  // 0 layer migration, 1 stage exchange, 2 stage dispersion, 3 policy
   int x, y;  // 0: boundaries x+1..y shift by -1 (x < y) or x+1..y by +1 (swapped: y < x holds
-             //    the lower stage); 1: stages x, y; 3: new policy; 4: device x, position y
+             //    the lower stage); 1: stages x, y; 3: new policy
   int lo1, hi1, lo2, hi2;
 };
 
 // Byte p of the neighbour (p inside one of its spans). rec: the current record, reserved bytes
 // cleared; S, v: its stage count and stages per device.
 __device__ __forceinline__ uint32_t a1_byte(const A1Edit& e, const uint8_t* rec, int p, int L,
-                                            int s_max, int S, int v, int po) {
+                                            int s_max, int S, int v) {
   auto bnd = [&](int s) -> int { return s == 0 ? 0 : s == S ? L : rec[3 + s]; };
   switch (e.kind) {
     case 0:  // boundary b[k] at byte 3 + k
@@ -3577,16 +3577,8 @@ __device__ __forceinline__ uint32_t a1_byte(const A1Edit& e, const uint8_t* rec,
       const int s = p - 3 - s_max;  // new stage s on the device of old stage s mod S
       return s < 2 * S ? rec[3 + s_max + s % S] : 0;
     }
-    case 3:
+    default:
       return p == 0 ? (uint32_t)e.x : p == 2 ? 0u : rec[p];
-    case 5:
-      return 1u;  // the flags byte
-    default: {
-      if (p == 2) return (uint32_t)(rec[2] + 1);
-      const int q = p - (po + 6 * rec[2]);  // the appended move {device, from, to}, u16 LE
-      const int val = q < 2 ? e.x : q < 4 ? e.y : e.y + 1;
-      return (uint32_t)((q & 1) ? (val >> 8) & 0xFF : val & 0xFF);
-    }
   }
 }
 
@@ -3599,10 +3591,9 @@ __device__ __forceinline__ uint32_t a1_byte(const A1Edit& e, const uint8_t* rec,
 //    other device's (devices, then its stages, then theirs, ascending); then, when v can double
 //    and every stage has two layers, every stage splits at its middle layer and the 2S stages
 //    go round the old devices (new stage k on the device of old stage k mod S), moves cleared;
-//  2 scheduling: each other policy (moves cleared); then, with a move slot free, each adjacent
-//    swap of the device with the largest bubble between its first and last op, as a move; then
-//    (A1F_INSERT) as many placeholders as that device can have overlap-aware insertions, which
-//    k_alg1_insert fills.
+//  2 scheduling: each other policy (moves cleared); then, with a move slot free, the moves of the
+//    device with the largest bubble between its first and last op — adjacent swaps, then
+//    (A1F_INSERT) overlap-aware insertions — which k_alg1_moves finds and appends to the batch.
 // The phase: Algorithm 1's branch, or (A1F_RANDOM) the (u mod n)-th of the n open phases, u the
 // first word of Philox4x64-10(counter (record, iteration, 1, 0), key (seed, 0)).
 __global__ void __launch_bounds__(WAVE) k_alg1_expand(A1Args a) {
@@ -3611,7 +3602,6 @@ __global__ void __launch_bounds__(WAVE) k_alg1_expand(A1Args a) {
   __shared__ uint8_t alist[8];   // partitioning: the loaded device's stages that can give a layer
   const int lane = lane_id();
   const int P = a.pr.P, M = a.pr.M, L = a.pr.L, s_max = a.pr.s_max, stride = a.pr.stride;
-  const int po = pert_off(s_max);
   int64_t tl = INT64_MAX;  // t_layer = M * the smallest layer's F + B + W
   for (int l = lane; l < L; l += WAVE) {
     const int64_t c = a.costs[3 * l] + a.costs[3 * l + 1] + a.costs[3 * l + 2];
@@ -3692,18 +3682,15 @@ __global__ void __launch_bounds__(WAVE) k_alg1_expand(A1Args a) {
       const bool disp = 2 * v <= a.pr.v_max && __ballot(thin) == 0;
       cnt = (P - 1) * v * v + (disp ? 1 : 0);
     }
-    const int qlen = (policy == POL_ZB ? 3 : 2) * v * M;
-    const int nswap = phase == 2 && np < a.pr.max_pert ? qlen - 1 : 0;
-    const int nins = phase == 2 && np < a.pr.max_pert && (a.flags & A1F_INSERT) ? qlen - 1 : 0;
-    if (phase == 2) cnt = 3 + nswap + nins;
+    if (phase == 2) cnt = 3;
     int base = 0;
     if (lane == 0) {
       base = atomicAdd(a.total, cnt);
       st[A1_PHASE] = phase, st[A1_BASE] = base, st[A1_CNT] = cnt;
-      st[A1_INSB] = base + 3 + nswap, st[A1_NINS] = nins, st[A1_DR] = dr;
+      st[A1_CNT2] = 0, st[A1_DR] = dr;
       a.stats[i * 4 + 3] += 1;
       if (a.pit) a.pit[i * 3 + phase] += 1;
-      if (nins > 0) a.ins_list[atomicAdd(a.ins_n, 1)] = (int32_t)i;
+      if (phase == 2 && np < a.pr.max_pert) a.mv_list[atomicAdd(a.mv_n, 1)] = (int32_t)i;
     }
     base = __shfl(base, 0);
     __syncthreads();
@@ -3729,18 +3716,10 @@ __global__ void __launch_bounds__(WAVE) k_alg1_expand(A1Args a) {
           e.kind = 2;
           e.lo1 = 1, e.hi1 = 3 + 2 * s_max;
         }
-      } else if (j < 3) {
+      } else {
         e.kind = 3;
         e.x = j < policy ? j : j + 1;
         e.lo1 = 0, e.hi1 = 3;
-      } else if (j < 3 + nswap) {
-        e.kind = 4;
-        e.x = dr, e.y = j - 3;
-        e.lo1 = 2, e.hi1 = 3;
-        e.lo2 = po + 6 * np, e.hi2 = e.lo2 + 6;
-      } else {
-        e.kind = 5;
-        e.lo1 = 3, e.hi1 = 4;
       }
       uint4* dst = reinterpret_cast<uint4*>(a.nb_rec + (int64_t)(base + j) * stride);
       for (int q = 0; q < stride / 16; ++q) {
@@ -3752,7 +3731,7 @@ __global__ void __launch_bounds__(WAVE) k_alg1_expand(A1Args a) {
           for (int b = 0; b < 16; ++b) {
             const int p = p0 + b;
             if ((p >= e.lo1 && p < e.hi1) || (p >= e.lo2 && p < e.hi2)) {
-              const uint32_t nv = a1_byte(e, rec, p, L, s_max, S, v, po) & 0xFF;
+              const uint32_t nv = a1_byte(e, rec, p, L, s_max, S, v) & 0xFF;
               w[b >> 2] = (w[b >> 2] & ~(0xFFu << (8 * (b & 3)))) | (nv << (8 * (b & 3)));
             }
           }
@@ -3765,177 +3744,297 @@ __global__ void __launch_bounds__(WAVE) k_alg1_expand(A1Args a) {
   }
 }
 
-// Overlap-aware insertions (§6 "Scheduling Tuning", the second policy) of the records on
-// b.ins_list, written into the placeholders k_alg1_expand reserved. One group per record
-// (64-bit finish tables), lane = device: the record's queues with its moves, the asynchronous
-// rounds recording every op's start and finish, then the lane of the searched device walks its
-// queue: at each position k >= 1 with A = Q[k-1], B = Q[k], if the device idles between them and
-// A's output goes to another device while B does not run during that transfer [end A,
-// end A + c], or B's input comes from another device while A does not run during that transfer
-// (§5: a node overlaps when a computation runs beside it for a positive time), the first later
-// op Z = Q[j] that is ready when A ends (each producer's end, plus the transfer time across
-// devices) becomes the move (device, j, k) of the next placeholder (flags byte cleared, one
-// more move). Placeholders left over stay invalid. The group's lanes share the walk: each takes
-// every G-th position, then every G-th insertion point, and the insertions found are numbered
-// in position order by a ballot.
-template <int VMAX>
-__global__ void __launch_bounds__(WAVE) k_alg1_insert(SimArgs a, A1Args b,
-                                                      int64_t* __restrict__ tbuf) {
+// The scheduling phase's moves of the records on the list, appended to the batch: the adjacent
+// swaps {d, i, i+1} of the searched device d, then (A1F_INSERT) its overlap-aware insertions (§6
+// "Scheduling Tuning", the second policy) as moves {d, j, k}: at each position k >= 1 with
+// A = Q[k-1], B = Q[k], if the device idles between them and A's output goes to another device
+// while B does not run during that transfer [end A, end A + c], or B's input comes from another
+// device while A does not run during that transfer (§5: a node overlaps when a computation runs
+// beside it for a positive time), the first later op Z = Q[j] that is ready when A ends (each
+// producer's end, plus the transfer time across devices) moves to index k.
+// Only the best neighbour that shortens the makespan T is ever kept (k_alg1_select), so moves that
+// provably do not are left out, and the batch evaluates a few moves per record instead of its
+// whole queue twice (on 4,096 records of the P = 8, M = 64 batch: the evaluation of the moves took
+// 31 of 54 ms a call). With every op's end e(x) from the asynchronous rounds and its tail t(x) —
+// the longest path from its start to the end of the schedule — from the same rounds over the
+// mirrored graph:
+//  * a move replaces queue edges; while some path of length T uses none of those it removes, the
+//    makespan stays at least T. Swapping a = Q[i] and b = Q[i+1] removes Q[i-1] -> a -> b ->
+//    Q[i+2]; an insertion removes Q[j-1] -> Z -> Q[j+1] (and A -> B, which idles). An edge x -> y
+//    is on such a path iff e(x) + t(y) = T.
+//  * after a feasible swap the longest path through a or b has an exact length (the ends of their
+//    inputs and the tails of their outputs do not change), after an insertion the paths
+//    A, Z, Z's outputs and A, Z, Q[k..j-1], Q[j+1] are lower bounds; a move whose bound reaches T
+//    cannot shorten it. (An infeasible move deadlocks and is never kept either.)
+// One wave per record: the rounds on the lanes of its devices (40-bit full rows), the search over
+// the device's queue on all 64. WIDE (64-bit tables, the records of the first pass whose costs
+// pass 32 bits or whose times pass the 40-bit slots): no tails, every move is appended.
+// Scratch per block (64-bit words): ends and tails by node, then per position of the searched
+// queue: readiness, gap threshold, end, tail, output tail, durations before; then the move list.
+constexpr int A1_COLS = 6;
+__host__ __device__ __forceinline__ size_t a1_scratch(size_t nodes, int qcap) {
+  return 2 * nodes + (size_t)(A1_COLS + 2) * qcap;
+}
+template <int VMAX, bool WIDE>
+__global__ void __launch_bounds__(WAVE) k_alg1_moves(SimArgs a, A1Args b,
+                                                     int64_t* __restrict__ tbuf) {
   extern __shared__ __align__(16) uint8_t smem[];
-  const int G = a.G, P = a.pr.P, M = a.pr.M;
-  const int g = lane_id() / G;
-  const int d = lane_id() % G;
-  uint8_t* lds_group = smem + (size_t)(g < a.CPW ? g : 0) * a.group_bytes;
-  const auto T = group_table<false>(lds_group, a.slots);
-  uint8_t* rec = lds_group + a.table_bytes;
-  const int slot = (int)blockIdx.x * a.CPW + (g < a.CPW ? g : 0);
+  uint8_t* full = smem;  // the whole record, over the table once the rounds are done
+  const int P = a.pr.P, M = a.pr.M, stride = a.pr.stride;
+  const int d = lane_id();
+  const auto T = group_table<!WIDE>(smem, a.slots);
+  uint8_t* rec = smem + a.table_bytes;
   const int dl = d < P ? d : 0;
-  uint16_t* row = a.qscratch + ((size_t)slot * P + dl) * a.qcap;
+  uint16_t* rows = a.qscratch + (size_t)blockIdx.x * P * a.qcap;
+  uint16_t* row = rows + (size_t)dl * a.qcap;
   const size_t nodes = (size_t)3 * a.pr.s_max * M;
-  // per slot: finish times, start times (node-indexed), then two rows of the searched queue
-  int64_t* tb = tbuf + (size_t)slot * (2 * nodes + 2 * (size_t)a.qcap);
-  int64_t* ts = tb + nodes;
-  uint64_t gbit, lsb;
-  group_bits(G, &gbit, &lsb);
-  const int64_t n_groups = (int64_t)gridDim.x * a.CPW;
-  const int64_t total = *b.ins_n;
+  int64_t* tb = tbuf + (size_t)blockIdx.x * a1_scratch(nodes, a.qcap);
+  int64_t* tq = tb + nodes;
+  int64_t* rdy = tq + nodes;
+  int64_t *thr = rdy + a.qcap, *ce = thr + a.qcap, *ct = ce + a.qcap, *co = ct + a.qcap;
+  int64_t* cp = co + a.qcap;
+  int2* list = reinterpret_cast<int2*>(cp + a.qcap);
+  const int64_t total = WIDE ? *b.mv_wide_n : *b.mv_n;
   const Ring ring = make_ring(M, M);
   const int po = pert_off(a.pr.s_max);
-  for (int64_t base = (int64_t)blockIdx.x * a.CPW; base < total; base += n_groups) {
-    const bool has = g < a.CPW && base + g < total;
-    const int64_t i = has ? (int64_t)b.ins_list[base + g] : 0;
-    const uint8_t* grec = b.recs + i * a.pr.stride;
-    if (has) stage_record(rec, grec, a.rec_bytes, d, G);
+  for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
+    const int64_t i = WIDE ? b.mv_wide[it] : b.mv_list[it];
+    const uint8_t* grec = b.recs + i * stride;
+    stage_record(rec, grec, a.rec_bytes, d, WAVE);
     __syncthreads();
-    Resolved r;
-    r.valid = 0, r.v = 1, r.split = 0, r.gen = GEN_AFAB, r.n_pert = 0;
-    if (has) r = resolve_record(a.pr, grec);
-    const bool valid = has && r.valid;
-    const int v = valid ? r.v : 1;
-    const int S = P * v;
+    // (valid: it was evaluated)
+    const Resolved r = resolve_record(a.pr, rec, grec + po);
+    const int v = r.valid ? r.v : 1, S = P * v;
+    int32_t* st = b.st + i * A1_WORDS;
+    const int dr = st[A1_DR];
     Chunks<VMAX> c;
     Lane L;
     L.clock = 0, L.pos = 0, L.nops = 0, L.mem = L.peak = 0;
     L.cm.reset();
     L.fs = -1;
-    L.tb = tb, L.ts = ts, L.tl = nullptr, L.tS = S, L.tM = M, L.rnd = 0;
-    if (valid && d < P) {
-      (void)setup_chunks<VMAX>(c, a.pr, rec, a.pre, a.link, d, v, r.split, ring, nullptr,
-                               nullptr, XR);
+    L.tb = tb, L.ts = nullptr, L.tl = nullptr, L.tS = S, L.tM = M, L.rnd = 0;
+    if (r.valid && d < P) {
+      (void)setup_chunks<VMAX>(c, a.pr, rec, a.pre, a.link, d, v, r.split, ring, nullptr, nullptr,
+                               XR);
       L.nops = materialise<VMAX>(a, c, v, r.gen, r.split, row);
-      const uint8_t* pp = grec + po;
       for (int q = 0; q < r.n_pert; ++q) {
-        const int pd = pp[6 * q] | (pp[6 * q + 1] << 8);
+        const uint8_t* pp = grec + po + 6 * q;
+        const int pd = pp[0] | (pp[1] << 8);
         if (pd != d) continue;
-        move_entry(row, pp[6 * q + 2] | (pp[6 * q + 3] << 8), pp[6 * q + 4] | (pp[6 * q + 5] << 8));
+        move_entry(row, pp[2] | (pp[3] << 8), pp[4] | (pp[5] << 8));
       }
     } else {
       zero_chunks<VMAX>(c);
     }
-    const bool mine = valid && d < P;
-    if (!mine) L.nops = 0;
-    if (valid) T.clear(S * M, d, G);
+    const int nops = L.nops;
+    T.clear(S * M, d, WAVE);
     __syncthreads();
-    bool dead = false;
-    rounds_mat<VMAX, XT, false>(row, a.qcap, c, v, ring, L, T, G, gbit, lsb, dead, nullptr, nullptr);
-    __syncthreads();  // every lane's times visible to the group
-    // the searched device's queue, decoded by every lane of the group: (1) per position p, when
-    // the op could start (its inputs' arrivals) and, for an insertion before p, the end of
-    // op p - 1 when the device idles there and a communication there is alone (else -1);
-    // (2) per such p, the first later op ready by then; (3) the placeholders, in p order
-    const int32_t* st = b.st + i * A1_WORDS;
-    const int dr = has ? st[A1_DR] : 0, insb = has ? st[A1_INSB] : 0;
-    const int nins = has ? st[A1_NINS] : 0, np = rec[2];
-    const bool go = valid && !dead && nins > 0;
-    Chunks<VMAX> cr;
-    if (go) {
-      (void)setup_chunks<VMAX>(cr, a.pr, rec, a.pre, a.link, dr, v, r.split, ring, nullptr,
-                               nullptr, XR);
+    bool dead = false, fits = true;
+    const int64_t ms = b.ms[i];
+    if constexpr (WIDE) {
+      rounds_mat<VMAX, XT, false>(row, a.qcap, c, v, ring, L, T, WAVE, 1ull, 1ull, dead, nullptr,
+                                  nullptr);
     } else {
-      zero_chunks<VMAX>(cr);
+      fits = __ballot(!lstreams_fit<VMAX>(c)) == 0 && ms < Table40::LIMIT;
+      // (the mirrored weights are other entries of the link matrix: the outputs')
+      uint64_t cw = 0;
+#pragma unroll
+      for (int k = 0; k < VMAX; ++k) cw |= (uint64_t)c.cF[k] | (uint64_t)c.cB[k];
+      fits = fits && __ballot((cw >> 32) != 0) == 0;
+      if (!fits) {
+        if (d == 0) b.mv_wide[atomicAdd(b.mv_wide_n, 1)] = (int32_t)i;
+        __syncthreads();
+        continue;
+      }
+      LStreams<VMAX, false> Sx;
+      Sx.init(c, v, T.lg, T.g, smem + a.strm_off);
+      relax_lean<VMAX, XT, false>(row, a.qcap, Sx, c, ring, L, T, WAVE, 1ull, 1ull, dead);
+      __syncthreads();
+      // tails: the mirrored graph
+      T.clear(S * M, d, WAVE);
+      Sx.template init<true>(c, v, T.lg, T.g, smem + a.strm_off);
+      L.clock = 0, L.nops = nops, L.tb = tq;
+      __syncthreads();
+      relax_lean<VMAX, XT, false, true>(row, a.qcap, Sx, c, ring, L, T, WAVE, 1ull, 1ull, dead);
     }
-    const uint16_t* rrow = a.qscratch + ((size_t)slot * P + dr) * a.qcap;
-    const int nq = go ? (r.split ? 3 : 2) * v * M : 0;
-    int64_t* rdy = tb + 2 * nodes;
-    int64_t* thr = rdy + a.qcap;
+    __syncthreads();  // every lane's times visible to the wave
+    // the searched device's queue, decoded by every lane: per position p the op's end, tail,
+    // readiness (its inputs' arrivals), output tail, the durations before it and, for an insertion
+    // before p, the end of op p - 1 when the device idles there and a communication there is alone
+    // (else -1)
+    Chunks<VMAX> cr;
+    (void)setup_chunks<VMAX>(cr, a.pr, rec, a.pre, a.link, dr, v, r.split, ring, nullptr, nullptr, XR);
+    const uint16_t* rrow = rows + (size_t)dr * a.qcap;
+    const int nq = r.valid && !dead ? (r.split ? 3 : 2) * v * M : 0;
     auto node = [&](int kind, int s, int m) { return (kind * S + s) * M + m; };
-    for (int q = d; q < nq && d < G; q += G) {
-      const uint32_t eb = rrow[q];
+    auto dur_of = [&](int kind, int k) {
+      return kind == KF ? pick<VMAX>(cr.dF, k) : kind == KB ? pick<VMAX>(cr.dB, k) : pick<VMAX>(cr.dW, k);
+    };
+    int64_t before = 0;  // durations of the positions of the earlier passes
+    for (int q0 = 0; q0 < nq; q0 += WAVE) {
+      const int q = q0 + d;
+      const bool in = q < nq;
+      const uint32_t eb = rrow[in ? q : 0];
       const int kindB = (eb >> 14) & 3, kB = (eb >> 11) & 7, mB = eb & 0x7FF;
       const int sB = pick<VMAX>(cr.st, kB);
-      int64_t ry = 0;
-      if (kindB == KF) {
-        if (sB > 0) ry = tb[node(KF, sB - 1, mB)] + pick<VMAX>(cr.wF, kB);
-      } else if (kindB == KB) {
-        ry = tb[node(KF, sB, mB)];
-        if (sB < S - 1) {
-          const int64_t y = tb[node(KB, sB + 1, mB)] + pick<VMAX>(cr.wB, kB);
-          ry = y > ry ? y : ry;
-        }
-      } else {
-        ry = tb[node(KB, sB, mB)];
+      int64_t dsum = in ? dur_of(kindB, kB) : 0;
+      const int64_t durB = dsum;
+      for (int o = 1; o < WAVE; o <<= 1) {
+        const int64_t y = __shfl_up(dsum, o, WAVE);
+        dsum += d >= o ? y : 0;
       }
-      rdy[q] = ry;
-      int64_t t = -1;
-      if (q >= 1) {
-        const uint32_t ea = rrow[q - 1];
-        const int kindA = (ea >> 14) & 3, kA = (ea >> 11) & 7, mA = ea & 0x7FF;
-        const int sA = pick<VMAX>(cr.st, kA);
-        const int64_t finA = tb[node(kindA, sA, mA)], stA = ts[node(kindA, sA, mA)];
-        const int64_t finB = tb[node(kindB, sB, mB)], stB = ts[node(kindB, sB, mB)];
-        if (stB > finA) {
-          const int cxA =
-              kindA == KF ? pick<VMAX>(cr.xF, kA) : kindA == KB ? pick<VMAX>(cr.xB, kA) : 0;
-          const int cxB =
-              kindB == KF ? pick<VMAX>(cr.xF, kB) : kindB == KB ? pick<VMAX>(cr.xB, kB) : 0;
-          bool alone = false;
-          if (cxA & CX_OUT) {  // A's output in flight over [finA, finA + c]; does B run then?
-            const int64_t hi =
-                finA + (kindA == KF ? pick<VMAX>(cr.cF, kA) : pick<VMAX>(cr.cB, kA));
-            alone = alone || (finB < hi ? finB : hi) - (stB > finA ? stB : finA) <= 0;
+      if (in) {
+        int64_t ry = 0;
+        if (kindB == KF) {
+          if (sB > 0) ry = tb[node(KF, sB - 1, mB)] + pick<VMAX>(cr.wF, kB);
+        } else if (kindB == KB) {
+          ry = tb[node(KF, sB, mB)];
+          if (sB < S - 1) {
+            const int64_t y = tb[node(KB, sB + 1, mB)] + pick<VMAX>(cr.wB, kB);
+            ry = y > ry ? y : ry;
           }
-          if (cxB & CX_IN) {  // B's input in flight from its producer's end; does A run then?
-            const int64_t fx = tb[node(kindB, kindB == KF ? sB - 1 : sB + 1, mB)];
-            const int64_t hi =
-                fx + (kindB == KF ? pick<VMAX>(cr.wF, kB) : pick<VMAX>(cr.wB, kB));
-            alone = alone || (finA < hi ? finA : hi) - (stA > fx ? stA : fx) <= 0;
-          }
-          t = alone ? finA : -1;
+        } else {
+          ry = tb[node(KB, sB, mB)];
         }
+        rdy[q] = ry;
+        const int64_t finB = tb[node(kindB, sB, mB)], stB = finB - durB;
+        ce[q] = finB;
+        cp[q] = before + dsum - durB;
+        if constexpr (!WIDE) {
+          ct[q] = tq[node(kindB, sB, mB)];
+          int64_t ot = 0;
+          if (kindB == KF)
+            ot = sB < S - 1 ? tq[node(KF, sB + 1, mB)] + pick<VMAX>(cr.cF, kB) : tq[node(KB, sB, mB)];
+          else if (kindB == KB && sB > 0)
+            ot = tq[node(KB, sB - 1, mB)] + pick<VMAX>(cr.cB, kB);
+          if (kindB == KB && r.split) {
+            const int64_t y = tq[node(KW, sB, mB)];
+            ot = y > ot ? y : ot;
+          }
+          co[q] = ot;
+        }
+        int64_t t = -1;
+        if (q >= 1 && (b.flags & A1F_INSERT)) {
+          const uint32_t ea = rrow[q - 1];
+          const int kindA = (ea >> 14) & 3, kA = (ea >> 11) & 7, mA = ea & 0x7FF;
+          const int sA = pick<VMAX>(cr.st, kA);
+          const int64_t finA = tb[node(kindA, sA, mA)], stA = finA - dur_of(kindA, kA);
+          if (stB > finA) {
+            const int cxA =
+                kindA == KF ? pick<VMAX>(cr.xF, kA) : kindA == KB ? pick<VMAX>(cr.xB, kA) : 0;
+            const int cxB =
+                kindB == KF ? pick<VMAX>(cr.xF, kB) : kindB == KB ? pick<VMAX>(cr.xB, kB) : 0;
+            bool alone = false;
+            if (cxA & CX_OUT) {  // A's output in flight over [finA, finA + c]; does B run then?
+              const int64_t hi =
+                  finA + (kindA == KF ? pick<VMAX>(cr.cF, kA) : pick<VMAX>(cr.cB, kA));
+              alone = alone || (finB < hi ? finB : hi) - (stB > finA ? stB : finA) <= 0;
+            }
+            if (cxB & CX_IN) {  // B's input in flight from its producer's end; does A run then?
+              const int64_t fx = tb[node(kindB, kindB == KF ? sB - 1 : sB + 1, mB)];
+              const int64_t hi =
+                  fx + (kindB == KF ? pick<VMAX>(cr.wF, kB) : pick<VMAX>(cr.wB, kB));
+              alone = alone || (finA < hi ? finA : hi) - (stA > fx ? stA : fx) <= 0;
+            }
+            t = alone ? finA : -1;
+          }
+        }
+        thr[q] = t;
       }
-      thr[q] = t;
+      before += __shfl(dsum, WAVE - 1);
     }
-    __syncthreads();  // the group's rdy and thr visible to all its lanes
-    const uint64_t gmask = G >= WAVE ? ~0ull : ((1ull << G) - 1);
-    const int g0 = lane_id() - d;
+    __syncthreads();  // the columns visible to all lanes
     int found = 0;
-    for (int k0 = 0; k0 < nq; k0 += G) {
-      const int k = k0 + d;
-      int jk = -1;
-      if (d < G && k >= 1 && k < nq) {
-        const int64_t t = thr[k];
-        // the first later op ready by t: eight readiness times loaded together per step
-        if (t >= 0)
-          for (int j0 = k + 1; j0 < nq && jk < 0; j0 += 8) {
-            int64_t r8[8];
+    auto keep = [&](bool yes, int from, int to) {
+      const uint64_t m = __ballot(yes);
+      if (yes) list[found + __popcll(m & ((1ull << d) - 1))] = make_int2(from, to);
+      found += __popcll(m);
+    };
+    for (int q0 = 0; q0 + 1 < nq; q0 += WAVE) {  // swaps of positions q, q + 1
+      const int q = q0 + d;
+      bool yes = q + 1 < nq;
+      if constexpr (!WIDE) {
+        if (yes) {
+          const int64_t ep = q > 0 ? ce[q - 1] : 0, ea = ce[q], eb = ce[q + 1];
+          const int64_t tn = q + 2 < nq ? ct[q + 2] : 0;
+          const int64_t pa = cp[q + 1] - cp[q];
+          const int64_t pb = (q + 2 < nq ? cp[q + 2] : before) - cp[q + 1];
+          const bool tight = (q > 0 && ep + ct[q] == ms) || ea + ct[q + 1] == ms ||
+                             (q + 2 < nq && eb + tn == ms);
+          const int64_t sb = ep > rdy[q + 1] ? ep : rdy[q + 1];       // b's start
+          const int64_t sa = sb + pb > rdy[q] ? sb + pb : rdy[q];     // then a's
+          const int64_t ta = pa + (tn > co[q] ? tn : co[q]);          // a's tail
+          const int64_t tbb = pb + (ta > co[q + 1] ? ta : co[q + 1]); // b's
+          yes = tight && sa + ta < ms && sb + tbb < ms;
+        }
+      }
+      keep(yes, q, q + 1);
+    }
+    if (b.flags & A1F_INSERT) {
+      for (int k0 = 0; k0 < nq; k0 += WAVE) {
+        const int k = k0 + d;
+        int jk = -1;
+        int64_t t = -1;
+        if (k >= 1 && k < nq) {
+          t = thr[k];
+          // the first later op ready by t: eight readiness times loaded together per step
+          if (t >= 0)
+            for (int j0 = k + 1; j0 < nq && jk < 0; j0 += 8) {
+              int64_t r8[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) r8[u] = j0 + u < nq ? rdy[j0 + u] : INT64_MAX;
+              for (int u = 0; u < 8; ++u) r8[u] = j0 + u < nq ? rdy[j0 + u] : INT64_MAX;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) jk = jk < 0 && r8[u] <= t ? j0 + u : jk;
+              for (int u = 0; u < 8; ++u) jk = jk < 0 && r8[u] <= t ? j0 + u : jk;
+            }
+        }
+        bool yes = jk >= 0;
+        if constexpr (!WIDE) {
+          if (yes) {
+            const int64_t tn = jk + 1 < nq ? ct[jk + 1] : 0;
+            const bool tight = ce[jk - 1] + ct[jk] == ms || (jk + 1 < nq && ce[jk] + tn == ms);
+            const int64_t pz = (jk + 1 < nq ? cp[jk + 1] : before) - cp[jk];
+            yes = tight && t + pz + co[jk] < ms && t + pz + (cp[jk] - cp[k]) + tn < ms;
           }
+        }
+        keep(yes, jk, k);
       }
-      const uint64_t gm = (__ballot(jk >= 0) >> g0) & gmask;
-      const int at = found + __popcll(gm & ((1ull << d) - 1));
-      if (jk >= 0 && at < nins) {
-        uint8_t* nb = b.nb_rec + (int64_t)(insb + at) * a.pr.stride;
-        nb[3] = 0;
-        nb[2] = (uint8_t)(np + 1);
-        uint8_t* mv = nb + po + 6 * np;
-        mv[0] = (uint8_t)dr, mv[1] = 0;
-        mv[2] = (uint8_t)(jk & 0xFF), mv[3] = (uint8_t)(jk >> 8);
-        mv[4] = (uint8_t)(k & 0xFF), mv[5] = (uint8_t)(k >> 8);
+    }
+    int base = 0;
+    if (d == 0) {
+      base = atomicAdd(b.total, found);
+      st[A1_BASE2] = base, st[A1_CNT2] = found;
+    }
+    base = __shfl(base, 0);
+    // the records: reserved boundary and placement bytes cleared (as every neighbour has them), one
+    // move appended
+    for (int q = d; q < stride / 16; q += WAVE)
+      reinterpret_cast<uint4*>(full)[q] = reinterpret_cast<const uint4*>(grec)[q];
+    __syncthreads();
+    const int np = full[2];
+    for (int p = 3 + S + d; p < 3 + a.pr.s_max; p += WAVE) full[p] = 0;
+    for (int p = 3 + a.pr.s_max + S + d; p < 3 + 2 * a.pr.s_max; p += WAVE) full[p] = 0;
+    __syncthreads();
+    const int w16 = stride / 16;
+    for (int x = d; x < found * w16; x += WAVE) {
+      const int j = x / w16, q = x - j * w16;
+      const int2 mv = list[j];
+      uint4 y = reinterpret_cast<const uint4*>(full)[q];
+      uint32_t w[4] = {y.x, y.y, y.z, y.w};
+      // the move's three half-words (device, from, to) where they fall in this 16-byte chunk, and
+      // the move count (half-word 1, with the flags byte)
+#pragma unroll
+      for (int h = 0; h < 8; ++h) {
+        const int at = 8 * q + h, u = at - (po + 6 * np) / 2;
+        uint32_t val = (w[h >> 1] >> (16 * (h & 1))) & 0xFFFFu;
+        val = at == 1 ? (uint32_t)(np + 1) | (uint32_t)full[3] << 8
+              : u == 0 ? (uint32_t)dr
+              : u == 1 ? (uint32_t)mv.x
+              : u == 2 ? (uint32_t)mv.y
+                       : val;
+        w[h >> 1] = (w[h >> 1] & ~(0xFFFFu << (16 * (h & 1)))) | val << (16 * (h & 1));
       }
-      found += __popcll(gm);
+      reinterpret_cast<uint4*>(b.nb_rec + (int64_t)(base + j) * stride)[q] =
+          make_uint4(w[0], w[1], w[2], w[3]);
     }
     __syncthreads();  // before the next record reuses the staged record and the tables
   }
@@ -3952,10 +4051,12 @@ __global__ void __launch_bounds__(WAVE) k_alg1_select(A1Args a) {
     const int flags = st[A1_FLAGS];
     if (flags & A1_OVER) continue;
     const int phase = st[A1_PHASE], base = st[A1_BASE], cnt = st[A1_CNT];
+    // the moves (scheduling phase) follow the other neighbours in the order that settles ties
+    const int base2 = st[A1_BASE2], cnt2 = phase == 2 ? st[A1_CNT2] : 0;
     int64_t best = INT64_MAX;
     int bj = INT32_MAX;
-    for (int j = lane; j < cnt; j += WAVE) {
-      const int64_t x = a.nb_ms[base + j];
+    for (int j = lane; j < cnt + cnt2; j += WAVE) {
+      const int64_t x = a.nb_ms[j < cnt ? base + j : base2 + j - cnt];
       if (x >= 0 && x < best) best = x, bj = j;
     }
     for (int o = WAVE >> 1; o > 0; o >>= 1) {
@@ -3964,7 +4065,7 @@ __global__ void __launch_bounds__(WAVE) k_alg1_select(A1Args a) {
       if (y < best || (y == best && k < bj)) best = y, bj = k;
     }
     if (bj != INT32_MAX && best < a.ms[i]) {
-      const int64_t nb = base + bj;
+      const int64_t nb = bj < cnt ? base + bj : base2 + bj - cnt;
       const uint4* src = reinterpret_cast<const uint4*>(a.nb_rec + nb * stride);
       uint4* dst = reinterpret_cast<uint4*>(a.recs + i * stride);
       for (int q = lane; q < stride / 16; q += WAVE) dst[q] = src[q];
@@ -4147,6 +4248,23 @@ Plan ring_plan(const octo_problem* p, int lds_max, int s_cap, int R) {
   pl.CPW = std::min(WAVE / pl.G, (lds_max - strm) / pl.group_bytes);
   pl.strm_off = (int)align_up((size_t)std::max(pl.CPW, 0) * pl.group_bytes, 16);
   pl.lds_bytes = pl.strm_off + strm;
+  pl.qcap = queue_cap(p);
+  return pl;
+}
+
+// Plan of k_alg1_moves: one record per wave, full rows of slot_bytes-byte slots, the staged
+// record, then (40-bit slots) the lean rounds' streams.
+Plan moves_plan(const octo_problem* p, int slot_bytes) {
+  Plan pl;
+  pl.G = WAVE, pl.CPW = 1;
+  pl.slots = (int)align_up((size_t)p->P * p->v_max * p->M, 16);
+  pl.rec_bytes = pert_off(p->P * p->v_max);
+  pl.rec_stride = (int)align_up(pl.rec_bytes, 16);
+  // (at the end the table's memory holds the whole record)
+  pl.table_bytes = std::max(pl.slots * slot_bytes, p->cand_stride);
+  pl.group_bytes = pl.table_bytes + pl.rec_stride;
+  pl.strm_off = pl.group_bytes;
+  pl.lds_bytes = pl.strm_off + (slot_bytes == 5 ? lean_streams(p) * WAVE * 8 : 0);
   pl.qcap = queue_cap(p);
   return pl;
 }
@@ -5154,7 +5272,7 @@ int tune_step_impl(const octo_problem* prob, const int64_t* layer_costs, const i
 // neighbourhoods over v <= v_max).
 int64_t alg1_slots(const octo_problem* p) {
   const int64_t v = p->v_max;
-  // scheduling: 3 policies, qlen - 1 swaps and qlen - 1 insertion placeholders
+  // scheduling: 3 policies, at most qlen - 1 swaps and qlen - 1 insertions
   return std::max({v * v, (int64_t)(p->P - 1) * v * v + 1, 6 * v * p->M + 1});
 }
 
@@ -5178,19 +5296,25 @@ int alg1_impl(const octo_problem* prob, const int64_t* layer_costs, const int64_
   std::lock_guard<std::mutex> lock(g_mu);
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return OCTO_EHIP;
-  // the insertion pass: 64-bit finish tables, one group per record; its grid bounds the group
-  // slots whose finish and start times it keeps
-  int ins_grid = 0;
+  // the moves of the scheduling phase: one wave per record on 40-bit full rows, then on 64-bit
+  // ones; the grids bound the blocks whose times and queues are kept
   Setup su;
-  if (flags & A1F_INSERT) {
-    if ((rc = prepare(prob, layer_costs, nullptr, stream, n, &su))) return rc;
-    if ((rc = prob->v_max <= 2
-                  ? occupancy_grid(k_alg1_insert<2>, su.big.lds_bytes, su.di.cus, &ins_grid)
-                  : occupancy_grid(k_alg1_insert<8>, su.big.lds_bytes, su.di.cus, &ins_grid)))
-      return rc;
-    ins_grid = (int)std::max<int64_t>(
-        1, std::min<int64_t>(std::min(ins_grid, su.mat_grid), (n + su.big.CPW - 1) / su.big.CPW));
-  }
+  DevInfo di;
+  if ((rc = dev_info(dev, &di))) return rc;
+  const Plan mp = moves_plan(prob, 5), mw = moves_plan(prob, 8);
+  int mgrid = 0, wgrid = 0;
+  if (mw.lds_bytes > di.lds_max) return OCTO_EUNSUPPORTED;
+  const bool lean = mp.lds_bytes <= di.lds_max;
+  if (lean && (rc = prob->v_max <= 2
+                        ? occupancy_grid(k_alg1_moves<2, false>, mp.lds_bytes, di.cus, &mgrid)
+                        : occupancy_grid(k_alg1_moves<8, false>, mp.lds_bytes, di.cus, &mgrid)))
+    return rc;
+  if ((rc = prob->v_max <= 2
+                ? occupancy_grid(k_alg1_moves<2, true>, mw.lds_bytes, di.cus, &wgrid)
+                : occupancy_grid(k_alg1_moves<8, true>, mw.lds_bytes, di.cus, &wgrid)))
+    return rc;
+  mgrid = (int)std::min<int64_t>(mgrid, n), wgrid = (int)std::min<int64_t>(wgrid, n);
+  const int slots_mv = std::max(mgrid, wgrid);
   const size_t nodes = (size_t)3 * prob->P * prob->v_max * prob->M;
   Workspace& ws = g_ws[std::make_pair(dev, stream)];
   const int P = prob->P;
@@ -5209,12 +5333,10 @@ int alg1_impl(const octo_problem* prob, const int64_t* layer_costs, const int64_
   o = align_up(o + (size_t)nb * P * 8, 256);
   const size_t o_nbnd = o;
   o = align_up(o + (size_t)nb * P * 16, 256);
-  const size_t o_ins = o;
-  o = align_up(o + (size_t)n * 4, 256);
+  const size_t o_mv = o;
+  o = align_up(o + (size_t)n * 8, 256);
   const size_t o_tbuf = o;
-  o = align_up(o + (size_t)ins_grid * std::max(su.big.CPW, 0) *
-                       (2 * nodes + 2 * (size_t)std::max(su.big.qcap, 0)) * 8,
-                256);
+  o = align_up(o + (size_t)slots_mv * a1_scratch(nodes, mp.qcap) * 8, 256);
   if ((rc = ensure_buf(ws.a1, ws.a1_bytes, o, stream))) return rc;
   char* base = static_cast<char*>(ws.a1);
   A1Args a;
@@ -5232,8 +5354,10 @@ int alg1_impl(const octo_problem* prob, const int64_t* layer_costs, const int64_
   a.flags = flags;
   a.seed = seed;
   a.iter = 0;
-  a.ins_list = reinterpret_cast<int32_t*>(base + o_ins);
-  a.ins_n = reinterpret_cast<int32_t*>(base + o_total) + 1;
+  a.mv_list = reinterpret_cast<int32_t*>(base + o_mv);
+  a.mv_wide = a.mv_list + n;
+  a.mv_n = reinterpret_cast<int32_t*>(base + o_total) + 1;
+  a.mv_wide_n = a.mv_n + 1;
   a.nb_rec = reinterpret_cast<uint8_t*>(base + o_rec);
   a.nb_ms = reinterpret_cast<int64_t*>(base + o_ms);
   a.nb_bub = reinterpret_cast<int64_t*>(base + o_bub);
@@ -5254,20 +5378,33 @@ int alg1_impl(const octo_problem* prob, const int64_t* layer_costs, const int64_
   for (int it = 0; it < iters; ++it) {
     a.iter = it;
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(WAVE), 0, stream,
-                       reinterpret_cast<uint32_t*>(a.total), 2, 0u);  // cursor, insertion count
+                       reinterpret_cast<uint32_t*>(a.total), 3, 0u);  // cursor, move list counts
     if ((rc = launch_ok())) return rc;
     hipLaunchKernelGGL(k_alg1_expand, dim3(grid), dim3(WAVE), 0, stream, a);
     if ((rc = launch_ok())) return rc;
-    if (flags & A1F_INSERT) {
-      if ((rc = prepare(prob, layer_costs, nullptr, stream, n, &su))) return rc;
-      SimArgs sa = make_args(prob, su.big, su, link, records, n, nullptr, nullptr);
+    if (prob->max_pert > 0) {
+      if ((rc = prepare(prob, layer_costs, nullptr, stream, n, &su, slots_mv))) return rc;
       int64_t* tbuf = reinterpret_cast<int64_t*>(static_cast<char*>(ws.a1) + o_tbuf);
+      A1Args am = a;
+      if (lean) {
+        SimArgs sa = make_args(prob, mp, su, link, records, n, nullptr, nullptr);
+        if (prob->v_max <= 2)
+          hipLaunchKernelGGL((k_alg1_moves<2, false>), dim3(mgrid), dim3(WAVE), mp.lds_bytes,
+                             stream, sa, a, tbuf);
+        else
+          hipLaunchKernelGGL((k_alg1_moves<8, false>), dim3(mgrid), dim3(WAVE), mp.lds_bytes,
+                             stream, sa, a, tbuf);
+        if ((rc = launch_ok())) return rc;
+      } else {
+        am.mv_wide = a.mv_list, am.mv_wide_n = a.mv_n;
+      }
+      SimArgs sw = make_args(prob, mw, su, link, records, n, nullptr, nullptr);
       if (prob->v_max <= 2)
-        hipLaunchKernelGGL(k_alg1_insert<2>, dim3(ins_grid), dim3(WAVE), su.big.lds_bytes, stream,
-                           sa, a, tbuf);
+        hipLaunchKernelGGL((k_alg1_moves<2, true>), dim3(wgrid), dim3(WAVE), mw.lds_bytes, stream,
+                           sw, am, tbuf);
       else
-        hipLaunchKernelGGL(k_alg1_insert<8>, dim3(ins_grid), dim3(WAVE), su.big.lds_bytes, stream,
-                           sa, a, tbuf);
+        hipLaunchKernelGGL((k_alg1_moves<8, true>), dim3(wgrid), dim3(WAVE), mw.lds_bytes, stream,
+                           sw, am, tbuf);
       if ((rc = launch_ok())) return rc;
     }
     if ((rc = sim_batch_run<XB>(prob, layer_costs, nullptr, link, a.nb_rec, nb,

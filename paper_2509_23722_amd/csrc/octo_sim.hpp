@@ -435,6 +435,25 @@ __device__ __forceinline__ LStream lstream(const Chunks<VMAX>& c, int kind, int 
   x.fl = need | (kind == KF ? LS_F | LS_PAR : kind == KB ? LS_F | LS_B | LS_PAR : 0u) << 8;
   return x;
 }
+// The same stream in the mirrored graph (every edge reversed, each queue run back to front), whose
+// finishes are the tails of the original: an op's longest path to the end, itself included. A
+// backward reads the row of stage s - 1 (needing its F bit: B(s - 1) has run), a forward that of
+// stage s + 1, the last one its own backward's, and a weight gradient has no producer. Needs the
+// output transfer times (cF, cB) and full rows (a W reads its own, still empty slot).
+template <int VMAX>
+__device__ __forceinline__ LStream lstream_mirror(const Chunks<VMAX>& c, int kind, int k, int lg,
+                                                  int g) {
+  LStream x;
+  const int own = c.base[k], off = kind == KF ? c.brow[k] : kind == KB ? c.frow[k] : 0;
+  x.base = (uint32_t)((own + off) << lg | g) | (uint32_t)(own << lg | g) << 16;
+  x.w = (uint32_t)(kind == KF ? c.cF[k] : kind == KB ? c.cB[k] : 0);
+  x.dur = (uint32_t)(kind == KF ? c.dF[k] : kind == KB ? c.dB[k] : c.dW[k]);
+  const uint32_t need = kind == KF   ? (uint32_t)c.bmask[k] << 5
+                        : kind == KB ? (uint32_t)c.fmask[k] << 5
+                                     : 0u;
+  x.fl = need | (kind == KF ? LS_F | LS_B | LS_PAR : kind == KB ? LS_F | LS_PAR : 0u) << 8;
+  return x;
+}
 // Whether every weight and duration of the lane's chunks fits the streams.
 template <int VMAX>
 __device__ __forceinline__ bool lstreams_fit(const Chunks<VMAX>& c) {
@@ -455,7 +474,9 @@ struct LStreams {
   LStream f[REG ? VMAX : 1], b[REG ? VMAX : 1], wg[REG ? VMAX : 1];
   const uint8_t* rec;
   int vm;
+  template <bool MIRROR = false>
   __device__ __forceinline__ void init(const Chunks<VMAX>& c, int v, int lg, int g, uint8_t* lds) {
+    static_assert(!(REG && MIRROR), "mirrored streams are kept in LDS");
     if constexpr (REG) {
 #pragma unroll
       for (int k = 0; k < VMAX; ++k) {
@@ -470,7 +491,8 @@ struct LStreams {
 #pragma unroll
         for (int k = 0; k < VMAX; ++k)
           if (k < v) {
-            const LStream x = lstream<VMAX>(c, kind, k, lg, g);
+            const LStream x = MIRROR ? lstream_mirror<VMAX>(c, kind, k, lg, g)
+                                     : lstream<VMAX>(c, kind, k, lg, g);
             *reinterpret_cast<uint4*>(p + (kind * v + k) * 1024) =
                 make_uint4(x.base, x.w, x.dur, x.fl);
           }
@@ -511,36 +533,71 @@ struct LStreams {
 // spans of eight entries, the last one in flight while the rounds consume the first two; a window
 // of the next four entries, shifted as they are taken and refilled every four rounds (a lane takes
 // at most one entry a round).
+// REV: the row's n entries back to front (position p is entry n - 1 - p; s1 and s2 are the spans
+// before s0, and the window's next entry is its high end).
+template <bool REV>
 struct LeanQueue {
   const uint4* row;
-  int qmax, q, pn;  // last span of the row; span of s0; position after the current entry
+  int qmax, q, pn, n;  // last span of the row; span of s0; position after the current entry
   uint4 s0, s1, s2;
   uint64_t win;
-  __device__ __forceinline__ void init(const uint16_t* r, int cap) {
+  __device__ __forceinline__ int entry_of(int p) const {
+    const int x = n - 1 - p;
+    return x > 0 ? x : 0;
+  }
+  __device__ __forceinline__ uint32_t init(const uint16_t* r, int cap, int n_) {
     row = reinterpret_cast<const uint4*>(r);
-    qmax = (cap >> 3) - 1;
-    q = 0, pn = 1;
-    s0 = row[0], s1 = row[qmax < 1 ? qmax : 1], s2 = row[qmax < 2 ? qmax : 2];
-    win = 0;
+    qmax = (cap >> 3) - 1, n = n_;
+    pn = 1, win = 0;
+    if constexpr (REV) {
+      const int x = entry_of(0);
+      q = x >> 3;
+      s0 = row[q], s1 = row[q > 1 ? q - 1 : 0], s2 = row[q > 2 ? q - 2 : 0];
+      const uint64_t d = (x & 4) ? (uint64_t)s0.z | (uint64_t)s0.w << 32
+                                 : (uint64_t)s0.x | (uint64_t)s0.y << 32;
+      return (uint32_t)(d >> (x & 3) * 16) & 0xFFFFu;
+    } else {
+      q = 0;
+      s0 = row[0], s1 = row[qmax < 1 ? qmax : 1], s2 = row[qmax < 2 ? qmax : 2];
+      return s0.x & 0xFFFFu;
+    }
   }
   // every eighth round: the spans move up when the first is used up, and the third is requested
   __device__ __forceinline__ void spans() {
-    const int nq = pn >> 3;
+    const int nq = REV ? entry_of(pn) >> 3 : pn >> 3;
     const bool up = nq != q;
     s0.x = up ? s1.x : s0.x, s0.y = up ? s1.y : s0.y, s0.z = up ? s1.z : s0.z, s0.w = up ? s1.w : s0.w;
     s1.x = up ? s2.x : s1.x, s1.y = up ? s2.y : s1.y, s1.z = up ? s2.z : s1.z, s1.w = up ? s2.w : s1.w;
     q = nq;
-    const int n2 = nq + 2;
-    s2 = row[n2 < qmax ? n2 : qmax];
+    const int n2 = REV ? nq - 2 : nq + 2;
+    s2 = row[REV ? (n2 > 0 ? n2 : 0) : n2 < qmax ? n2 : qmax];
   }
-  // every fourth round: the window from entry pn on (pn - 8 q <= 11)
+  // every fourth round: the window from entry pn on (pn - 8 q <= 11; REV: at least 4 above the
+  // start of s1)
   __device__ __forceinline__ void refill() {
-    const int o = pn - 8 * q;
-    const uint64_t d0 = (uint64_t)s0.x | (uint64_t)s0.y << 32, d1 = (uint64_t)s0.z | (uint64_t)s0.w << 32;
-    const uint64_t d2 = (uint64_t)s1.x | (uint64_t)s1.y << 32, d3 = (uint64_t)s1.z | (uint64_t)s1.w << 32;
-    const uint64_t lo = o < 4 ? d0 : o < 8 ? d1 : d2, hi = o < 4 ? d1 : o < 8 ? d2 : d3;
-    const int sh = (o & 3) * 16;
-    win = lo >> sh | (hi << 1) << (63 - sh);
+    const uint64_t a0 = (uint64_t)s0.x | (uint64_t)s0.y << 32, a1 = (uint64_t)s0.z | (uint64_t)s0.w << 32;
+    const uint64_t b0 = (uint64_t)s1.x | (uint64_t)s1.y << 32, b1 = (uint64_t)s1.z | (uint64_t)s1.w << 32;
+    if constexpr (REV) {
+      int o = entry_of(pn) - 8 * (q - 1) - 3;  // the lowest of the four, in (s1, s0)
+      o = o > 0 ? o : 0;
+      const uint64_t lo = o < 4 ? b0 : o < 8 ? b1 : o < 12 ? a0 : a1;
+      const uint64_t hi = o < 4 ? b1 : o < 8 ? a0 : a1;
+      const int sh = (o & 3) * 16;
+      win = lo >> sh | (hi << 1) << (63 - sh);
+    } else {
+      const int o = pn - 8 * q;
+      const uint64_t lo = o < 4 ? a0 : o < 8 ? a1 : b0, hi = o < 4 ? a1 : o < 8 ? b0 : b1;
+      const int sh = (o & 3) * 16;
+      win = lo >> sh | (hi << 1) << (63 - sh);
+    }
+  }
+  __device__ __forceinline__ uint32_t next() const {
+    return REV ? (uint32_t)(win >> 48) : (uint32_t)win & 0xFFFFu;
+  }
+  __device__ __forceinline__ void take(bool ok) {
+    if constexpr (REV) win <<= ok ? 16 : 0;
+    else win >>= ok ? 16 : 0;
+    pn += ok ? 1 : 0;
   }
 };
 
@@ -577,13 +634,13 @@ __device__ __forceinline__ LeanOp lean_decode(uint32_t e, bool last, const LStre
 
 // One round; decodes the entry at the window's low end as the next op. Returns whether the lane
 // ran its op.
-template <int VMAX, int X, bool REG>
-__device__ __forceinline__ bool lean_round(LeanQueue& Q, const LStreams<VMAX, REG>& S,
+template <int VMAX, int X, bool REG, bool REV>
+__device__ __forceinline__ bool lean_round(LeanQueue<REV>& Q, const LStreams<VMAX, REG>& S,
                                            const Ring& ring, const Table40& T, LeanOp& c, Lane& L,
                                            const Chunks<VMAX>& ch) {
   const uint32_t lo = T.lo[c.rd];
   const uint32_t hi = T.hi[c.rd];
-  LeanOp n = lean_decode<VMAX, X, REG>((uint32_t)Q.win & 0xFFFFu, Q.pn >= L.nops, S, ring, T.lg, L, ch);
+  LeanOp n = lean_decode<VMAX, X, REG>(Q.next(), Q.pn >= L.nops, S, ring, T.lg, L, ch);
   __asm__ volatile("" : "+v"(n.rd), "+v"(n.wr), "+v"(n.want), "+v"(n.state));
   const bool ok = (hi & c.mask) == c.want;
   unsigned cy, cz;
@@ -611,8 +668,7 @@ __device__ __forceinline__ bool lean_round(LeanQueue& Q, const LStreams<VMAX, RE
     c.nd = ok ? n.nd : c.nd;
   }
   L.clock = ok ? fin : L.clock;
-  Q.win >>= ok ? 16 : 0;
-  Q.pn += ok ? 1 : 0;
+  Q.take(ok);
   c.rd = ok ? n.rd : c.rd, c.wr = ok ? n.wr : c.wr;
   c.mask = ok ? n.mask : c.mask, c.want = ok ? n.want : c.want, c.state = ok ? n.state : c.state;
   c.w = ok ? n.w : c.w, c.dur = ok ? n.dur : c.dur;
@@ -623,23 +679,23 @@ __device__ __forceinline__ bool lean_round(LeanQueue& Q, const LStreams<VMAX, RE
 // The rounds of one evaluation over a queue row of capacity cap (see relax): unrolled eight
 // times, settled when no lane ran an op in the last of eight rounds (a round after one in which
 // no lane moved changes nothing either).
-template <int VMAX, int X, bool REG>
+template <int VMAX, int X, bool REG, bool REV = false>
 __device__ __forceinline__ void relax_lean(const uint16_t* row, int cap,
                                            const LStreams<VMAX, REG>& S, const Chunks<VMAX>& ch,
                                            const Ring& ring, Lane& L, const Table40& T, int G,
                                            uint64_t gbit, uint64_t lsb, bool& dead) {
-  LeanQueue Q;
-  Q.init(row, cap);
-  LeanOp c = lean_decode<VMAX, X, REG>(Q.s0.x & 0xFFFFu, L.nops <= 0, S, ring, T.lg, L, ch);
+  LeanQueue<REV> Q;
+  const uint32_t e0 = Q.init(row, cap, L.nops);
+  LeanOp c = lean_decode<VMAX, X, REG>(e0, L.nops <= 0, S, ring, T.lg, L, ch);
   for (;;) {
     Q.spans();
     Q.refill();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) lean_round<VMAX, X, REG>(Q, S, ring, T, c, L, ch);
+    for (int u = 0; u < 4; ++u) lean_round<VMAX, X, REG, REV>(Q, S, ring, T, c, L, ch);
     Q.refill();
 #pragma unroll
-    for (int u = 0; u < 3; ++u) lean_round<VMAX, X, REG>(Q, S, ring, T, c, L, ch);
-    if (__ballot(lean_round<VMAX, X, REG>(Q, S, ring, T, c, L, ch)) == 0) break;
+    for (int u = 0; u < 3; ++u) lean_round<VMAX, X, REG, REV>(Q, S, ring, T, c, L, ch);
+    if (__ballot(lean_round<VMAX, X, REG, REV>(Q, S, ring, T, c, L, ch)) == 0) break;
   }
   const uint64_t actm = __ballot(c.want != LS_NEVER);
   if (actm != 0 && (fold_groups(actm, G, lsb) & gbit)) dead = true;

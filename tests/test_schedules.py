@@ -190,3 +190,42 @@ def test_tuner_skips(P, v_max, M, L):
     np.testing.assert_array_equal(ms, r[1])
     np.testing.assert_array_equal(bub, r[2])
     np.testing.assert_array_equal(acc, r[3])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,v_max,M,L,big", [
+    (2, 1, 4, 5, 0), (3, 2, 6, 9, 0), (4, 1, 33, 9, 0), (2, 3, 5, 11, 0), (8, 2, 16, 20, 0),
+    # weights or durations past 32 bits; times past 37 bits: every move is evaluated
+    (4, 1, 6, 9, 33), (3, 2, 9, 8, 33), (4, 2, 64, 12, 31),
+])
+def test_alg1_moves(P, v_max, M, L, big):
+    """Algorithm 1 with its scheduling moves bounded first (only those that may shorten the
+    makespan are evaluated) against the oracle's search, which evaluates every one."""
+    import torch
+    from oracle import alg1 as A
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(500 + 10 * P + M + big)
+    print(f"alg1 moves: P={P} v_max={v_max} M={M} L={L} big={big}", flush=True)
+    # few distinct costs: many ties and several critical paths
+    costs = rng.integers(0, 4, size=(L, 3)).astype(np.int64) * 1000
+    link = rng.integers(0, 3, size=(P, P)).astype(np.int64) * 1500
+    if big:
+        costs[rng.integers(0, L)] += 1 << big
+        link[0, P - 1] += 1 << big
+    n, iters, mp = 24, 8, 3
+    recs = I.random_candidates(rng, L, P, v_max, M, n, max_pert=mp, pert_rate=0.3)
+    gp = _lib.problem(L, P, v_max, M, recs.shape[1], mp)
+    rp = R.problem(L, P, v_max, M, recs.shape[1], mp)
+    for flags in (0, _lib.A1_INSERT, _lib.A1_INSERT | _lib.A1_RANDOM):
+        rec = torch.from_numpy(recs.copy()).cuda()
+        ms, bub, stats, _ = _lib.alg1_tune_ex(gp, torch.from_numpy(costs).cuda(),
+                                              torch.from_numpy(link).cuda(), rec, iters, flags, 5)
+        torch.cuda.synchronize()
+        r = A.tune(rp, costs, link, recs, iters, nthreads=NTHREADS,
+                   insert=bool(flags & _lib.A1_INSERT), random_search=bool(flags & _lib.A1_RANDOM), seed=5)
+        np.testing.assert_array_equal(rec.cpu().numpy(), r[0])
+        np.testing.assert_array_equal(ms.cpu().numpy(), r[1])
+        np.testing.assert_array_equal(bub.cpu().numpy(), r[2])
+        np.testing.assert_array_equal(stats.cpu().numpy()[:, :3], r[3])
