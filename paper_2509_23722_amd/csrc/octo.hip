@@ -99,6 +99,7 @@ struct SimArgs {
   // slots, rounds until every device has started}
   const uint32_t* stab;
   const int32_t* smeta;
+  bool pipe;  // the v = 1 classes are k_pipe's
   // k_sched over MERGE bins: the stage rows of v = sr_v (null: none), S + 1 rows of sr_rowlen[split]
   // entries from sr_off[split], of which sr_steps[split] are steps
   const uint32_t* srow;
@@ -630,7 +631,7 @@ __global__ void __launch_bounds__(CLS_THREADS) k_classify(SimArgs a, uint8_t* __
         bin = r.n_pert > 0 ? BIN_MAT + mat_sub(r.v, r.split) : bin_of(r.v, r.gen, r.split);
         if (a.smeta) {
           const int sc = static_class(a.pr, heads + threadIdx.x * hb + 3 + a.pr.s_max, r);
-          if (sc >= 0 && a.smeta[4 * sc] != 0) bin = BIN_STATIC + sc;
+          if (sc >= 0 && ((a.pipe && sc < 2) || a.smeta[4 * sc] != 0)) bin = BIN_STATIC + sc;
         }
       }
       bins[i] = (uint8_t)bin;
@@ -1450,8 +1451,9 @@ __global__ void __launch_bounds__(WAVE) k_sched(SimArgs a, int sbase, int lbase,
   const uint32_t lcell = lb + (uint32_t)lbase + (uint32_t)lane_id() * 8u;  // XS: link cells
   uint8_t* rec = st_smem + rbase + gg * a.rec_stride;
   // the bins' counts, first positions and chunk ranges, one bin per lane
-  constexpr int C0 = NR == 1 && VC > 2 ? NSC2 : 0;  // first class of this launch
-  constexpr int NB = NR > 1 ? 2 : VC > 2 ? NSC - NSC2 : NSC2;
+  // the classes of this launch (v <= 2: from a.sr_v on, the earlier ones having another kernel)
+  const int C0 = NR > 1 ? 0 : VC > 2 ? NSC2 : a.sr_v;
+  const int NB = NR > 1 ? 2 : VC > 2 ? NSC - NSC2 : NSC2 - C0;
   const int ci = lane_id();
   const int bin_i = NR == 1 ? BIN_STATIC + C0 + ci : bin_of(a.sr_v, GEN_MERGE, ci == 0 ? 1 : 0);
   const int cnt_i = ci < NB ? a.ctl[CTL_COUNTS + bin_i] : 0;
@@ -1596,6 +1598,225 @@ __global__ void __launch_bounds__(WAVE) k_sched(SimArgs a, int sbase, int lbase,
       }
     }
     __asm__ volatile("" ::: "memory");
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// v = 1 interleaved orders (1F1B, and the split one with deferred W) as a systolic array: lane =
+// stage, no tables, no LDS in the rounds. Give F(s, m) the round s + 2m and B(s, m) the round
+// 2S - 1 - s + 2m: then every device's ops follow its queue (warm-up min(S-1-s, M) forwards, then
+// F, B pairs), and every op's input, F(s-1, m) or B(s+1, m), was produced one round earlier — it is
+// the neighbour lane's latest output, which one DPP exchange brings. In even rounds the even
+// stages run forwards and the odd ones backwards, in odd rounds the other way round, so each lane
+// alternates between two fixed {weight, duration} pairs. W(s, i - lag), lag = s, follows B(s, i) on
+// its own device and feeds nobody: it only moves the clock. Idle rounds exist only before round 2S
+// (3S when split: until every lane has passed its lag) and from round 2M on; the steady ones need
+// no test.
+// Times are doubles holding integers: every weight and duration is below 2^32 (else the candidate
+// goes to the 64-bit redo list), so a time is below 3 * 64 * 2047 * 2^33 < 2^53 and every sum and
+// maximum is exact; an add, a max and an add cost one instruction each (64-bit integers: two,
+// three and two).
+// Lanes: a row of 16 holds 16 / G groups (G = the power of two >= P, at least 2), even stages in
+// its first eight lanes, odd stages in the last eight, so that one exchange is a rotation by 8 and
+// the other by 9 (even stages) or 7 (odd ones). P <= 16.
+// XM: closed form — a device holds at most min(S - s, M) micro-batches (split: min(S, M), the lag
+// adds s). XB: a device's first op is F(s, 0), in round s. XS: the output's transfer queues on its
+// link (forward outputs and backward outputs of a device use different links), and the arrival is
+// what the neighbour reads, with weight 0.
+// Bound by VALU issue: 6 instructions a round (3 of them the exchange) against 13 and three LDS
+// accesses of the class schedules' entries.
+// ---------------------------------------------------------------------------------------------
+constexpr int PIPE_MAX = 16;           // devices
+constexpr double PIPE_NONE = -4.0e18;  // weight of an op without a cross-device input
+// x moved by a DPP control in the banks of the mask; elsewhere `old`, or anything without one.
+template <int CTRL, int BANKS>
+__device__ __forceinline__ double dpp64(double old, double x) {
+  const uint64_t o = __builtin_bit_cast(uint64_t, old), v = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)o, (int)(uint32_t)v,
+                                                            CTRL, 0xF, BANKS, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(o >> 32),
+                                                            (int)(uint32_t)(v >> 32), CTRL, 0xF,
+                                                            BANKS, false);
+  return __builtin_bit_cast(double, (uint64_t)lo | (uint64_t)hi << 32);
+}
+template <int CTRL, int BANKS>
+__device__ __forceinline__ double dpp64(double x) {
+  const uint64_t v = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, CTRL, 0xF, BANKS, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), CTRL, 0xF, BANKS,
+                                                         false);
+  return __builtin_bit_cast(double, (uint64_t)lo | (uint64_t)hi << 32);
+}
+constexpr int DPP_ROR = 0x120;  // row_ror:n — a lane reads the lane n below it, modulo 16
+
+// State of a lane: clock (its last op's end, W included), out (what its neighbours read).
+template <int X, bool SPLIT>
+struct PipeLane {
+  double clk, out;
+  double w[2], d[2], g[2];   // by round parity: weight, duration, W's duration after the op
+  double c[2], lf[2];        // XS: the output's transfer time, its link's free time
+  double fs;                 // XB
+};
+template <int X, bool SPLIT, int PAR>
+__device__ __forceinline__ double pipe_in(const PipeLane<X, SPLIT>& p) {
+  // even rounds: stage s reads s - 1 (s even) or s + 1 (s odd); odd rounds: the other neighbour
+  if constexpr (PAR == 0)
+    return dpp64<DPP_ROR + 7, 0xC>(dpp64<DPP_ROR + 9, 0xF>(p.out), p.out);
+  else
+    return dpp64<DPP_ROR + 8, 0xF>(p.out);
+}
+__device__ __forceinline__ double dmax(double a, double b) { return __builtin_fmax(a, b); }
+
+// One round; TEST: the lane runs its op only if `run` (and its W only if `wrun`).
+template <int X, bool SPLIT, int PAR, bool TEST>
+__device__ __forceinline__ void pipe_round(PipeLane<X, SPLIT>& p, bool run, bool wrun, bool first) {
+  const double in = pipe_in<X, SPLIT, PAR>(p);
+  const double beg = dmax(p.clk, in + p.w[PAR]);
+  const double fin = beg + p.d[PAR];
+  double out = fin;
+  if constexpr (X == XS) {
+    out = dmax(fin, p.lf[PAR]) + p.c[PAR];
+    if constexpr (TEST) p.lf[PAR] = run ? out : p.lf[PAR];
+    else p.lf[PAR] = out;
+  }
+  double clk = fin;
+  if constexpr (SPLIT) clk = TEST ? fin + (wrun ? p.g[PAR] : 0.0) : fin + p.g[PAR];
+  if constexpr (TEST) {
+    p.out = run ? out : p.out;
+    p.clk = run ? clk : p.clk;
+    if constexpr (X == XB) p.fs = first ? beg : p.fs;
+  } else {
+    p.out = out;
+    p.clk = clk;
+  }
+}
+
+template <int X, bool SPLIT>
+__device__ __forceinline__ void pipe_run(PipeLane<X, SPLIT>& p, int S, int M, int s) {
+  const int fpar = s & 1;  // parity of the lane's forward rounds
+  auto tested = [&](int r0, int r1) {  // rounds [r0, r1), both even
+    for (int r = r0; r < r1; r += 2) {
+      // micro-batch of the lane's forward and backward in these two rounds
+      const int rf = r + fpar, rb = r + (fpar ^ 1);
+      const int mf = (rf - s) >> 1, mb = (rb - (2 * S - 1 - s)) >> 1;
+      const bool okf = mf >= 0 && mf < M, okb = mb >= 0 && mb < M, okw = okb && mb >= s;
+      const bool fst = okf && mf == 0;
+      pipe_round<X, SPLIT, 0, true>(p, fpar == 0 ? okf : okb, fpar != 0 && okw, fpar == 0 && fst);
+      pipe_round<X, SPLIT, 1, true>(p, fpar == 1 ? okf : okb, fpar != 1 && okw, fpar == 1 && fst);
+    }
+  };
+  const int r1 = SPLIT ? (3 * S + 1) & ~1 : 2 * S, r2 = 2 * M > r1 ? 2 * M : r1;
+  const int end = 2 * S + 2 * M - 2;
+  tested(0, r1 < end ? r1 : end);
+  auto steady = [&]() {
+    pipe_round<X, SPLIT, 0, false>(p, true, true, false);
+    pipe_round<X, SPLIT, 1, false>(p, true, true, false);
+  };
+  int r = r1;
+  for (; r + 8 <= r2; r += 8) steady(), steady(), steady(), steady();
+  for (; r < r2; r += 2) steady();
+  tested(r2, end);
+}
+
+template <int X>
+__global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int P = a.pr.P, M = a.pr.M, L = a.pr.L, S = P;
+  // layer prefix sums and links: every lane reads its stage's entries
+  int64_t* pre = reinterpret_cast<int64_t*>(smem);
+  int64_t* link = pre + 3 * (L + 1);
+  for (int i = lane_id(); i < 3 * (L + 1); i += WAVE) pre[i] = a.pre[i];
+  for (int i = lane_id(); i < P * P; i += WAVE) link[i] = a.link[i];
+  __syncthreads();
+  const int h = a.G >> 1, x = lane_id() & 15;
+  const int s = 2 * ((x & 7) & (h - 1)) + (x >> 3);
+  const int g = (lane_id() >> 4) * (8 / h) + (x & 7) / h;
+  // the two bins (fused, split) and their chunk ranges, one bin per lane
+  const int ci = lane_id();
+  const int cnt_i = ci < 2 ? a.ctl[CTL_COUNTS + BIN_STATIC + ci] : 0;
+  const int start_i = ci < 2 ? a.ctl[CTL_START + BIN_STATIC + ci] : 0;
+  const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
+  const int nch0 = __shfl(nch_i, 0, WAVE), nch1 = __shfl(nch_i, 1, WAVE);
+  // chunks by grid stride, the longer (split) ones first
+  for (int ch = (int)blockIdx.x; ch < nch0 + nch1; ch += (int)gridDim.x) {
+    const int split = ch < nch1 ? 1 : 0;
+    const int cnt = __shfl(cnt_i, split, WAVE), pos0 = __shfl(start_i, split, WAVE);
+    const int e = (split ? ch : ch - nch1) * a.CPW + g;
+    const int64_t cand = e < cnt ? (int64_t)a.idx[pos0 + e] : -1;
+    const bool mine = cand >= 0 && s < P;
+    int d = 0;
+    int64_t f = 0, b = 0, wg = 0, wF = 0, wB = 0, cF = 0, cB = 0, act = 0, stat = 0;
+    if (mine) {
+      const uint8_t* rec = a.cands + cand * a.pr.stride;
+      const uint8_t* bnd = rec + 4;
+      const uint8_t* dev = rec + 3 + a.pr.s_max;
+      const int b0 = s > 0 ? bnd[s - 1] : 0, b1 = s < S - 1 ? bnd[s] : L;
+      d = dev[s];
+      const int dp = s > 0 ? dev[s - 1] : d, dn = s < S - 1 ? dev[s + 1] : d;
+      f = pre[3 * b1] - pre[3 * b0];
+      b = pre[3 * b1 + 1] - pre[3 * b0 + 1];
+      wg = pre[3 * b1 + 2] - pre[3 * b0 + 2];
+      wF = s > 0 ? link[dp * P + d] : 0, wB = s < S - 1 ? link[dn * P + d] : 0;
+      if constexpr (X == XS)
+        cF = s < S - 1 ? link[d * P + dn] : 0, cB = s > 0 ? link[d * P + dp] : 0;
+      if constexpr (X == XM) {
+        act = a.pre_mem[2 * b1] - a.pre_mem[2 * b0];
+        stat = a.pre_mem[2 * b1 + 1] - a.pre_mem[2 * b0 + 1];
+      }
+    }
+    const int64_t dB = split ? b : b + wg;
+    const bool fits =
+        ((uint64_t)f | (uint64_t)dB | (uint64_t)wg | (uint64_t)wF | (uint64_t)wB) >> 32 == 0;
+    // the group's lanes: xor over the stage pairs, then over the two halves
+    const auto group_or = [&](int y) {
+      for (int o = 1; o < h; o <<= 1) y |= __shfl_xor(y, o, WAVE);
+      return y | __shfl_xor(y, 8, WAVE);
+    };
+    const bool wide = group_or(mine && !fits) != 0;
+    const int fpar = s & 1;
+    // an idle lane (or a wide candidate's) keeps clock 0: no input, no duration
+    const bool on = mine && !wide;
+    const double xF = on && s > 0 ? (X == XS ? 0.0 : (double)wF) : PIPE_NONE;
+    const double xB = on && s < S - 1 ? (X == XS ? 0.0 : (double)wB) : PIPE_NONE;
+    const double dF = on ? (double)f : 0.0, dBd = on ? (double)dB : 0.0;
+    const double dW = on && split ? (double)wg : 0.0;
+    double ms = 0.0, fs = 0.0, clk = 0.0;
+    auto run = [&](auto tag) {
+      constexpr bool SPLIT = decltype(tag)::value;
+      PipeLane<X, SPLIT> p;
+      p.clk = p.out = 0.0, p.fs = -1.0;
+      p.w[0] = fpar ? xB : xF, p.w[1] = fpar ? xF : xB;
+      p.d[0] = fpar ? dBd : dF, p.d[1] = fpar ? dF : dBd;
+      p.g[0] = fpar ? dW : 0.0, p.g[1] = fpar ? 0.0 : dW;
+      p.c[0] = on ? (double)(fpar ? cB : cF) : 0.0, p.c[1] = on ? (double)(fpar ? cF : cB) : 0.0;
+      p.lf[0] = p.lf[1] = 0.0;
+      pipe_run<X, SPLIT>(p, S, M, s);
+      // the W's still deferred
+      if (SPLIT) p.clk += (double)(s < M ? s : M) * dW;
+      clk = p.clk, fs = p.fs;
+    };
+    if (split) run(std::true_type{});
+    else run(std::false_type{});
+    ms = clk;
+    for (int o = 1; o < h; o <<= 1) ms = dmax(ms, __shfl_xor(ms, o, WAVE));
+    ms = dmax(ms, __shfl_xor(ms, 8, WAVE));
+    if (mine) {
+      if (wide) {
+        if (s == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
+      } else {
+        const int64_t m = (int64_t)ms;
+        if (s == 0) a.out_ms[cand] = m;
+        a.out_bub[cand * P + d] = m - (f + b + wg) * M;
+        if constexpr (X == XM) {
+          const int held = split ? (S < M ? S : M) : (S - s < M ? S - s : M);
+          a.out_peak[cand * P + d] = stat + (act > 0 ? act * held : 0);
+        }
+        if constexpr (X == XB) {
+          a.out_bound[(cand * P + d) * 2] = (int64_t)fs;
+          a.out_bound[(cand * P + d) * 2 + 1] = (int64_t)clk;
+        }
+      }
+    }
   }
 }
 
@@ -4799,6 +5020,7 @@ SimArgs make_args(const octo_problem* prob, const Plan& pl, const Setup& su, con
   a.strm_off = pl.strm_off;
   a.stab = nullptr;
   a.smeta = nullptr;
+  a.pipe = false;
   a.srow = nullptr;
   a.sr_v = 0;
   for (int i = 0; i < 2; ++i) a.sr_off[i] = 0, a.sr_rowlen[i] = 0, a.sr_steps[i] = 0;
@@ -4831,6 +5053,7 @@ int launch_sched(const SimArgs& base, const Setup& su, int64_t n, int v, hipStre
   const int rbase = lbase + (X == XS ? (2 * VC + 1) * WAVE * 8 : 0);
   const int lds = rbase + a.CPW * a.rec_stride;
   if (lds > su.di.lds_max) return OCTO_EUNSUPPORTED;  // at most 72 KB within the size limits
+  if (NR == 1) a.sr_v = VC <= 2 && a.pipe ? 2 : 0;  // first class
   if (NR > 1) {
     const StGeom& g = su.ws->sg;
     a.srow = reinterpret_cast<const uint32_t*>(static_cast<const char*>(su.ws->st) + g.rows);
@@ -4846,6 +5069,22 @@ int launch_sched(const SimArgs& base, const Setup& su, int64_t n, int v, hipStre
   grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
   hipLaunchKernelGGL((k_sched<NR, VC, X>), dim3(grid), dim3(WAVE), lds, stream, a, sbase, lbase,
                      rbase);
+  return launch_ok();
+}
+
+// Launch k_pipe over the v = 1 class bins.
+template <int X>
+int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, hipStream_t stream) {
+  SimArgs a = base;
+  a.G = std::max(2, lanes_per_candidate(a.pr.P));
+  a.CPW = WAVE / a.G;
+  const int lds = (3 * (a.pr.L + 1) + a.pr.P * a.pr.P) * 8;
+  int grid = 0;
+  int rc = occupancy_grid(k_pipe<X>, lds, su.di.cus, &grid);
+  if (rc) return rc;
+  const int64_t need = (n + a.CPW - 1) / a.CPW;
+  grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
+  hipLaunchKernelGGL(k_pipe<X>, dim3(grid), dim3(WAVE), lds, stream, a);
   return launch_ok();
 }
 
@@ -5071,6 +5310,8 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
     const char* st = static_cast<const char*>(su.ws->st);
     a.stab = reinterpret_cast<const uint32_t*>(st);
     a.smeta = reinterpret_cast<const int32_t*>(st + su.ws->sg.meta);
+    // (the communication tally needs more per op than the systolic rounds have room for)
+    a.pipe = X != XC && prob->P <= PIPE_MAX;
   }
   if ((rc = classify_sort(prob, su, a, n, stream))) return rc;
   // generated INTER / MERGE queues, one launch per v with finish tables sized for it (ring
@@ -5084,7 +5325,10 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   uint64_t taken = 0;  // MERGE bins that the stage rows cover
   if constexpr (X != XR) {
     if (sched) {
-      if ((rc = launch_sched<1, 2, X>(a, su, n, 0, stream))) return rc;
+      if constexpr (X != XC)
+        if (a.pipe && (rc = launch_pipe<X>(a, su, n, stream))) return rc;
+      if ((!a.pipe || prob->v_max >= 2) && (rc = launch_sched<1, 2, X>(a, su, n, 0, stream)))
+        return rc;
       if (prob->v_max >= 3 && (rc = launch_sched<1, 8, X>(a, su, n, 0, stream))) return rc;
       for (int v = 2; v <= prob->v_max; ++v) {
         if (!su.ws->sg.sr_ok[v]) continue;
