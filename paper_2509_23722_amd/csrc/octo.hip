@@ -589,6 +589,30 @@ __device__ __forceinline__ int64_t live_count(const SimArgs& a) {
   return l < a.n ? l : a.n;
 }
 
+// Work bin of record i (head: its staged first bytes); writes the sentinels of an invalid one
+// (BIN_NONE).
+__device__ __forceinline__ int classify_record(const SimArgs& a, int64_t i, const uint8_t* head) {
+  const Resolved r = resolve_record(a.pr, head, a.cands + i * a.pr.stride + pert_off(a.pr.s_max));
+  if (!r.valid) {
+    a.out_ms[i] = OCTO_MS_INVALID;
+    for (int d = 0; d < a.pr.P; ++d) a.out_bub[i * a.pr.P + d] = OCTO_MS_INVALID;
+    if (a.out_peak)
+      for (int d = 0; d < a.pr.P; ++d) a.out_peak[i * a.pr.P + d] = OCTO_MS_INVALID;
+    if (a.out_comm)
+      for (int k = 0; k < 4; ++k) a.out_comm[i * 4 + k] = OCTO_MS_INVALID;
+    if (a.out_bound)
+      for (int k = 0; k < 2 * a.pr.P; ++k) a.out_bound[i * 2 * a.pr.P + k] = OCTO_MS_INVALID;
+    return BIN_NONE;
+  }
+  if (r.n_pert > 0) return BIN_MAT + mat_sub(r.v, r.split);
+  if (a.smeta || a.pipe) {
+    const int sc = static_class(a.pr, head + 3 + a.pr.s_max, r);
+    if (sc >= 0 && ((a.pipe && sc < 2) || (a.smeta && a.smeta[4 * sc] != 0)))
+      return BIN_STATIC + sc;
+  }
+  return bin_of(r.v, r.gen, r.split);
+}
+
 // One thread per candidate, blocks of CLS_THREADS taking CLS_ITEMS runs of CLS_THREADS
 // candidates each, so that each block adds its bin counts to the global counters once for all
 // its runs (one global atomic per bin and block: with one block per run, thousands of blocks
@@ -616,24 +640,7 @@ __global__ void __launch_bounds__(CLS_THREADS) k_classify(SimArgs a, uint8_t* __
     const int64_t i = first + threadIdx.x;
     int bin = BIN_NONE;
     if (threadIdx.x < cnt) {
-      const Resolved r = resolve_record(a.pr, heads + threadIdx.x * hb,
-                                        a.cands + i * a.pr.stride + pert_off(a.pr.s_max));
-      if (!r.valid) {
-        a.out_ms[i] = OCTO_MS_INVALID;
-        for (int d = 0; d < a.pr.P; ++d) a.out_bub[i * a.pr.P + d] = OCTO_MS_INVALID;
-        if (a.out_peak)
-          for (int d = 0; d < a.pr.P; ++d) a.out_peak[i * a.pr.P + d] = OCTO_MS_INVALID;
-        if (a.out_comm)
-          for (int k = 0; k < 4; ++k) a.out_comm[i * 4 + k] = OCTO_MS_INVALID;
-        if (a.out_bound)
-          for (int k = 0; k < 2 * a.pr.P; ++k) a.out_bound[i * 2 * a.pr.P + k] = OCTO_MS_INVALID;
-      } else {
-        bin = r.n_pert > 0 ? BIN_MAT + mat_sub(r.v, r.split) : bin_of(r.v, r.gen, r.split);
-        if (a.smeta) {
-          const int sc = static_class(a.pr, heads + threadIdx.x * hb + 3 + a.pr.s_max, r);
-          if (sc >= 0 && ((a.pipe && sc < 2) || a.smeta[4 * sc] != 0)) bin = BIN_STATIC + sc;
-        }
-      }
+      bin = classify_record(a, i, heads + threadIdx.x * hb);
       bins[i] = (uint8_t)bin;
     }
     wave_hist_add(hist, bin, bin != BIN_NONE);
@@ -685,6 +692,82 @@ __global__ void __launch_bounds__(CLS_THREADS) k_scatter(SimArgs a, const uint8_
 #pragma unroll
   for (int run = 0; run < CLS_ITEMS; ++run)
     if (bin[run] != BIN_NONE) idx[res[bin[run]] + local[run]] = (int32_t)(first + run * CLS_THREADS);
+}
+
+// Inclusive prefix sum over a wave.
+template <class T>
+__device__ __forceinline__ T wave_scan(T x) {
+  const int l = lane_id();
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const T y = __shfl_up(x, o, WAVE);
+    x += l >= o ? y : (T)0;
+  }
+  return x;
+}
+
+// A small batch's k_prep, k_classify, k_plan and k_scatter in one block of FRONT_THREADS threads
+// (up to FRONT_MAX records): each of those kernels takes about as long as its launch there.
+constexpr int FRONT_THREADS = 1024, FRONT_MAX = 4096;
+__global__ void __launch_bounds__(FRONT_THREADS) k_front(SimArgs a, const int64_t* __restrict__ costs,
+                                                         const int64_t* __restrict__ mem,
+                                                         int64_t* __restrict__ pre,
+                                                         int64_t* __restrict__ pre_mem,
+                                                         int32_t* __restrict__ idx, int hb) {
+  extern __shared__ __align__(16) uint8_t heads[];
+  __shared__ int hist[2 * WAVE], first[2 * WAVE];
+  static_assert(NBINS <= 2 * WAVE, "two lanes' worth of bins");
+  const int t = (int)threadIdx.x, L = a.pr.L;
+  for (int i = t; i < CTL_WORDS; i += FRONT_THREADS) a.ctl[i] = 0;
+  if (t < 2 * WAVE) hist[t] = 0;
+  // prefix sums: one wave per column
+  const int col = t / WAVE;
+  if (col < 3 || (mem && col < 5)) {
+    const int64_t* src = col < 3 ? costs + col : mem + (col - 3);
+    int64_t* dst = col < 3 ? pre + col : pre_mem + (col - 3);
+    const int st = col < 3 ? 3 : 2;
+    int64_t acc = 0;
+    if (lane_id() == 0) dst[0] = 0;
+    for (int l0 = 0; l0 < L; l0 += WAVE) {
+      const int l = l0 + lane_id();
+      const int64_t x = wave_scan<int64_t>(l < L ? src[(int64_t)st * l] : 0) + acc;
+      if (l < L) dst[(int64_t)st * (l + 1)] = x;
+      acc = __shfl(x, WAVE - 1, WAVE);
+    }
+  }
+  const int n = (int)live_count(a);
+  const int q = hb / 16, stride16 = a.pr.stride / 16;
+  int bin[FRONT_MAX / FRONT_THREADS], local[FRONT_MAX / FRONT_THREADS];
+#pragma unroll
+  for (int run = 0; run < FRONT_MAX / FRONT_THREADS; ++run) {
+    const int i0 = run * FRONT_THREADS;
+    bin[run] = BIN_NONE, local[run] = 0;
+    if (i0 >= n) continue;  // (uniform)
+    const int cnt = n - i0 < FRONT_THREADS ? n - i0 : FRONT_THREADS;
+    const uint4* src = reinterpret_cast<const uint4*>(a.cands + (int64_t)i0 * a.pr.stride);
+    uint4* dst = reinterpret_cast<uint4*>(heads);
+    __syncthreads();  // the previous run's heads are read
+    for (int j = t; j < cnt * q; j += FRONT_THREADS) {
+      const int r = j / q, c = j - r * q;
+      dst[j] = src[(int64_t)r * stride16 + c];
+    }
+    __syncthreads();
+    if (t < cnt) bin[run] = classify_record(a, i0 + t, heads + t * hb);
+    local[run] = wave_hist_add(hist, bin[run], bin[run] != BIN_NONE);
+  }
+  __syncthreads();
+  if (t < WAVE) {  // first position of every bin
+    const int c0 = hist[t], c1 = hist[WAVE + t];
+    const int e0 = wave_scan<int>(c0), s0 = __shfl(e0, WAVE - 1, WAVE);
+    const int e1 = wave_scan<int>(c1) + s0;
+    first[t] = e0 - c0, first[WAVE + t] = e1 - c1;
+    a.ctl[CTL_COUNTS + t] = c0, a.ctl[CTL_START + t] = e0 - c0;
+    if (WAVE + t < NBINS) a.ctl[CTL_COUNTS + WAVE + t] = c1, a.ctl[CTL_START + WAVE + t] = e1 - c1;
+    if (t == WAVE - 1) a.ctl[CTL_TOTAL] = e1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int run = 0; run < FRONT_MAX / FRONT_THREADS; ++run)
+    if (bin[run] != BIN_NONE) idx[first[bin[run]] + local[run]] = run * FRONT_THREADS + t;
 }
 
 // The chunks of the bins in `mask` (bins < nbins <= 64), one bin per lane: its candidate count,
@@ -1627,6 +1710,7 @@ __global__ void __launch_bounds__(WAVE) k_sched(SimArgs a, int sbase, int lbase,
 // accesses of the class schedules' entries.
 // ---------------------------------------------------------------------------------------------
 constexpr int PIPE_MAX = 16;           // devices
+constexpr int64_t PIPE_GPIPE_MAX = 1 << 17;  // batch size up to which GPipe rows are k_pipe's
 constexpr double PIPE_NONE = -4.0e18;  // weight of an op without a cross-device input
 // x moved by a DPP control in the banks of the mask; elsewhere `old`, or anything without one.
 template <int CTRL, int BANKS>
@@ -1718,8 +1802,44 @@ __device__ __forceinline__ void pipe_run(PipeLane<X, SPLIT>& p, int S, int M, in
   tested(r2, end);
 }
 
+// GPipe rows on the same lanes (small batches, where k_afab's one lane per candidate leaves the
+// chip idle): F(s, m) in round s + m, then B(s, m) in round S - 1 - s + m of a second pass, every
+// producer one round before its consumer.
 template <int X>
-__global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a) {
+__device__ __forceinline__ void pipe_gpipe(PipeLane<X, false>& p, int S, int M, int s) {
+  auto pass = [&](auto tag, int at) {
+    constexpr int PAR = decltype(tag)::value;  // which pair of weights and durations: 0 F, 1 B
+    const int end = M + S - 1;
+    auto round = [&](bool test, int r) {
+      // forwards read stage s - 1, backwards stage s + 1
+      const double in = PAR == 0 ? dpp64<DPP_ROR + 8, 0xC>(dpp64<DPP_ROR + 9, 0xF>(p.out), p.out)
+                                 : dpp64<DPP_ROR + 7, 0xC>(dpp64<DPP_ROR + 8, 0xF>(p.out), p.out);
+      const bool run = !test || (r >= at && r < at + M);
+      const double beg = dmax(p.clk, in + p.w[PAR]);
+      const double fin = beg + p.d[PAR];
+      double out = fin;
+      if constexpr (X == XS) {
+        out = dmax(fin, p.lf[PAR]) + p.c[PAR];
+        p.lf[PAR] = run ? out : p.lf[PAR];
+      }
+      if constexpr (X == XB && PAR == 0) p.fs = test && r == at ? beg : p.fs;
+      p.out = run ? out : p.out;
+      p.clk = run ? fin : p.clk;
+    };
+    const int r1 = S < end ? S : end, r2 = M > r1 ? M : r1;
+    for (int r = 0; r < r1; ++r) round(true, r);
+    int r = r1;
+    for (; r + 4 <= r2; r += 4) round(false, r), round(false, r + 1), round(false, r + 2), round(false, r + 3);
+    for (; r < r2; ++r) round(false, r);
+    for (; r < end; ++r) round(true, r);
+  };
+  pass(std::integral_constant<int, 0>{}, s);
+  // a lane's backward reads its neighbour's latest backward; the first reads are of no use
+  pass(std::integral_constant<int, 1>{}, S - 1 - s);
+}
+
+template <int X>
+__global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a, int gpipe) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int P = a.pr.P, M = a.pr.M, L = a.pr.L, S = P;
   // layer prefix sums and links: every lane reads its stage's entries
@@ -1731,17 +1851,20 @@ __global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a) {
   const int h = a.G >> 1, x = lane_id() & 15;
   const int s = 2 * ((x & 7) & (h - 1)) + (x >> 3);
   const int g = (lane_id() >> 4) * (8 / h) + (x & 7) / h;
-  // the two bins (fused, split) and their chunk ranges, one bin per lane
-  const int ci = lane_id();
-  const int cnt_i = ci < 2 ? a.ctl[CTL_COUNTS + BIN_STATIC + ci] : 0;
-  const int start_i = ci < 2 ? a.ctl[CTL_START + BIN_STATIC + ci] : 0;
+  // the bins (split, fused, GPipe where it is this kernel's) and their chunk ranges, one per lane
+  const int ci = lane_id(), nb = gpipe ? 3 : 2;
+  const int bin_i = ci == 2 ? bin_of(1, GEN_AFAB, 0) : BIN_STATIC + (ci == 0 ? 1 : 0);
+  const int cnt_i = ci < nb ? a.ctl[CTL_COUNTS + bin_i] : 0;
+  const int start_i = ci < nb ? a.ctl[CTL_START + bin_i] : 0;
   const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
-  const int nch0 = __shfl(nch_i, 0, WAVE), nch1 = __shfl(nch_i, 1, WAVE);
+  const int end0 = __shfl(nch_i, 0, WAVE), end1 = end0 + __shfl(nch_i, 1, WAVE);
+  const int end2 = end1 + __shfl(nch_i, 2, WAVE);
   // chunks by grid stride, the longer (split) ones first
-  for (int ch = (int)blockIdx.x; ch < nch0 + nch1; ch += (int)gridDim.x) {
-    const int split = ch < nch1 ? 1 : 0;
-    const int cnt = __shfl(cnt_i, split, WAVE), pos0 = __shfl(start_i, split, WAVE);
-    const int e = (split ? ch : ch - nch1) * a.CPW + g;
+  for (int ch = (int)blockIdx.x; ch < end2; ch += (int)gridDim.x) {
+    const int ib = ch < end0 ? 0 : ch < end1 ? 1 : 2;
+    const int split = ib == 0 ? 1 : 0;
+    const int cnt = __shfl(cnt_i, ib, WAVE), pos0 = __shfl(start_i, ib, WAVE);
+    const int e = (ch - (ib == 0 ? 0 : ib == 1 ? end0 : end1)) * a.CPW + g;
     const int64_t cand = e < cnt ? (int64_t)a.idx[pos0 + e] : -1;
     const bool mine = cand >= 0 && s < P;
     int d = 0;
@@ -1795,8 +1918,19 @@ __global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a) {
       if (SPLIT) p.clk += (double)(s < M ? s : M) * dW;
       clk = p.clk, fs = p.fs;
     };
-    if (split) run(std::true_type{});
-    else run(std::false_type{});
+    if (ib == 2) {
+      PipeLane<X, false> p;
+      p.clk = p.out = 0.0, p.fs = -1.0;
+      p.w[0] = xF, p.w[1] = xB, p.d[0] = dF, p.d[1] = dBd;
+      p.c[0] = on ? (double)cF : 0.0, p.c[1] = on ? (double)cB : 0.0;
+      p.lf[0] = p.lf[1] = 0.0;
+      pipe_gpipe<X>(p, S, M, s);
+      clk = p.clk, fs = p.fs;
+    } else if (split) {
+      run(std::true_type{});
+    } else {
+      run(std::false_type{});
+    }
     ms = clk;
     for (int o = 1; o < h; o <<= 1) ms = dmax(ms, __shfl_xor(ms, o, WAVE));
     ms = dmax(ms, __shfl_xor(ms, 8, WAVE));
@@ -1808,8 +1942,8 @@ __global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a) {
         if (s == 0) a.out_ms[cand] = m;
         a.out_bub[cand * P + d] = m - (f + b + wg) * M;
         if constexpr (X == XM) {
-          const int held = split ? (S < M ? S : M) : (S - s < M ? S - s : M);
-          a.out_peak[cand * P + d] = stat + (act > 0 ? act * held : 0);
+          const int held = ib == 2 ? M : split ? (S < M ? S : M) : (S - s < M ? S - s : M);
+          a.out_peak[cand * P + d] = stat + (act > 0 || ib == 2 ? act * held : 0);
         }
         if constexpr (X == XB) {
           a.out_bound[(cand * P + d) * 2] = (int64_t)fs;
@@ -4321,6 +4455,7 @@ struct StGeom {
   size_t meta, rows, bytes;  // byte offsets, total
   SrGeom sr;
   bool sr_ok[9];
+  bool inter_ok[9];  // the interleaved order's class schedules of v are valid
 };
 
 struct Workspace {
@@ -4706,6 +4841,39 @@ int stage_steps(int S, int M, int split) {
   return steps;
 }
 
+// Whether k_static_build's schedule of the interleaved order (looped, P devices, v stages each) is
+// valid: the same lockstep rounds, counting the values alive between their producer's and their
+// reader's round.
+bool inter_schedule_fits(int P, int M, int v, int split) {
+  if (v >= 2 && M % P != 0) return true;  // no such record is valid
+  const int S = P * v, n = (split ? 3 : 2) * v * M, neg = sc_neg(sc_slots(P, v));
+  std::vector<char> done((size_t)2 * S * M, 0);
+  std::vector<GenInter> g(P);
+  std::vector<int> pos(P, 0);
+  std::vector<size_t> now;
+  for (int c = 0; c < P; ++c) g[c].init(P, v, M, c, split, split ? c : 0);
+  int live = 0, left = P;
+  for (int round = 0; left > 0; ++round) {
+    if (round >= sc_round_cap(P, M, v)) return false;
+    now.clear();
+    for (int c = 0; c < P; ++c) {
+      if (pos[c] == n) continue;
+      const int kind = g[c].kind, m = g[c].m, s = c + g[c].k * P;
+      const int ps = kind == KF ? s - 1 : kind == KB ? s + 1 : -1;
+      const bool cross = ps >= 0 && ps < S;
+      if (cross && !done[((size_t)kind * S + ps) * M + m]) continue;
+      if (cross && P > 1) --live;  // read, and nobody else's
+      if (kind != KW) now.push_back(((size_t)kind * S + s) * M + m);
+      if (P > 1 && ((kind == KF && s < S - 1) || (kind == KB && s > 0))) ++live;
+      if (++pos[c] == n) --left;
+      g[c].advance(true);
+    }
+    if (live > neg) return false;
+    for (size_t x : now) done[x] = 1;
+  }
+  return true;
+}
+
 // Geometry of the static schedules for a problem (cached in the workspace).
 const StGeom& st_geom(const octo_problem* p, Workspace& ws) {
   if (ws.sg_P == p->P && ws.sg_vmax == p->v_max && ws.sg_M == p->M) return ws.sg;
@@ -4714,6 +4882,8 @@ const StGeom& st_geom(const octo_problem* p, Workspace& ws) {
   const int last = p->v_max >= 3 ? NSC2 + 2 * (p->v_max - 2) : NSC2;
   g.meta = align_up((size_t)sc_offset(P, M, last) * 4, 256);
   g.rows = g.meta + align_up(NSC * 16, 256);
+  for (int v = 1; v <= p->v_max; ++v)
+    g.inter_ok[v] = inter_schedule_fits(P, M, v, 0) && inter_schedule_fits(P, M, v, 1);
   int64_t off = 0;
   for (int v = 2; v <= p->v_max; ++v) {
     g.sr_ok[v] = true;
@@ -4889,9 +5059,10 @@ int scratch_regions(const octo_problem* prob, int dev, int64_t n, Setup* su) {
 // noalloc: take every buffer from the device's static scratch (octo_sim_batch_noalloc) instead
 // of the grow-only workspace; the persistent materialised-queue launches are then narrowed to
 // the queue rows that fit, and a batch whose other buffers do not fit is OCTO_ESCRATCH.
+// prep: launch k_prep (else the caller's k_front does its work).
 int prepare(const octo_problem* prob, const int64_t* costs, const int64_t* mem,
             hipStream_t stream, int64_t n, Setup* su, int64_t extra_slots = 0,
-            bool noalloc = false) {
+            bool noalloc = false, bool prep = true) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return OCTO_EHIP;
   int rc = dev_info(dev, &su->di);
@@ -4934,11 +5105,13 @@ int prepare(const octo_problem* prob, const int64_t* costs, const int64_t* mem,
   if (rc) return rc;
   su->ws = &ws;
   char* base = static_cast<char*>(ws.base);
-  hipLaunchKernelGGL(k_prep, dim3(1), dim3(256), 0, stream, costs, mem, prob->L,
-                     reinterpret_cast<int64_t*>(base + su->l.pre),
-                     reinterpret_cast<int64_t*>(base + su->l.pre_mem),
-                     reinterpret_cast<int32_t*>(base + su->l.ctl));
-  if ((rc = launch_ok())) return rc;
+  if (prep) {
+    hipLaunchKernelGGL(k_prep, dim3(1), dim3(256), 0, stream, costs, mem, prob->L,
+                       reinterpret_cast<int64_t*>(base + su->l.pre),
+                       reinterpret_cast<int64_t*>(base + su->l.pre_mem),
+                       reinterpret_cast<int32_t*>(base + su->l.ctl));
+    if ((rc = launch_ok())) return rc;
+  }
   if (prob->v_max >= 2) {
     void* old = ws.mt;
     rc = ensure_buf(ws.mt, ws.mt_bytes, std::max<size_t>(mtab_entries(prob) * 4, 256), stream);
@@ -5072,9 +5245,9 @@ int launch_sched(const SimArgs& base, const Setup& su, int64_t n, int v, hipStre
   return launch_ok();
 }
 
-// Launch k_pipe over the v = 1 class bins.
+// Launch k_pipe over the v = 1 class bins (gpipe: and the v = 1 GPipe bin).
 template <int X>
-int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, hipStream_t stream) {
+int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, bool gpipe, hipStream_t stream) {
   SimArgs a = base;
   a.G = std::max(2, lanes_per_candidate(a.pr.P));
   a.CPW = WAVE / a.G;
@@ -5084,7 +5257,7 @@ int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, hipStream_t str
   if (rc) return rc;
   const int64_t need = (n + a.CPW - 1) / a.CPW;
   grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
-  hipLaunchKernelGGL(k_pipe<X>, dim3(grid), dim3(WAVE), lds, stream, a);
+  hipLaunchKernelGGL(k_pipe<X>, dim3(grid), dim3(WAVE), lds, stream, a, gpipe ? 1 : 0);
   return launch_ok();
 }
 
@@ -5130,12 +5303,12 @@ int launch_sim(const octo_problem* prob, const Setup& su, const int64_t* link, c
   return launch_ok();
 }
 
-// Launch k_afab over the AFAB bins of every v: one lane per candidate, each lane's row of M
+// Launch k_afab over the AFAB bins of v >= v_lo: one lane per candidate, each lane's row of M
 // int64 plus 2 P device words in LDS (at most 64 KiB per wave).
 template <int X>
 int launch_afab(const octo_problem* prob, const Setup& su, const int64_t* link, const void* cands,
                 int64_t n, int64_t* ms, int64_t* bub, int64_t* peak, int64_t* comm,
-                int64_t* bound, hipStream_t stream) {
+                int64_t* bound, int v_lo, hipStream_t stream) {
   // rows as line envelopes (plain, memory and bounds variants); the communication and
   // serialised-link variants, which need every op, keep rows of exactly 32 or 64 micro-batches
   // in registers and other lengths (and the communication variant's, whose unrolled sweep would
@@ -5165,7 +5338,7 @@ int launch_afab(const octo_problem* prob, const Setup& su, const int64_t* link, 
   SimArgs a = make_args(prob, su.big, su, link, cands, n, ms, bub, peak);
   a.out_comm = comm;
   a.out_bound = bound;
-  a.bin_mask = bins_of(1, prob->v_max, true);
+  a.bin_mask = bins_of(v_lo, prob->v_max, true);
   a.work = CTL_WORK + 3;
   int grid = 0;
   const int64_t need = (n + lanes - 1) / lanes;
@@ -5293,7 +5466,9 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   constexpr bool MEM = X == XM;
   if (n == 0) return OCTO_OK;
   Setup su;
-  int rc = prepare(prob, layer_costs, MEM ? layer_mem : nullptr, stream, n, &su, 0, noalloc);
+  const bool front = n <= FRONT_MAX;
+  int rc = prepare(prob, layer_costs, MEM ? layer_mem : nullptr, stream, n, &su, 0, noalloc,
+                   !front);
   if (rc) return rc;
   int64_t* pk = MEM ? ex.peak : nullptr;
   int64_t* cm = X == XC ? ex.comm : nullptr;
@@ -5306,27 +5481,43 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   // (asynchronous transfers only: blocking ones change the order of execution)
   const bool sched = X != XR && su.sched;
   if (sched) {
-    if ((rc = build_static(prob, *su.ws, stream))) return rc;
-    const char* st = static_cast<const char*>(su.ws->st);
-    a.stab = reinterpret_cast<const uint32_t*>(st);
-    a.smeta = reinterpret_cast<const int32_t*>(st + su.ws->sg.meta);
     // (the communication tally needs more per op than the systolic rounds have room for)
     a.pipe = X != XC && prob->P <= PIPE_MAX;
+    if (!a.pipe || prob->v_max >= 2) {
+      if ((rc = build_static(prob, *su.ws, stream))) return rc;
+      const char* st = static_cast<const char*>(su.ws->st);
+      a.stab = reinterpret_cast<const uint32_t*>(st);
+      a.smeta = reinterpret_cast<const int32_t*>(st + su.ws->sg.meta);
+    }
   }
-  if ((rc = classify_sort(prob, su, a, n, stream))) return rc;
+  if (front) {
+    char* base = static_cast<char*>(su.ws->base);
+    const int hb = (int)align_up((size_t)pert_off(prob->P * prob->v_max), 16);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_front),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, FRONT_THREADS * hb);
+    hipLaunchKernelGGL(k_front, dim3(1), dim3(FRONT_THREADS),
+                       (size_t)std::min<int64_t>(n, FRONT_THREADS) * hb, stream, a, layer_costs,
+                       MEM ? layer_mem : nullptr, reinterpret_cast<int64_t*>(base + su.l.pre),
+                       reinterpret_cast<int64_t*>(base + su.l.pre_mem),
+                       reinterpret_cast<int32_t*>(base + su.l.idx), hb);
+    if ((rc = launch_ok())) return rc;
+  } else if ((rc = classify_sort(prob, su, a, n, stream))) {
+    return rc;
+  }
   // generated INTER / MERGE queues, one launch per v with finish tables sized for it (ring
   // rows of the next power of two >= P v where the in-flight bound allows): v = 2, v = 1, then
   // v = 3..8; then AFAB queues; then materialised queues (perturbations, 64-bit redo).
-  compute_inflight(prob, *su.ws);
-  if (X != XS && X != XR && (rc = build_qtab(prob, *su.ws, su.di.lds_max, X != XP, stream)))
-    return rc;
   const int P = prob->P, M = prob->M;
   if ((rc = record_mark(0, stream))) return rc;
-  uint64_t taken = 0;  // MERGE bins that the stage rows cover
+  // GPipe rows at v = 1 run in k_pipe while k_afab, one lane per candidate, would leave most of the
+  // chip idle: 32,768 of them at P = 8, M = 32 take 21.6 us there and 6 here, 131,072 at M = 64
+  // about 30 and 45
+  const bool gpipe = a.pipe && n <= PIPE_GPIPE_MAX;
+  uint64_t taken = 0;  // bins that the schedules and k_pipe cover
   if constexpr (X != XR) {
     if (sched) {
       if constexpr (X != XC)
-        if (a.pipe && (rc = launch_pipe<X>(a, su, n, stream))) return rc;
+        if (a.pipe && (rc = launch_pipe<X>(a, su, n, gpipe, stream))) return rc;
       if ((!a.pipe || prob->v_max >= 2) && (rc = launch_sched<1, 2, X>(a, su, n, 0, stream)))
         return rc;
       if (prob->v_max >= 3 && (rc = launch_sched<1, 8, X>(a, su, n, 0, stream))) return rc;
@@ -5339,27 +5530,42 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
         if (rc) return rc;
         taken |= 1ull << bin_of(v, GEN_MERGE, 0) | 1ull << bin_of(v, GEN_MERGE, 1);
       }
+      for (int v = 1; v <= prob->v_max; ++v)
+        if ((v == 1 && a.pipe) || su.ws->sg.inter_ok[v])
+          taken |= 1ull << bin_of(v, GEN_INTER, 0) | 1ull << bin_of(v, GEN_INTER, 1);
+      taken |= 1ull << bin_of(1, GEN_MERGE, 0) | 1ull << bin_of(1, GEN_MERGE, 1);  // (no such queue)
     }
   }
   if ((rc = record_mark(1, stream))) return rc;
-  if (prob->v_max >= 2 &&
+  // what is left takes the generated-queue kernels
+  const uint64_t left1 = bins_of(1, 1, false) & ~taken;
+  const uint64_t left2 = prob->v_max >= 2 ? bins_of(2, 2, false) & ~taken : 0;
+  const uint64_t left8 = prob->v_max >= 3 ? bins_of(3, prob->v_max, false) & ~taken : 0;
+  if (left1 | left2 | left8) compute_inflight(prob, *su.ws);
+  if (X != XS && X != XR && (left1 | left2) &&
+      (rc = build_qtab(prob, *su.ws, su.di.lds_max, X != XP, stream)))
+    return rc;
+  if (left2 &&
       (rc = launch_sim<2, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
-                             2 * P, 2 * P, bins_of(2, 2, false) & ~taken, CTL_WORK + 1, stream)))
+                             2 * P, 2 * P, left2, CTL_WORK + 1, stream)))
     return rc;
   if ((rc = record_mark(2, stream))) return rc;
-  if ((rc = launch_sim<1, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
-                             P, P, bins_of(1, 1, false), CTL_WORK + 0, stream)))
+  if (left1 &&
+      (rc = launch_sim<1, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
+                             P, P, left1, CTL_WORK + 0, stream)))
     return rc;
   if ((rc = record_mark(3, stream))) return rc;
   for (int v = 3; v <= prob->v_max; ++v)
-    if ((rc = launch_sim<8, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm,
-                               bd, P * v, P * v, bins_of(v, v, false) & ~taken, CTL_WORK_V + v - 3,
-                               stream)))
+    if ((left8 & bins_of(v, v, false)) &&
+        (rc = launch_sim<8, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm,
+                               bd, P * v, P * v, left8 & bins_of(v, v, false),
+                               CTL_WORK_V + v - 3, stream)))
       return rc;
   if ((rc = record_mark(4, stream))) return rc;
   if constexpr (X != XR) {
-    if ((rc = launch_afab<X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
-                             stream)))
+    if ((!gpipe || prob->v_max >= 2) &&
+        (rc = launch_afab<X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
+                             gpipe ? 2 : 1, stream)))
       return rc;
   } else {
     // rendezvous: GPipe queues in the generated kernels, per v class, with one slot per stage
@@ -5381,7 +5587,7 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   // candidates with moves: 40-bit rings, 40-bit full rows for those wider than the ring, then
   // the 64-bit redo list
   bool m40_any = false;
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int pass = 0; pass < 2 && prob->max_pert > 0; ++pass) {
     const Plan& pl = pass == 0 ? su.m40 : su.m40f;
     // a ring as long as M needs no second pass; nor does a ring pass that did not fit (then
     // the full rows do not fit either and the 64-bit kernel takes every perturbed candidate)

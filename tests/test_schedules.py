@@ -229,3 +229,41 @@ def test_alg1_moves(P, v_max, M, L, big):
         np.testing.assert_array_equal(ms.cpu().numpy(), r[1])
         np.testing.assert_array_equal(bub.cpu().numpy(), r[2])
         np.testing.assert_array_equal(stats.cpu().numpy()[:, :3], r[3])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,M,n", [
+    (1, 1, 1), (1, 5, 40), (2, 1, 200), (2, 9, 200), (3, 2, 200), (3, 8, 300), (4, 3, 300),
+    (5, 11, 300), (7, 6, 300), (8, 8, 300), (8, 7, 300), (8, 40, 300), (9, 17, 300), (11, 36, 300),
+    (15, 4, 300), (16, 15, 300), (16, 50, 300), (17, 20, 300),
+    # one block's classification: its largest batches and the first of the general path's
+    (8, 9, 1023), (8, 9, 1025), (4, 4, 4096), (4, 4, 4097),
+])
+@pytest.mark.parametrize("call", ["plain", "mem", "serial", "bounds", "comm"])
+def test_one_stage_per_device(P, M, n, call):
+    """v = 1: every policy, with fewer micro-batches than stages, as many, and more."""
+    import torch
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(11000 + 100 * P + M + n)
+    print(f"one stage per device: {call} P={P} M={M} n={n}", flush=True)
+    L = P + int(rng.integers(1, 20))
+    costs = rng.integers(0, 1 << 31, size=(L, 3)).astype(np.int64) // (4 if M & 1 else 4000)
+    link = rng.integers(0, 1 << 30, size=(P, P)).astype(np.int64) // (1 if M & 1 else 2000)
+    mem = rng.integers(-5, 1 << 40, size=(L, 2)).astype(np.int64)
+    mem[:, 1] = np.abs(mem[:, 1])
+    recs = I.random_candidates(rng, L, P, 1, M, n, invalid_rate=0.05)
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    gp = _lib.problem(L, P, 1, M, recs.shape[1], 0)
+    rp = R.problem(L, P, 1, M, recs.shape[1], 0)
+    if call == "mem":
+        g = _lib.sim_batch_mem(gp, t(costs), t(mem), t(link), t(recs))
+        r = R.sim_batch_mem(rp, costs, mem, link, recs, nthreads=NTHREADS)
+    else:
+        name = "sim_batch" if call == "plain" else "sim_batch_" + call
+        g = getattr(_lib, name)(gp, t(costs), t(link), t(recs))
+        r = getattr(R, name)(rp, costs, link, recs, nthreads=NTHREADS)
+    torch.cuda.synchronize()
+    for x, y in zip(g, r):
+        np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
