@@ -99,7 +99,7 @@ struct SimArgs {
   // slots, rounds until every device has started}
   const uint32_t* stab;
   const int32_t* smeta;
-  bool pipe;  // the v = 1 classes are k_pipe's
+  bool pipe, pipe2;  // the v = 1 classes are k_pipe's, the v = 2 interleaved ones k_pipe2's
   // k_sched over MERGE bins: the stage rows of v = sr_v (null: none), S + 1 rows of sr_rowlen[split]
   // entries from sr_off[split], of which sr_steps[split] are steps
   const uint32_t* srow;
@@ -607,7 +607,8 @@ __device__ __forceinline__ int classify_record(const SimArgs& a, int64_t i, cons
   if (r.n_pert > 0) return BIN_MAT + mat_sub(r.v, r.split);
   if (a.smeta || a.pipe) {
     const int sc = static_class(a.pr, head + 3 + a.pr.s_max, r);
-    if (sc >= 0 && ((a.pipe && sc < 2) || (a.smeta && a.smeta[4 * sc] != 0)))
+    if (sc >= 0 && ((a.pipe && sc < 2) || (a.pipe2 && sc >= 2 && sc < 4) ||
+                    (a.smeta && a.smeta[4 * sc] != 0)))
       return BIN_STATIC + sc;
   }
   return bin_of(r.v, r.gen, r.split);
@@ -1947,6 +1948,350 @@ __global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a, int gpipe) {
         }
         if constexpr (X == XB) {
           a.out_bound[(cand * P + d) * 2] = (int64_t)fs;
+          a.out_bound[(cand * P + d) * 2 + 1] = (int64_t)clk;
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// v = 2 interleaved orders (looped) as a systolic array: lane = rank r. With N = 2M virtual
+// micro-batches, give F index j of rank r the pair step j + r and B index i the pair step
+// i + (P - 1 - r) + 2P - 1, F before B in a step. That is every device's queue order (B_0 falls in
+// the step of F_w, w = 2(P-1-r) + P the warm-up), and each input is the previous step's output of
+// the neighbour on the ring of ranks: F reads rank r - 1 (rank 0, chunk 1: rank P - 1's chunk 0), B
+// reads rank r + 1 (rank P - 1, chunk 0: rank 0's chunk 1). W's index in step t is
+// t - (3P - 2) on every rank (the lag r cancels the skew), up to the flush. One rank per step
+// enters its next chunk for F, one for B. Doubles holding integers, as in k_pipe.
+// The exchange is a rotation by one lane: DPP at P = 16 (ROT), else ds_bpermute.
+// XB: a rank's first op is F index 0, in step r. Plain and bounds variants. (Serial links, 131,072
+// candidates at P = 8, M = 64: 399 us with the links' times here, 369 on the class schedules.)
+// ---------------------------------------------------------------------------------------------
+template <bool ROT>
+__device__ __forceinline__ double ring_shift(double x, int from, bool fwd) {
+  if constexpr (ROT) {
+    return fwd ? dpp64<DPP_ROR + 1, 0xF>(x) : dpp64<DPP_ROR + 15, 0xF>(x);
+  } else {
+    const uint64_t v = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(v >> 32));
+    return __builtin_bit_cast(double, (uint64_t)lo | (uint64_t)hi << 32);
+  }
+}
+
+template <int X>
+struct Pipe2Lane {
+  double clk, oF, oB;                      // clock, latest forward and backward outputs
+  double wF, dF, wF1, dF1;                 // current and other chunk's forward
+  double wB, dB, wB1, dB1;                 // ... and backward
+  double fs;                               // XB
+};
+
+template <int X, bool SPLIT, bool ROT>
+__device__ __forceinline__ double pipe2_run(Pipe2Lane<X>& p, int P, int M, int r, double dW0,
+                                            double dW1) {
+  const int N = 2 * M, skew = 3 * P - 2;
+  const int row = lane_id() - r;
+  const int left = (row + (r > 0 ? r - 1 : P - 1)) * 4, right = (row + (r < P - 1 ? r + 1 : 0)) * 4;
+  int nf = r;                         // steps until this rank's next forward chunk
+  int nb = P - 1 - r + 2 * P - 1;     // ... and backward chunk (from its first ones)
+  // W chunk of index u = t - skew: backward index u's, 1 first, changing every P steps
+  int nw = P;
+  double dw = dW1, dwo = dW0;
+  auto step = [&](auto test, int t) {
+    constexpr bool TEST = decltype(test)::value;
+    const double iF = ring_shift<ROT>(p.oF, left, true), iB = ring_shift<ROT>(p.oB, right, false);
+    // the chunk pairs start swapped: the first chunk is entered with the first op
+    const bool sf = nf == 0, sb = nb == 0;
+    nf = sf ? P - 1 : nf - 1, nb = sb ? P - 1 : nb - 1;
+    auto swap = [](bool c, double& a, double& b) {
+      const double x = c ? b : a, y = c ? a : b;
+      a = x, b = y;
+    };
+    swap(sf, p.wF, p.wF1), swap(sf, p.dF, p.dF1), swap(sb, p.wB, p.wB1), swap(sb, p.dB, p.dB1);
+    const int j = t - r, i = t - (P - 1 - r) - (2 * P - 1);
+    const bool okF = !TEST || (j >= 0 && j < N), okB = !TEST || (i >= 0 && i < N);
+    {
+      const double beg = dmax(p.clk, iF + p.wF), fin = beg + p.dF;
+      if constexpr (X == XB) p.fs = TEST && j == 0 ? beg : p.fs;
+      p.oF = okF ? fin : p.oF;
+      p.clk = okF ? fin : p.clk;
+    }
+    {
+      const double fin = dmax(p.clk, iB + p.wB) + p.dB;
+      p.oB = okB ? fin : p.oB;
+      p.clk = okB ? fin : p.clk;
+    }
+    if constexpr (SPLIT) {
+      if (!TEST || t >= skew) {
+        p.clk += dw;
+        if (--nw == 0) {
+          const double y = dw;
+          dw = dwo, dwo = y, nw = P;
+        }
+      }
+    }
+  };
+  const int t1 = skew < N + skew ? skew : N + skew, t2 = N > t1 ? N : t1;
+  for (int t = 0; t < t1; ++t) step(std::true_type{}, t);
+  int t = t1;
+  for (; t + 2 <= t2; t += 2) step(std::false_type{}, t), step(std::false_type{}, t + 1);
+  for (; t < t2; ++t) step(std::false_type{}, t);
+  for (; t < N + skew; ++t) step(std::true_type{}, t);
+  return p.clk;
+}
+
+// The same array on 32-bit integers: times relative to a moving origin, C = 2^30 + 2^26 at first. The
+// origin stands still in the first 2P - 1 steps, then moves by D, about the candidate's time per
+// step, in every step (an input was produced one step earlier, so its weight loses D), and every P
+// steps from the first W on to rank P / 2's clock. An op without an input has the weight -2^31.
+// Exact as long as the clocks stay in [0, 2^31): their extremes are kept every second
+// step; with q no less than D and the most that a step adds to a value, extremes inside
+// [2 q, 2^31 - 2 q) prove it; else the wave runs its candidates again on doubles (one wave in
+// fifty at P = 16, M = 128, stages of 5 to 25 ms; none where q is a tenth of that). The chunk of a
+// lane is a bit of a scalar mask: with bF, bB the lanes that enter their next chunk, a step costs
+// two selects, two adds and a maximum per direction, all at the full rate (doubles run at half of
+// it). At P = 16 the main loop's P steps are unrolled with constant masks.
+// 262,144 candidates at P = 16, M = 128: 656 us; on doubles 1333, on the class schedules 1282.
+struct Pipe2Int {
+  int w[2], f[2], v[2], b[2], g[2];  // F weight and duration, B weight and duration, W by chunk
+  int D;
+  int clk, oF, oB, fs, hi, lo;
+  int64_t org;                       // origin's moves to rank P / 2
+};
+constexpr int PIPE_ORG = (1 << 30) + (1 << 26);
+
+__device__ __forceinline__ int iadd(int x, int y) { return (int)((uint32_t)x + (uint32_t)y); }
+__device__ __forceinline__ int isel(uint64_t m, int x, int y) {
+  return __builtin_amdgcn_inverse_ballot_w64(m) ? x : y;
+}
+
+template <int X, bool SPLIT, bool ROT>
+__device__ __forceinline__ void pipe2_run32(Pipe2Int& p, int P, int M, int G, int r) {
+  const int N = 2 * M, skew = 3 * P - 2;
+  const int row = lane_id() - r;
+  const int left = (row + (r > 0 ? r - 1 : P - 1)) * 4, right = (row + (r < P - 1 ? r + 1 : 0)) * 4;
+  uint64_t rank0 = 0x0001000100010001ull;  // lanes of rank 0
+  if constexpr (!ROT) {
+    rank0 = 0;
+    for (int i = 0; i < WAVE; i += G) rank0 |= 1ull << i;
+  }
+  const uint64_t rankl = rank0 << (P - 1);
+  uint64_t mF = ~0ull, mB = 0, okF = 0, okB = 0, bF = rank0, bB = rankl;
+  int nd = 0;                      // -D while the origin moves
+  int dw = p.g[1], dwo = p.g[0];   // W runs chunk 1 first
+  // FW, BW: 0 no lane, 1 all, 2 those of okF / okB
+  auto step = [&](auto fw, auto bw, uint64_t tF, uint64_t tB, int dc) {
+    constexpr int FW = decltype(fw)::value, BW = decltype(bw)::value;
+    int iF = 0, iB = 0;
+    if constexpr (ROT) {
+      if constexpr (FW) iF = __builtin_amdgcn_mov_dpp(p.oF, DPP_ROR + 1, 0xF, 0xF, false);
+      if constexpr (BW) iB = __builtin_amdgcn_mov_dpp(p.oB, DPP_ROR + 15, 0xF, 0xF, false);
+    } else {
+      if constexpr (FW) iF = __builtin_amdgcn_ds_bpermute(left, p.oF);
+      if constexpr (BW) iB = __builtin_amdgcn_ds_bpermute(right, p.oB);
+    }
+    if constexpr (FW) {
+      mF ^= tF;
+      const int in = iadd(iF, isel(mF, p.w[1], p.w[0]));
+      const int beg = in > p.clk ? in : p.clk;
+      if constexpr (X == XB && FW == 2 && !BW) p.fs = isel(tF & ~okF, beg, p.fs);
+      const int fin = iadd(beg, isel(mF, p.f[1], p.f[0]));
+      if constexpr (FW == 2 && !BW) okF |= tF;
+      p.oF = FW == 2 ? isel(okF, fin, p.oF) : fin;
+      p.clk = FW == 2 ? isel(okF, fin, p.clk) : fin;
+    }
+    if constexpr (BW) {
+      mB ^= tB;
+      const int in = iadd(iB, isel(mB, p.v[1], p.v[0]));
+      const int beg = in > p.clk ? in : p.clk;
+      const int fin = iadd(beg, isel(mB, p.b[1], p.b[0]));
+      p.oB = BW == 2 ? isel(okB, fin, p.oB) : fin;
+      p.clk = BW == 2 ? isel(okB, fin, p.clk) : fin;
+    }
+    p.clk = iadd(p.clk, dc);
+  };
+  auto range = [&]() {
+    p.hi = p.clk > p.hi ? p.clk : p.hi;
+    p.lo = p.clk < p.lo ? p.clk : p.lo;
+  };
+  auto origin = [&]() {
+    const int y = iadd(__builtin_amdgcn_ds_bpermute((row + P / 2) * 4, p.clk), -PIPE_ORG);
+    p.org += y;
+    p.clk = iadd(p.clk, -y), p.oF = iadd(p.oF, -y), p.oB = iadd(p.oB, -y);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  // steps t .. e - 1 of one kind (bB is the lanes of rank 3 P - 2 - t modulo P)
+  auto run = [&](auto fw, auto bw, int t, int e, auto before) {
+    for (; t < e; ++t) {
+      before();
+      step(fw, bw, bF, bB, SPLIT && t >= skew ? iadd(dw, nd) : nd);
+      if (t & 1) range();
+      bF = bF == rankl ? rank0 : bF << 1;
+      bB = bB == rank0 ? rankl : bB >> 1;
+      if (t >= skew && bB == rank0) {
+        origin();
+        if constexpr (SPLIT) {
+          const int y = dw;
+          dw = dwo, dwo = y;
+        }
+      }
+    }
+  };
+  auto none = []() {};
+  bB = P > 2 ? rank0 << (P - 2) : rank0;
+  run(I2{}, I0{}, 0, 2 * P - 1, none);
+  nd = -p.D, p.clk = iadd(p.clk, nd);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    p.w[k] = p.w[k] == INT32_MIN ? p.w[k] : p.w[k] - p.D;
+    p.v[k] = p.v[k] == INT32_MIN ? p.v[k] : p.v[k] - p.D;
+  }
+  run(I1{}, I2{}, 2 * P - 1, skew, [&]() { okB |= bB; });
+  origin();
+  int t = skew;
+  if constexpr (ROT) {
+    for (; t + 16 <= N; t += 16) {
+      const int dc = SPLIT ? iadd(dw, nd) : nd;
+      auto two = [&](int u) {
+        step(I1{}, I1{}, 0x0001000100010001ull << ((14 + u) & 15),
+             0x0001000100010001ull << ((16 - u) & 15), dc);
+        step(I1{}, I1{}, 0x0001000100010001ull << ((15 + u) & 15),
+             0x0001000100010001ull << ((15 - u) & 15), dc);
+        range();
+      };
+      two(0), two(2), two(4), two(6), two(8), two(10), two(12), two(14);
+      origin();
+      if constexpr (SPLIT) {
+        const int y = dw;
+        dw = dwo, dwo = y;
+      }
+    }
+  }
+  run(I1{}, I1{}, t, N, none);
+  okF = okB = ~0ull;
+  run(I2{}, I1{}, N, N + P, [&]() { okF &= ~bF; });
+  run(I0{}, I1{}, N + P, N + 2 * P - 1, none);
+  run(I0{}, I2{}, N + 2 * P - 1, N + skew, [&]() { okB &= ~bB; });
+  range();
+}
+
+template <int X, bool ROT>
+__global__ void __launch_bounds__(WAVE) k_pipe2(SimArgs a) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int P = a.pr.P, M = a.pr.M, L = a.pr.L, S = 2 * P, G = a.G;
+  int64_t* pre = reinterpret_cast<int64_t*>(smem);
+  int64_t* link = pre + 3 * (L + 1);
+  for (int i = lane_id(); i < 3 * (L + 1); i += WAVE) pre[i] = a.pre[i];
+  for (int i = lane_id(); i < P * P; i += WAVE) link[i] = a.link[i];
+  __syncthreads();
+  const int g = lane_id() / G, x = lane_id() % G;
+  const int r = x < P ? x : 0;  // (an idle lane stands in as rank 0 and is read by nobody)
+  // the two bins (split first: longer) and their chunk ranges
+  const int ci = lane_id();
+  const int cnt_i = ci < 2 ? a.ctl[CTL_COUNTS + BIN_STATIC + 3 - ci] : 0;
+  const int start_i = ci < 2 ? a.ctl[CTL_START + BIN_STATIC + 3 - ci] : 0;
+  const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
+  const int end0 = __shfl(nch_i, 0, WAVE), end1 = end0 + __shfl(nch_i, 1, WAVE);
+  for (int ch = (int)blockIdx.x; ch < end1; ch += (int)gridDim.x) {
+    const int ib = ch < end0 ? 0 : 1, split = 1 - ib;
+    const int cnt = __shfl(cnt_i, ib, WAVE), pos0 = __shfl(start_i, ib, WAVE);
+    const int e = (ch - (ib == 0 ? 0 : end0)) * a.CPW + g;
+    const int64_t cand = g < a.CPW && e < cnt ? (int64_t)a.idx[pos0 + e] : -1;
+    const bool mine = cand >= 0 && x < P;
+    int d = 0;
+    int64_t f[2] = {0, 0}, b[2] = {0, 0}, wg[2] = {0, 0}, wF[2] = {0, 0}, wB[2] = {0, 0};
+    if (mine) {
+      const uint8_t* rec = a.cands + cand * a.pr.stride;
+      const uint8_t* bnd = rec + 4;
+      const uint8_t* dev = rec + 3 + a.pr.s_max;
+      d = dev[r];
+      const int dl = dev[r > 0 ? r - 1 : P - 1], dn = dev[r < P - 1 ? r + 1 : 0];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int s = r + k * P;
+        const int b0 = s > 0 ? bnd[s - 1] : 0, b1 = s < S - 1 ? bnd[s] : L;
+        f[k] = pre[3 * b1] - pre[3 * b0];
+        b[k] = pre[3 * b1 + 1] - pre[3 * b0 + 1];
+        wg[k] = pre[3 * b1 + 2] - pre[3 * b0 + 2];
+        wF[k] = s > 0 ? link[dl * P + d] : 0, wB[k] = s < S - 1 ? link[dn * P + d] : 0;
+      }
+    }
+    uint64_t bits = 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      bits |= (uint64_t)f[k] | (uint64_t)(split ? b[k] : b[k] + wg[k]) | (uint64_t)wg[k] |
+              (uint64_t)wF[k] | (uint64_t)wB[k];
+    uint64_t gbit, lsb;
+    group_bits(G, &gbit, &lsb);
+    const bool wide = (fold_groups(__ballot(mine && (bits >> 32) != 0), G, lsb) & gbit) != 0;
+    const bool on = mine && !wide;
+    double W[2], D[2], V[2], E[2];  // forward and backward weights and durations by chunk
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int s = r + k * P;
+      W[k] = on && s > 0 ? (double)wF[k] : PIPE_NONE;
+      V[k] = on && s < S - 1 ? (double)wB[k] : PIPE_NONE;
+      D[k] = on ? (double)f[k] : 0.0;
+      E[k] = on ? (double)(split ? b[k] : b[k] + wg[k]) : 0.0;
+    }
+    double clk = 0.0, fst = -1.0;
+    bool again = true;  // on doubles
+    if (M > P) {  // (N >= 3 P - 2: M is a multiple of P)
+      // q and the time per step, over the group
+      int64_t q = 0, per = 0;
+      auto most = [](const int64_t (&y)[2]) { return y[0] > y[1] ? y[0] : y[1]; };
+      if (on) {
+        per = (f[0] + f[1] + b[0] + b[1] + wg[0] + wg[1]) >> 1;
+        const int64_t lF = most(wF), lB = most(wB);
+        q = most(f) + most(b) + most(wg) + (lF > lB ? lF : lB);
+        q = q > per ? q : per;
+      }
+      q = group_max(q, G), per = group_max(per, G);
+      const bool ok32 = q < (int64_t)1 << 28, u = on && ok32;
+      Pipe2Int p;
+      p.D = ok32 ? (int)per : 0;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int s = r + k * P;
+        p.w[k] = u && s > 0 ? (int)wF[k] : INT32_MIN;
+        p.v[k] = u && s < S - 1 ? (int)wB[k] : INT32_MIN;
+        p.f[k] = u ? (int)f[k] : 0, p.b[k] = u ? (int)(split ? b[k] : b[k] + wg[k]) : 0;
+        p.g[k] = u ? (int)wg[k] : 0;
+      }
+      p.clk = PIPE_ORG, p.oF = p.oB = PIPE_ORG;
+      p.fs = PIPE_ORG, p.hi = INT32_MIN, p.lo = INT32_MAX, p.org = 0;
+      if (split) pipe2_run32<X, true, ROT>(p, P, M, G, r);
+      else pipe2_run32<X, false, ROT>(p, P, M, G, r);
+      clk = (double)(p.org + (p.clk - PIPE_ORG) + (int64_t)(2 * M + P) * p.D);
+      fst = (double)(p.fs - PIPE_ORG);
+      again = __ballot(on && (!ok32 || p.hi > INT32_MAX - 2 * (int)q || p.lo < 2 * (int)q)) != 0;
+    }
+    if (again) {
+      Pipe2Lane<X> p;
+      p.clk = p.oF = p.oB = 0.0, p.fs = -1.0;
+      // forwards run chunk 0 first, backwards chunk 1; each pair starts swapped
+      p.wF = W[1], p.dF = D[1], p.wF1 = W[0], p.dF1 = D[0];
+      p.wB = V[0], p.dB = E[0], p.wB1 = V[1], p.dB1 = E[1];
+      const double w0 = on ? (double)wg[0] : 0.0, w1 = on ? (double)wg[1] : 0.0;
+      clk = split ? pipe2_run<X, true, ROT>(p, P, M, r, w0, w1)
+                  : pipe2_run<X, false, ROT>(p, P, M, r, w0, w1);
+      fst = p.fs;
+    }
+    double ms = x < P ? clk : 0.0;
+    for (int o = 1; o < G; o <<= 1) ms = dmax(ms, __shfl_xor(ms, o, WAVE));
+    if (mine) {
+      if (wide) {
+        if (x == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
+      } else {
+        const int64_t m = (int64_t)ms;
+        if (x == 0) a.out_ms[cand] = m;
+        a.out_bub[cand * P + d] = m - (f[0] + b[0] + wg[0] + f[1] + b[1] + wg[1]) * M;
+        if constexpr (X == XB) {
+          a.out_bound[(cand * P + d) * 2] = (int64_t)fst;
           a.out_bound[(cand * P + d) * 2 + 1] = (int64_t)clk;
         }
       }
@@ -5193,7 +5538,7 @@ SimArgs make_args(const octo_problem* prob, const Plan& pl, const Setup& su, con
   a.strm_off = pl.strm_off;
   a.stab = nullptr;
   a.smeta = nullptr;
-  a.pipe = false;
+  a.pipe = a.pipe2 = false;
   a.srow = nullptr;
   a.sr_v = 0;
   for (int i = 0; i < 2; ++i) a.sr_off[i] = 0, a.sr_rowlen[i] = 0, a.sr_steps[i] = 0;
@@ -5226,7 +5571,8 @@ int launch_sched(const SimArgs& base, const Setup& su, int64_t n, int v, hipStre
   const int rbase = lbase + (X == XS ? (2 * VC + 1) * WAVE * 8 : 0);
   const int lds = rbase + a.CPW * a.rec_stride;
   if (lds > su.di.lds_max) return OCTO_EUNSUPPORTED;  // at most 72 KB within the size limits
-  if (NR == 1) a.sr_v = VC <= 2 && a.pipe ? 2 : 0;  // first class
+  // first class (where the v = 2 ones have another kernel, the v = 1 ones have too)
+  if (NR == 1) a.sr_v = VC > 2 ? 0 : a.pipe2 ? 4 : a.pipe ? 2 : 0;
   if (NR > 1) {
     const StGeom& g = su.ws->sg;
     a.srow = reinterpret_cast<const uint32_t*>(static_cast<const char*>(su.ws->st) + g.rows);
@@ -5258,6 +5604,22 @@ int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, bool gpipe, hip
   const int64_t need = (n + a.CPW - 1) / a.CPW;
   grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
   hipLaunchKernelGGL(k_pipe<X>, dim3(grid), dim3(WAVE), lds, stream, a, gpipe ? 1 : 0);
+  return launch_ok();
+}
+
+// Launch k_pipe2 over the v = 2 interleaved class bins.
+template <int X, bool ROT>
+int launch_pipe2(const SimArgs& base, const Setup& su, int64_t n, hipStream_t stream) {
+  SimArgs a = base;
+  a.G = lanes_per_candidate(a.pr.P);
+  a.CPW = WAVE / a.G;
+  const int lds = (3 * (a.pr.L + 1) + a.pr.P * a.pr.P) * 8;
+  int grid = 0;
+  int rc = occupancy_grid(k_pipe2<X, ROT>, lds, su.di.cus, &grid);
+  if (rc) return rc;
+  const int64_t need = (n + a.CPW - 1) / a.CPW;
+  grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
+  hipLaunchKernelGGL((k_pipe2<X, ROT>), dim3(grid), dim3(WAVE), lds, stream, a);
   return launch_ok();
 }
 
@@ -5483,6 +5845,10 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   if (sched) {
     // (the communication tally needs more per op than the systolic rounds have room for)
     a.pipe = X != XC && prob->P <= PIPE_MAX;
+    // (the memory model's running totals need 64-bit integers, and k_pipe2 with links' times was
+    // the slower one)
+    a.pipe2 = (X == XP || X == XB) && a.pipe && prob->v_max >= 2 && prob->P >= 2 &&
+              prob->M % prob->P == 0;
     if (!a.pipe || prob->v_max >= 2) {
       if ((rc = build_static(prob, *su.ws, stream))) return rc;
       const char* st = static_cast<const char*>(su.ws->st);
@@ -5518,6 +5884,10 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
     if (sched) {
       if constexpr (X != XC)
         if (a.pipe && (rc = launch_pipe<X>(a, su, n, gpipe, stream))) return rc;
+      if constexpr (X == XP || X == XB)
+        if (a.pipe2 && (rc = P == 16 ? launch_pipe2<X, true>(a, su, n, stream)
+                                     : launch_pipe2<X, false>(a, su, n, stream)))
+          return rc;
       if ((!a.pipe || prob->v_max >= 2) && (rc = launch_sched<1, 2, X>(a, su, n, 0, stream)))
         return rc;
       if (prob->v_max >= 3 && (rc = launch_sched<1, 8, X>(a, su, n, 0, stream))) return rc;
@@ -5531,7 +5901,7 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
         taken |= 1ull << bin_of(v, GEN_MERGE, 0) | 1ull << bin_of(v, GEN_MERGE, 1);
       }
       for (int v = 1; v <= prob->v_max; ++v)
-        if ((v == 1 && a.pipe) || su.ws->sg.inter_ok[v])
+        if ((v == 1 && a.pipe) || (v == 2 && a.pipe2) || su.ws->sg.inter_ok[v])
           taken |= 1ull << bin_of(v, GEN_INTER, 0) | 1ull << bin_of(v, GEN_INTER, 1);
       taken |= 1ull << bin_of(1, GEN_MERGE, 0) | 1ull << bin_of(1, GEN_MERGE, 1);  // (no such queue)
     }

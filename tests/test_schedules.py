@@ -267,3 +267,44 @@ def test_one_stage_per_device(P, M, n, call):
     torch.cuda.synchronize()
     for x, y in zip(g, r):
         np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,M,n", [
+    (2, 2, 100), (2, 8, 200), (3, 3, 200), (3, 12, 200), (4, 4, 200), (4, 20, 200), (5, 5, 200),
+    (6, 18, 200), (8, 8, 200), (8, 16, 200), (8, 64, 200), (12, 24, 200), (15, 15, 200),
+    (16, 16, 200), (16, 32, 200), (16, 64, 200), (17, 17, 200),
+])
+@pytest.mark.parametrize("call", ["plain", "mem", "serial", "bounds", "comm"])
+def test_interleaved(P, M, n, call):
+    """v = 2 looped placements under every policy, from one round of micro-batches (warm-up longer
+    than the steady part) to several; costs from hundreds (times in 32 bits throughout) past the largest for which the
+    32-bit times suffice to some past 32 bits."""
+    import torch
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(12000 + 100 * P + M)
+    print(f"interleaved: {call} P={P} M={M}", flush=True)
+    L = 2 * P + int(rng.integers(1, 20))
+    top = int(10 ** rng.uniform(2, 8))
+    costs = rng.integers(0, top, size=(L, 3)).astype(np.int64)
+    costs[L // 2] += int(rng.integers(0, 4) == 0) << 33
+    link = rng.integers(0, top // 3 + 1, size=(P, P)).astype(np.int64)
+    mem = rng.integers(0, 1 << 40, size=(L, 2)).astype(np.int64)
+    dev = np.stack([rng.permutation(P)[np.arange(2 * P) % P] for _ in range(n)])
+    pol = rng.integers(0, 4, size=n)
+    recs = I.pack_records(P, 2, 0, pol, np.full(n, 2), I.random_cuts(rng, L, 2 * P, n), dev)
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    gp = _lib.problem(L, P, 2, M, recs.shape[1], 0)
+    rp = R.problem(L, P, 2, M, recs.shape[1], 0)
+    if call == "mem":
+        g = _lib.sim_batch_mem(gp, t(costs), t(mem), t(link), t(recs))
+        r = R.sim_batch_mem(rp, costs, mem, link, recs, nthreads=NTHREADS)
+    else:
+        name = "sim_batch" if call == "plain" else "sim_batch_" + call
+        g = getattr(_lib, name)(gp, t(costs), t(link), t(recs))
+        r = getattr(R, name)(rp, costs, link, recs, nthreads=NTHREADS)
+    torch.cuda.synchronize()
+    for x, y in zip(g, r):
+        np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
