@@ -2441,7 +2441,7 @@ __device__ __forceinline__ auto group_table(uint8_t* p, int slots) {
 // Whether a kernel's rounds are the lean ones (relax_lean): 40-bit slots, no variant that needs
 // more per op. Their candidates' weights and durations have to fit 32 bits (lean_fits).
 template <int X, class Tab>
-constexpr bool LEAN = std::is_same<Tab, Table40>::value && (X == XP || X == XB || X == XT);
+constexpr bool LEAN = std::is_same<Tab, Table40>::value && (X == XP || X == XB || X == XT || X == XQ || X == XL);
 template <int VMAX>
 __device__ __forceinline__ bool lean_fits(const Chunks<VMAX>& c, int G, uint64_t gbit, uint64_t lsb) {
   return (fold_groups(__ballot(!lstreams_fit<VMAX>(c)), G, lsb) & gbit) == 0;
@@ -2694,7 +2694,7 @@ __global__ void __launch_bounds__(WAVE) k_sim_mat40(SimArgs a, int mode) {
 // sorted by (time, communication before computation, then the producer's id (kind, stage, m) for
 // a transfer or the queue position for a computation); a compute item's time is its start.
 // One group per candidate (lane = device), queues materialised, 64-bit finish table:
-//   A. the plain rounds, recording each op's finish (by node) in the slot's time buffer;
+//   A. the plain rounds, recording each op's finish and input time by queue position;
 //   B. each lane builds its program: computations and sends come in queue order already, its
 //      receives (keyed by their producers' ends) are insertion-sorted, then the three merge;
 //   C. rounds over the programs: a send first announces itself in the sender's outbox (once its
@@ -2711,17 +2711,12 @@ constexpr int32_t OB_NONE = -1;
 
 // Per-slot scratch of k_ordered.
 // A communication item of the reordering: its key is (producer end, level, producer node);
-// pk = level << 37 | node << 17 | receive << 16 | gap, so that comparing pk compares (level,
-// node), which no two items of a lane share. Levels (lockstep rounds of a live group) and
-// nodes are below 3 S M <= 3 * 64 * 2047 < 2^19; gaps are at most 3 v M < 2^16.
+// pk = node << 17 | receive << 16 | gap. No two items of a lane share (level, node), and the level
+// is looked up (by node) only where two ends are equal. Gaps are at most 3 v M < 2^16.
 struct __align__(16) CItem {
   int64_t key;
   uint64_t pk;
 };
-__device__ __forceinline__ bool item_less(const CItem& a, const CItem& b) {
-  return a.key != b.key ? a.key < b.key : a.pk < b.pk;
-}
-
 // Per-lane scratch of a wave, lane-interleaved: element i of lane l is at [i][l] of the wave's
 // block, so that the lanes' accesses at one index share cache lines.
 template <class T>
@@ -2735,17 +2730,15 @@ __device__ __forceinline__ LaneArr<T> lane_arr(T* base, int cap) {
 }
 
 struct OrdBufs {
-  int64_t* tb;      // [slot][3 S_max M] finish time of each op (REORDER, phase C: arrivals)
-  // the rest: [wave][cap][WAVE], lane-interleaved
+  // [wave][cap][WAVE], lane-interleaved
+  OpTime* rq;       // qcap: times of each queue position's op
   int64_t* rkey;    // rcap: receive keys (producer end)
   uint32_t* rid;    // rcap: receive producers (pitem with type 0)
   uint4* prog;      // pcap / 4: programs, four items per entry
   int rcap, pcap;
   // REORDER only
-  int64_t* ts;      // [slot][3 S_max M] start time of each op
   int32_t* tl;      // [slot][3 S_max M] level of each op
   CItem* items;     // icap: in-order items from the front, mismatched ones from the back
-  int64_t* pst;     // pcap2: post time of each gap (end of the computation before)
   int64_t* pdur;    // pcap2: durations of the computations before each gap
   int pcap2;
   int64_t* stats;   // [n][2] (nullable): transfers, mismatched receives
@@ -2773,10 +2766,6 @@ struct ProgOut {
     return n;
   }
 };
-__device__ __forceinline__ uint32_t prog_at(LaneArr<uint4> prog, int i) {
-  return reinterpret_cast<const uint32_t*>(&prog[i >> 2])[i & 3];
-}
-
 // (t, cls, tie) < (t', cls', tie')
 __device__ __forceinline__ bool key_less(int64_t t, uint32_t cls, uint32_t tie, int64_t t2,
                                          uint32_t cls2, uint32_t tie2) {
@@ -2815,9 +2804,8 @@ struct RowCursor {
 // Phase B for lane d: returns the program length.
 template <int VMAX>
 __device__ __forceinline__ int build_program(const Chunks<VMAX>& c, const uint16_t* row, int nq,
-                                             const int64_t* tb, int S, int M, LaneArr<int64_t> rkey,
+                                             LaneArr<OpTime> rq, LaneArr<int64_t> rkey,
                                              LaneArr<uint32_t> rid, LaneArr<uint4> prog) {
-  auto node = [&](int kind, int s, int m) { return (kind * S + s) * M + m; };
   auto dur_of = [&](int kind, int k) {
     return kind == KF ? pick<VMAX>(c.dF, k) : kind == KB ? pick<VMAX>(c.dB, k) : pick<VMAX>(c.dW, k);
   };
@@ -2841,7 +2829,7 @@ __device__ __forceinline__ int build_program(const Chunks<VMAX>& c, const uint16
       isr[u] = i0 + u < nq && (cx & CX_IN) != 0;
       const int ps = kind == KF ? s - 1 : s + 1;
       id[u] = pitem(0, kind, ps, m);
-      key[u] = isr[u] ? tb[node(kind, ps, m)] : 0;
+      key[u] = isr[u] ? rq[i0 + u].in - (kind == KF ? pick<VMAX>(c.wF, k) : pick<VMAX>(c.wB, k)) : 0;
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
@@ -2876,7 +2864,7 @@ __device__ __forceinline__ int build_program(const Chunks<VMAX>& c, const uint16
     const uint32_t e = rc_c.at(i < nq ? i : 0);
     const int kind = (e >> 14) & 3, k = (e >> 11) & 7, m = e & 0x7FF;
     const int s = pick<VMAX>(c.st, k);
-    fin = i < nq ? tb[node(kind, s, m)] : 0;
+    fin = i < nq ? rq[i].fin : 0;
     dur = dur_of(kind, k);
     item = pitem(PI_COMP, kind, s, m);
   };
@@ -2891,7 +2879,7 @@ __device__ __forceinline__ int build_program(const Chunks<VMAX>& c, const uint16
       if (cx & CX_OUT) break;
     }
     const int s = pick<VMAX>(c.st, k);
-    key = j < nq ? tb[node(kind, s, m)] : 0;
+    key = j < nq ? rq[j].fin : 0;
     id = pitem(0, kind, s, m);
     return j;
   };
@@ -2951,28 +2939,37 @@ __device__ __forceinline__ int build_program(const Chunks<VMAX>& c, const uint16
 // the consumer)) among the gaps between the in-order items around its key, at most its
 // consumer's, whose post time is not before the producer starts (the highest gap always
 // qualifies; ties: the highest); then the items, in key order, are merged with the computations
-// by gap. Returns the program length; *nrecv and *nmis get the two counts. pst and pdur
-// (nq + 1 entries) hold each gap's post time and the prefix sums of the computations'
-// durations, so that a window's costs read two arrays instead of walking the queue.
+// by gap. Returns the program length; *nrecv and *nmis get the two counts. pdur (nq + 1
+// entries) holds the prefix sums of the computations' durations; stage_dur(kind, s) is an op's
+// duration, so that a window's costs read two arrays instead of walking the queue.
 // A send is never mismatched: its key is its own op's end, which is later than the end of every
 // earlier op and of every producer an earlier op received from.
-template <int VMAX>
+template <int VMAX, class StageDur>
 __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint16_t* row, int nq,
-                                              const int64_t* tb, const int64_t* ts,
-                                              const int32_t* tl, int S, int M,
-                                              LaneArr<CItem> items, int icap,
-                                              LaneArr<int64_t> pst, LaneArr<int64_t> pdur,
-                                              LaneArr<uint4> prog, int* nrecv, int* nmis) {
+                                              LaneArr<OpTime> rq, const int32_t* tl, int S,
+                                              int M, LaneArr<CItem> items, int icap,
+                                              LaneArr<int64_t> pdur, LaneArr<uint4> prog,
+                                              StageDur stage_dur, int* nrecv, int* nmis) {
   auto node = [&](int kind, int s, int m) { return (kind * S + s) * M + m; };
   auto dur_of = [&](int kind, int k) {
     return kind == KF ? pick<VMAX>(c.dF, k) : kind == KB ? pick<VMAX>(c.dB, k) : pick<VMAX>(c.dW, k);
   };
   // the node field is kind << 17 | stage << 11 | m, ordered as the node index is
-  auto pack = [](int level, int kind, int s, int m, uint32_t recv, int gap) {
-    return (uint64_t)(uint32_t)level << 37 |
-           (uint64_t)((uint32_t)kind << 17 | (uint32_t)s << 11 | (uint32_t)m) << 17 |
+  auto pack = [](int kind, int s, int m, uint32_t recv, int gap) {
+    return (uint64_t)((uint32_t)kind << 17 | (uint32_t)s << 11 | (uint32_t)m) << 17 |
            (uint64_t)recv << 16 | (uint64_t)(uint32_t)gap;
   };
+  auto level = [&](const CItem& x) {
+    const uint32_t code = (uint32_t)(x.pk >> 17) & 0x7FFFFu;
+    return tl[node(code >> 17, (code >> 11) & 63, code & 0x7FF)];
+  };
+  auto item_less = [&](const CItem& x, const CItem& y) {
+    if (x.key != y.key) return x.key < y.key;
+    const int32_t lx = level(x), ly = level(y);
+    return lx != ly ? lx < ly : x.pk < y.pk;
+  };
+  // post time of a gap: the end of the computation before it
+  auto post = [&](int g) { return g > 0 ? rq[g - 1].fin : 0; };
   auto gap_of = [](const CItem& x) { return (int)(x.pk & 0xFFFFu); };
   // mismatched item j sits at icap - 1 - j
   auto mis = [&](int j) -> CItem& { return items[icap - 1 - j]; };
@@ -2991,27 +2988,23 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
       mis(nf++) = x;
     }
   };
-  pst[0] = 0, pdur[0] = 0;
+  pdur[0] = 0;
   int64_t dsum = 0;
   for (int i0 = 0; i0 < nq; i0 += 8) {
     const uint4 b = row_span(row, i0 >> 3, nq);
     int64_t fy[8], fx[8], ds[8];
-    int32_t ly[8], lx[8];
     int cxs[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const uint32_t e = span_entry(b, u);
-      const int kind = (e >> 14) & 3, k = (e >> 11) & 7, m = e & 0x7FF;
-      const int s = pick<VMAX>(c.st, k);
+      const int kind = (e >> 14) & 3, k = (e >> 11) & 7;
       const bool in = i0 + u < nq;
       const int cx =
           !in ? 0 : kind == KF ? pick<VMAX>(c.xF, k) : kind == KB ? pick<VMAX>(c.xB, k) : 0;
-      const int y = node(kind, s, m), x = node(kind, kind == KF ? s - 1 : s + 1, m);
       cxs[u] = cx;
-      fy[u] = in ? tb[y] : 0;
-      fx[u] = (cx & CX_IN) ? tb[x] : 0;
-      lx[u] = (cx & CX_IN) ? tl[x] : 0;
-      ly[u] = (cx & CX_OUT) ? tl[y] : 0;
+      const OpTime x = rq[in ? i0 + u : 0];
+      fy[u] = x.fin;
+      fx[u] = x.in - (kind == KF ? pick<VMAX>(c.wF, k) : pick<VMAX>(c.wB, k));
       dsum += in ? dur_of(kind, k) : 0;
       ds[u] = dsum;
     }
@@ -3021,12 +3014,12 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
       const uint32_t e = span_entry(b, u);
       const int kind = (e >> 14) & 3, k = (e >> 11) & 7, m = e & 0x7FF;
       const int s = pick<VMAX>(c.st, k);
-      pst[i0 + u + 1] = fy[u], pdur[i0 + u + 1] = ds[u];
+      pdur[i0 + u + 1] = ds[u];
       if (cxs[u] & CX_IN) {
-        add(fx[u], pack(lx[u], kind, kind == KF ? s - 1 : s + 1, m, 1u, i0 + u));
+        add(fx[u], pack(kind, kind == KF ? s - 1 : s + 1, m, 1u, i0 + u));
         ++nrv;
       }
-      if (cxs[u] & CX_OUT) add(fy[u], pack(ly[u], kind, s, m, 0u, i0 + u + 1));
+      if (cxs[u] & CX_OUT) add(fy[u], pack(kind, s, m, 0u, i0 + u + 1));
     }
   }
   *nrecv = nrv, *nmis = nf;
@@ -3057,7 +3050,7 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
     const int lo = lastg > logap ? lastg : logap;
     const int iY = gap_of(f);
     const uint32_t code = (uint32_t)(f.pk >> 17) & 0x7FFFFu;
-    const int64_t xst = ts[node(code >> 17, (code >> 11) & 63, code & 0x7FF)];
+    const int64_t xst = f.key - stage_dur(code >> 17, (code >> 11) & 63);
     // the transfer's time: the consumer's input weight
     const uint32_t ey = row[iY];
     const int ky = (ey >> 11) & 7;
@@ -3067,7 +3060,7 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
     int gx = lo, ge = hi + 1;
     while (gx < ge) {
       const int mid = (gx + ge) >> 1;
-      if (pst[mid] < xst) gx = mid + 1;
+      if (post(mid) < xst) gx = mid + 1;
       else ge = mid;
     }
     const int first = gx < hi ? gx : hi;
@@ -3075,7 +3068,7 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
     int best = hi;
     int64_t bestc = 0;
     for (int gp = hi; gp >= first; --gp) {
-      const int64_t pt = pst[gp], D = pY - pdur[gp];
+      const int64_t pt = post(gp), D = pY - pdur[gp];
       const int64_t span = fk > pt ? fk - pt : pt - fk;
       const int64_t cost = span - (D < cw ? D : cw);
       if (gp == hi || cost < bestc) best = gp, bestc = cost;
@@ -3123,9 +3116,8 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
 // one whose times pass 40 bits the redo list, which the 64-bit kernel (list, list_n) takes.
 // REORDER: the executor's three-step reordering (build_program3) with handshake transfers in
 // phase C: a receive completes when the sender has announced itself, at h = max(the sender's
-// announce time, the receiver's clock); both clocks go to h, and the data's arrival h + w is kept
-// in the finish-time buffer at the producer's node (phase B is done with it), where the consumer,
-// a later computation of the same lane, takes it as its input time.
+// announce time, the receiver's clock); both clocks go to h, and the data's arrival h + w replaces
+// the producer's finish in its slot, where the consumer takes it as its input time.
 // Three waves per SIMD for the ideal-start variant (its phases wait on global loads: 27.5 ->
 // 25.1 ms on 65,536 candidates of the P = 8, M = 64 batch, a few registers spilled); the
 // reordering variant keeps its registers (at three waves it spills and slows by a third).
@@ -3149,8 +3141,7 @@ k_ordered(SimArgs a, OrdBufs ob,
   const int slot = (int)blockIdx.x * a.CPW + (g < a.CPW ? g : 0);
   const int dl = d < P ? d : 0;
   uint16_t* row = a.qscratch + ((size_t)slot * P + dl) * a.qcap;
-  int64_t* tb = ob.tb + (size_t)slot * 3 * a.pr.s_max * M;
-  int64_t* ts = REORDER ? ob.ts + (size_t)slot * 3 * a.pr.s_max * M : nullptr;
+  const LaneArr<OpTime> rq = lane_arr(ob.rq, a.qcap);
   int32_t* tl = REORDER ? ob.tl + (size_t)slot * 3 * a.pr.s_max * M : nullptr;
   const LaneArr<uint4> prog = lane_arr(ob.prog, ob.pcap / 4);
   uint64_t gbit, lsb;
@@ -3176,8 +3167,7 @@ k_ordered(SimArgs a, OrdBufs ob,
     L.clock = 0, L.pos = 0, L.nops = 0, L.mem = L.peak = 0;
     L.cm.reset();
     L.fs = -1;
-    L.tb = tb, L.tS = S, L.tM = M;
-    L.ts = ts, L.tl = tl, L.rnd = 0;
+    L.rq = &rq[0], L.tl = tl, L.tS = S, L.tM = M, L.rnd = 0;
     int wl = 0;
     if (valid && d < P) {
       busy = setup_chunks<VMAX>(c, a.pr, rec, a.pre, a.link, d, v, r.split, ring, nullptr,
@@ -3200,23 +3190,27 @@ k_ordered(SimArgs a, OrdBufs ob,
     if (!mine) L.nops = 0;
     if (run) T.clear(S * ring.R, d, G);
     __syncthreads();
-    // A: the asynchronous schedule, finish times recorded
+    // A: the asynchronous schedule, times recorded
     bool dead = false;
-    {
-      rounds_mat<VMAX, XT, false>(row, a.qcap, c, v, ring, L, T, G, gbit, lsb, dead, nullptr,
-                           smem + a.strm_off);
-    }
-    __syncthreads();  // every lane's finish times visible to the group
+    rounds_mat<VMAX, REORDER ? XL : XQ, false>(row, a.qcap, c, v, ring, L, T, G, gbit, lsb, dead,
+                                               nullptr, smem + a.strm_off);
+    __syncthreads();  // every lane's levels visible to the group
     // B: programs
     int plen = 0, nrecv = 0, nmis = 0;
     if constexpr (REORDER) {
+      const uint8_t* bnd = rec + 4;
+      auto stage_dur = [&](int kind, int s) {
+        const int64_t* p0 = a.pre + 3 * (s > 0 ? bnd[s - 1] : 0);
+        const int64_t* p1 = a.pre + 3 * (s < S - 1 ? bnd[s] : a.pr.L);
+        return p1[kind] - p0[kind] + (kind == KB && !c.split ? p1[KW] - p0[KW] : 0);
+      };
       if (mine && !dead)
-        plen = build_program3<VMAX>(c, row, L.nops, tb, ts, tl, S, M, lane_arr(ob.items, ob.icap),
-                                    ob.icap, lane_arr(ob.pst, ob.pcap2),
-                                    lane_arr(ob.pdur, ob.pcap2), prog, &nrecv, &nmis);
+        plen = build_program3<VMAX>(c, row, L.nops, rq, tl, S, M, lane_arr(ob.items, ob.icap),
+                                    ob.icap, lane_arr(ob.pdur, ob.pcap2), prog, stage_dur, &nrecv,
+                                    &nmis);
     } else {
       if (mine && !dead)
-        plen = build_program<VMAX>(c, row, L.nops, tb, S, M, lane_arr(ob.rkey, ob.rcap),
+        plen = build_program<VMAX>(c, row, L.nops, rq, lane_arr(ob.rkey, ob.rcap),
                                    lane_arr(ob.rid, ob.rcap), prog);
     }
     if (run) T.clear(S * ring.R, d, G);
@@ -3225,101 +3219,115 @@ k_ordered(SimArgs a, OrdBufs ob,
     obt[me] = 0;
     __syncthreads();
     // C: rounds over the programs
-    int64_t clock = 0;
+    int64_t clock = 0, last = 0;  // the lane's clock; its latest time (arrivals too)
     bool cdead = false;
     if (!dead) {
       const uint8_t* devs = rec + 3 + a.pr.s_max;
       int pos = 0;
       bool live = pos < plen, arrived = false;
-      // the next item is loaded one advance ahead, so decoding never waits for memory
-      uint32_t nitem = plen > 1 ? prog_at(prog, 1) : 0u;
+      // the program is read four items at a time, two entries ahead of the one at hand; every
+      // fourth round the entries move up (a lane takes at most one item a round) and the
+      // third is requested, four rounds before its first use
+      const int pmax = ob.pcap / 4 - 1;
+      uint4 pa = prog[0], pb = prog[1 < pmax ? 1 : pmax], pc = prog[2 < pmax ? 2 : pmax];
+      int pq = 0;
+      auto item_at = [&](int o) {  // item 4 pq + o, o < 8
+        const bool h = (o & 4) != 0, q1 = (o & 1) != 0;
+        const uint32_t x = h ? pb.x : pa.x, y = h ? pb.y : pa.y, z = h ? pb.z : pa.z,
+                       w = h ? pb.w : pa.w;
+        const uint32_t e0 = q1 ? y : x, e1 = q1 ? w : z;
+        return (o & 2) ? e1 : e0;
+      };
       // the current item, decoded
       uint32_t type = 0, tag = 0;
       int rd = 0, wr = 0, store = 0, src = 0;
       uint32_t mask = 0, want = 0, state = 0;
-      int64_t w = 0, dur = 0;
-      // REORDER: a computation with a cross-device input takes the arrival its receive left at
-      // the producer's node (xat); a receive names that node (xnode). Only a real item (real:
-      // the lane has one; otherwise the code 0 stands in, whose op need not be the lane's)
-      // loads an arrival.
-      bool xarr = false;
-      int64_t xat = 0;
-      int xnode = 0;
-      auto decode = [&](uint32_t it, bool real) {
+      int64_t w = 0, dur = 0, amax = 0;
+      // REORDER: a receive leaves its transfer's arrival as the producer's time in the producer's
+      // slot, which only the consumer (a later computation of the same lane) takes a time from
+      // (xin): whatever else reads it is an op of the producer's own device, whose clock is past
+      // the producer's end
+      bool xin = false;
+      auto decode = [&](uint32_t it) {
         type = it >> 30;
         const int kind = (int)((it >> 28) & 3u), s = (int)((it >> 16) & 63u), m = (int)(it & 0x7FFu);
         tag = it & 0x3FFFFFFFu;
-        xarr = false;
         if (type == PI_COMP) {
           Desc D;
           describe<VMAX>(D, c, ring, kind, chunk_of<VMAX>(c, s, v), m);
           rd = D.rd, wr = D.wr, store = D.store, mask = (uint32_t)D.mask, want = (uint32_t)D.want;
           state = D.state, w = D.w, dur = D.dur;
-          if constexpr (REORDER) {
-            xarr = real && (D.cx & CX_IN) != 0;
-            if (xarr) xat = tb[(kind * S + (kind == KF ? s - 1 : s + 1)) * M + m];
+          xin = (D.cx & CX_IN) != 0;
+        } else {
+          rd = wr = s * ring.R + (m & ring.mask);
+          if (type == PI_SEND) {  // its producer (an own op) must have finished
+            const uint32_t par = ((uint32_t)m >> ring.lg) & 1u;
+            mask = (kind == KF ? ST_F : ST_B) | ST_PAR;
+            want = (kind == KF ? ST_F : ST_B) | (par ? ST_PAR : 0u);
+          } else {  // receive: the producer's device and the consumer's link weight
+            src = devs[s];
+            const int cs = kind == KF ? s + 1 : s - 1;
+            const int ck = chunk_of<VMAX>(c, cs, v);
+            w = kind == KF ? pick<VMAX>(c.wF, ck) : pick<VMAX>(c.wB, ck);
           }
-        } else if (type == PI_SEND) {  // its producer (an own op) must have finished
-          rd = s * ring.R + (m & ring.mask);
-          const uint32_t par = ((uint32_t)m >> ring.lg) & 1u;
-          mask = (kind == KF ? ST_F : ST_B) | ST_PAR;
-          want = (kind == KF ? ST_F : ST_B) | (par ? ST_PAR : 0u);
-        } else {  // receive: the producer's device and the consumer's link weight
-          src = devs[s];
-          const int cs = kind == KF ? s + 1 : s - 1;
-          const int ck = chunk_of<VMAX>(c, cs, v);
-          w = kind == KF ? pick<VMAX>(c.wF, ck) : pick<VMAX>(c.wB, ck);
-          xnode = (kind * S + s) * M + m;
         }
       };
-      decode(live ? prog_at(prog, 0) : 0u, live);
-      for (;;) {
-        uint32_t plo, phi;
-        T.issue(live && type != PI_RECV ? rd : 0, plo, phi);
-        const int64_t box = mbox[me];
-        const int32_t on = obn[g0 + (type == PI_RECV ? src : 0)];
-        const int64_t ot = obt[g0 + (type == PI_RECV ? src : 0)];
-        const uint64_t p = (uint64_t)plo | ((uint64_t)phi << 32);
-        const bool rdy = (plo & mask) == want;
-        const bool okC = live && type == PI_COMP && rdy;
-        const int64_t tin = xarr ? xat : (int64_t)(p >> 3) + w;
-        const int64_t st = tin > clock ? tin : clock;
-        const int64_t fin = st + dur;
-        const bool okSA = live && type == PI_SEND && !arrived && rdy;
-        const bool okSD = live && type == PI_SEND && arrived && box != RDV_EMPTY;
-        const bool okR = live && type == PI_RECV && on == (int32_t)tag;
-        // the handshake, and where both clocks go: its end (blocking) or its start (REORDER)
-        const int64_t hs = ot > clock ? ot : clock;
-        const int64_t xend = REORDER ? hs : hs + w;
-        if (okC && store) T.store(wr, ((uint64_t)fin << 3) | state);
-        if (okSA) obn[me] = (int32_t)tag, obt[me] = clock;
-        if (okSD) mbox[me] = RDV_EMPTY, obn[me] = OB_NONE;
-        if (okR) mbox[g0 + src] = xend;
-        if (REORDER && okR) tb[xnode] = hs + w;
-        clock = okC ? fin : okSD ? box : okR ? xend : clock;
-        arrived = okSA ? true : okSD ? false : arrived;
-        const bool done = okC || okSD || okR;
-        if (done) {
-          ++pos;
-          live = pos < plen;
-          const uint32_t it = live ? nitem : 0u;
-          __asm__ volatile("" : "+v"(nitem));
-          nitem = pos + 1 < plen ? prog_at(prog, pos + 1) : 0u;
-          decode(it, live);
-        }
-        __asm__ volatile("" ::: "memory");
-        if (__ballot(okC || okSA || okSD || okR) == 0) {
-          const uint64_t actm = __ballot(live);
-          if (actm != 0 && (fold_groups(actm, G, lsb) & gbit)) cdead = true;
-          break;
+      decode(live ? item_at(0) : 0u);
+      for (bool more = true; more;) {
+        const bool up = (pos >> 2) != pq;
+        pa.x = up ? pb.x : pa.x, pa.y = up ? pb.y : pa.y, pa.z = up ? pb.z : pa.z, pa.w = up ? pb.w : pa.w;
+        pb.x = up ? pc.x : pb.x, pb.y = up ? pc.y : pb.y, pb.z = up ? pc.z : pb.z, pb.w = up ? pc.w : pb.w;
+        pq = pos >> 2;
+        pc = prog[pq + 2 < pmax ? pq + 2 : pmax];
+#pragma unroll 1
+        for (int u = 0; u < 4; ++u) {
+          uint32_t plo, phi;
+          T.issue(live ? rd : 0, plo, phi);
+          const int64_t box = mbox[me];
+          const int32_t on = obn[g0 + (type == PI_RECV ? src : 0)];
+          const int64_t ot = obt[g0 + (type == PI_RECV ? src : 0)];
+          const uint64_t p = (uint64_t)plo | ((uint64_t)phi << 32);
+          const bool rdy = (plo & mask) == want;
+          const bool okC = live && type == PI_COMP && rdy;
+          const int64_t tin = REORDER ? (xin ? (int64_t)(p >> 3) : 0) : (int64_t)(p >> 3) + w;
+          const int64_t st = tin > clock ? tin : clock;
+          const int64_t fin = st + dur;
+          const bool okSA = live && type == PI_SEND && !arrived && rdy;
+          const bool okSD = live && type == PI_SEND && arrived && box != RDV_EMPTY;
+          const bool okR = live && type == PI_RECV && on == (int32_t)tag;
+          // the handshake, and where both clocks go: its end (blocking) or its start (REORDER)
+          const int64_t hs = ot > clock ? ot : clock;
+          const int64_t arr = hs + w;
+          const int64_t xend = REORDER ? hs : arr;
+          if ((okC && store) || (REORDER && okR))
+            T.store(wr, okC ? ((uint64_t)fin << 3) | state : ((uint64_t)arr << 3) | (p & 7u));
+          if (okSA) obn[me] = (int32_t)tag, obt[me] = clock;
+          if (okSD) mbox[me] = RDV_EMPTY, obn[me] = OB_NONE;
+          if (okR) mbox[g0 + src] = xend;
+          if (REORDER && RING) amax = okR && arr > amax ? arr : amax;
+          clock = okC ? fin : okSD ? box : okR ? xend : clock;
+          arrived = okSA ? true : okSD ? false : arrived;
+          if (okC || okSD || okR) {
+            ++pos;
+            live = pos < plen;
+            decode(live ? item_at(pos - 4 * pq) : 0u);
+          }
+          __asm__ volatile("" ::: "memory");
+          if (__ballot(okC || okSA || okSD || okR) == 0) {
+            more = false;
+            break;
+          }
         }
       }
+      const uint64_t actm = __ballot(live);
+      if (actm != 0 && (fold_groups(actm, G, lsb) & gbit)) cdead = true;
+      last = amax > clock ? amax : clock;
     }
     const int64_t ms = group_max(clock, G);
     int64_t srecv = 0, smis = 0;
     if constexpr (REORDER) srecv = group_sum(nrecv, G), smis = group_sum(nmis, G);
     // overflow test over both rounds' clocks (phase A's alone when it deadlocked)
-    const int64_t top = RING ? group_max(clock > L.clock ? clock : L.clock, G) : 0;
+    const int64_t top = RING ? group_max(last > L.clock ? last : L.clock, G) : 0;
     if (has && valid && (!on_ring || top >= Table40::LIMIT)) {
       // too wide for the ring: the full-row 40-bit pass (when one follows); overflow: 64 bits
       if (d == 0) {
@@ -4512,7 +4520,7 @@ __global__ void __launch_bounds__(WAVE) k_alg1_moves(SimArgs a, A1Args b,
     L.clock = 0, L.pos = 0, L.nops = 0, L.mem = L.peak = 0;
     L.cm.reset();
     L.fs = -1;
-    L.tb = tb, L.ts = nullptr, L.tl = nullptr, L.tS = S, L.tM = M, L.rnd = 0;
+    L.tb = tb, L.tS = S, L.tM = M, L.rnd = 0;
     if (r.valid && d < P) {
       (void)setup_chunks<VMAX>(c, a.pr, rec, a.pre, a.link, d, v, r.split, ring, nullptr, nullptr,
                                XR);
@@ -6259,12 +6267,12 @@ int launch_ordered(const octo_problem* prob, const int64_t* layer_costs, const i
   ob.icap = REORDER ? 4 * prob->v_max * prob->M : 0;
   ob.pcap2 = REORDER ? queue_cap(prob) + 1 : 0;
   const size_t nodes = (size_t)3 * prob->P * prob->v_max * prob->M;
-  // at most 4 GiB of scratch per launch: per group slot the finish times (REORDER: start times
-  // and levels too) and queue rows, per lane the receive keys or the communication items and gap
-  // tables, and the program
-  const size_t per_slot = nodes * (REORDER ? 8 + 8 + 4 : 8) + (size_t)prob->P * queue_cap(prob) * 2;
-  const size_t per_lane = (size_t)ob.rcap * 12 + (size_t)ob.pcap * 4 + (size_t)ob.icap * 16 +
-                          (size_t)ob.pcap2 * 16;
+  // at most 4 GiB of scratch per launch: per group slot the queue rows (REORDER: levels too), per
+  // lane the ops' times, the receive keys or the communication items and durations, and the
+  // program
+  const size_t per_slot = nodes * (REORDER ? 4 : 0) + (size_t)prob->P * queue_cap(prob) * 2;
+  const size_t per_lane = (size_t)queue_cap(prob) * 16 + (size_t)ob.rcap * 12 +
+                          (size_t)ob.pcap * 4 + (size_t)ob.icap * 16 + (size_t)ob.pcap2 * 8;
   auto grid_of = [&](auto kern, const Plan& pl, int* g) {
     int rc2 = occupancy_grid(kern, pl.lds_bytes, di.cus, g);
     if (rc2) return rc2;
@@ -6305,25 +6313,21 @@ int launch_ordered(const octo_problem* prob, const int64_t* layer_costs, const i
     return at;
   };
   const size_t lanes = waves * WAVE;
-  const size_t o_tb = take(slots * nodes * 8);
+  const size_t o_rq = take(lanes * queue_cap(prob) * 16);
   const size_t o_rk = take(lanes * ob.rcap * 8);
   const size_t o_ri = take(lanes * ob.rcap * 4);
   const size_t o_pg = take(lanes * ob.pcap * 4);
-  const size_t o_ts = take(REORDER ? slots * nodes * 8 : 0);
   const size_t o_tl = take(REORDER ? slots * nodes * 4 : 0);
   const size_t o_it = take(lanes * ob.icap * 16);
-  const size_t o_ps = take(lanes * ob.pcap2 * 8);
   const size_t o_pd = take(lanes * ob.pcap2 * 8);
   if ((rc = ensure_buf(su.ws->ord, su.ws->ord_bytes, o, stream))) return rc;
   char* base = static_cast<char*>(su.ws->ord);
-  ob.tb = reinterpret_cast<int64_t*>(base + o_tb);
+  ob.rq = reinterpret_cast<OpTime*>(base + o_rq);
   ob.rkey = reinterpret_cast<int64_t*>(base + o_rk);
   ob.rid = reinterpret_cast<uint32_t*>(base + o_ri);
   ob.prog = reinterpret_cast<uint4*>(base + o_pg);
-  ob.ts = reinterpret_cast<int64_t*>(base + o_ts);
   ob.tl = reinterpret_cast<int32_t*>(base + o_tl);
   ob.items = reinterpret_cast<CItem*>(base + o_it);
-  ob.pst = reinterpret_cast<int64_t*>(base + o_ps);
   ob.pdur = reinterpret_cast<int64_t*>(base + o_pd);
   ob.stats = stats;
   if (stats) {  // sentinels for the invalid records, which no group takes

@@ -45,8 +45,13 @@ constexpr uint32_t ST_B = 1, ST_F = 2, ST_PAR = 4;
 // device's first start and last finish (its leading and trailing idle).
 // XR: blocking rendezvous transfers (a device receives an op's cross-device input right before
 // the op and sends its cross-device output right after it; a transfer holds both devices).
-// XT: the plain times, each op's finish recorded by node id (L.tb) for building programs.
-constexpr int XP = 0, XM = 1, XC = 2, XS = 3, XB = 4, XR = 5, XT = 6;
+// XT: the plain times, each op's finish recorded by node id (L.tb).
+// XQ: the plain times, each op's finish and input time recorded by queue position (L.rq), for
+// building programs; XL: each op's level by node id too (L.tl).
+constexpr int XP = 0, XM = 1, XC = 2, XS = 3, XB = 4, XR = 5, XT = 6, XQ = 7, XL = 8;
+struct __align__(16) OpTime {
+  int64_t fin, in;  // finish; producer's finish + link weight (no producer: anything)
+};
 // Weight of a weight-gradient op's read under serialised links: its B is on its own device and
 // earlier in its queue, so only the readiness bit matters, not the (possibly delayed) slot time.
 constexpr int64_t W_NO_TIME = -((int64_t)1 << 50);
@@ -212,9 +217,9 @@ struct Lane : Desc {
                       // (forward outputs of chunk k at k, backward outputs at VMAX + k)
   int64_t fs;         // start of the device's first op (-1 before it), bounds variants
   int64_t* tb;        // XT: finish time of every op, at (kind * tS + stage) * tM + m
-  int64_t* ts;        // XT (nullable): start time of every op, same index
-  int32_t* tl;        // XT (nullable): the round each op ran in — its level, the number of ops on the
-                      // longest dependency chain before it (queue order included)
+  OpTime* rq;         // XQ, XL: where the next op's times go (lane-interleaved: every 64th element)
+  int32_t* tl;        // XL: the round each op ran in — its level, the number of ops on the longest
+                      // dependency chain before it (queue order included) —, indexed as tb
   int tS, tM, rnd;
 };
 
@@ -334,14 +339,17 @@ __device__ __forceinline__ bool relax_round(Gen& gen, const Chunks<VMAX>& c, con
       rec[L.pos] = ((uint32_t)st << 16) | ((uint32_t)gen.kind << 12) | (uint32_t)gen.m;
     if constexpr (X == XC) L.cm.op(ok, L.cx, tin, L.w, L.clock, st, fin, L.cout);
     if constexpr (X == XB) L.fs = (ok && L.fs < 0) ? st : L.fs;
-    if constexpr (X == XT) {
+    if constexpr (X == XT || X == XL) {
       const int nd = (gen.kind * L.tS + pick<VMAX>(c.st, gen.k)) * L.tM + gen.m;
-      if (ok) {
-        L.tb[nd] = fin;
-        if (L.ts) L.ts[nd] = st;
-        if (L.tl) L.tl[nd] = L.rnd;
-      }
+      if (X == XT && ok) L.tb[nd] = fin;
+      if (X == XL && ok) L.tl[nd] = L.rnd;
       L.rnd += 1;
+    }
+    if constexpr (X == XQ || X == XL) {
+      if (ok) {
+        *L.rq = OpTime{fin, tin};
+        L.rq += 64;
+      }
     }
     L.clock = ok ? fin : L.clock;
     if constexpr (X == XM) {
@@ -625,7 +633,7 @@ __device__ __forceinline__ LeanOp lean_decode(uint32_t e, bool last, const LStre
   o.state = (st.fl >> 8) & parw;
   o.w = st.w, o.dur = st.dur;
   o.nd = 0;
-  if constexpr (X == XT) {
+  if constexpr (X == XT || X == XL) {
     const int kind = (int)(e >> 14), k = (int)(e >> 11) & (VMAX <= 2 ? 1 : 7);
     o.nd = (kind * L.tS + pick<VMAX>(ch.st, k)) * L.tM + (int)m;
   }
@@ -658,14 +666,17 @@ __device__ __forceinline__ bool lean_round(LeanQueue<REV>& Q, const LStreams<VMA
   }
   const int64_t fin = (int64_t)((uint64_t)fl | (uint64_t)fh << 32);
   if constexpr (X == XB) L.fs = (ok && L.fs < 0) ? beg : L.fs;
-  if constexpr (X == XT) {
-    if (ok) {
-      L.tb[c.nd] = fin;
-      if (L.ts) L.ts[c.nd] = beg;
-      if (L.tl) L.tl[c.nd] = L.rnd;
-    }
+  if constexpr (X == XT || X == XL) {
+    if (X == XT && ok) L.tb[c.nd] = fin;
+    if (X == XL && ok) L.tl[c.nd] = L.rnd;
     L.rnd += 1;
     c.nd = ok ? n.nd : c.nd;
+  }
+  if constexpr (X == XQ || X == XL) {
+    if (ok) {
+      *L.rq = OpTime{fin, tin};
+      L.rq += 64;
+    }
   }
   L.clock = ok ? fin : L.clock;
   Q.take(ok);
