@@ -73,7 +73,8 @@ struct SimArgs {
   int32_t* redo;         // candidates to recompute with 64-bit slots
   int32_t* wide;         // perturbed candidates too wide for the ring (k_sim_mat40 full rows)
   const uint32_t* mtab;  // MERGE tables, merge_offset() entries apart
-  const uint16_t* mrows; // v = 2 MERGE queues by (split, s0, s1) (merge_rows); null: none
+  const uint16_t* mrows; // v = 2 MERGE queues by (split, s0, s1), with the v <= 2 INTER and GPipe
+                         // ones in the rows of no pair (k_merge_rows); null: none
   int mrow_stride;       // entries per row of mrows
   uint16_t* qscratch;    // materialised queues, [group slot][P][qcap]
   int G, CPW;            // lanes per candidate, candidates per wave
@@ -2355,7 +2356,28 @@ __global__ void k_merge_rows(int P, int M, const uint32_t* __restrict__ mtab,
   const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (t >= 2 * S * S) return;
   const int split = t / (S * S), s0 = (t / S) % S, s1 = t % S;
-  if (s0 >= s1) return;
+  if (s0 >= s1) {
+    // the rows that no pair has: (split, S - 1, (2 - v) P + r) the INTER row of rank r, (v - 1,
+    // S - 2, 0) the GPipe row (see materialise)
+    uint16_t* row = rows + (size_t)t * stride;
+    if (s0 == S - 1) {
+      const int v = s1 < P ? 2 : 1, r = s1 < P ? s1 : s1 - P, n = (split ? 3 : 2) * v * M;
+      if ((P & (P - 1)) == 0) {
+        GenInterP2 g;
+        g.init(P, v, M, r, split, split ? r : 0);
+        emit_queue(g, row, n);
+      } else {
+        GenInter g;
+        g.init(P, v, M, r, split, split ? r : 0);
+        emit_queue(g, row, n);
+      }
+    } else if (s0 == S - 2 && s1 == 0) {
+      GenAfab g;
+      g.init(split + 1, M);
+      emit_queue(g, row, 2 * (split + 1) * M);
+    }
+    return;
+  }
   GenMerge<2> g;
   g.init(mtab + merge_offset(P, M, 2, split), (split ? 3 : 2) * M, 2,
          [&](int k) { return k == 0 ? s0 : s1; });
@@ -2368,7 +2390,14 @@ __device__ __forceinline__ int materialise(const SimArgs& a, const Chunks<VMAX>&
                                            int gen, int split, uint16_t* row) {
   const int P = a.pr.P, M = a.pr.M;
   const int n = (split ? 3 : 2) * v * M;
-  if (gen == GEN_AFAB) {
+  if (v <= 2 && a.mrows && (gen != GEN_MERGE || v == 2)) {
+    // (generated entry by entry, a queue of 768 took 96 us of a wave's time)
+    const int S2 = 2 * P;
+    const int t = gen == GEN_MERGE   ? (split * S2 + c.st[0]) * S2 + c.st[1]
+                  : gen == GEN_INTER ? (split * S2 + S2 - 1) * S2 + (2 - v) * P + c.st[0]
+                                     : ((v - 1) * S2 + S2 - 2) * S2;
+    copy_row(a.mrows + (size_t)t * a.mrow_stride, row, n);
+  } else if (gen == GEN_AFAB) {
     GenAfab g;
     g.init(v, M);
     emit_queue(g, row, n);
@@ -2377,9 +2406,6 @@ __device__ __forceinline__ int materialise(const SimArgs& a, const Chunks<VMAX>&
     const int r = c.st[0];
     g.init(P, v, M, r, split, split ? r : 0);
     emit_queue(g, row, n);
-  } else if (v == 2 && a.mrows) {
-    const int S2 = 2 * P;
-    copy_row(a.mrows + ((size_t)(split * S2 + c.st[0]) * S2 + c.st[1]) * a.mrow_stride, row, n);
   } else {
     GenMerge<VMAX> g;
     g.init(a.mtab + (v >= 2 ? merge_offset(P, M, v, split) : 0), (split ? 3 : 2) * M, v,
@@ -2473,30 +2499,47 @@ __device__ __forceinline__ void rounds_mat(const uint16_t* row, int qcap, const 
   }
 }
 
-// Move row[from] so that it ends at index to.
-// Eight entries are read before any is written, so that their loads are in flight together.
-__device__ __forceinline__ void move_entry(uint16_t* row, int from, int to) {
-  const uint16_t x = row[from];
-  uint16_t t[8];
-  int i = from;
-  if (from < to) {
-    for (; i + 8 <= to; i += 8) {
+// Move row[from] so that it ends at index to (both inside the row, which starts 16-byte aligned):
+// the spans between them are shifted by one entry, eight in flight. (A 768-entry move by single
+// entries, eight in flight, was a third of k_sim_mat40's time on such records.)
+__device__ __forceinline__ uint4 shift_span(const uint4& b, const uint4& nb, bool up, int i0, int lo,
+                                            int hi, int at, uint32_t x) {
+  // up: entry i takes entry i - 1 (nb: the span below), else entry i + 1 (nb: the span above),
+  // for i in [lo, hi]; entry `at` becomes x
+  const uint32_t w[4] = {b.x, b.y, b.z, b.w};
+  uint32_t y[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = row[i + 1 + u];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) row[i + u] = t[u];
-    }
-    for (; i < to; ++i) row[i] = row[i + 1];
-  } else {
-    for (; i - 8 >= to; i -= 8) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = row[i - 1 - u];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) row[i - u] = t[u];
-    }
-    for (; i > to; --i) row[i] = row[i - 1];
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t below = j ? w[j - 1] : nb.w, above = j < 3 ? w[j + 1] : nb.x;
+    const uint32_t sh = up ? w[j] << 16 | below >> 16 : above << 16 | w[j] >> 16;
+    const int i = i0 + 2 * j;
+    uint32_t m = i >= lo && i <= hi ? 0xFFFFu : 0u;
+    m |= i + 1 >= lo && i + 1 <= hi ? 0xFFFF0000u : 0u;
+    uint32_t v = (sh & m) | (w[j] & ~m);
+    v = at == i ? (v & 0xFFFF0000u) | x : v;
+    v = at == i + 1 ? (v & 0xFFFFu) | x << 16 : v;
+    y[j] = v;
   }
-  row[to] = x;
+  return make_uint4(y[0], y[1], y[2], y[3]);
+}
+__device__ __forceinline__ void move_entry(uint16_t* row, int from, int to) {
+  if (from == to) return;
+  uint4* r = reinterpret_cast<uint4*>(row);
+  const bool up = from > to;
+  const uint32_t x = row[from];
+  const int q0 = from >> 3, n = up ? q0 - (to >> 3) : (to >> 3) - q0, dq = up ? -1 : 1;
+  const int lo = up ? to + 1 : from, hi = up ? from : to - 1;
+  for (int i = 0; i <= n; i += 8) {
+    uint4 b[9];
+#pragma unroll
+    for (int u = 0; u < 9; ++u) b[u] = r[q0 + dq * min(i + u, n)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (i + u > n) break;
+      const int q = q0 + dq * (i + u);
+      r[q] = shift_span(b[u], b[u + 1], up, 8 * q, lo, hi, to, x);
+    }
+  }
 }
 
 // Candidates with perturbations, then candidates whose times overflowed the 40-bit slots:
