@@ -2746,15 +2746,17 @@ __global__ void __launch_bounds__(WAVE) k_sim_mat40(SimArgs a, int mode) {
 //      mailbox; the sender resumes from there.
 // ---------------------------------------------------------------------------------------------
 constexpr uint32_t PI_COMP = 0, PI_SEND = 1, PI_RECV = 2;
-// program item: type << 30 | op kind << 28 | stage << 16 | m; a transfer is named by its producer
-__device__ __forceinline__ uint32_t pitem(uint32_t type, int kind, int s, int m) {
-  return type << 30 | (uint32_t)kind << 28 | (uint32_t)s << 16 | (uint32_t)m;
+// program item: type << 30 | op kind << 28 | stage << 20 | m << 8 | chunk; a transfer is named by its
+// producer; chunk: the lane's own, of the computation, the send's producer or the receive's
+// consumer (an item's kind, stage and m imply it, so that it never decides a comparison)
+__device__ __forceinline__ uint32_t pitem(uint32_t type, int kind, int s, int m, int k) {
+  return type << 30 | (uint32_t)kind << 28 | (uint32_t)s << 20 | (uint32_t)m << 8 | (uint32_t)k;
 }
 constexpr int32_t OB_NONE = -1;
 
 // Per-slot scratch of k_ordered.
 // A communication item of the reordering: its key is (producer end, level, producer node);
-// pk = node << 17 | receive << 16 | gap. No two items of a lane share (level, node), and the level
+// pk = node << 20 | chunk << 17 | receive << 16 | gap. No two items of a lane share (level, node), and the level
 // is looked up (by node) only where two ends are equal. Gaps are at most 3 v M < 2^16.
 struct __align__(16) CItem {
   int64_t key;
@@ -2815,16 +2817,6 @@ __device__ __forceinline__ bool key_less(int64_t t, uint32_t cls, uint32_t tie, 
   return t != t2 ? t < t2 : cls != cls2 ? cls < cls2 : tie < tie2;
 }
 
-// The local chunk of stage s (hosted by this device; unused chunk slots hold stage 0, so only
-// the device's v chunks are searched).
-template <int VMAX>
-__device__ __forceinline__ int chunk_of(const Chunks<VMAX>& c, int s, int v) {
-  int k = 0;
-#pragma unroll
-  for (int i = 0; i < VMAX; ++i) k = (i < v && c.st[i] == s) ? i : k;
-  return k;
-}
-
 // Entry j (0..7, a run-time value) of a 16-byte span: one select of a 64-bit half and a shift.
 __device__ __forceinline__ uint32_t span_entry_at(const uint4& b, int j) {
   const uint64_t lo = (uint64_t)b.x | ((uint64_t)b.y << 32);
@@ -2871,7 +2863,7 @@ __device__ __forceinline__ int build_program(const Chunks<VMAX>& c, const uint16
       const int cx = kind == KF ? pick<VMAX>(c.xF, k) : kind == KB ? pick<VMAX>(c.xB, k) : 0;
       isr[u] = i0 + u < nq && (cx & CX_IN) != 0;
       const int ps = kind == KF ? s - 1 : s + 1;
-      id[u] = pitem(0, kind, ps, m);
+      id[u] = pitem(0, kind, ps, m, k);
       key[u] = isr[u] ? rq[i0 + u].in - (kind == KF ? pick<VMAX>(c.wF, k) : pick<VMAX>(c.wB, k)) : 0;
     }
 #pragma unroll
@@ -2909,7 +2901,7 @@ __device__ __forceinline__ int build_program(const Chunks<VMAX>& c, const uint16
     const int s = pick<VMAX>(c.st, k);
     fin = i < nq ? rq[i].fin : 0;
     dur = dur_of(kind, k);
-    item = pitem(PI_COMP, kind, s, m);
+    item = pitem(PI_COMP, kind, s, m, k);
   };
   // sends: the first send entry at or after position i (nq: none)
   auto send_from = [&](int i, int64_t& key, uint32_t& id) {
@@ -2923,7 +2915,7 @@ __device__ __forceinline__ int build_program(const Chunks<VMAX>& c, const uint16
     }
     const int s = pick<VMAX>(c.st, k);
     key = j < nq ? rq[j].fin : 0;
-    id = pitem(0, kind, s, m);
+    id = pitem(0, kind, s, m, k);
     return j;
   };
   int ci = 0, ri = 0, n = 0;
@@ -2998,12 +2990,12 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
     return kind == KF ? pick<VMAX>(c.dF, k) : kind == KB ? pick<VMAX>(c.dB, k) : pick<VMAX>(c.dW, k);
   };
   // the node field is kind << 17 | stage << 11 | m, ordered as the node index is
-  auto pack = [](int kind, int s, int m, uint32_t recv, int gap) {
-    return (uint64_t)((uint32_t)kind << 17 | (uint32_t)s << 11 | (uint32_t)m) << 17 |
-           (uint64_t)recv << 16 | (uint64_t)(uint32_t)gap;
+  auto pack = [](int kind, int s, int m, int k, uint32_t recv, int gap) {
+    return (uint64_t)((uint32_t)kind << 17 | (uint32_t)s << 11 | (uint32_t)m) << 20 |
+           (uint64_t)(uint32_t)k << 17 | (uint64_t)recv << 16 | (uint64_t)(uint32_t)gap;
   };
   auto level = [&](const CItem& x) {
-    const uint32_t code = (uint32_t)(x.pk >> 17) & 0x7FFFFu;
+    const uint32_t code = (uint32_t)(x.pk >> 20);
     return tl[node(code >> 17, (code >> 11) & 63, code & 0x7FF)];
   };
   auto item_less = [&](const CItem& x, const CItem& y) {
@@ -3059,10 +3051,10 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
       const int s = pick<VMAX>(c.st, k);
       pdur[i0 + u + 1] = ds[u];
       if (cxs[u] & CX_IN) {
-        add(fx[u], pack(kind, kind == KF ? s - 1 : s + 1, m, 1u, i0 + u));
+        add(fx[u], pack(kind, kind == KF ? s - 1 : s + 1, m, k, 1u, i0 + u));
         ++nrv;
       }
-      if (cxs[u] & CX_OUT) add(fy[u], pack(kind, s, m, 0u, i0 + u + 1));
+      if (cxs[u] & CX_OUT) add(fy[u], pack(kind, s, m, k, 0u, i0 + u + 1));
     }
   }
   *nrecv = nrv, *nmis = nf;
@@ -3092,29 +3084,37 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
     const int hi = gap_of(rh);
     const int lo = lastg > logap ? lastg : logap;
     const int iY = gap_of(f);
-    const uint32_t code = (uint32_t)(f.pk >> 17) & 0x7FFFFu;
+    const uint32_t code = (uint32_t)(f.pk >> 20);
     const int64_t xst = f.key - stage_dur(code >> 17, (code >> 11) & 63);
     // the transfer's time: the consumer's input weight
     const uint32_t ey = row[iY];
     const int ky = (ey >> 11) & 7;
     const int64_t cw = ((ey >> 14) & 3) == KF ? pick<VMAX>(c.wF, ky) : pick<VMAX>(c.wB, ky);
-    // the window's lowest gap: the first at or above lo posted at or after X's start (post
-    // times never decrease), or just hi
-    int gx = lo, ge = hi + 1;
-    while (gx < ge) {
-      const int mid = (gx + ge) >> 1;
-      if (post(mid) < xst) gx = mid + 1;
-      else ge = mid;
-    }
-    const int first = gx < hi ? gx : hi;
+    // the window, from hi down to the lowest gap at or above lo posted at or after X's start
+    // (post times never decrease; hi itself always qualifies): four gaps' post times and
+    // duration sums in flight, instead of a bisection's dependent loads
     const int64_t pY = pdur[iY], fk = f.key;
     int best = hi;
     int64_t bestc = 0;
-    for (int gp = hi; gp >= first; --gp) {
-      const int64_t pt = post(gp), D = pY - pdur[gp];
-      const int64_t span = fk > pt ? fk - pt : pt - fk;
-      const int64_t cost = span - (D < cw ? D : cw);
-      if (gp == hi || cost < bestc) best = gp, bestc = cost;
+    for (int g4 = hi; g4 >= lo; g4 -= 4) {
+      int64_t pt[4], ps[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int gp = g4 - u > lo ? g4 - u : lo;
+        pt[u] = post(gp), ps[u] = pdur[gp];
+      }
+      bool in = true;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int gp = g4 - u;
+        in = in && gp >= lo && (gp == hi || pt[u] >= xst);
+        const int64_t D = pY - ps[u];
+        const int64_t span = fk > pt[u] ? fk - pt[u] : pt[u] - fk;
+        const int64_t cost = span - (D < cw ? D : cw);
+        const bool take = in && (gp == hi || cost < bestc);
+        best = take ? gp : best, bestc = take ? cost : bestc;
+      }
+      if (!in) break;
     }
     f.pk = (f.pk & ~(uint64_t)0xFFFFu) | (uint64_t)best;
     mis(a2) = f;
@@ -3133,11 +3133,12 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
     const CItem h = tr ? rh2 : fh;
     for (const int gp = gap_of(h); ci < gp; ++ci) {
       const uint32_t e = cc.at(ci);
-      po.emit(pitem(PI_COMP, (e >> 14) & 3, pick<VMAX>(c.st, (e >> 11) & 7), e & 0x7FF));
+      po.emit(pitem(PI_COMP, (e >> 14) & 3, pick<VMAX>(c.st, (e >> 11) & 7), e & 0x7FF,
+                    (e >> 11) & 7));
     }
-    const uint32_t code = (uint32_t)(h.pk >> 17) & 0x7FFFFu;
+    const uint32_t code = (uint32_t)(h.pk >> 20);
     po.emit(((h.pk >> 16) & 1u ? PI_RECV : PI_SEND) << 30 |
-            pitem(0, code >> 17, (code >> 11) & 63, code & 0x7FF));
+            pitem(0, code >> 17, (code >> 11) & 63, code & 0x7FF, (int)(h.pk >> 17) & 7));
     if (tr) {
       if (++ri < nr) rh2 = items[ri];
     } else {
@@ -3146,9 +3147,139 @@ __device__ __forceinline__ int build_program3(const Chunks<VMAX>& c, const uint1
   }
   for (; ci < nq; ++ci) {
     const uint32_t e = cc.at(ci);
-    po.emit(pitem(PI_COMP, (e >> 14) & 3, pick<VMAX>(c.st, (e >> 11) & 7), e & 0x7FF));
+    po.emit(pitem(PI_COMP, (e >> 14) & 3, pick<VMAX>(c.st, (e >> 11) & 7), e & 0x7FF,
+                  (e >> 11) & 7));
   }
   return po.finish();
+}
+
+// A program read four items at a time, two entries ahead of the one at hand: every fourth round
+// the entries move up (a lane takes at most one item a round) and the third is requested, four
+// rounds before its first use.
+struct ProgIn {
+  LaneArr<uint4> prog;
+  uint4 a, b, c;
+  int q, qmax;
+  __device__ __forceinline__ void init(LaneArr<uint4> p, int cap) {
+    prog = p, qmax = cap / 4 - 1, q = 0;
+    a = p[0], b = p[1 < qmax ? 1 : qmax], c = p[2 < qmax ? 2 : qmax];
+  }
+  __device__ __forceinline__ void refill(int pos) {
+    const bool up = (pos >> 2) != q;
+    a.x = up ? b.x : a.x, a.y = up ? b.y : a.y, a.z = up ? b.z : a.z, a.w = up ? b.w : a.w;
+    b.x = up ? c.x : b.x, b.y = up ? c.y : b.y, b.z = up ? c.z : b.z, b.w = up ? c.w : b.w;
+    q = pos >> 2;
+    c = prog[q + 2 < qmax ? q + 2 : qmax];
+  }
+  __device__ __forceinline__ uint32_t at(int pos) const {  // pos - 4 q < 8
+    const int o = pos - 4 * q;
+    const bool h = (o & 4) != 0, q1 = (o & 1) != 0;
+    const uint32_t x = h ? b.x : a.x, y = h ? b.y : a.y, z = h ? b.z : a.z, w = h ? b.w : a.w;
+    const uint32_t e0 = q1 ? y : x, e1 = q1 ? w : z;
+    return (o & 2) ? e1 : e0;
+  }
+};
+
+// Phase C on 40-bit slots, as lean rounds (slot format and streams of relax_lean, whose records
+// phase A left in LDS): one stream record per item says all that a computation, a send or a receive
+// needs, and the next item is decoded while this one's reads are in flight. (One program item took
+// four rounds of 0.65 us when each decoded its item from the per-chunk arrays behind a branch per
+// type.) last: the lane's latest time.
+template <int VMAX, bool REORDER>
+__device__ __forceinline__ void program_rounds(LaneArr<uint4> prog, int cap, int plen,
+                                               const Chunks<VMAX>& c, int v, const Ring& ring,
+                                               const Table40& T, const uint8_t* strm, int64_t* mbox,
+                                               int64_t* obt, int32_t* obn, int g0, int G,
+                                               uint64_t gbit, uint64_t lsb, int64_t& clock,
+                                               int64_t& last, bool& dead) {
+  struct Op {
+    uint32_t type, tag, rd, wr, mask, want, state, w, dur;
+    int src;  // device its input comes from (-1: none)
+  };
+  const int me = lane_id();
+  LStreams<VMAX, false> S;
+  S.rec = strm + me * 16, S.vm = v;
+  auto decode = [&](uint32_t it, bool none) {
+    const uint32_t kind = (it >> 28) & 3u, k = it & 7u, m = (it >> 8) & 0x7FFu;
+    const LStream x = S.get(kind << 14 | k << 11);
+    const uint32_t mr = (m & (uint32_t)ring.mask) << T.lg;
+    const uint32_t parw = ((m >> ring.lg) & 1u) << 7 | LS_B | LS_F;
+    const uint32_t in = (x.base & 0xFFFFu) + mr, own = (x.base >> 16) + mr;
+    Op o;
+    o.type = it >> 30, o.tag = (it & 0x3FFFFFFFu) >> 8;
+    const bool send = o.type == PI_SEND, recv = o.type == PI_RECV;
+    const uint32_t need = send ? (kind == KF ? LS_F | LS_PAR : LS_B | LS_PAR) : x.fl & 0xFFu;
+    o.rd = none ? 0u : send ? own : in;
+    o.wr = recv ? in : own;
+    o.mask = need;
+    o.want = none ? LS_NEVER : need & parw;
+    o.state = (x.fl >> 8) & parw;
+    o.w = x.w, o.dur = x.dur;
+    const int sF = pick<VMAX>(c.dnF, (int)k), sB = pick<VMAX>(c.dnB, (int)k);
+    o.src = none ? -1 : kind == KF ? sF : kind == KB ? sB : -1;
+    o.type = none ? PI_COMP : o.type;
+    return o;
+  };
+  ProgIn pin;
+  pin.init(prog, cap);
+  int pos = 0;
+  bool arrived = false;
+  Op o = decode(pin.at(0), plen <= 0);
+  int64_t amax = 0;
+  for (bool more = true; more;) {
+    pin.refill(pos);
+#pragma unroll 1
+    for (int u = 0; u < 4; ++u) {
+      const bool send = o.type == PI_SEND, recv = o.type == PI_RECV, comp = o.type == PI_COMP;
+      const int from = g0 + (recv ? o.src : 0);
+      const uint32_t lo = T.lo[o.rd], hi = T.hi[o.rd];
+      const int64_t box = mbox[me], ot = obt[from];
+      const int32_t on = obn[from];
+      Op n = decode(pin.at(pos + 1), pos + 1 >= plen);
+      __asm__ volatile("" : "+v"(n.rd), "+v"(n.wr), "+v"(n.want), "+v"(n.state));
+      const bool rdy = (hi & o.mask) == o.want;
+      const bool okC = comp && rdy;
+      const bool okSA = send && !arrived && rdy;
+      const bool okSD = send && arrived && box != RDV_EMPTY;
+      const bool okR = recv && on == (int32_t)o.tag;
+      const int64_t slot = (int64_t)((uint64_t)lo | (uint64_t)(hi & 31u) << 32);
+      // REORDER: a receive leaves its transfer's arrival as the producer's time in the producer's
+      // slot, which only the consumer, a later computation of the same lane, takes a time from:
+      // whatever else reads it is an op of the producer's own device, whose clock is past the
+      // producer's end
+      const int64_t tin = REORDER ? (o.src >= 0 ? slot : 0) : slot + o.w;
+      const int64_t fin = (tin > clock ? tin : clock) + o.dur;
+      // the handshake, and where both clocks go: its end (blocking) or its start (REORDER)
+      const int64_t hs = ot > clock ? ot : clock, arr = hs + o.w;
+      const int64_t xend = REORDER ? hs : arr;
+      if ((okC && o.state) || (REORDER && okR)) {
+        const int64_t t = okC ? fin : arr;
+        T.lo[o.wr] = (uint32_t)t;
+        T.hi[o.wr] = (uint8_t)(((uint32_t)((uint64_t)t >> 32) & 31u) | (okC ? o.state : hi & 0xE0u));
+      }
+      if (okSA) obn[me] = (int32_t)o.tag, obt[me] = clock;
+      if (okSD) mbox[me] = RDV_EMPTY, obn[me] = OB_NONE;
+      if (okR) mbox[from] = xend;
+      if (REORDER) amax = okR && arr > amax ? arr : amax;
+      clock = okC ? fin : okSD ? box : okR ? xend : clock;
+      arrived = okSA ? true : okSD ? false : arrived;
+      const bool done = okC || okSD || okR;
+      pos += done ? 1 : 0;
+      o.type = done ? n.type : o.type, o.tag = done ? n.tag : o.tag;
+      o.rd = done ? n.rd : o.rd, o.wr = done ? n.wr : o.wr;
+      o.mask = done ? n.mask : o.mask, o.want = done ? n.want : o.want;
+      o.state = done ? n.state : o.state, o.w = done ? n.w : o.w, o.dur = done ? n.dur : o.dur;
+      o.src = done ? n.src : o.src;
+      __asm__ volatile("" ::: "memory");
+      if (__ballot(done || okSA) == 0) {
+        more = false;
+        break;
+      }
+    }
+  }
+  const uint64_t actm = __ballot(pos < plen);
+  if (actm != 0 && (fold_groups(actm, G, lsb) & gbit)) dead = true;
+  last = amax > clock ? amax : clock;
 }
 
 // RING: 40-bit ring tables of a.ring rows per stage per group. Phase C keeps each device's
@@ -3265,106 +3396,89 @@ k_ordered(SimArgs a, OrdBufs ob,
     int64_t clock = 0, last = 0;  // the lane's clock; its latest time (arrivals too)
     bool cdead = false;
     if (!dead) {
-      const uint8_t* devs = rec + 3 + a.pr.s_max;
-      int pos = 0;
-      bool live = pos < plen, arrived = false;
-      // the program is read four items at a time, two entries ahead of the one at hand; every
-      // fourth round the entries move up (a lane takes at most one item a round) and the
-      // third is requested, four rounds before its first use
-      const int pmax = ob.pcap / 4 - 1;
-      uint4 pa = prog[0], pb = prog[1 < pmax ? 1 : pmax], pc = prog[2 < pmax ? 2 : pmax];
-      int pq = 0;
-      auto item_at = [&](int o) {  // item 4 pq + o, o < 8
-        const bool h = (o & 4) != 0, q1 = (o & 1) != 0;
-        const uint32_t x = h ? pb.x : pa.x, y = h ? pb.y : pa.y, z = h ? pb.z : pa.z,
-                       w = h ? pb.w : pa.w;
-        const uint32_t e0 = q1 ? y : x, e1 = q1 ? w : z;
-        return (o & 2) ? e1 : e0;
-      };
-      // the current item, decoded
-      uint32_t type = 0, tag = 0;
-      int rd = 0, wr = 0, store = 0, src = 0;
-      uint32_t mask = 0, want = 0, state = 0;
-      int64_t w = 0, dur = 0, amax = 0;
-      // REORDER: a receive leaves its transfer's arrival as the producer's time in the producer's
-      // slot, which only the consumer (a later computation of the same lane) takes a time from
-      // (xin): whatever else reads it is an op of the producer's own device, whose clock is past
-      // the producer's end
-      bool xin = false;
-      auto decode = [&](uint32_t it) {
-        type = it >> 30;
-        const int kind = (int)((it >> 28) & 3u), s = (int)((it >> 16) & 63u), m = (int)(it & 0x7FFu);
-        tag = it & 0x3FFFFFFFu;
-        if (type == PI_COMP) {
-          Desc D;
-          describe<VMAX>(D, c, ring, kind, chunk_of<VMAX>(c, s, v), m);
-          rd = D.rd, wr = D.wr, store = D.store, mask = (uint32_t)D.mask, want = (uint32_t)D.want;
-          state = D.state, w = D.w, dur = D.dur;
-          xin = (D.cx & CX_IN) != 0;
-        } else {
-          rd = wr = s * ring.R + (m & ring.mask);
-          if (type == PI_SEND) {  // its producer (an own op) must have finished
-            const uint32_t par = ((uint32_t)m >> ring.lg) & 1u;
-            mask = (kind == KF ? ST_F : ST_B) | ST_PAR;
-            want = (kind == KF ? ST_F : ST_B) | (par ? ST_PAR : 0u);
-          } else {  // receive: the producer's device and the consumer's link weight
-            src = devs[s];
-            const int cs = kind == KF ? s + 1 : s - 1;
-            const int ck = chunk_of<VMAX>(c, cs, v);
-            w = kind == KF ? pick<VMAX>(c.wF, ck) : pick<VMAX>(c.wB, ck);
+      if constexpr (RING) {
+        program_rounds<VMAX, REORDER>(prog, ob.pcap, plen, c, v, ring, T, smem + a.strm_off, mbox,
+                                      obt, obn, g0, G, gbit, lsb, clock, last, cdead);
+      } else {
+        const uint8_t* devs = rec + 3 + a.pr.s_max;
+        int pos = 0;
+        bool live = pos < plen, arrived = false;
+        ProgIn pin;
+        pin.init(prog, ob.pcap);
+        // the current item, decoded
+        uint32_t type = 0, tag = 0;
+        int rd = 0, wr = 0, store = 0, src = 0;
+        uint32_t mask = 0, want = 0, state = 0;
+        int64_t w = 0, dur = 0;
+        bool xin = false;
+        auto decode = [&](uint32_t it) {
+          type = it >> 30;
+          const int kind = (int)((it >> 28) & 3u), s = (int)((it >> 20) & 63u),
+                    m = (int)((it >> 8) & 0x7FFu), k = (int)(it & 7u);
+          tag = (it & 0x3FFFFFFFu) >> 8;
+          if (type == PI_COMP) {
+            Desc D;
+            describe<VMAX>(D, c, ring, kind, k, m);
+            rd = D.rd, wr = D.wr, store = D.store, mask = (uint32_t)D.mask, want = (uint32_t)D.want;
+            state = D.state, w = D.w, dur = D.dur;
+            xin = (D.cx & CX_IN) != 0;
+          } else {
+            rd = wr = s * ring.R + (m & ring.mask);
+            if (type == PI_SEND) {  // its producer (an own op) must have finished
+              const uint32_t par = ((uint32_t)m >> ring.lg) & 1u;
+              mask = (kind == KF ? ST_F : ST_B) | ST_PAR;
+              want = (kind == KF ? ST_F : ST_B) | (par ? ST_PAR : 0u);
+            } else {  // receive: the producer's device and the consumer's link weight
+              src = devs[s];
+              w = kind == KF ? pick<VMAX>(c.wF, k) : pick<VMAX>(c.wB, k);
+            }
           }
-        }
-      };
-      decode(live ? item_at(0) : 0u);
-      for (bool more = true; more;) {
-        const bool up = (pos >> 2) != pq;
-        pa.x = up ? pb.x : pa.x, pa.y = up ? pb.y : pa.y, pa.z = up ? pb.z : pa.z, pa.w = up ? pb.w : pa.w;
-        pb.x = up ? pc.x : pb.x, pb.y = up ? pc.y : pb.y, pb.z = up ? pc.z : pb.z, pb.w = up ? pc.w : pb.w;
-        pq = pos >> 2;
-        pc = prog[pq + 2 < pmax ? pq + 2 : pmax];
+        };
+        decode(live ? pin.at(0) : 0u);
+        for (bool more = true; more;) {
+          pin.refill(pos);
 #pragma unroll 1
-        for (int u = 0; u < 4; ++u) {
-          uint32_t plo, phi;
-          T.issue(live ? rd : 0, plo, phi);
-          const int64_t box = mbox[me];
-          const int32_t on = obn[g0 + (type == PI_RECV ? src : 0)];
-          const int64_t ot = obt[g0 + (type == PI_RECV ? src : 0)];
-          const uint64_t p = (uint64_t)plo | ((uint64_t)phi << 32);
-          const bool rdy = (plo & mask) == want;
-          const bool okC = live && type == PI_COMP && rdy;
-          const int64_t tin = REORDER ? (xin ? (int64_t)(p >> 3) : 0) : (int64_t)(p >> 3) + w;
-          const int64_t st = tin > clock ? tin : clock;
-          const int64_t fin = st + dur;
-          const bool okSA = live && type == PI_SEND && !arrived && rdy;
-          const bool okSD = live && type == PI_SEND && arrived && box != RDV_EMPTY;
-          const bool okR = live && type == PI_RECV && on == (int32_t)tag;
-          // the handshake, and where both clocks go: its end (blocking) or its start (REORDER)
-          const int64_t hs = ot > clock ? ot : clock;
-          const int64_t arr = hs + w;
-          const int64_t xend = REORDER ? hs : arr;
-          if ((okC && store) || (REORDER && okR))
-            T.store(wr, okC ? ((uint64_t)fin << 3) | state : ((uint64_t)arr << 3) | (p & 7u));
-          if (okSA) obn[me] = (int32_t)tag, obt[me] = clock;
-          if (okSD) mbox[me] = RDV_EMPTY, obn[me] = OB_NONE;
-          if (okR) mbox[g0 + src] = xend;
-          if (REORDER && RING) amax = okR && arr > amax ? arr : amax;
-          clock = okC ? fin : okSD ? box : okR ? xend : clock;
-          arrived = okSA ? true : okSD ? false : arrived;
-          if (okC || okSD || okR) {
-            ++pos;
-            live = pos < plen;
-            decode(live ? item_at(pos - 4 * pq) : 0u);
-          }
-          __asm__ volatile("" ::: "memory");
-          if (__ballot(okC || okSA || okSD || okR) == 0) {
-            more = false;
-            break;
+          for (int u = 0; u < 4; ++u) {
+            uint32_t plo, phi;
+            T.issue(live ? rd : 0, plo, phi);
+            const int64_t box = mbox[me];
+            const int32_t on = obn[g0 + (type == PI_RECV ? src : 0)];
+            const int64_t ot = obt[g0 + (type == PI_RECV ? src : 0)];
+            const uint64_t p = (uint64_t)plo | ((uint64_t)phi << 32);
+            const bool rdy = (plo & mask) == want;
+            const bool okC = live && type == PI_COMP && rdy;
+            const int64_t tin = REORDER ? (xin ? (int64_t)(p >> 3) : 0) : (int64_t)(p >> 3) + w;
+            const int64_t st = tin > clock ? tin : clock;
+            const int64_t fin = st + dur;
+            const bool okSA = live && type == PI_SEND && !arrived && rdy;
+            const bool okSD = live && type == PI_SEND && arrived && box != RDV_EMPTY;
+            const bool okR = live && type == PI_RECV && on == (int32_t)tag;
+            // the handshake, and where both clocks go: its end (blocking) or its start (REORDER)
+            const int64_t hs = ot > clock ? ot : clock;
+            const int64_t arr = hs + w;
+            const int64_t xend = REORDER ? hs : arr;
+            if ((okC && store) || (REORDER && okR))
+              T.store(wr, okC ? ((uint64_t)fin << 3) | state : ((uint64_t)arr << 3) | (p & 7u));
+            if (okSA) obn[me] = (int32_t)tag, obt[me] = clock;
+            if (okSD) mbox[me] = RDV_EMPTY, obn[me] = OB_NONE;
+            if (okR) mbox[g0 + src] = xend;
+            clock = okC ? fin : okSD ? box : okR ? xend : clock;
+            arrived = okSA ? true : okSD ? false : arrived;
+            if (okC || okSD || okR) {
+              ++pos;
+              live = pos < plen;
+              decode(live ? pin.at(pos) : 0u);
+            }
+            __asm__ volatile("" ::: "memory");
+            if (__ballot(okC || okSA || okSD || okR) == 0) {
+              more = false;
+              break;
+            }
           }
         }
+        const uint64_t actm = __ballot(live);
+        if (actm != 0 && (fold_groups(actm, G, lsb) & gbit)) cdead = true;
       }
-      const uint64_t actm = __ballot(live);
-      if (actm != 0 && (fold_groups(actm, G, lsb) & gbit)) cdead = true;
-      last = amax > clock ? amax : clock;
     }
     const int64_t ms = group_max(clock, G);
     int64_t srecv = 0, smis = 0;
