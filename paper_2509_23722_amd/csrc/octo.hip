@@ -900,6 +900,45 @@ __device__ __forceinline__ int64_t sweep_row(int64_t* row, int stride, int M, in
   return f;
 }
 
+// The communication tally of a row (CommTally::op over its M ops). From the second op on the op
+// before is of the same row, so that the clock, the op before's start and its transfer's end are f,
+// f - dur and f + cout: a receive overlaps when r < f and r + w > f - dur, a send when f + cout
+// > r + w (and dur, w and cout are not 0), for min(dur, w) and min(dur, cout) each time. An op
+// only counts them; the rest is the row's. (262,144 candidates at P = 8, M = 64, a quarter of them
+// GPipe: k_afab 112 us; 430 with the op-wise tally, whose rows were in LDS for want of registers.)
+struct AfabTally {
+  int nr, ns;
+  int64_t st;  // start of the latest op
+  __device__ __forceinline__ int64_t first(CommTally& ct, int64_t r, int64_t f, int64_t w,
+                                           int64_t dur, int cx, int64_t cout) {
+    nr = ns = 0;
+    const int64_t y = r + w;
+    st = y > f ? y : f;
+    ct.op(true, cx, y, w, f, st, st + dur, cout);
+    return st + dur;
+  }
+  __device__ __forceinline__ int64_t next(int64_t r, int64_t f, int64_t w, int64_t dur,
+                                          int64_t cout) {
+    const int64_t y = r + w;
+    nr += r < f && y > st ? 1 : 0;
+    ns += f + cout > y ? 1 : 0;
+    st = y > f ? y : f;
+    return st + dur;
+  }
+  // ops: those after the first
+  __device__ __forceinline__ void finish(CommTally& ct, int ops, int64_t f, int64_t w, int64_t dur,
+                                         int cx, int64_t cout) const {
+    const bool in = (cx & CX_IN) != 0, out = (cx & CX_OUT) != 0;
+    const int64_t r = in && dur > 0 && w > 0 ? nr : 0, s = out && dur > 0 && cout > 0 ? ns : 0;
+    ct.n += ops * ((in ? 1 : 0) + (out ? 1 : 0));
+    ct.t += ops * ((in ? w : 0) + (out ? cout : 0));
+    ct.nov += (int)(r + s);
+    ct.tov += r * (dur < w ? dur : w) + s * (dur < cout ? dur : cout);
+    ct.pst = st;
+    ct.pend = out ? f + cout : -1;
+  }
+};
+
 // The previous row of a k_afab lane: MMAX > 0 keeps it in registers (M == MMAX, the loop fully
 // unrolled), MMAX = 0 in LDS (M int64 per lane, lanes interleaved).
 template <int MMAX>
@@ -937,14 +976,15 @@ struct AfabRow {
   // the same row, tallying each op's communication nodes (flags cx, output transfer cout)
   __device__ __forceinline__ int64_t sweep_c(int, int64_t f, int64_t w, int64_t dur, int cx,
                                              int64_t cout, CommTally& ct) {
+    AfabTally q;
+    f = q.first(ct, r[0], f, w, dur, cx, cout);
+    r[0] = f;
 #pragma unroll
-    for (int m = 0; m < MMAX; ++m) {
-      const int64_t y = r[m] + w;
-      const int64_t st = y > f ? y : f;
-      ct.op(true, cx, y, w, f, st, st + dur, cout);
-      f = st + dur;
+    for (int m = 1; m < MMAX; ++m) {
+      f = q.next(r[m], f, w, dur, cout);
       r[m] = f;
     }
+    q.finish(ct, MMAX - 1, f, w, dur, cx, cout);
     return f;
   }
 };
@@ -976,13 +1016,19 @@ struct AfabRow<0> {
   }
   __device__ __forceinline__ int64_t sweep_c(int M, int64_t f, int64_t w, int64_t dur, int cx,
                                              int64_t cout, CommTally& ct) {
-    for (int m = 0; m < M; ++m) {
-      const int64_t y = row[m * stride] + w;
-      const int64_t st = y > f ? y : f;
-      ct.op(true, cx, y, w, f, st, st + dur, cout);
-      f = st + dur;
-      row[m * stride] = f;
+    AfabTally q;
+    f = q.first(ct, row[0], f, w, dur, cx, cout);
+    row[0] = f;
+    int m = 1;
+    for (; m + 8 <= M; m += 8) {
+      int64_t x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = row[(m + i) * stride];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f = q.next(x[i], f, w, dur, cout), row[(m + i) * stride] = f;
     }
+    for (; m < M; ++m) f = q.next(row[m * stride], f, w, dur, cout), row[m * stride] = f;
+    q.finish(ct, M - 1, f, w, dur, cx, cout);
     return f;
   }
 };
@@ -5838,10 +5884,9 @@ int launch_afab(const octo_problem* prob, const Setup& su, const int64_t* link, 
                 int64_t* bound, int v_lo, hipStream_t stream) {
   // rows as line envelopes (plain, memory and bounds variants); the communication and
   // serialised-link variants, which need every op, keep rows of exactly 32 or 64 micro-batches
-  // in registers and other lengths (and the communication variant's, whose unrolled sweep would
-  // not fit the register file) in LDS
+  // in registers and other lengths in LDS
   constexpr bool LINES = X == XP || X == XM || X == XB;
-  const int mmax = LINES ? -1 : X == XC ? 0 : prob->M == 32 ? 32 : prob->M == 64 ? 64 : 0;
+  const int mmax = LINES ? -1 : prob->M == 32 ? 32 : prob->M == 64 ? 64 : 0;
   // per device: the clock, the busy time (in registers for the plain variant at P <= 8), then
   // the variant's own words
   const int words = (X == XM || X == XB) ? 3 : X == XC ? 4 : (X == XP && prob->P <= 8) ? 1 : 2;

@@ -308,3 +308,34 @@ def test_interleaved(P, M, n, call):
     torch.cuda.synchronize()
     for x, y in zip(g, r):
         np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,v_max,M", [
+    (1, 2, 1), (2, 2, 2), (3, 2, 8), (4, 2, 9), (3, 3, 17), (4, 2, 32), (5, 2, 33), (8, 2, 64),
+    (6, 2, 65),
+])
+def test_gpipe_tally(P, v_max, M):
+    """The communication tally of GPipe rows counted row by row: one micro-batch, lengths around
+    the unrolled ones, durations and links of zero and near each other."""
+    import torch
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(15000 + 100 * P + M)
+    print(f"GPipe tally: P={P} v_max={v_max} M={M}", flush=True)
+    L = P * v_max + 3
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    for top in (3, 40, 3_000_000):
+        costs = rng.integers(0, top, size=(L, 3)).astype(np.int64)
+        costs[rng.random(L) < 0.2] = 0
+        link = rng.integers(0, 2 * top, size=(P, P)).astype(np.int64)
+        link[rng.random((P, P)) < 0.2] = 0
+        recs = I.random_candidates(rng, L, P, v_max, M, 300, policies=(0,))
+        gp = _lib.problem(L, P, v_max, M, recs.shape[1], 0)
+        rp = R.problem(L, P, v_max, M, recs.shape[1], 0)
+        g = _lib.sim_batch_comm(gp, t(costs), t(link), t(recs))
+        r = R.sim_batch_comm(rp, costs, link, recs, nthreads=NTHREADS)
+        torch.cuda.synchronize()
+        for x, y in zip(g, r):
+            np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
