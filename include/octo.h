@@ -370,7 +370,8 @@ int octo_tune_step_mem(const octo_problem* prob, const int64_t* layer_costs,
  *   out_makespan  int64 [n], out_bubble int64 [n][P]: the final records' evaluation.
  *   out_stats     int64 [n][4]: moves kept in the partitioning, placement and scheduling
  *                 phases, and the iterations in which a phase was searched.
- * The library evaluates each iteration's neighbours as one batch in its workspace, at most
+ * The library evaluates each iteration's neighbours (of the scheduling moves those that can
+ * shorten the makespan) as one batch in its workspace, at most
  * n * max(v_max^2, (P-1) v_max^2 + 1, 6 v_max M + 1) records (OCTO_EINVAL above 2^31 - 1;
  * OCTO_ENOMEM if it cannot be allocated). Returns OCTO_OK or a negative status.
  */

@@ -7,6 +7,8 @@
 //               sentinel of invalid candidates, count candidates per work bin.
 //   k_plan      start position of each bin.
 //   k_scatter   candidate indices grouped by bin (counting sort).
+//   k_front     the four above (k_merge_tab aside) in one block, for small batches.
+//   k_pipe, k_pipe2  the v = 1 orders and the interleaved ones of v = 2 as systolic arrays.
 //   k_sched     persistent waves; each takes a chunk of CPW candidates of one bin and runs them
 //               together from precomputed entries (the hot kernel): the round schedules of the
 //               structure classes, the stage rows of the MERGE orders.
@@ -2782,7 +2784,7 @@ __global__ void __launch_bounds__(WAVE) k_sim_mat40(SimArgs a, int mode) {
 // asynchronous schedule — with blocking rendezvous transfers. A device's program is its items
 // sorted by (time, communication before computation, then the producer's id (kind, stage, m) for
 // a transfer or the queue position for a computation); a compute item's time is its start.
-// One group per candidate (lane = device), queues materialised, 64-bit finish table:
+// One group per candidate (lane = device), queues materialised, finish tables in LDS:
 //   A. the plain rounds, recording each op's finish and input time by queue position;
 //   B. each lane builds its program: computations and sends come in queue order already, its
 //      receives (keyed by their producers' ends) are insertion-sorted, then the three merge;
@@ -3338,9 +3340,12 @@ __device__ __forceinline__ void program_rounds(LaneArr<uint4> prog, int cap, int
 // phase C: a receive completes when the sender has announced itself, at h = max(the sender's
 // announce time, the receiver's clock); both clocks go to h, and the data's arrival h + w replaces
 // the producer's finish in its slot, where the consumer takes it as its input time.
-// Three waves per SIMD for the ideal-start variant (its phases wait on global loads: 27.5 ->
-// 25.1 ms on 65,536 candidates of the P = 8, M = 64 batch, a few registers spilled); the
+// Three waves per SIMD for the ideal-start variant (its phases wait on global loads); the
 // reordering variant keeps its registers (at three waves it spills and slows by a third).
+// Bound: phase B, a chain of dependent lane-interleaved loads and stores per lane. On 16,384 mixed
+// candidates at P = 8, M = 64, ring and full-row pass: ideal-start 5.6 + 4.8 -> 4.8 + 4.1 ms,
+// reordering 9.1 + 6.9 -> 5.9 + 5.0 ms; per wave of the reordering's v = 2 ZB orders A 0.4, items 0.9,
+// sort 0.5, windows 1.9 (a bisection; less now), merge 0.7, C 2.1 ms (before its lean rounds).
 template <int VMAX, bool RING, bool REORDER>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(REORDER ? 2 : 3, 8)))
 k_ordered(SimArgs a, OrdBufs ob,
@@ -5038,7 +5043,7 @@ struct Workspace {
   // Algorithm 1: search state and each iteration's neighbour batch
   void* a1 = nullptr;
   size_t a1_bytes = 0;
-  // reordered coordination: per-slot finish times, receive lists and programs
+  // reordered coordination: op times, receive lists or items, and programs
   void* ord = nullptr;
   size_t ord_bytes = 0;
   // static round schedules of the structure classes, their metadata and the stage rows, same
