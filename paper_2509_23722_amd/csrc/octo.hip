@@ -2201,6 +2201,7 @@ __device__ __forceinline__ void pipe2_run32(Pipe2Int& p, int P, int M, int G, in
   }
   run(I1{}, I2{}, 2 * P - 1, skew, [&]() { okB |= bB; });
   origin();
+  p.oB = isel(rank0, 0, p.oB);  // (no output yet: a value in range for the lanes without an input)
   int t = skew;
   if constexpr (ROT) {
     for (; t + 16 <= N; t += 16) {

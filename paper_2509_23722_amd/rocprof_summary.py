@@ -71,7 +71,8 @@ def main():
     for k in ("fetch", "write", "copy-fetch", "copy-write"):
         ap.add_argument("--" + k)
     ap.add_argument("--sq", action="append", default=[])
-    ap.add_argument("--kernel", help="short name of the dominant kernel")
+    ap.add_argument("--kernel", help="short name of the dominant kernel, or NAME=KERNEL+KERNEL.. "
+                    "for kernels that one event interval of the bench covers")
     ap.add_argument("--workload", required=True)
     ap.add_argument("--tag", help="file name tag (default: the workload)")
     ap.add_argument("--what", default="one `bench.py --headline-only` run: every simulation "
@@ -127,7 +128,9 @@ def traffic_summary(args, cmds, tag):
              "Commands:", "", "```", cmds, "```", "",
              "| kernel | dispatches | FETCH KiB | WRITE KiB | HBM MB (scaled) |",
              "|---|---:|---:|---:|---:|"]
-    rec = None
+    name, _, parts = args.kernel.partition("=")
+    parts = parts.split("+") if parts else [name]
+    got = []
     for k in fetch:
         if "copyBuffer" in k:
             continue
@@ -135,15 +138,16 @@ def traffic_summary(args, cmds, tag):
         wk = write.get(k, {}).get("WRITE_SIZE", (0.0, 0))[0]
         mb = (fk * 1024 * ff + wk * 1024 * wf) / 1e6
         lines.append(f"| {k} | {n} | {fk:.1f} | {wk:.1f} | {mb:.2f} |")
-        if k == args.kernel:
-            rec = {"kernel": k, "kernel_source_sha": kernel_source_hash(),
-                   "hbm_bytes_per_launch": int(fk * 1024 * ff + wk * 1024 * wf),
-                   "fetch_kib": fk, "write_kib": wk, "fetch_factor": ff, "write_factor": wf,
-                   "workload": args.workload}
+        if k in parts:
+            got.append((fk, wk))
     with open(os.path.join(args.out_dir, f"hbm_traffic_{tag}.md"), "w") as f:
         f.write("\n".join(lines) + "\n")
-    if rec is None:
+    if len(got) != len(parts):
         raise SystemExit(f"kernel {args.kernel} not in the counter runs")
+    fk, wk = sum(x for x, _ in got), sum(y for _, y in got)
+    rec = {"kernel": name, "kernels": parts, "kernel_source_sha": kernel_source_hash(),
+           "hbm_bytes_per_launch": int(fk * 1024 * ff + wk * 1024 * wf), "fetch_kib": fk,
+           "write_kib": wk, "fetch_factor": ff, "write_factor": wf, "workload": args.workload}
     with open(os.path.join(args.out_dir, f"traffic_{tag}.json"), "w") as f:
         json.dump(rec, f, indent=1)
         f.write("\n")

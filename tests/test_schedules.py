@@ -273,7 +273,7 @@ def test_one_stage_per_device(P, M, n, call):
 @pytest.mark.parametrize("P,M,n", [
     (2, 2, 100), (2, 8, 200), (3, 3, 200), (3, 12, 200), (4, 4, 200), (4, 20, 200), (5, 5, 200),
     (6, 18, 200), (8, 8, 200), (8, 16, 200), (8, 64, 200), (12, 24, 200), (15, 15, 200),
-    (16, 16, 200), (16, 32, 200), (16, 64, 200), (17, 17, 200),
+    (16, 16, 200), (16, 32, 200), (16, 64, 200), (17, 17, 200), (24, 48, 60), (32, 96, 60),
 ])
 @pytest.mark.parametrize("call", ["plain", "mem", "serial", "bounds", "comm"])
 def test_interleaved(P, M, n, call):
