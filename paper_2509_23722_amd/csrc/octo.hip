@@ -8,7 +8,7 @@
 //   k_plan      start position of each bin.
 //   k_scatter   candidate indices grouped by bin (counting sort).
 //   k_front     the four above (k_merge_tab aside) in one block, for small batches.
-//   k_pipe, k_pipe2  the v = 1 orders and the interleaved ones of v = 2 as systolic arrays.
+//   k_pipe      the v = 1 orders and the looped interleaved ones of v = 2 as systolic arrays.
 //   k_sched     persistent waves; each takes a chunk of CPW candidates of one bin and runs them
 //               together from precomputed entries (the hot kernel): the round schedules of the
 //               structure classes, the stage rows of the MERGE orders.
@@ -102,7 +102,7 @@ struct SimArgs {
   // slots, rounds until every device has started}
   const uint32_t* stab;
   const int32_t* smeta;
-  bool pipe, pipe2;  // the v = 1 classes are k_pipe's, the v = 2 interleaved ones k_pipe2's
+  bool pipe, pipe2;  // the v = 1 classes are k_pipe's, the v = 2 interleaved ones k_pipe's too
   // k_sched over MERGE bins: the stage rows of v = sr_v (null: none), S + 1 rows of sr_rowlen[split]
   // entries from sr_off[split], of which sr_steps[split] are steps
   const uint32_t* srow;
@@ -1888,122 +1888,6 @@ __device__ __forceinline__ void pipe_gpipe(PipeLane<X, false>& p, int S, int M, 
   pass(std::integral_constant<int, 1>{}, S - 1 - s);
 }
 
-template <int X>
-__global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a, int gpipe) {
-  extern __shared__ __align__(16) uint8_t smem[];
-  const int P = a.pr.P, M = a.pr.M, L = a.pr.L, S = P;
-  // layer prefix sums and links: every lane reads its stage's entries
-  int64_t* pre = reinterpret_cast<int64_t*>(smem);
-  int64_t* link = pre + 3 * (L + 1);
-  for (int i = lane_id(); i < 3 * (L + 1); i += WAVE) pre[i] = a.pre[i];
-  for (int i = lane_id(); i < P * P; i += WAVE) link[i] = a.link[i];
-  __syncthreads();
-  const int h = a.G >> 1, x = lane_id() & 15;
-  const int s = 2 * ((x & 7) & (h - 1)) + (x >> 3);
-  const int g = (lane_id() >> 4) * (8 / h) + (x & 7) / h;
-  // the bins (split, fused, GPipe where it is this kernel's) and their chunk ranges, one per lane
-  const int ci = lane_id(), nb = gpipe ? 3 : 2;
-  const int bin_i = ci == 2 ? bin_of(1, GEN_AFAB, 0) : BIN_STATIC + (ci == 0 ? 1 : 0);
-  const int cnt_i = ci < nb ? a.ctl[CTL_COUNTS + bin_i] : 0;
-  const int start_i = ci < nb ? a.ctl[CTL_START + bin_i] : 0;
-  const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
-  const int end0 = __shfl(nch_i, 0, WAVE), end1 = end0 + __shfl(nch_i, 1, WAVE);
-  const int end2 = end1 + __shfl(nch_i, 2, WAVE);
-  // chunks by grid stride, the longer (split) ones first
-  for (int ch = (int)blockIdx.x; ch < end2; ch += (int)gridDim.x) {
-    const int ib = ch < end0 ? 0 : ch < end1 ? 1 : 2;
-    const int split = ib == 0 ? 1 : 0;
-    const int cnt = __shfl(cnt_i, ib, WAVE), pos0 = __shfl(start_i, ib, WAVE);
-    const int e = (ch - (ib == 0 ? 0 : ib == 1 ? end0 : end1)) * a.CPW + g;
-    const int64_t cand = e < cnt ? (int64_t)a.idx[pos0 + e] : -1;
-    const bool mine = cand >= 0 && s < P;
-    int d = 0;
-    int64_t f = 0, b = 0, wg = 0, wF = 0, wB = 0, cF = 0, cB = 0, act = 0, stat = 0;
-    if (mine) {
-      const uint8_t* rec = a.cands + cand * a.pr.stride;
-      const uint8_t* bnd = rec + 4;
-      const uint8_t* dev = rec + 3 + a.pr.s_max;
-      const int b0 = s > 0 ? bnd[s - 1] : 0, b1 = s < S - 1 ? bnd[s] : L;
-      d = dev[s];
-      const int dp = s > 0 ? dev[s - 1] : d, dn = s < S - 1 ? dev[s + 1] : d;
-      f = pre[3 * b1] - pre[3 * b0];
-      b = pre[3 * b1 + 1] - pre[3 * b0 + 1];
-      wg = pre[3 * b1 + 2] - pre[3 * b0 + 2];
-      wF = s > 0 ? link[dp * P + d] : 0, wB = s < S - 1 ? link[dn * P + d] : 0;
-      if constexpr (X == XS)
-        cF = s < S - 1 ? link[d * P + dn] : 0, cB = s > 0 ? link[d * P + dp] : 0;
-      if constexpr (X == XM) {
-        act = a.pre_mem[2 * b1] - a.pre_mem[2 * b0];
-        stat = a.pre_mem[2 * b1 + 1] - a.pre_mem[2 * b0 + 1];
-      }
-    }
-    const int64_t dB = split ? b : b + wg;
-    const bool fits =
-        ((uint64_t)f | (uint64_t)dB | (uint64_t)wg | (uint64_t)wF | (uint64_t)wB) >> 32 == 0;
-    // the group's lanes: xor over the stage pairs, then over the two halves
-    const auto group_or = [&](int y) {
-      for (int o = 1; o < h; o <<= 1) y |= __shfl_xor(y, o, WAVE);
-      return y | __shfl_xor(y, 8, WAVE);
-    };
-    const bool wide = group_or(mine && !fits) != 0;
-    const int fpar = s & 1;
-    // an idle lane (or a wide candidate's) keeps clock 0: no input, no duration
-    const bool on = mine && !wide;
-    const double xF = on && s > 0 ? (X == XS ? 0.0 : (double)wF) : PIPE_NONE;
-    const double xB = on && s < S - 1 ? (X == XS ? 0.0 : (double)wB) : PIPE_NONE;
-    const double dF = on ? (double)f : 0.0, dBd = on ? (double)dB : 0.0;
-    const double dW = on && split ? (double)wg : 0.0;
-    double ms = 0.0, fs = 0.0, clk = 0.0;
-    auto run = [&](auto tag) {
-      constexpr bool SPLIT = decltype(tag)::value;
-      PipeLane<X, SPLIT> p;
-      p.clk = p.out = 0.0, p.fs = -1.0;
-      p.w[0] = fpar ? xB : xF, p.w[1] = fpar ? xF : xB;
-      p.d[0] = fpar ? dBd : dF, p.d[1] = fpar ? dF : dBd;
-      p.g[0] = fpar ? dW : 0.0, p.g[1] = fpar ? 0.0 : dW;
-      p.c[0] = on ? (double)(fpar ? cB : cF) : 0.0, p.c[1] = on ? (double)(fpar ? cF : cB) : 0.0;
-      p.lf[0] = p.lf[1] = 0.0;
-      pipe_run<X, SPLIT>(p, S, M, s);
-      // the W's still deferred
-      if (SPLIT) p.clk += (double)(s < M ? s : M) * dW;
-      clk = p.clk, fs = p.fs;
-    };
-    if (ib == 2) {
-      PipeLane<X, false> p;
-      p.clk = p.out = 0.0, p.fs = -1.0;
-      p.w[0] = xF, p.w[1] = xB, p.d[0] = dF, p.d[1] = dBd;
-      p.c[0] = on ? (double)cF : 0.0, p.c[1] = on ? (double)cB : 0.0;
-      p.lf[0] = p.lf[1] = 0.0;
-      pipe_gpipe<X>(p, S, M, s);
-      clk = p.clk, fs = p.fs;
-    } else if (split) {
-      run(std::true_type{});
-    } else {
-      run(std::false_type{});
-    }
-    ms = clk;
-    for (int o = 1; o < h; o <<= 1) ms = dmax(ms, __shfl_xor(ms, o, WAVE));
-    ms = dmax(ms, __shfl_xor(ms, 8, WAVE));
-    if (mine) {
-      if (wide) {
-        if (s == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
-      } else {
-        const int64_t m = (int64_t)ms;
-        if (s == 0) a.out_ms[cand] = m;
-        a.out_bub[cand * P + d] = m - (f + b + wg) * M;
-        if constexpr (X == XM) {
-          const int held = ib == 2 ? M : split ? (S < M ? S : M) : (S - s < M ? S - s : M);
-          a.out_peak[cand * P + d] = stat + (act > 0 || ib == 2 ? act * held : 0);
-        }
-        if constexpr (X == XB) {
-          a.out_bound[(cand * P + d) * 2] = (int64_t)fs;
-          a.out_bound[(cand * P + d) * 2 + 1] = (int64_t)clk;
-        }
-      }
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // v = 2 interleaved orders (looped) as a systolic array: lane = rank r. With N = 2M virtual
 // micro-batches, give F index j of rank r the pair step j + r and B index i the pair step
@@ -2229,15 +2113,13 @@ __device__ __forceinline__ void pipe2_run32(Pipe2Int& p, int P, int M, int G, in
   range();
 }
 
+// Runs the block's chunks of the two class bins; returns its first chunk of the v = 1 ones, which
+// go to the blocks after those that take a last chunk here (so that the two kinds share a launch: a
+// launch of its own added 20 us to batches with few of these orders).
 template <int X, bool ROT>
-__global__ void __launch_bounds__(WAVE) k_pipe2(SimArgs a) {
-  extern __shared__ __align__(16) uint8_t smem[];
+__device__ __forceinline__ int pipe2_chunks(const SimArgs& a, const int64_t* pre,
+                                            const int64_t* link) {
   const int P = a.pr.P, M = a.pr.M, L = a.pr.L, S = 2 * P, G = a.G;
-  int64_t* pre = reinterpret_cast<int64_t*>(smem);
-  int64_t* link = pre + 3 * (L + 1);
-  for (int i = lane_id(); i < 3 * (L + 1); i += WAVE) pre[i] = a.pre[i];
-  for (int i = lane_id(); i < P * P; i += WAVE) link[i] = a.link[i];
-  __syncthreads();
   const int g = lane_id() / G, x = lane_id() % G;
   const int r = x < P ? x : 0;  // (an idle lane stands in as rank 0 and is read by nobody)
   // the two bins (split first: longer) and their chunk ranges
@@ -2342,6 +2224,127 @@ __global__ void __launch_bounds__(WAVE) k_pipe2(SimArgs a) {
         a.out_bub[cand * P + d] = m - (f[0] + b[0] + wg[0] + f[1] + b[1] + wg[1]) * M;
         if constexpr (X == XB) {
           a.out_bound[(cand * P + d) * 2] = (int64_t)fst;
+          a.out_bound[(cand * P + d) * 2 + 1] = (int64_t)clk;
+        }
+      }
+    }
+  }
+  const int n = (int)gridDim.x;
+  return ((int)blockIdx.x + n - end1 % n) % n;
+}
+
+// TWO: also the looped interleaved orders of v = 2 (1: ds_bpermute, 2: DPP at P = 16).
+template <int X, int TWO>
+__global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a, int gpipe) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int P = a.pr.P, M = a.pr.M, L = a.pr.L, S = P;
+  // layer prefix sums and links: every lane reads its stage's entries
+  int64_t* pre = reinterpret_cast<int64_t*>(smem);
+  int64_t* link = pre + 3 * (L + 1);
+  for (int i = lane_id(); i < 3 * (L + 1); i += WAVE) pre[i] = a.pre[i];
+  for (int i = lane_id(); i < P * P; i += WAVE) link[i] = a.link[i];
+  __syncthreads();
+  const int h = a.G >> 1, x = lane_id() & 15;
+  const int s = 2 * ((x & 7) & (h - 1)) + (x >> 3);
+  const int g = (lane_id() >> 4) * (8 / h) + (x & 7) / h;
+  // the bins (split, fused, GPipe where it is this kernel's) and their chunk ranges, one per lane
+  const int ci = lane_id(), nb = gpipe ? 3 : 2;
+  const int bin_i = ci == 2 ? bin_of(1, GEN_AFAB, 0) : BIN_STATIC + (ci == 0 ? 1 : 0);
+  const int cnt_i = ci < nb ? a.ctl[CTL_COUNTS + bin_i] : 0;
+  const int start_i = ci < nb ? a.ctl[CTL_START + bin_i] : 0;
+  const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
+  const int end0 = __shfl(nch_i, 0, WAVE), end1 = end0 + __shfl(nch_i, 1, WAVE);
+  const int end2 = end1 + __shfl(nch_i, 2, WAVE);
+  int first = (int)blockIdx.x;
+  if constexpr (TWO != 0) first = pipe2_chunks<X, TWO == 2>(a, pre, link);
+  // chunks by grid stride, the longer (split) ones first
+  for (int ch = first; ch < end2; ch += (int)gridDim.x) {
+    const int ib = ch < end0 ? 0 : ch < end1 ? 1 : 2;
+    const int split = ib == 0 ? 1 : 0;
+    const int cnt = __shfl(cnt_i, ib, WAVE), pos0 = __shfl(start_i, ib, WAVE);
+    const int e = (ch - (ib == 0 ? 0 : ib == 1 ? end0 : end1)) * a.CPW + g;
+    const int64_t cand = e < cnt ? (int64_t)a.idx[pos0 + e] : -1;
+    const bool mine = cand >= 0 && s < P;
+    int d = 0;
+    int64_t f = 0, b = 0, wg = 0, wF = 0, wB = 0, cF = 0, cB = 0, act = 0, stat = 0;
+    if (mine) {
+      const uint8_t* rec = a.cands + cand * a.pr.stride;
+      const uint8_t* bnd = rec + 4;
+      const uint8_t* dev = rec + 3 + a.pr.s_max;
+      const int b0 = s > 0 ? bnd[s - 1] : 0, b1 = s < S - 1 ? bnd[s] : L;
+      d = dev[s];
+      const int dp = s > 0 ? dev[s - 1] : d, dn = s < S - 1 ? dev[s + 1] : d;
+      f = pre[3 * b1] - pre[3 * b0];
+      b = pre[3 * b1 + 1] - pre[3 * b0 + 1];
+      wg = pre[3 * b1 + 2] - pre[3 * b0 + 2];
+      wF = s > 0 ? link[dp * P + d] : 0, wB = s < S - 1 ? link[dn * P + d] : 0;
+      if constexpr (X == XS)
+        cF = s < S - 1 ? link[d * P + dn] : 0, cB = s > 0 ? link[d * P + dp] : 0;
+      if constexpr (X == XM) {
+        act = a.pre_mem[2 * b1] - a.pre_mem[2 * b0];
+        stat = a.pre_mem[2 * b1 + 1] - a.pre_mem[2 * b0 + 1];
+      }
+    }
+    const int64_t dB = split ? b : b + wg;
+    const bool fits =
+        ((uint64_t)f | (uint64_t)dB | (uint64_t)wg | (uint64_t)wF | (uint64_t)wB) >> 32 == 0;
+    // the group's lanes: xor over the stage pairs, then over the two halves
+    const auto group_or = [&](int y) {
+      for (int o = 1; o < h; o <<= 1) y |= __shfl_xor(y, o, WAVE);
+      return y | __shfl_xor(y, 8, WAVE);
+    };
+    const bool wide = group_or(mine && !fits) != 0;
+    const int fpar = s & 1;
+    // an idle lane (or a wide candidate's) keeps clock 0: no input, no duration
+    const bool on = mine && !wide;
+    const double xF = on && s > 0 ? (X == XS ? 0.0 : (double)wF) : PIPE_NONE;
+    const double xB = on && s < S - 1 ? (X == XS ? 0.0 : (double)wB) : PIPE_NONE;
+    const double dF = on ? (double)f : 0.0, dBd = on ? (double)dB : 0.0;
+    const double dW = on && split ? (double)wg : 0.0;
+    double ms = 0.0, fs = 0.0, clk = 0.0;
+    auto run = [&](auto tag) {
+      constexpr bool SPLIT = decltype(tag)::value;
+      PipeLane<X, SPLIT> p;
+      p.clk = p.out = 0.0, p.fs = -1.0;
+      p.w[0] = fpar ? xB : xF, p.w[1] = fpar ? xF : xB;
+      p.d[0] = fpar ? dBd : dF, p.d[1] = fpar ? dF : dBd;
+      p.g[0] = fpar ? dW : 0.0, p.g[1] = fpar ? 0.0 : dW;
+      p.c[0] = on ? (double)(fpar ? cB : cF) : 0.0, p.c[1] = on ? (double)(fpar ? cF : cB) : 0.0;
+      p.lf[0] = p.lf[1] = 0.0;
+      pipe_run<X, SPLIT>(p, S, M, s);
+      // the W's still deferred
+      if (SPLIT) p.clk += (double)(s < M ? s : M) * dW;
+      clk = p.clk, fs = p.fs;
+    };
+    if (ib == 2) {
+      PipeLane<X, false> p;
+      p.clk = p.out = 0.0, p.fs = -1.0;
+      p.w[0] = xF, p.w[1] = xB, p.d[0] = dF, p.d[1] = dBd;
+      p.c[0] = on ? (double)cF : 0.0, p.c[1] = on ? (double)cB : 0.0;
+      p.lf[0] = p.lf[1] = 0.0;
+      pipe_gpipe<X>(p, S, M, s);
+      clk = p.clk, fs = p.fs;
+    } else if (split) {
+      run(std::true_type{});
+    } else {
+      run(std::false_type{});
+    }
+    ms = clk;
+    for (int o = 1; o < h; o <<= 1) ms = dmax(ms, __shfl_xor(ms, o, WAVE));
+    ms = dmax(ms, __shfl_xor(ms, 8, WAVE));
+    if (mine) {
+      if (wide) {
+        if (s == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
+      } else {
+        const int64_t m = (int64_t)ms;
+        if (s == 0) a.out_ms[cand] = m;
+        a.out_bub[cand * P + d] = m - (f + b + wg) * M;
+        if constexpr (X == XM) {
+          const int held = ib == 2 ? M : split ? (S < M ? S : M) : (S - s < M ? S - s : M);
+          a.out_peak[cand * P + d] = stat + (act > 0 || ib == 2 ? act * held : 0);
+        }
+        if constexpr (X == XB) {
+          a.out_bound[(cand * P + d) * 2] = (int64_t)fs;
           a.out_bound[(cand * P + d) * 2 + 1] = (int64_t)clk;
         }
       }
@@ -5808,35 +5811,20 @@ int launch_sched(const SimArgs& base, const Setup& su, int64_t n, int v, hipStre
   return launch_ok();
 }
 
-// Launch k_pipe over the v = 1 class bins (gpipe: and the v = 1 GPipe bin).
-template <int X>
+// Launch k_pipe over the v = 1 class bins (gpipe: and the v = 1 GPipe bin; a.pipe2: and the v = 2
+// interleaved ones).
+template <int X, int TWO>
 int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, bool gpipe, hipStream_t stream) {
   SimArgs a = base;
   a.G = std::max(2, lanes_per_candidate(a.pr.P));
   a.CPW = WAVE / a.G;
   const int lds = (3 * (a.pr.L + 1) + a.pr.P * a.pr.P) * 8;
   int grid = 0;
-  int rc = occupancy_grid(k_pipe<X>, lds, su.di.cus, &grid);
+  int rc = occupancy_grid(k_pipe<X, TWO>, lds, su.di.cus, &grid);
   if (rc) return rc;
   const int64_t need = (n + a.CPW - 1) / a.CPW;
   grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
-  hipLaunchKernelGGL(k_pipe<X>, dim3(grid), dim3(WAVE), lds, stream, a, gpipe ? 1 : 0);
-  return launch_ok();
-}
-
-// Launch k_pipe2 over the v = 2 interleaved class bins.
-template <int X, bool ROT>
-int launch_pipe2(const SimArgs& base, const Setup& su, int64_t n, hipStream_t stream) {
-  SimArgs a = base;
-  a.G = lanes_per_candidate(a.pr.P);
-  a.CPW = WAVE / a.G;
-  const int lds = (3 * (a.pr.L + 1) + a.pr.P * a.pr.P) * 8;
-  int grid = 0;
-  int rc = occupancy_grid(k_pipe2<X, ROT>, lds, su.di.cus, &grid);
-  if (rc) return rc;
-  const int64_t need = (n + a.CPW - 1) / a.CPW;
-  grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
-  hipLaunchKernelGGL((k_pipe2<X, ROT>), dim3(grid), dim3(WAVE), lds, stream, a);
+  hipLaunchKernelGGL((k_pipe<X, TWO>), dim3(grid), dim3(WAVE), lds, stream, a, gpipe ? 1 : 0);
   return launch_ok();
 }
 
@@ -6061,7 +6049,7 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   if (sched) {
     // (the communication tally needs more per op than the systolic rounds have room for)
     a.pipe = X != XC && prob->P <= PIPE_MAX;
-    // (the memory model's running totals need 64-bit integers, and k_pipe2 with links' times was
+    // (the memory model's running totals need 64-bit integers, and the ring of ranks with link times was
     // the slower one)
     a.pipe2 = (X == XP || X == XB) && a.pipe && prob->v_max >= 2 && prob->P >= 2 &&
               prob->M % prob->P == 0;
@@ -6098,12 +6086,14 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   uint64_t taken = 0;  // bins that the schedules and k_pipe cover
   if constexpr (X != XR) {
     if (sched) {
-      if constexpr (X != XC)
-        if (a.pipe && (rc = launch_pipe<X>(a, su, n, gpipe, stream))) return rc;
-      if constexpr (X == XP || X == XB)
-        if (a.pipe2 && (rc = P == 16 ? launch_pipe2<X, true>(a, su, n, stream)
-                                     : launch_pipe2<X, false>(a, su, n, stream)))
+      if constexpr (X == XP || X == XB) {
+        if (a.pipe && (rc = !a.pipe2 ? launch_pipe<X, 0>(a, su, n, gpipe, stream)
+                            : P == 16 ? launch_pipe<X, 2>(a, su, n, gpipe, stream)
+                                      : launch_pipe<X, 1>(a, su, n, gpipe, stream)))
           return rc;
+      } else if constexpr (X != XC) {
+        if (a.pipe && (rc = launch_pipe<X, 0>(a, su, n, gpipe, stream))) return rc;
+      }
       if ((!a.pipe || prob->v_max >= 2) && (rc = launch_sched<1, 2, X>(a, su, n, 0, stream)))
         return rc;
       if (prob->v_max >= 3 && (rc = launch_sched<1, 8, X>(a, su, n, 0, stream))) return rc;
