@@ -1976,12 +1976,21 @@ __device__ __forceinline__ double pipe2_run(Pipe2Lane<X>& p, int P, int M, int r
 }
 
 // The same array on 32-bit integers: times relative to a moving origin, C = 2^30 + 2^26 at first. The
-// origin stands still in the first 2P - 1 steps, then moves by D, about the candidate's time per
+// origin stands still in the first 2P - 1 steps, then moves by D, the most loaded rank's time per
 // step, in every step (an input was produced one step earlier, so its weight loses D), and every P
 // steps from the first W on to rank P / 2's clock. An op without an input has the weight -2^31.
-// Exact as long as the clocks stay in [0, 2^31): their extremes are kept every second
-// step; with q no less than D and the most that a step adds to a value, extremes inside
-// [2 q, 2^31 - 2 q) prove it; else the wave runs its candidates again on doubles (one wave in
+// Exact as long as the clocks stay in [0, 2^31), which their extremes prove. They are taken every
+// second step and after every move to a rank's clock, and have to lie inside [2 q, 2^31 - 2 q), with
+// q < 2^28 no less than D and than the most that a step adds to the largest clock:
+//  * two steps (and the first move by D) from such clocks, none is below 0 or at 2^31 and above;
+//  * a move takes the difference of two clocks, less C, from a clock: the exact result lies in
+//    (C - 2^31, C + 2^31), so that its low 32 bits, read as a signed number, are the result or, where
+//    that passes 2^31, a negative number. Taken right after the move, the extremes see both;
+//  * an output is no later than its lane's clock (plus D), so it does not pass 2^31 either. The move
+//    can leave it below 0, where the weight -2^31 would wrap: it is set to 0 then. Its reader's
+//    clock is at least 2 q, no earlier than 0 plus any weight, so the reader starts at its clock with
+//    either value.
+// Where the extremes leave the range the wave runs its candidates again on doubles (one wave in
 // fifty at P = 16, M = 128, stages of 5 to 25 ms; none where q is a tenth of that). The chunk of a
 // lane is a bit of a scalar mask: with bF, bB the lanes that enter their next chunk, a step costs
 // two selects, two adds and a maximum per direction, all at the full rate (doubles run at half of
@@ -2000,8 +2009,9 @@ __device__ __forceinline__ int isel(uint64_t m, int x, int y) {
   return __builtin_amdgcn_inverse_ballot_w64(m) ? x : y;
 }
 
+// on: the lane's clock counts; q: as above. Returns false where the wave needs the doubles.
 template <int X, bool SPLIT, bool ROT>
-__device__ __forceinline__ void pipe2_run32(Pipe2Int& p, int P, int M, int G, int r) {
+__device__ __forceinline__ bool pipe2_run32(Pipe2Int& p, int P, int M, int G, int r, bool on, int q) {
   const int N = 2 * M, skew = 3 * P - 2;
   const int row = lane_id() - r;
   const int left = (row + (r > 0 ? r - 1 : P - 1)) * 4, right = (row + (r < P - 1 ? r + 1 : 0)) * 4;
@@ -2049,10 +2059,16 @@ __device__ __forceinline__ void pipe2_run32(Pipe2Int& p, int P, int M, int G, in
     p.hi = p.clk > p.hi ? p.clk : p.hi;
     p.lo = p.clk < p.lo ? p.clk : p.lo;
   };
+  auto left_range = [&]() {
+    return __ballot(on && (p.hi > INT32_MAX - 2 * q || p.lo < 2 * q)) != 0;
+  };
   auto origin = [&]() {
     const int y = iadd(__builtin_amdgcn_ds_bpermute((row + P / 2) * 4, p.clk), -PIPE_ORG);
     p.org += y;
-    p.clk = iadd(p.clk, -y), p.oF = iadd(p.oF, -y), p.oB = iadd(p.oB, -y);
+    p.clk = iadd(p.clk, -y);
+    range();
+    const int oF = iadd(p.oF, -y), oB = iadd(p.oB, -y);
+    p.oF = oF > 0 ? oF : 0, p.oB = oB > 0 ? oB : 0;
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
@@ -2095,9 +2111,9 @@ __device__ __forceinline__ void pipe2_run32(Pipe2Int& p, int P, int M, int G, in
              0x0001000100010001ull << ((16 - u) & 15), dc);
         step(I1{}, I1{}, 0x0001000100010001ull << ((15 + u) & 15),
              0x0001000100010001ull << ((15 - u) & 15), dc);
-        range();
       };
-      two(0), two(2), two(4), two(6), two(8), two(10), two(12), two(14);
+      two(0), range(), two(2), range(), two(4), range(), two(6), range();
+      two(8), range(), two(10), range(), two(12), range(), two(14);
       origin();
       if constexpr (SPLIT) {
         const int y = dw;
@@ -2111,6 +2127,7 @@ __device__ __forceinline__ void pipe2_run32(Pipe2Int& p, int P, int M, int G, in
   run(I0{}, I1{}, N + P, N + 2 * P - 1, none);
   run(I0{}, I2{}, N + 2 * P - 1, N + skew, [&]() { okB &= ~bB; });
   range();
+  return !left_range();
 }
 
 // Runs the block's chunks of the two class bins; returns its first chunk of the v = 1 ones, which
@@ -2183,24 +2200,25 @@ __device__ __forceinline__ int pipe2_chunks(const SimArgs& a, const int64_t* pre
         q = q > per ? q : per;
       }
       q = group_max(q, G), per = group_max(per, G);
-      const bool ok32 = q < (int64_t)1 << 28, u = on && ok32;
-      Pipe2Int p;
-      p.D = ok32 ? (int)per : 0;
+      const bool fit = q < (int64_t)1 << 28;
+      if (__ballot(on && !fit) == 0) {
+        Pipe2Int p;
+        p.D = (int)per;
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int s = r + k * P;
-        p.w[k] = u && s > 0 ? (int)wF[k] : INT32_MIN;
-        p.v[k] = u && s < S - 1 ? (int)wB[k] : INT32_MIN;
-        p.f[k] = u ? (int)f[k] : 0, p.b[k] = u ? (int)(split ? b[k] : b[k] + wg[k]) : 0;
-        p.g[k] = u ? (int)wg[k] : 0;
+        for (int k = 0; k < 2; ++k) {
+          const int s = r + k * P;
+          p.w[k] = on && s > 0 ? (int)wF[k] : INT32_MIN;
+          p.v[k] = on && s < S - 1 ? (int)wB[k] : INT32_MIN;
+          p.f[k] = on ? (int)f[k] : 0, p.b[k] = on ? (int)(split ? b[k] : b[k] + wg[k]) : 0;
+          p.g[k] = on ? (int)wg[k] : 0;
+        }
+        p.clk = PIPE_ORG, p.oF = p.oB = PIPE_ORG;
+        p.fs = PIPE_ORG, p.hi = INT32_MIN, p.lo = INT32_MAX, p.org = 0;
+        again = split ? !pipe2_run32<X, true, ROT>(p, P, M, G, r, on, (int)q)
+                      : !pipe2_run32<X, false, ROT>(p, P, M, G, r, on, (int)q);
+        clk = (double)(p.org + (p.clk - PIPE_ORG) + (int64_t)(2 * M + P) * p.D);
+        fst = (double)(p.fs - PIPE_ORG);
       }
-      p.clk = PIPE_ORG, p.oF = p.oB = PIPE_ORG;
-      p.fs = PIPE_ORG, p.hi = INT32_MIN, p.lo = INT32_MAX, p.org = 0;
-      if (split) pipe2_run32<X, true, ROT>(p, P, M, G, r);
-      else pipe2_run32<X, false, ROT>(p, P, M, G, r);
-      clk = (double)(p.org + (p.clk - PIPE_ORG) + (int64_t)(2 * M + P) * p.D);
-      fst = (double)(p.fs - PIPE_ORG);
-      again = __ballot(on && (!ok32 || p.hi > INT32_MAX - 2 * (int)q || p.lo < 2 * (int)q)) != 0;
     }
     if (again) {
       Pipe2Lane<X> p;
