@@ -47,11 +47,13 @@ constexpr int CTL_REDO = 170;     // candidates for the 64-bit path (40-bit over
 constexpr int CTL_WIDE = 171;     // perturbed candidates whose queue window passes the ring
 constexpr int CTL_WORK_WIDE = 172;// chunk counter of k_sim_mat40 over the wide list
 constexpr int CTL_TOTAL = 173;    // valid records (all bins; set by k_plan)
+constexpr int CTL_LEFT = 288;     // v = 2 interleaved chunks that k_pipe leaves to k_sched (a line of
+                                  // its own)
 constexpr int CTL_START = 176;    // [NBINS] first index position of each bin
 constexpr int CTL_WORK_V = 256;   // chunk counters of the v = 3..8 k_sim launches (6), then of
                                   // their rendezvous GPipe launches (6)
 constexpr int CTL_WORDS = 320;
-static_assert(CTL_START + NBINS <= CTL_WORK_V && CTL_WORK_V + 12 <= CTL_WORDS, "control words");
+static_assert(CTL_START + NBINS <= CTL_WORK_V && CTL_WORK_V + 12 <= CTL_LEFT, "control words");
 static_assert(NBINS <= 80, "bin arrays of the control block hold 80 bins");
 // rounds a materialised queue is read ahead of its use (GenMatK; rows of at least 8 entries)
 constexpr int QK = 6;
@@ -73,7 +75,8 @@ struct SimArgs {
   int32_t* ctl;
   const int32_t* idx;    // candidate indices sorted by bin
   int32_t* redo;         // candidates to recompute with 64-bit slots
-  int32_t* wide;         // perturbed candidates too wide for the ring (k_sim_mat40 full rows)
+  int32_t* wide;         // perturbed candidates too wide for the ring (k_sim_mat40 full rows); before
+                         // them, the v = 2 interleaved chunks that k_pipe leaves
   const uint32_t* mtab;  // MERGE tables, merge_offset() entries apart
   const uint16_t* mrows; // v = 2 MERGE queues by (split, s0, s1), with the v <= 2 INTER and GPipe
                          // ones in the rows of no pair (k_merge_rows); null: none
@@ -103,6 +106,7 @@ struct SimArgs {
   const uint32_t* stab;
   const int32_t* smeta;
   bool pipe, pipe2;  // the v = 1 classes are k_pipe's, the v = 2 interleaved ones k_pipe's too
+  int sc_first;      // k_sched over the classes of v <= 2: the first one of this launch
   // k_sched over MERGE bins: the stage rows of v = sr_v (null: none), S + 1 rows of sr_rowlen[split]
   // entries from sr_off[split], of which sr_steps[split] are steps
   const uint32_t* srow;
@@ -1584,14 +1588,22 @@ __global__ void __launch_bounds__(WAVE) k_sched(SimArgs a, int sbase, int lbase,
   const uint32_t lcell = lb + (uint32_t)lbase + (uint32_t)lane_id() * 8u;  // XS: link cells
   uint8_t* rec = st_smem + rbase + gg * a.rec_stride;
   // the bins' counts, first positions and chunk ranges, one bin per lane
-  // the classes of this launch (v <= 2: from a.sr_v on, the earlier ones having another kernel)
-  const int C0 = NR > 1 ? 0 : VC > 2 ? NSC2 : a.sr_v;
+  // the classes of this launch (v <= 2: from a.sc_first on, the earlier ones having another kernel;
+  // with a.pipe2 the first one stands for the chunks of both interleaved ones that k_pipe left)
+  const int C0 = NR > 1 ? 0 : VC > 2 ? NSC2 : a.sc_first;
   const int NB = NR > 1 ? 2 : VC > 2 ? NSC - NSC2 : NSC2 - C0;
+  constexpr bool LEFT = NR == 1 && VC <= 2 && (X == XP || X == XB);
+  const bool left = LEFT && a.pipe2;
   const int ci = lane_id();
   const int bin_i = NR == 1 ? BIN_STATIC + C0 + ci : bin_of(a.sr_v, GEN_MERGE, ci == 0 ? 1 : 0);
   const int cnt_i = ci < NB ? a.ctl[CTL_COUNTS + bin_i] : 0;
   const int start_i = ci < NB ? a.ctl[CTL_START + bin_i] : 0;
-  const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
+  int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
+  const int nsp = left ? bcast(nch_i) : 0;  // chunks of the split one, which k_pipe numbers first
+  // (where k_pipe left every chunk, they go in order and not in the list's)
+  const int nall = left ? nsp + (bcast(a.ctl[CTL_COUNTS + BIN_STATIC + 2]) + a.CPW - 1) / a.CPW : 0;
+  if (left && ci == 0) nch_i = a.ctl[CTL_LEFT];
+  const bool listed = left && bcast(nch_i) < nall;
   int end_i = nch_i;  // inclusive prefix: chunks of bins 0..ci
   for (int off = 1; off < 16; off <<= 1) {
     const int y = __shfl_up(end_i, off, WAVE);
@@ -1604,10 +1616,17 @@ __global__ void __launch_bounds__(WAVE) k_sched(SimArgs a, int sbase, int lbase,
     // the bin whose chunk range holds ch: the number of bins that end at or before it
     const int ib = __popcll(__ballot(ci < NB && end_i <= ch));
     if (ib >= NB) break;
-    const int cnt = __shfl(cnt_i, ib, WAVE);
-    const int pos0 = __shfl(start_i, ib, WAVE);
-    const int entry0 = (ch - (__shfl(end_i, ib, WAVE) - __shfl(nch_i, ib, WAVE))) * a.CPW;
-    const int cls = C0 + ib;
+    int cnt = __shfl(cnt_i, ib, WAVE);
+    int pos0 = __shfl(start_i, ib, WAVE);
+    int entry0 = (ch - (__shfl(end_i, ib, WAVE) - __shfl(nch_i, ib, WAVE))) * a.CPW;
+    int cls = C0 + ib;
+    if (LEFT && left && ib == 0) {
+      // (scalars: a class that the compiler takes to differ by lane costs the rounds a third)
+      const int c = listed ? bcast(a.wide[ch]) : ch;
+      cls = c < nsp ? 3 : 2;
+      cnt = a.ctl[CTL_COUNTS + BIN_STATIC + cls], pos0 = a.ctl[CTL_START + BIN_STATIC + cls];
+      entry0 = (c < nsp ? c : c - nsp) * a.CPW;
+    }
     int v = a.sr_v, gen = GEN_MERGE, split = ib == 0 ? 1 : 0, pat = 0;
     if constexpr (NR == 1) sc_decode(cls, &v, &gen, &split, &pat);
     const int ns = NR == 1 ? sc_slots(P, v) : sr_slots(P * v);
@@ -1896,86 +1915,11 @@ __device__ __forceinline__ void pipe_gpipe(PipeLane<X, false>& p, int S, int M, 
 // the neighbour on the ring of ranks: F reads rank r - 1 (rank 0, chunk 1: rank P - 1's chunk 0), B
 // reads rank r + 1 (rank P - 1, chunk 0: rank 0's chunk 1). W's index in step t is
 // t - (3P - 2) on every rank (the lag r cancels the skew), up to the flush. One rank per step
-// enters its next chunk for F, one for B. Doubles holding integers, as in k_pipe.
-// The exchange is a rotation by one lane: DPP at P = 16 (ROT), else ds_bpermute.
-// XB: a rank's first op is F index 0, in step r. Plain and bounds variants. (Serial links, 131,072
-// candidates at P = 8, M = 64: 399 us with the links' times here, 369 on the class schedules.)
-// ---------------------------------------------------------------------------------------------
-template <bool ROT>
-__device__ __forceinline__ double ring_shift(double x, int from, bool fwd) {
-  if constexpr (ROT) {
-    return fwd ? dpp64<DPP_ROR + 1, 0xF>(x) : dpp64<DPP_ROR + 15, 0xF>(x);
-  } else {
-    const uint64_t v = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(v >> 32));
-    return __builtin_bit_cast(double, (uint64_t)lo | (uint64_t)hi << 32);
-  }
-}
-
-template <int X>
-struct Pipe2Lane {
-  double clk, oF, oB;                      // clock, latest forward and backward outputs
-  double wF, dF, wF1, dF1;                 // current and other chunk's forward
-  double wB, dB, wB1, dB1;                 // ... and backward
-  double fs;                               // XB
-};
-
-template <int X, bool SPLIT, bool ROT>
-__device__ __forceinline__ double pipe2_run(Pipe2Lane<X>& p, int P, int M, int r, double dW0,
-                                            double dW1) {
-  const int N = 2 * M, skew = 3 * P - 2;
-  const int row = lane_id() - r;
-  const int left = (row + (r > 0 ? r - 1 : P - 1)) * 4, right = (row + (r < P - 1 ? r + 1 : 0)) * 4;
-  int nf = r;                         // steps until this rank's next forward chunk
-  int nb = P - 1 - r + 2 * P - 1;     // ... and backward chunk (from its first ones)
-  // W chunk of index u = t - skew: backward index u's, 1 first, changing every P steps
-  int nw = P;
-  double dw = dW1, dwo = dW0;
-  auto step = [&](auto test, int t) {
-    constexpr bool TEST = decltype(test)::value;
-    const double iF = ring_shift<ROT>(p.oF, left, true), iB = ring_shift<ROT>(p.oB, right, false);
-    // the chunk pairs start swapped: the first chunk is entered with the first op
-    const bool sf = nf == 0, sb = nb == 0;
-    nf = sf ? P - 1 : nf - 1, nb = sb ? P - 1 : nb - 1;
-    auto swap = [](bool c, double& a, double& b) {
-      const double x = c ? b : a, y = c ? a : b;
-      a = x, b = y;
-    };
-    swap(sf, p.wF, p.wF1), swap(sf, p.dF, p.dF1), swap(sb, p.wB, p.wB1), swap(sb, p.dB, p.dB1);
-    const int j = t - r, i = t - (P - 1 - r) - (2 * P - 1);
-    const bool okF = !TEST || (j >= 0 && j < N), okB = !TEST || (i >= 0 && i < N);
-    {
-      const double beg = dmax(p.clk, iF + p.wF), fin = beg + p.dF;
-      if constexpr (X == XB) p.fs = TEST && j == 0 ? beg : p.fs;
-      p.oF = okF ? fin : p.oF;
-      p.clk = okF ? fin : p.clk;
-    }
-    {
-      const double fin = dmax(p.clk, iB + p.wB) + p.dB;
-      p.oB = okB ? fin : p.oB;
-      p.clk = okB ? fin : p.clk;
-    }
-    if constexpr (SPLIT) {
-      if (!TEST || t >= skew) {
-        p.clk += dw;
-        if (--nw == 0) {
-          const double y = dw;
-          dw = dwo, dwo = y, nw = P;
-        }
-      }
-    }
-  };
-  const int t1 = skew < N + skew ? skew : N + skew, t2 = N > t1 ? N : t1;
-  for (int t = 0; t < t1; ++t) step(std::true_type{}, t);
-  int t = t1;
-  for (; t + 2 <= t2; t += 2) step(std::false_type{}, t), step(std::false_type{}, t + 1);
-  for (; t < t2; ++t) step(std::false_type{}, t);
-  for (; t < N + skew; ++t) step(std::true_type{}, t);
-  return p.clk;
-}
-
-// The same array on 32-bit integers: times relative to a moving origin, C = 2^30 + 2^26 at first. The
+// enters its next chunk for F, one for B. XB: a rank's first op is F index 0, in step r. Plain and
+// bounds variants. (Serial links, 131,072 candidates at P = 8, M = 64: 399 us with the links' times
+// here, on doubles, 369 on the class schedules.) The exchange is a rotation by one lane: DPP at
+// P = 16 (ROT), else ds_bpermute. M > P.
+// Times are 32-bit integers relative to a moving origin, C = 2^30 + 2^26 at first. The
 // origin stands still in the first 2P - 1 steps, then moves by D, the most loaded rank's time per
 // step, in every step (an input was produced one step earlier, so its weight loses D), and every P
 // steps from the first W on to rank P / 2's clock. An op without an input has the weight -2^31.
@@ -1990,12 +1934,19 @@ __device__ __forceinline__ double pipe2_run(Pipe2Lane<X>& p, int P, int M, int r
 //    can leave it below 0, where the weight -2^31 would wrap: it is set to 0 then. Its reader's
 //    clock is at least 2 q, no earlier than 0 plus any weight, so the reader starts at its clock with
 //    either value.
-// Where the extremes leave the range the wave runs its candidates again on doubles (one wave in
-// fifty at P = 16, M = 128, stages of 5 to 25 ms; none where q is a tenth of that). The chunk of a
-// lane is a bit of a scalar mask: with bF, bB the lanes that enter their next chunk, a step costs
-// two selects, two adds and a maximum per direction, all at the full rate (doubles run at half of
-// it). At P = 16 the main loop's P steps are unrolled with constant masks.
-// 262,144 candidates at P = 16, M = 128: 656 us; on doubles 1333, on the class schedules 1282.
+// Where the extremes leave the range (tested after the fill and at the end) the wave leaves its
+// chunk to the class schedules of k_sched. In the fill a rank without backwards falls by up to
+// (P - 1) D from C, so a chunk with (P - 1) D + 2 q > 7 2^27 is left to them at once: of candidates
+// with random stage times (P = 4 to 16) 99 % stay in the range while the sum is below 0.9 2^30, half
+// at 1.05 2^30, none from 1.3 2^30 on, and a chunk run for nothing costs more than one run in k_sched
+// (a P = 8 wave needs eight candidates in the range). 262,144 candidates at P = 16, M = 128: 549 us and
+// 62 in k_sched (stages of 5 to 25 ms, a few chunks left), 47 and 1294 (ten times as long, all left;
+// on doubles here 1333). M = P, where the forwards end before the fill does (2 M < 3 P - 2), takes the
+// class schedules: a call of as many candidates 283 us at P = 16, on doubles 513.
+// The chunk of a lane is a bit of a scalar mask: with bF, bB the lanes that enter their next chunk, a
+// step costs two selects, two adds and a maximum per direction, all at the full rate (doubles run at
+// half of it). At P = 16 the main loop's P steps are unrolled with constant masks.
+// ---------------------------------------------------------------------------------------------
 struct Pipe2Int {
   int w[2], f[2], v[2], b[2], g[2];  // F weight and duration, B weight and duration, W by chunk
   int D;
@@ -2009,7 +1960,7 @@ __device__ __forceinline__ int isel(uint64_t m, int x, int y) {
   return __builtin_amdgcn_inverse_ballot_w64(m) ? x : y;
 }
 
-// on: the lane's clock counts; q: as above. Returns false where the wave needs the doubles.
+// on: the lane's clock counts; q: as above. Returns false where a clock may have left the range.
 template <int X, bool SPLIT, bool ROT>
 __device__ __forceinline__ bool pipe2_run32(Pipe2Int& p, int P, int M, int G, int r, bool on, int q) {
   const int N = 2 * M, skew = 3 * P - 2;
@@ -2102,6 +2053,7 @@ __device__ __forceinline__ bool pipe2_run32(Pipe2Int& p, int P, int M, int G, in
   run(I1{}, I2{}, 2 * P - 1, skew, [&]() { okB |= bB; });
   origin();
   p.oB = isel(rank0, 0, p.oB);  // (no output yet: a value in range for the lanes without an input)
+  if (left_range()) return false;
   int t = skew;
   if constexpr (ROT) {
     for (; t + 16 <= N; t += 16) {
@@ -2130,12 +2082,41 @@ __device__ __forceinline__ bool pipe2_run32(Pipe2Int& p, int P, int M, int G, in
   return !left_range();
 }
 
-// Runs the block's chunks of the two class bins; returns its first chunk of the v = 1 ones, which
-// go to the blocks after those that take a last chunk here (so that the two kinds share a launch: a
+// The chunks that the waves of a k_pipe block leave to k_sched, listed in a.wide in one piece by the
+// last wave to end (a wave with 64 of them lists those itself). On 65,536 chunks that are all left,
+// one atomic per chunk took 850 us, one per wave 100, one per block of PIPE_WAVES 15.
+constexpr int PIPE_WAVES = 8;
+struct LeftChunks {
+  int cnt, ended, ch[PIPE_WAVES * WAVE];
+  // lane l < k: one chunk each
+  __device__ __forceinline__ static void list(const SimArgs& a, int chunk, int k) {
+    int at = 0;
+    if (lane_id() == 0) at = atomicAdd(&a.ctl[CTL_LEFT], k);
+    at = bcast(at);
+    if (lane_id() < k) a.wide[at + lane_id()] = chunk;
+  }
+  __device__ __forceinline__ void last(const SimArgs& a, int chunk, int k) {
+    int at = 0, e = 0;
+    if (lane_id() == 0) at = atomicAdd(&cnt, k);
+    at = bcast(at);
+    if (lane_id() < k) ch[at + lane_id()] = chunk;
+    __threadfence_block();
+    if (lane_id() == 0) e = atomicAdd(&ended, 1);
+    if (bcast(e) != PIPE_WAVES - 1) return;
+    __threadfence_block();
+    const int all = *(volatile int*)&cnt;
+    for (int i = 0; i < all; i += WAVE)
+      list(a, i + lane_id() < all ? ((volatile int*)ch)[i + lane_id()] : 0, min(all - i, WAVE));
+  }
+};
+
+// Runs the wave's chunks of the two class bins (those of k_sched's geometry: CPW = 64 / G; wave w of
+// n) and lists the ones it leaves to k_sched; returns its first chunk of the v = 1 ones, which
+// go to the waves after those that take a last chunk here (so that the two kinds share a launch: a
 // launch of its own added 20 us to batches with few of these orders).
 template <int X, bool ROT>
 __device__ __forceinline__ int pipe2_chunks(const SimArgs& a, const int64_t* pre,
-                                            const int64_t* link) {
+                                            const int64_t* link, int w, int n, LeftChunks& lc) {
   const int P = a.pr.P, M = a.pr.M, L = a.pr.L, S = 2 * P, G = a.G;
   const int g = lane_id() / G, x = lane_id() % G;
   const int r = x < P ? x : 0;  // (an idle lane stands in as rank 0 and is read by nobody)
@@ -2145,7 +2126,8 @@ __device__ __forceinline__ int pipe2_chunks(const SimArgs& a, const int64_t* pre
   const int start_i = ci < 2 ? a.ctl[CTL_START + BIN_STATIC + 3 - ci] : 0;
   const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
   const int end0 = __shfl(nch_i, 0, WAVE), end1 = end0 + __shfl(nch_i, 1, WAVE);
-  for (int ch = (int)blockIdx.x; ch < end1; ch += (int)gridDim.x) {
+  int nleft = 0, mine_left = 0;  // chunks left to k_sched, one per lane
+  for (int ch = w; ch < end1; ch += n) {
     const int ib = ch < end0 ? 0 : 1, split = 1 - ib;
     const int cnt = __shfl(cnt_i, ib, WAVE), pos0 = __shfl(start_i, ib, WAVE);
     const int e = (ch - (ib == 0 ? 0 : end0)) * a.CPW + g;
@@ -2178,89 +2160,76 @@ __device__ __forceinline__ int pipe2_chunks(const SimArgs& a, const int64_t* pre
     group_bits(G, &gbit, &lsb);
     const bool wide = (fold_groups(__ballot(mine && (bits >> 32) != 0), G, lsb) & gbit) != 0;
     const bool on = mine && !wide;
-    double W[2], D[2], V[2], E[2];  // forward and backward weights and durations by chunk
+    // q and the time per step, over the group
+    int64_t q = 0, per = 0;
+    auto most = [](const int64_t (&y)[2]) { return y[0] > y[1] ? y[0] : y[1]; };
+    if (on) {
+      per = (f[0] + f[1] + b[0] + b[1] + wg[0] + wg[1]) >> 1;
+      const int64_t lF = most(wF), lB = most(wB);
+      q = most(f) + most(b) + most(wg) + (lF > lB ? lF : lB);
+      q = q > per ? q : per;
+    }
+    q = group_max(q, G), per = group_max(per, G);
+    const bool fit = q < (int64_t)1 << 28 && (P - 1) * per + 2 * q <= (int64_t)7 << 27;
+    bool done = false;
+    Pipe2Int p;
+    if (__ballot(on && !fit) == 0) {
+      p.D = (int)per;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int s = r + k * P;
-      W[k] = on && s > 0 ? (double)wF[k] : PIPE_NONE;
-      V[k] = on && s < S - 1 ? (double)wB[k] : PIPE_NONE;
-      D[k] = on ? (double)f[k] : 0.0;
-      E[k] = on ? (double)(split ? b[k] : b[k] + wg[k]) : 0.0;
-    }
-    double clk = 0.0, fst = -1.0;
-    bool again = true;  // on doubles
-    if (M > P) {  // (N >= 3 P - 2: M is a multiple of P)
-      // q and the time per step, over the group
-      int64_t q = 0, per = 0;
-      auto most = [](const int64_t (&y)[2]) { return y[0] > y[1] ? y[0] : y[1]; };
-      if (on) {
-        per = (f[0] + f[1] + b[0] + b[1] + wg[0] + wg[1]) >> 1;
-        const int64_t lF = most(wF), lB = most(wB);
-        q = most(f) + most(b) + most(wg) + (lF > lB ? lF : lB);
-        q = q > per ? q : per;
+      for (int k = 0; k < 2; ++k) {
+        const int s = r + k * P;
+        p.w[k] = on && s > 0 ? (int)wF[k] : INT32_MIN;
+        p.v[k] = on && s < S - 1 ? (int)wB[k] : INT32_MIN;
+        p.f[k] = on ? (int)f[k] : 0, p.b[k] = on ? (int)(split ? b[k] : b[k] + wg[k]) : 0;
+        p.g[k] = on ? (int)wg[k] : 0;
       }
-      q = group_max(q, G), per = group_max(per, G);
-      const bool fit = q < (int64_t)1 << 28;
-      if (__ballot(on && !fit) == 0) {
-        Pipe2Int p;
-        p.D = (int)per;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const int s = r + k * P;
-          p.w[k] = on && s > 0 ? (int)wF[k] : INT32_MIN;
-          p.v[k] = on && s < S - 1 ? (int)wB[k] : INT32_MIN;
-          p.f[k] = on ? (int)f[k] : 0, p.b[k] = on ? (int)(split ? b[k] : b[k] + wg[k]) : 0;
-          p.g[k] = on ? (int)wg[k] : 0;
-        }
-        p.clk = PIPE_ORG, p.oF = p.oB = PIPE_ORG;
-        p.fs = PIPE_ORG, p.hi = INT32_MIN, p.lo = INT32_MAX, p.org = 0;
-        again = split ? !pipe2_run32<X, true, ROT>(p, P, M, G, r, on, (int)q)
-                      : !pipe2_run32<X, false, ROT>(p, P, M, G, r, on, (int)q);
-        clk = (double)(p.org + (p.clk - PIPE_ORG) + (int64_t)(2 * M + P) * p.D);
-        fst = (double)(p.fs - PIPE_ORG);
-      }
+      p.clk = PIPE_ORG, p.oF = p.oB = PIPE_ORG;
+      p.fs = PIPE_ORG, p.hi = INT32_MIN, p.lo = INT32_MAX, p.org = 0;
+      done = split ? pipe2_run32<X, true, ROT>(p, P, M, G, r, on, (int)q)
+                   : pipe2_run32<X, false, ROT>(p, P, M, G, r, on, (int)q);
     }
-    if (again) {
-      Pipe2Lane<X> p;
-      p.clk = p.oF = p.oB = 0.0, p.fs = -1.0;
-      // forwards run chunk 0 first, backwards chunk 1; each pair starts swapped
-      p.wF = W[1], p.dF = D[1], p.wF1 = W[0], p.dF1 = D[0];
-      p.wB = V[0], p.dB = E[0], p.wB1 = V[1], p.dB1 = E[1];
-      const double w0 = on ? (double)wg[0] : 0.0, w1 = on ? (double)wg[1] : 0.0;
-      clk = split ? pipe2_run<X, true, ROT>(p, P, M, r, w0, w1)
-                  : pipe2_run<X, false, ROT>(p, P, M, r, w0, w1);
-      fst = p.fs;
+    if (!done) {
+      mine_left = lane_id() == nleft ? ch : mine_left;
+      if (++nleft == WAVE) lc.list(a, mine_left, nleft), nleft = 0;
+      continue;
     }
-    double ms = x < P ? clk : 0.0;
-    for (int o = 1; o < G; o <<= 1) ms = dmax(ms, __shfl_xor(ms, o, WAVE));
+    const int64_t clk = p.org + (p.clk - PIPE_ORG) + (int64_t)(2 * M + P) * p.D;
+    const int64_t ms = group_max(x < P ? clk : 0, G);
     if (mine) {
       if (wide) {
         if (x == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
       } else {
-        const int64_t m = (int64_t)ms;
-        if (x == 0) a.out_ms[cand] = m;
-        a.out_bub[cand * P + d] = m - (f[0] + b[0] + wg[0] + f[1] + b[1] + wg[1]) * M;
+        if (x == 0) a.out_ms[cand] = ms;
+        a.out_bub[cand * P + d] = ms - (f[0] + b[0] + wg[0] + f[1] + b[1] + wg[1]) * M;
         if constexpr (X == XB) {
-          a.out_bound[(cand * P + d) * 2] = (int64_t)fst;
-          a.out_bound[(cand * P + d) * 2 + 1] = (int64_t)clk;
+          a.out_bound[(cand * P + d) * 2] = p.fs - PIPE_ORG;
+          a.out_bound[(cand * P + d) * 2 + 1] = clk;
         }
       }
     }
   }
-  const int n = (int)gridDim.x;
-  return ((int)blockIdx.x + n - end1 % n) % n;
+  lc.last(a, mine_left, nleft);
+  return (w + n - end1 % n) % n;
 }
 
 // TWO: also the looped interleaved orders of v = 2 (1: ds_bpermute, 2: DPP at P = 16).
 template <int X, int TWO>
-__global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a, int gpipe) {
+__global__ void __launch_bounds__(TWO ? PIPE_WAVES* WAVE : WAVE) k_pipe(SimArgs a, int gpipe) {
   extern __shared__ __align__(16) uint8_t smem[];
+  constexpr int NT = TWO ? PIPE_WAVES * WAVE : WAVE;
+  const int tid = (int)threadIdx.x;
+  // this wave among those of the launch (neighbours in different blocks: few chunks spread over the
+  // CUs)
+  const int wv = (TWO ? bcast(tid / WAVE) * (int)gridDim.x : 0) + (int)blockIdx.x;
+  const int nwv = TWO ? (int)gridDim.x * PIPE_WAVES : (int)gridDim.x;
   const int P = a.pr.P, M = a.pr.M, L = a.pr.L, S = P;
   // layer prefix sums and links: every lane reads its stage's entries
   int64_t* pre = reinterpret_cast<int64_t*>(smem);
   int64_t* link = pre + 3 * (L + 1);
-  for (int i = lane_id(); i < 3 * (L + 1); i += WAVE) pre[i] = a.pre[i];
-  for (int i = lane_id(); i < P * P; i += WAVE) link[i] = a.link[i];
+  for (int i = tid; i < 3 * (L + 1); i += NT) pre[i] = a.pre[i];
+  for (int i = tid; i < P * P; i += NT) link[i] = a.link[i];
+  LeftChunks& lc = *reinterpret_cast<LeftChunks*>(link + P * P);
+  if (TWO && tid == 0) lc.cnt = lc.ended = 0;
   __syncthreads();
   const int h = a.G >> 1, x = lane_id() & 15;
   const int s = 2 * ((x & 7) & (h - 1)) + (x >> 3);
@@ -2273,10 +2242,10 @@ __global__ void __launch_bounds__(WAVE) k_pipe(SimArgs a, int gpipe) {
   const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
   const int end0 = __shfl(nch_i, 0, WAVE), end1 = end0 + __shfl(nch_i, 1, WAVE);
   const int end2 = end1 + __shfl(nch_i, 2, WAVE);
-  int first = (int)blockIdx.x;
-  if constexpr (TWO != 0) first = pipe2_chunks<X, TWO == 2>(a, pre, link);
+  int first = wv;
+  if constexpr (TWO != 0) first = pipe2_chunks<X, TWO == 2>(a, pre, link, wv, nwv, lc);
   // chunks by grid stride, the longer (split) ones first
-  for (int ch = first; ch < end2; ch += (int)gridDim.x) {
+  for (int ch = first; ch < end2; ch += nwv) {
     const int ib = ch < end0 ? 0 : ch < end1 ? 1 : 2;
     const int split = ib == 0 ? 1 : 0;
     const int cnt = __shfl(cnt_i, ib, WAVE), pos0 = __shfl(start_i, ib, WAVE);
@@ -2702,9 +2671,11 @@ __global__ void __launch_bounds__(WAVE) k_sim_mat(SimArgs a) {
 // it): queues materialised in global memory, moves applied. A candidate whose window reaches
 // the ring joins the wide list, which a second launch (wide_pass, full rows: a.ring = M) takes;
 // one whose times pass the 40-bit slots joins the redo list of the 64-bit kernel, which runs
-// after both.
+// after both. Placed on a page of its own: the same code took 91 or 100 us a dispatch (Algorithm 1 on
+// 4,096 records at P = 8, M = 64) by where the kernels before it left its start.
 template <int VMAX, int X>
-__global__ void __launch_bounds__(WAVE) k_sim_mat40(SimArgs a, int mode) {
+__global__ void __launch_bounds__(WAVE) __attribute__((aligned(4096)))
+k_sim_mat40(SimArgs a, int mode) {
   extern __shared__ __align__(16) uint8_t smem[];
   __shared__ int64_t mbox[X == XR ? WAVE : 1];  // rendezvous mailboxes
   const int G = a.G, P = a.pr.P, M = a.pr.M;
@@ -5288,11 +5259,11 @@ int ensure_buf(void*& ptr, size_t& have, size_t bytes, hipStream_t stream) {
 }
 
 template <typename K>
-int occupancy_grid(K kernel, int lds, int cus, int* grid) {
+int occupancy_grid(K kernel, int lds, int cus, int* grid, int waves = 1) {
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, WAVE, lds) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, waves * WAVE, lds) != hipSuccess)
     return OCTO_EHIP;
   if (per_cu < 1) return OCTO_EUNSUPPORTED;
   *grid = per_cu * cus;
@@ -5777,6 +5748,7 @@ SimArgs make_args(const octo_problem* prob, const Plan& pl, const Setup& su, con
   a.stab = nullptr;
   a.smeta = nullptr;
   a.pipe = a.pipe2 = false;
+  a.sc_first = 0;
   a.srow = nullptr;
   a.sr_v = 0;
   for (int i = 0; i < 2; ++i) a.sr_off[i] = 0, a.sr_rowlen[i] = 0, a.sr_steps[i] = 0;
@@ -5809,8 +5781,8 @@ int launch_sched(const SimArgs& base, const Setup& su, int64_t n, int v, hipStre
   const int rbase = lbase + (X == XS ? (2 * VC + 1) * WAVE * 8 : 0);
   const int lds = rbase + a.CPW * a.rec_stride;
   if (lds > su.di.lds_max) return OCTO_EUNSUPPORTED;  // at most 72 KB within the size limits
-  // first class (where the v = 2 ones have another kernel, the v = 1 ones have too)
-  if (NR == 1) a.sr_v = VC > 2 ? 0 : a.pipe2 ? 4 : a.pipe ? 2 : 0;
+  // (the v = 2 interleaved classes are 2 and 3)
+  if (NR == 1 && VC <= 2) a.sc_first = a.pipe2 ? 3 : a.pipe ? 2 : 0;
   if (NR > 1) {
     const StGeom& g = su.ws->sg;
     a.srow = reinterpret_cast<const uint32_t*>(static_cast<const char*>(su.ws->st) + g.rows);
@@ -5836,13 +5808,15 @@ int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, bool gpipe, hip
   SimArgs a = base;
   a.G = std::max(2, lanes_per_candidate(a.pr.P));
   a.CPW = WAVE / a.G;
-  const int lds = (3 * (a.pr.L + 1) + a.pr.P * a.pr.P) * 8;
+  const int waves = TWO ? PIPE_WAVES : 1;
+  const int lds = (3 * (a.pr.L + 1) + a.pr.P * a.pr.P) * 8 + (TWO ? (int)sizeof(LeftChunks) : 0);
   int grid = 0;
-  int rc = occupancy_grid(k_pipe<X, TWO>, lds, su.di.cus, &grid);
+  int rc = occupancy_grid(k_pipe<X, TWO>, lds, su.di.cus, &grid, waves);
   if (rc) return rc;
-  const int64_t need = (n + a.CPW - 1) / a.CPW;
+  const int64_t need = (n + a.CPW * waves - 1) / (a.CPW * waves);
   grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
-  hipLaunchKernelGGL((k_pipe<X, TWO>), dim3(grid), dim3(WAVE), lds, stream, a, gpipe ? 1 : 0);
+  hipLaunchKernelGGL((k_pipe<X, TWO>), dim3(grid), dim3(waves * WAVE), lds, stream, a,
+                     gpipe ? 1 : 0);
   return launch_ok();
 }
 
@@ -6070,7 +6044,8 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
     // (the memory model's running totals need 64-bit integers, and the ring of ranks with link times was
     // the slower one)
     a.pipe2 = (X == XP || X == XB) && a.pipe && prob->v_max >= 2 && prob->P >= 2 &&
-              prob->M % prob->P == 0;
+              prob->M % prob->P == 0 && prob->M > prob->P &&
+              st_geom(prob, *su.ws).inter_ok[2];  // (k_sched takes what k_pipe leaves)
     if (!a.pipe || prob->v_max >= 2) {
       if ((rc = build_static(prob, *su.ws, stream))) return rc;
       const char* st = static_cast<const char*>(su.ws->st);

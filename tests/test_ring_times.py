@@ -209,3 +209,28 @@ def test_uneven_ranks(P, M):
         L = 2 * P + int(rng.integers(0, 3 * P))
         link = rng.integers(0, 2_000_000, size=(P, P)).astype(np.int64)
         _compare(P, M, _uneven(rng, P, L), link, _looped(rng, L, P, rng.integers(2, 4, size=97)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,M,n", [(2, 6, 5000), (5, 15, 2500), (8, 24, 4000), (16, 48, 3000)])
+@pytest.mark.parametrize("share", [0.0, 0.02, 0.5, 1.0])
+def test_left_chunks(P, M, n, share):
+    """Batches of many waves of which about that share of the records leaves the range: none, few,
+    half, all of them (the waves that leave it take the class schedules)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"ring times: left chunks P={P} M={M} n={n} share={share}", flush=True)
+    rng = np.random.default_rng(P + int(100 * share))
+    L, S = 4 * P, 2 * P
+    costs = rng.integers(0, 300_000, size=(L, 3)).astype(np.int64)
+    # the last two layers are long: apart the groups are well inside the range, in one stage outside
+    costs[L - 2:] = int(1.2 * 7 * 2 ** 27 / (P + 3)) // 3
+    recs = _looped(rng, L, P, rng.integers(2, 4, size=n))
+    cut = np.sort(rng.permuted(np.tile(np.arange(1, L - 2), (n, 1)), axis=1)[:, :S - 1], axis=1)
+    one = rng.random(n) < share
+    cut[:, -1] = np.where(one, L - 2, L - 1)
+    if S > 2:
+        cut[:, -2] = np.where(one, cut[:, -2], L - 2)
+    recs[:, 4:4 + S - 1] = cut
+    _compare(P, M, costs, rng.integers(0, 900_000, size=(P, P)).astype(np.int64), recs)
