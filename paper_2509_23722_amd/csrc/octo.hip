@@ -47,6 +47,7 @@ constexpr int CTL_REDO = 170;     // candidates for the 64-bit path (40-bit over
 constexpr int CTL_WIDE = 171;     // perturbed candidates whose queue window passes the ring
 constexpr int CTL_WORK_WIDE = 172;// chunk counter of k_sim_mat40 over the wide list
 constexpr int CTL_TOTAL = 173;    // valid records (all bins; set by k_plan)
+constexpr int CTL_GPIPE = 174;    // whether the v = 1 GPipe records are k_pipe's (set by k_plan)
 constexpr int CTL_LEFT = 288;     // v = 2 interleaved chunks that k_pipe leaves to k_sched (a line of
                                   // its own)
 constexpr int CTL_START = 176;    // [NBINS] first index position of each bin
@@ -57,6 +58,12 @@ static_assert(CTL_START + NBINS <= CTL_WORK_V && CTL_WORK_V + 12 <= CTL_LEFT, "c
 static_assert(NBINS <= 80, "bin arrays of the control block hold 80 bins");
 // rounds a materialised queue is read ahead of its use (GenMatK; rows of at least 8 entries)
 constexpr int QK = 6;
+
+// v = 1 GPipe records up to which k_pipe takes them, and GPipe records of every v for which k_afab
+// has lanes at once (gpipe_in_pipe).
+struct GpipeRule {
+  int most, room;
+};
 
 struct SimArgs {
   Problem pr;
@@ -106,6 +113,7 @@ struct SimArgs {
   const uint32_t* stab;
   const int32_t* smeta;
   bool pipe, pipe2;  // the v = 1 classes are k_pipe's, the v = 2 interleaved ones k_pipe's too
+  GpipeRule gpipe;
   int sc_first;      // k_sched over the classes of v <= 2: the first one of this launch
   // k_sched over MERGE bins: the stage rows of v = sr_v (null: none), S + 1 rows of sr_rowlen[split]
   // entries from sr_off[split], of which sr_steps[split] are steps
@@ -658,17 +666,54 @@ __global__ void __launch_bounds__(CLS_THREADS) k_classify(SimArgs a, uint8_t* __
     if (hist[b]) atomicAdd(&a.ctl[CTL_COUNTS + b], hist[b]);
 }
 
-// One wave: first position of every bin in the index array (exclusive prefix sum), kept in
-// CTL_START and copied to the scatter cursors.
-__global__ void k_plan(int32_t* __restrict__ ctl) {
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int b = 0; b < NBINS; ++b) {
-      ctl[CTL_START + b] = ctl[CTL_POS + b] = acc;
-      acc += ctl[CTL_COUNTS + b];
-    }
-    ctl[CTL_TOTAL] = acc;
+// Whether the v = 1 GPipe records of a batch with these bin counts are k_pipe's: at most r.most of
+// them; beside others at v >= 2, whose time k_afab takes anyway, only where all of them would not run
+// there at once.
+__device__ __forceinline__ int gpipe_in_pipe(const GpipeRule& r, const int32_t* counts) {
+  if (r.most <= 0) return 0;
+  const int c1 = counts[bin_of(1, GEN_AFAB, 0)];
+  int more = 0;
+#pragma unroll
+  for (int v = 2; v <= 8; ++v) more += counts[bin_of(v, GEN_AFAB, 0)];
+  return c1 <= r.most && (more == 0 || c1 + more > r.room) ? 1 : 0;
+}
+
+// Inclusive prefix sum over a wave.
+template <class T>
+__device__ __forceinline__ T wave_scan(T x) {
+  const int l = lane_id();
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const T y = __shfl_up(x, o, WAVE);
+    x += l >= o ? y : (T)0;
   }
+  return x;
+}
+
+// First position of every bin (an exclusive prefix sum over the counts c0 of bins 0..63 and c1 of the
+// others, one bin of each per lane of one wave); the valid records in all bins.
+struct BinStarts {
+  int b0, b1, total;
+  __device__ __forceinline__ void init(int c0, int c1) {
+    const int e0 = wave_scan<int>(c0), s0 = __shfl(e0, WAVE - 1, WAVE);
+    const int e1 = wave_scan<int>(c1) + s0;
+    b0 = e0 - c0, b1 = e1 - c1;
+    total = __shfl(e1, WAVE - 1, WAVE);
+  }
+};
+
+// Two waves: the first position of every bin in the index array, kept in CTL_START and copied to the
+// scatter cursors; where the GPipe records run.
+__global__ void __launch_bounds__(2 * WAVE) k_plan(int32_t* __restrict__ ctl, GpipeRule r) {
+  const int t = (int)threadIdx.x;
+  if (t == WAVE) ctl[CTL_GPIPE] = gpipe_in_pipe(r, ctl + CTL_COUNTS);
+  if (t >= WAVE) return;
+  const int u = WAVE + t < NBINS ? WAVE + t : NBINS - 1;
+  const int c0 = ctl[CTL_COUNTS + t], c1 = ctl[CTL_COUNTS + u];
+  BinStarts st;
+  st.init(c0, WAVE + t < NBINS ? c1 : 0);
+  ctl[CTL_START + t] = ctl[CTL_POS + t] = st.b0;
+  if (WAVE + t < NBINS) ctl[CTL_START + u] = ctl[CTL_POS + u] = st.b1;
+  if (t == 0) ctl[CTL_TOTAL] = st.total;
 }
 
 // Index of every valid record at its bin's cursor; blocks cover the same CLS_ITEMS runs as
@@ -700,17 +745,6 @@ __global__ void __launch_bounds__(CLS_THREADS) k_scatter(SimArgs a, const uint8_
 #pragma unroll
   for (int run = 0; run < CLS_ITEMS; ++run)
     if (bin[run] != BIN_NONE) idx[res[bin[run]] + local[run]] = (int32_t)(first + run * CLS_THREADS);
-}
-
-// Inclusive prefix sum over a wave.
-template <class T>
-__device__ __forceinline__ T wave_scan(T x) {
-  const int l = lane_id();
-  for (int o = 1; o < WAVE; o <<= 1) {
-    const T y = __shfl_up(x, o, WAVE);
-    x += l >= o ? y : (T)0;
-  }
-  return x;
 }
 
 // A small batch's k_prep, k_classify, k_plan and k_scatter in one block of FRONT_THREADS threads
@@ -763,14 +797,15 @@ __global__ void __launch_bounds__(FRONT_THREADS) k_front(SimArgs a, const int64_
     local[run] = wave_hist_add(hist, bin[run], bin[run] != BIN_NONE);
   }
   __syncthreads();
+  if (t == WAVE) a.ctl[CTL_GPIPE] = gpipe_in_pipe(a.gpipe, hist);
   if (t < WAVE) {  // first position of every bin
     const int c0 = hist[t], c1 = hist[WAVE + t];
-    const int e0 = wave_scan<int>(c0), s0 = __shfl(e0, WAVE - 1, WAVE);
-    const int e1 = wave_scan<int>(c1) + s0;
-    first[t] = e0 - c0, first[WAVE + t] = e1 - c1;
-    a.ctl[CTL_COUNTS + t] = c0, a.ctl[CTL_START + t] = e0 - c0;
-    if (WAVE + t < NBINS) a.ctl[CTL_COUNTS + WAVE + t] = c1, a.ctl[CTL_START + WAVE + t] = e1 - c1;
-    if (t == WAVE - 1) a.ctl[CTL_TOTAL] = e1;
+    BinStarts st;
+    st.init(c0, c1);
+    first[t] = st.b0, first[WAVE + t] = st.b1;
+    a.ctl[CTL_COUNTS + t] = c0, a.ctl[CTL_START + t] = st.b0;
+    if (WAVE + t < NBINS) a.ctl[CTL_COUNTS + WAVE + t] = c1, a.ctl[CTL_START + WAVE + t] = st.b1;
+    if (t == 0) a.ctl[CTL_TOTAL] = st.total;
   }
   __syncthreads();
 #pragma unroll
@@ -785,8 +820,8 @@ struct ChunkMap {
   int cnt, start, nch, end;
   __device__ __forceinline__ void init(const int32_t* ctl, int CPW, uint64_t mask, int nbins) {
     const int b = lane_id();
-    const bool in = b < nbins && ((mask >> b) & 1);
-    cnt = in ? ctl[CTL_COUNTS + b] : 0;
+    const int c = b < nbins ? ctl[CTL_COUNTS + b] : 0;  // (not after the mask, which may be loaded)
+    cnt = (mask >> b) & 1 ? c : 0;
     start = b < nbins ? ctl[CTL_START + b] : 0;
     nch = (cnt + CPW - 1) / CPW;
     end = nch;
@@ -1154,7 +1189,8 @@ __global__ void __launch_bounds__(WAVE) k_afab(SimArgs a, int lanes, int tab_off
     pre = pre_l, pmem = pmem_l, link = link_l;
   }
   ChunkMap cmap;
-  cmap.init(a.ctl, lanes, a.bin_mask, NBIN_GEN);
+  cmap.init(a.ctl, lanes,
+            a.bin_mask & ~((uint64_t)a.ctl[CTL_GPIPE] << bin_of(1, GEN_AFAB, 0)), NBIN_GEN);
   // chunks by grid stride: AFAB candidates of one bin cost alike, and an atomic work counter
   // would serialise the waves
   for (int ch = (int)blockIdx.x;; ch += (int)gridDim.x) {
@@ -1779,7 +1815,6 @@ __global__ void __launch_bounds__(WAVE) k_sched(SimArgs a, int sbase, int lbase,
 // accesses of the class schedules' entries.
 // ---------------------------------------------------------------------------------------------
 constexpr int PIPE_MAX = 16;           // devices
-constexpr int64_t PIPE_GPIPE_MAX = 1 << 17;  // batch size up to which GPipe rows are k_pipe's
 constexpr double PIPE_NONE = -4.0e18;  // weight of an op without a cross-device input
 // x moved by a DPP control in the banks of the mask; elsewhere `old`, or anything without one.
 template <int CTRL, int BANKS>
@@ -1871,8 +1906,8 @@ __device__ __forceinline__ void pipe_run(PipeLane<X, SPLIT>& p, int S, int M, in
   tested(r2, end);
 }
 
-// GPipe rows on the same lanes (small batches, where k_afab's one lane per candidate leaves the
-// chip idle): F(s, m) in round s + m, then B(s, m) in round S - 1 - s + m of a second pass, every
+// GPipe rows on the same lanes (where k_afab's one lane per candidate would leave most of the chip
+// idle: gpipe_in_pipe): F(s, m) in round s + m, then B(s, m) in round S - 1 - s + m of a second pass, every
 // producer one round before its consumer.
 template <int X>
 __device__ __forceinline__ void pipe_gpipe(PipeLane<X, false>& p, int S, int M, int s) {
@@ -2214,7 +2249,7 @@ __device__ __forceinline__ int pipe2_chunks(const SimArgs& a, const int64_t* pre
 
 // TWO: also the looped interleaved orders of v = 2 (1: ds_bpermute, 2: DPP at P = 16).
 template <int X, int TWO>
-__global__ void __launch_bounds__(TWO ? PIPE_WAVES* WAVE : WAVE) k_pipe(SimArgs a, int gpipe) {
+__global__ void __launch_bounds__(TWO ? PIPE_WAVES* WAVE : WAVE) k_pipe(SimArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
   constexpr int NT = TWO ? PIPE_WAVES * WAVE : WAVE;
   const int tid = (int)threadIdx.x;
@@ -2235,10 +2270,11 @@ __global__ void __launch_bounds__(TWO ? PIPE_WAVES* WAVE : WAVE) k_pipe(SimArgs 
   const int s = 2 * ((x & 7) & (h - 1)) + (x >> 3);
   const int g = (lane_id() >> 4) * (8 / h) + (x & 7) / h;
   // the bins (split, fused, GPipe where it is this kernel's) and their chunk ranges, one per lane
-  const int ci = lane_id(), nb = gpipe ? 3 : 2;
+  const int ci = lane_id(), nb = 2 + (a.pr.v_max == 1 && a.n <= a.gpipe.most ? 1 : a.ctl[CTL_GPIPE]);
   const int bin_i = ci == 2 ? bin_of(1, GEN_AFAB, 0) : BIN_STATIC + (ci == 0 ? 1 : 0);
-  const int cnt_i = ci < nb ? a.ctl[CTL_COUNTS + bin_i] : 0;
-  const int start_i = ci < nb ? a.ctl[CTL_START + bin_i] : 0;
+  const int c_i = ci < 3 ? a.ctl[CTL_COUNTS + bin_i] : 0;
+  const int start_i = ci < 3 ? a.ctl[CTL_START + bin_i] : 0;
+  const int cnt_i = ci < nb ? c_i : 0;
   const int nch_i = (cnt_i + a.CPW - 1) / a.CPW;
   const int end0 = __shfl(nch_i, 0, WAVE), end1 = end0 + __shfl(nch_i, 1, WAVE);
   const int end2 = end1 + __shfl(nch_i, 2, WAVE);
@@ -5748,6 +5784,7 @@ SimArgs make_args(const octo_problem* prob, const Plan& pl, const Setup& su, con
   a.stab = nullptr;
   a.smeta = nullptr;
   a.pipe = a.pipe2 = false;
+  a.gpipe = GpipeRule{0, 0};
   a.sc_first = 0;
   a.srow = nullptr;
   a.sr_v = 0;
@@ -5801,10 +5838,10 @@ int launch_sched(const SimArgs& base, const Setup& su, int64_t n, int v, hipStre
   return launch_ok();
 }
 
-// Launch k_pipe over the v = 1 class bins (gpipe: and the v = 1 GPipe bin; a.pipe2: and the v = 2
-// interleaved ones).
+// Launch k_pipe over the v = 1 class bins (and the v = 1 GPipe bin: gpipe_in_pipe; a.pipe2: and the
+// v = 2 interleaved ones).
 template <int X, int TWO>
-int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, bool gpipe, hipStream_t stream) {
+int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, hipStream_t stream) {
   SimArgs a = base;
   a.G = std::max(2, lanes_per_candidate(a.pr.P));
   a.CPW = WAVE / a.G;
@@ -5815,8 +5852,7 @@ int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, bool gpipe, hip
   if (rc) return rc;
   const int64_t need = (n + a.CPW * waves - 1) / (a.CPW * waves);
   grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
-  hipLaunchKernelGGL((k_pipe<X, TWO>), dim3(grid), dim3(waves * WAVE), lds, stream, a,
-                     gpipe ? 1 : 0);
+  hipLaunchKernelGGL((k_pipe<X, TWO>), dim3(grid), dim3(waves * WAVE), lds, stream, a);
   return launch_ok();
 }
 
@@ -5862,12 +5898,13 @@ int launch_sim(const octo_problem* prob, const Setup& su, const int64_t* link, c
   return launch_ok();
 }
 
-// Launch k_afab over the AFAB bins of v >= v_lo: one lane per candidate, each lane's row of M
-// int64 plus 2 P device words in LDS (at most 64 KiB per wave).
+// Plan of k_afab: one lane per candidate, each lane's row of M int64 plus 2 P device words in LDS
+// (at most 64 KiB per wave).
+struct AfabPlan {
+  int mmax, lanes, tab_off, rec_off, lds, grid;
+};
 template <int X>
-int launch_afab(const octo_problem* prob, const Setup& su, const int64_t* link, const void* cands,
-                int64_t n, int64_t* ms, int64_t* bub, int64_t* peak, int64_t* comm,
-                int64_t* bound, int v_lo, hipStream_t stream) {
+int afab_plan(const octo_problem* prob, const Setup& su, AfabPlan* pl) {
   // rows as line envelopes (plain, memory and bounds variants); the communication and
   // serialised-link variants, which need every op, keep rows of exactly 32 or 64 micro-batches
   // in registers and other lengths in LDS
@@ -5893,31 +5930,32 @@ int launch_afab(const octo_problem* prob, const Setup& su, const int64_t* link, 
   const int lds =
       rec_off + (stage ? lanes * (int)align_up(pert_off(prob->P * prob->v_max), 16) : 0);
   if (lds > su.di.lds_max) return OCTO_EUNSUPPORTED;
-  SimArgs a = make_args(prob, su.big, su, link, cands, n, ms, bub, peak);
-  a.out_comm = comm;
-  a.out_bound = bound;
-  a.bin_mask = bins_of(v_lo, prob->v_max, true);
-  a.work = CTL_WORK + 3;
-  int grid = 0;
-  const int64_t need = (n + lanes - 1) / lanes;
-  if constexpr (LINES) {
-    const int rc = occupancy_grid(k_afab<-1, X>, lds, su.di.cus, &grid);
-    if (rc) return rc;
-    grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
-    hipLaunchKernelGGL((k_afab<-1, X>), dim3(grid), dim3(WAVE), lds, stream, a, lanes, tab_off, rec_off);
-  } else {
-    const int rc = mmax == 32   ? occupancy_grid(k_afab<32, X>, lds, su.di.cus, &grid)
-                   : mmax == 64 ? occupancy_grid(k_afab<64, X>, lds, su.di.cus, &grid)
-                                : occupancy_grid(k_afab<0, X>, lds, su.di.cus, &grid);
-    if (rc) return rc;
-    grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, need));
-    if (mmax == 32)
-      hipLaunchKernelGGL((k_afab<32, X>), dim3(grid), dim3(WAVE), lds, stream, a, lanes, tab_off, rec_off);
-    else if (mmax == 64)
-      hipLaunchKernelGGL((k_afab<64, X>), dim3(grid), dim3(WAVE), lds, stream, a, lanes, tab_off, rec_off);
-    else
-      hipLaunchKernelGGL((k_afab<0, X>), dim3(grid), dim3(WAVE), lds, stream, a, lanes, tab_off, rec_off);
-  }
+  *pl = AfabPlan{mmax, lanes, tab_off, rec_off, lds, 0};
+  if constexpr (LINES)
+    return occupancy_grid(k_afab<-1, X>, lds, su.di.cus, &pl->grid);
+  else
+    return mmax == 32   ? occupancy_grid(k_afab<32, X>, lds, su.di.cus, &pl->grid)
+           : mmax == 64 ? occupancy_grid(k_afab<64, X>, lds, su.di.cus, &pl->grid)
+                        : occupancy_grid(k_afab<0, X>, lds, su.di.cus, &pl->grid);
+}
+
+// Launch k_afab over the AFAB bins of base's batch.
+template <int X>
+int launch_afab(const octo_problem* prob, const Setup& su, const SimArgs& base, const AfabPlan& pl,
+                int64_t n, hipStream_t stream) {
+  SimArgs a = base;
+  a.bin_mask = bins_of(1, prob->v_max, true);
+  // (a last chunk for each v: a wave with two chunks would take twice as long as the others)
+  const int64_t need = (n + pl.lanes - 1) / pl.lanes + prob->v_max - 1;
+  const dim3 grid((int)std::max<int64_t>(1, std::min<int64_t>(pl.grid, need))), block(WAVE);
+  if constexpr (X == XP || X == XM || X == XB)
+    hipLaunchKernelGGL((k_afab<-1, X>), grid, block, pl.lds, stream, a, pl.lanes, pl.tab_off, pl.rec_off);
+  else if (pl.mmax == 32)
+    hipLaunchKernelGGL((k_afab<32, X>), grid, block, pl.lds, stream, a, pl.lanes, pl.tab_off, pl.rec_off);
+  else if (pl.mmax == 64)
+    hipLaunchKernelGGL((k_afab<64, X>), grid, block, pl.lds, stream, a, pl.lanes, pl.tab_off, pl.rec_off);
+  else
+    hipLaunchKernelGGL((k_afab<0, X>), grid, block, pl.lds, stream, a, pl.lanes, pl.tab_off, pl.rec_off);
   return launch_ok();
 }
 
@@ -6006,7 +6044,8 @@ int classify_sort(const octo_problem* prob, const Setup& su, const SimArgs& a, i
   hipLaunchKernelGGL(k_classify, dim3(nb), dim3(tb), tb * hb, stream, a, bins, hb);
   int rc = launch_ok();
   if (rc) return rc;
-  hipLaunchKernelGGL(k_plan, dim3(1), dim3(WAVE), 0, stream, a.ctl);
+  hipLaunchKernelGGL(k_plan, dim3(1), dim3(2 * WAVE), 0, stream, a.ctl,
+                     a.gpipe);
   if ((rc = launch_ok())) return rc;
   hipLaunchKernelGGL(k_scatter, dim3(nb), dim3(tb), 0, stream, a, bins,
                      reinterpret_cast<int32_t*>(base + su.l.idx));
@@ -6053,6 +6092,23 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
       a.smeta = reinterpret_cast<const int32_t*>(st + su.ws->sg.meta);
     }
   }
+  const int P = prob->P, M = prob->M;
+  // GPipe rows: one lane per candidate in k_afab, whose time hardly changes while the lanes fill the
+  // chip; in k_pipe it grows with records * G * (M + P). The sides cross near records * (M + P) =
+  // 5.4M at P = 8, M = 64, 5.8M at M = 200, 7.5M at P = 4, 4.2M at P = 6, M = 42; at 18M to 35M for
+  // P = 12 and 16, where a few candidates need more lines than k_afab's envelopes hold; with M about
+  // 2 P k_pipe is no slower at any size. us a call, k_afab / k_pipe, v = 1 at P = 8, M = 64: 46 / 36
+  // at 32,768 records, 48 / 45 at 65,536, 56 / 65 at 131,072; P = 16, M = 32: 184 / 95 at 131,072.
+  // With serialised links k_afab runs every op, and k_pipe is the faster one up to 524,288 records
+  // (P = 8: 232 / 217 at M = 64, 6,161 / 488 at M = 200). Beside rows of v >= 2, all of which k_afab
+  // runs at once: 131,072 records at P = 8, M = 64, half of them v = 1: 80 / 99.
+  AfabPlan ap{};
+  if constexpr (X != XR) {
+    const int most = X == XS || M <= 2 * P ? INT32_MAX : ((P <= 8 ? 5 : 20) << 20) / (M + P);
+    if ((!a.pipe || prob->v_max >= 2 || n > most) && (rc = afab_plan<X>(prob, su, &ap))) return rc;
+    a.gpipe.most = a.pipe ? most : 0;
+    a.gpipe.room = (ap.grid - prob->v_max + 1) * ap.lanes;
+  }
   if (front) {
     char* base = static_cast<char*>(su.ws->base);
     const int hb = (int)align_up((size_t)pert_off(prob->P * prob->v_max), 16);
@@ -6070,22 +6126,17 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   // generated INTER / MERGE queues, one launch per v with finish tables sized for it (ring
   // rows of the next power of two >= P v where the in-flight bound allows): v = 2, v = 1, then
   // v = 3..8; then AFAB queues; then materialised queues (perturbations, 64-bit redo).
-  const int P = prob->P, M = prob->M;
   if ((rc = record_mark(0, stream))) return rc;
-  // GPipe rows at v = 1 run in k_pipe while k_afab, one lane per candidate, would leave most of the
-  // chip idle: 32,768 of them at P = 8, M = 32 take 21.6 us there and 6 here, 131,072 at M = 64
-  // about 30 and 45
-  const bool gpipe = a.pipe && n <= PIPE_GPIPE_MAX;
   uint64_t taken = 0;  // bins that the schedules and k_pipe cover
   if constexpr (X != XR) {
     if (sched) {
       if constexpr (X == XP || X == XB) {
-        if (a.pipe && (rc = !a.pipe2 ? launch_pipe<X, 0>(a, su, n, gpipe, stream)
-                            : P == 16 ? launch_pipe<X, 2>(a, su, n, gpipe, stream)
-                                      : launch_pipe<X, 1>(a, su, n, gpipe, stream)))
+        if (a.pipe && (rc = !a.pipe2 ? launch_pipe<X, 0>(a, su, n, stream)
+                            : P == 16 ? launch_pipe<X, 2>(a, su, n, stream)
+                                      : launch_pipe<X, 1>(a, su, n, stream)))
           return rc;
       } else if constexpr (X != XC) {
-        if (a.pipe && (rc = launch_pipe<X, 0>(a, su, n, gpipe, stream))) return rc;
+        if (a.pipe && (rc = launch_pipe<X, 0>(a, su, n, stream))) return rc;
       }
       if ((!a.pipe || prob->v_max >= 2) && (rc = launch_sched<1, 2, X>(a, su, n, 0, stream)))
         return rc;
@@ -6132,9 +6183,7 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
       return rc;
   if ((rc = record_mark(4, stream))) return rc;
   if constexpr (X != XR) {
-    if ((!gpipe || prob->v_max >= 2) &&
-        (rc = launch_afab<X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
-                             gpipe ? 2 : 1, stream)))
+    if (ap.grid > 0 && (rc = launch_afab<X>(prob, su, a, ap, n, stream)))
       return rc;
   } else {
     // rendezvous: GPipe queues in the generated kernels, per v class, with one slot per stage
@@ -6268,7 +6317,7 @@ int tune_step_impl(const octo_problem* prob, const int64_t* layer_costs, const i
       int32_t* order = const_cast<int32_t*>(tr.s.idx);
       hipLaunchKernelGGL(k_chain_count, dim3(nb), dim3(256), 0, stream, tr);
       if ((rc = launch_ok())) return rc;
-      hipLaunchKernelGGL(k_plan, dim3(1), dim3(WAVE), 0, stream, tr.s.ctl);
+      hipLaunchKernelGGL(k_plan, dim3(1), dim3(2 * WAVE), 0, stream, tr.s.ctl, tr.s.gpipe);
       if ((rc = launch_ok())) return rc;
       hipLaunchKernelGGL(k_chain_scatter, dim3(nb), dim3(256), 0, stream, tr, order);
       if ((rc = launch_ok())) return rc;

@@ -339,3 +339,45 @@ def test_gpipe_tally(P, v_max, M):
         torch.cuda.synchronize()
         for x, y in zip(g, r):
             np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,v_max,M,n", [
+    # one v: below and above the most that one lane per device takes; M up to 2 P: always
+    (8, 1, 60, 77_000), (8, 1, 60, 77_200), (3, 1, 2000, 2617), (3, 1, 2000, 2618), (16, 1, 160, 119_200),
+    (4, 1, 8, 200_000),
+    # beside GPipe rows of other v: as many as run at once, and more (the serial links' few lanes)
+    (2, 3, 5, 1), (4, 2, 9, 700), (6, 2, 42, 60_000), (16, 2, 33, 40_000), (8, 4, 12, 9000),
+])
+@pytest.mark.parametrize("call", ["plain", "mem", "serial", "bounds"])
+def test_gpipe_route(P, v_max, M, n, call):
+    """Which of the two kernels takes the GPipe records, by their number at v = 1 and in all."""
+    import torch
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(17000 + 100 * P + M)
+    print(f"GPipe route: {call} P={P} v_max={v_max} M={M} n={n}", flush=True)
+    L = P * v_max + 5
+    costs = rng.integers(0, 3_000_000, size=(L, 3)).astype(np.int64)
+    link = rng.integers(0, 900_000, size=(P, P)).astype(np.int64)
+    mem = rng.integers(0, 1 << 40, size=(L, 2)).astype(np.int64)
+    # (a few hundred distinct records, in another order for each copy)
+    recs = I.random_candidates(rng, L, P, v_max, M, 300, policies=(0,) if v_max == 1 else (0, 0, 0, 2))
+    recs = recs[rng.integers(0, 300, size=n)]
+    one, at = np.unique(recs, axis=0, return_inverse=True)
+    at = at.reshape(-1)
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    gp = _lib.problem(L, P, v_max, M, recs.shape[1], 0)
+    rp = R.problem(L, P, v_max, M, recs.shape[1], 0)
+    if call == "mem":
+        g = _lib.sim_batch_mem(gp, t(costs), t(mem), t(link), t(recs))
+        r = R.sim_batch_mem(rp, costs, mem, link, one, nthreads=NTHREADS)
+    else:
+        name = "sim_batch" if call == "plain" else "sim_batch_" + call
+        g = getattr(_lib, name)(gp, t(costs), t(link), t(recs))
+        r = getattr(R, name)(rp, costs, link, one, nthreads=NTHREADS)
+    torch.cuda.synchronize()
+    for x, y in zip(g, r):
+        y = np.asarray(y).reshape(len(one), -1)
+        np.testing.assert_array_equal(x.cpu().numpy().reshape(n, -1), y[at])
