@@ -748,8 +748,13 @@ __global__ void __launch_bounds__(CLS_THREADS) k_scatter(SimArgs a, const uint8_
 }
 
 // A small batch's k_prep, k_classify, k_plan and k_scatter in one block of FRONT_THREADS threads
-// (up to FRONT_MAX records): each of those kernels takes about as long as its launch there.
+// (up to front_max(hb) records, hb the bytes of a record's head): each of those kernels takes about as
+// long as its launch there, while the one block stages and classifies 1,024 heads after another. us a
+// call, four kernels / one: P = 8, v = 1 (heads of 48 bytes) 50 / 36 at 1,024 records, 50 / 40 at
+// 2,048, 51.5 / 50.4 at 4,096; P = 16, v = 2 (80 bytes) 221 / 210 at 3,072, 217 / 221 at 4,096; P = 32,
+// v = 2 (144 bytes) 382 / 351 at 2,048, 404 / 406 at 3,072, 399 / 433 at 4,096.
 constexpr int FRONT_THREADS = 1024, FRONT_MAX = 4096;
+constexpr int front_max(int hb) { return hb <= 64 ? FRONT_MAX : FRONT_MAX - FRONT_THREADS; }
 __global__ void __launch_bounds__(FRONT_THREADS) k_front(SimArgs a, const int64_t* __restrict__ costs,
                                                          const int64_t* __restrict__ mem,
                                                          int64_t* __restrict__ pre,
@@ -6063,7 +6068,8 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   constexpr bool MEM = X == XM;
   if (n == 0) return OCTO_OK;
   Setup su;
-  const bool front = n <= FRONT_MAX;
+  const int hb = (int)align_up((size_t)pert_off(prob->P * prob->v_max), 16);
+  const bool front = n <= front_max(hb);
   int rc = prepare(prob, layer_costs, MEM ? layer_mem : nullptr, stream, n, &su, 0, noalloc,
                    !front);
   if (rc) return rc;
@@ -6111,7 +6117,6 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   }
   if (front) {
     char* base = static_cast<char*>(su.ws->base);
-    const int hb = (int)align_up((size_t)pert_off(prob->P * prob->v_max), 16);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_front),
                               hipFuncAttributeMaxDynamicSharedMemorySize, FRONT_THREADS * hb);
     hipLaunchKernelGGL(k_front, dim3(1), dim3(FRONT_THREADS),

@@ -342,6 +342,30 @@ def test_gpipe_tally(P, v_max, M):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("P,v_max,n", [(16, 2, 3072), (16, 2, 3073), (10, 3, 4096), (11, 3, 3073), (64, 1, 3072),
+                                       (64, 1, 3073)])
+def test_front_route(P, v_max, n):
+    """The largest batches of the one-block classification, by the length of a record's head, and the
+    first of the general path's."""
+    import torch
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(18000 + P + n)
+    print(f"front route: P={P} v_max={v_max} n={n}", flush=True)
+    L, M = P * v_max + 9, 6
+    costs = rng.integers(0, 3_000_000, size=(L, 3)).astype(np.int64)
+    link = rng.integers(0, 900_000, size=(P, P)).astype(np.int64)
+    recs = I.random_candidates(rng, L, P, v_max, M, n, max_pert=2, pert_rate=0.1, invalid_rate=0.05)
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    g = _lib.sim_batch(_lib.problem(L, P, v_max, M, recs.shape[1], 2), t(costs), t(link), t(recs))
+    r = R.sim_batch(R.problem(L, P, v_max, M, recs.shape[1], 2), costs, link, recs, nthreads=NTHREADS)
+    torch.cuda.synchronize()
+    for x, y in zip(g, r):
+        np.testing.assert_array_equal(x.cpu().numpy().reshape(-1), np.asarray(y).reshape(-1))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("P,v_max,M,n", [
     # one v: below and above the most that one lane per device takes; M up to 2 P: always
     (8, 1, 60, 77_000), (8, 1, 60, 77_200), (3, 1, 2000, 2617), (3, 1, 2000, 2618), (16, 1, 160, 119_200),
