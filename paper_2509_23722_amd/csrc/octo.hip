@@ -1444,6 +1444,7 @@ __global__ void __launch_bounds__(WAVE) k_static_build(int P, int M, int v_max,
       int rank = __popcll(wm & ((1ull << c) - 1)), need = __popcll(wm), sl = dummy;
 #pragma unroll
       for (int i = 0; i < SC_SLOTS_MAX / 64; ++i) {
+        if (64 * i >= neg) break;  // (a word without slots: two reductions over the wave a round)
         freem[i] |= wave_or(pin >= 0 && (rd >> 6) == i ? 1ull << (rd & 63) : 0);
         const int nf = __popcll(freem[i]);
         uint64_t take = 0;
