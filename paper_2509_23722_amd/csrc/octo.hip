@@ -31,6 +31,7 @@
 
 #include "../../include/octo.h"
 #include "octo_device.hpp"
+#include "octo_schedules.hpp"
 #include "octo_sim.hpp"
 
 namespace octo {
@@ -295,15 +296,10 @@ __device__ __forceinline__ void run_generated(const SimArgs& a, int64_t cand, in
   L.pos = 0;
   L.nops = 0;
   L.mem = L.peak = 0;
-  L.cm.reset();
-  L.fs = -1;
-  if constexpr (X == XS)
-    for (int i = 0; i < 16; ++i) L.lf[i] = 0;
-  int64_t busy = 0, stat = 0;
+  int64_t busy = 0;
   const bool mine = has && d < P;
   if (mine) {
-    busy = setup_chunks<VMAX>(c, a.pr, rec, a.pre, a.link, d, v, split, ring, a.pre_mem, &stat,
-                              X);
+    busy = setup_chunks<VMAX>(c, a.pr, rec, a.pre, a.link, d, v, split, ring, nullptr, nullptr, X);
     L.nops = (split ? 3 : 2) * v * M;
   } else {
     zero_chunks<VMAX>(c);
@@ -344,14 +340,12 @@ __device__ __forceinline__ void run_generated(const SimArgs& a, int64_t cand, in
   }
 
   const int64_t ms = group_max(L.clock, G);
-  CommTally tot = L.cm;
-  if constexpr (X == XC) tot = group_tally(L.cm, G);
   if (mine) {
     if (ms >= Table40::LIMIT) {
       // times beyond the 40-bit slots: recompute this candidate with 64-bit slots
       if (d == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
     } else {
-      put_results<X>(a, cand, d, dead, ms, busy, stat, L.peak, tot, L.fs, L.clock);
+      put_results<X>(a, cand, d, dead, ms, busy, 0, 0, CommTally{});
     }
   }
 }
@@ -372,7 +366,7 @@ __device__ __forceinline__ int qt_row(const SimArgs& a, int gen, int v, int spli
 // Table-driven simulation of one candidate per group (INTER or MERGE at v <= 2). Durations and
 // weights must fit 32 bits; a candidate with a larger one, or whose times pass the 40-bit
 // slots, is recomputed on the 64-bit path.
-template <int VMAX, int X>
+template <int VMAX>
 __device__ __forceinline__ void run_tab(const SimArgs& a, int64_t cand, int v, int gen,
                                         int split, uint8_t* lds_wave) {
   const int G = a.G, P = a.pr.P, M = a.pr.M;
@@ -381,8 +375,7 @@ __device__ __forceinline__ void run_tab(const SimArgs& a, int64_t cand, int v, i
   const Table40 T{reinterpret_cast<uint32_t*>(lds_wave),
                   lds_wave + (size_t)a.slots * a.CPW * 4, __ffs(a.CPW) - 1, g < a.CPW ? g : 0};
   uint8_t* rec = lds_wave + (size_t)(g < a.CPW ? g : 0) * a.rec_stride;
-  constexpr int SREC = X != XP ? 16 : 8;  // bytes per stream record
-  uint8_t* strm = lds_wave + a.strm_off + lane_id() * SREC;
+  uint8_t* strm = lds_wave + a.strm_off + lane_id() * 8;  // 8-byte stream records
   const bool has = cand >= 0;
   const int S = P * v;
   const Ring ring = make_ring(M, a.ring);
@@ -390,12 +383,11 @@ __device__ __forceinline__ void run_tab(const SimArgs& a, int64_t cand, int v, i
   __asm__ volatile("" ::: "memory");
 
   Chunks<VMAX> c;
-  int64_t busy = 0, stat = 0;
+  int64_t busy = 0;
   bool fits = true;
   const bool mine = has && d < P;
   if (mine) {
-    busy = setup_chunks<VMAX>(c, a.pr, rec, a.pre, a.link, d, v, split, ring, a.pre_mem, &stat,
-                              X);
+    busy = setup_chunks<VMAX>(c, a.pr, rec, a.pre, a.link, d, v, split, ring, nullptr, nullptr, XP);
 #pragma unroll
     for (int kind = 0; kind < 3; ++kind) {
 #pragma unroll
@@ -404,18 +396,7 @@ __device__ __forceinline__ void run_tab(const SimArgs& a, int64_t cand, int v, i
           const int64_t w = kind == KF ? c.wF[k] : kind == KB ? c.wB[k] : 0;
           const int64_t du = kind == KF ? c.dF[k] : kind == KB ? c.dB[k] : c.dW[k];
           fits = fits && (uint64_t)w <= 0xFFFFFFFFull && (uint64_t)du <= 0xFFFFFFFFull;
-          uint8_t* rec_e = strm + (kind * v + k) * 64 * SREC;
-          *reinterpret_cast<uint2*>(rec_e) = make_uint2((uint32_t)w, (uint32_t)du);
-          if constexpr (X == XM) {
-            const int64_t dm = kind == KF ? c.mA[k] : (kind == KB && split) ? 0 : -c.mA[k];
-            *reinterpret_cast<int64_t*>(rec_e + 8) = dm;
-          }
-          if constexpr (X == XC) {
-            const int64_t co = kind == KF ? c.cF[k] : kind == KB ? c.cB[k] : 0;
-            const int cx = kind == KF ? c.xF[k] : kind == KB ? c.xB[k] : 0;
-            fits = fits && (uint64_t)co <= 0xFFFFFFFFull;
-            *reinterpret_cast<uint2*>(rec_e + 8) = make_uint2((uint32_t)co, (uint32_t)cx);
-          }
+          *reinterpret_cast<uint2*>(strm + (kind * v + k) * 512) = make_uint2((uint32_t)w, (uint32_t)du);
         }
       }
     }
@@ -433,21 +414,15 @@ __device__ __forceinline__ void run_tab(const SimArgs& a, int64_t cand, int v, i
   __asm__ volatile("" ::: "memory");
 
   bool dead = false;
-  int64_t clock = 0, mem = 0, peak = 0;
-  CommTally cm;
-  cm.reset();
-  int64_t fs = -1;
-  relax_tab<X>(a.qtab, row, qt_row_stride(ring) << T.lg, strm, clock, T, G, gbit, lsb, dead, mem,
-               peak, cm, fs);
+  int64_t clock = 0;
+  relax_tab(a.qtab, row, qt_row_stride(ring) << T.lg, strm, clock, T, G, gbit, lsb, dead);
 
   const int64_t ms = group_max(clock, G);
-  CommTally tot = cm;
-  if constexpr (X == XC) tot = group_tally(cm, G);
   if (mine) {
     if (wide || ms >= Table40::LIMIT) {
       if (d == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
     } else {
-      put_results<X>(a, cand, d, dead, ms, busy, stat, peak, tot, fs, clock);
+      put_results<XP>(a, cand, d, dead, ms, busy, 0, 0, CommTally{});
     }
   }
 }
@@ -868,7 +843,7 @@ __device__ __forceinline__ void dispatch_gen(const SimArgs& a, int gen, int64_t 
 
 // Generated-queue simulation (INTER and MERGE) for the bins in a.bin_mask of one v class:
 // VC = 1 (v = 1), 2 (v = 2) or 8 (v = 3..8); finish tables sized for that class with a.ring
-// slots per row. X: XM also the peak activation memory per device, XC the communication tally.
+// slots per row. X: XP (the no-allocation call with a scratch too small for the schedules) or XR.
 template <int VC, int X>
 __global__ void __launch_bounds__(WAVE) k_sim(SimArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
@@ -899,9 +874,9 @@ __global__ void __launch_bounds__(WAVE) k_sim(SimArgs a) {
       if (cand >= 0 && d == 0) a.redo[atomicAdd(&a.ctl[CTL_REDO], 1)] = (int32_t)cand;
       continue;
     }
-    if constexpr (VC <= 2) {
+    if constexpr (VC <= 2 && X == XP) {
       if (a.qtab) {
-        run_tab<VC, X>(a, cand, v, gen, split, smem);
+        run_tab<VC>(a, cand, v, gen, split, smem);
         continue;
       }
     }
@@ -5387,87 +5362,12 @@ struct TabGeom {
   Plan plan;
   int lg;
 };
-// wide: 16-byte stream records (two 8-byte units) with the activation delta or the output
-// transfer.
-TabGeom tab_geom(const octo_problem* p, int lds_max, int v, bool wide) {
+TabGeom tab_geom(const octo_problem* p, int lds_max, int v) {
   TabGeom t;
   t.ring = make_ring(p->M, v * p->P);
-  t.plan = fast_plan(p, lds_max, v * p->P, qt_row_stride(t.ring), 3 * v * (wide ? 2 : 1));
+  t.plan = fast_plan(p, lds_max, v * p->P, qt_row_stride(t.ring), 3 * v);
   t.lg = t.plan.CPW > 0 ? __builtin_ctz(t.plan.CPW) : 0;
   return t;
-}
-
-// Steps of the ideal stage pipeline of MERGE (largest ideal start + 1) for S stages, or 0 if some
-// link would need more than two slots: every value of micro-batch m must be consumed in an
-// earlier step than the one that produces micro-batch m + 2 of its link (sr_entry). Longest-path
-// times of the unit-cost pipeline, each stage running the interleaved order at v = 1.
-int stage_steps(int S, int M, int split) {
-  std::vector<int> st((size_t)2 * S * M, -1);  // start of F(s, m), then B(s, m)
-  auto at = [&](int kind, int s, int m) -> int& { return st[((size_t)kind * S + s) * M + m]; };
-  const int durB = split ? 1 : 2, n = (split ? 3 : 2) * M;
-  std::vector<GenInter> g(S);
-  std::vector<int> pos(S, 0), clock(S, 0);
-  for (int s = 0; s < S; ++s) g[s].init(S, 1, M, s, split, split ? s : 0);
-  int steps = 0;
-  for (bool go = true; go;) {
-    go = false;
-    for (int s = 0; s < S; ++s)
-      for (; pos[s] < n; ++pos[s], go = true) {
-        const int kind = g[s].kind, m = g[s].m;
-        int in = 0;  // the producer's end
-        if (kind == KF && s > 0) {
-          if (at(KF, s - 1, m) < 0) break;
-          in = at(KF, s - 1, m) + 1;
-        } else if (kind == KB && s < S - 1) {
-          if (at(KB, s + 1, m) < 0) break;
-          in = at(KB, s + 1, m) + durB;
-        }
-        const int t = std::max(clock[s], in);
-        if (kind != KW) at(kind, s, m) = t;
-        clock[s] = t + (kind == KB ? durB : 1);
-        steps = std::max(steps, t + 1);
-        g[s].advance(true);
-      }
-  }
-  for (int s = 0; s < S; ++s)
-    for (int m = 0; m + 2 < M; ++m) {
-      if (s < S - 1 && at(KF, s + 1, m) >= at(KF, s, m + 2)) return 0;
-      if (s > 0 && at(KB, s - 1, m) >= at(KB, s, m + 2)) return 0;
-    }
-  return steps;
-}
-
-// Whether k_static_build's schedule of the interleaved order (looped, P devices, v stages each) is
-// valid: the same lockstep rounds, counting the values alive between their producer's and their
-// reader's round.
-bool inter_schedule_fits(int P, int M, int v, int split) {
-  if (v >= 2 && M % P != 0) return true;  // no such record is valid
-  const int S = P * v, n = (split ? 3 : 2) * v * M, neg = sc_neg(sc_slots(P, v));
-  std::vector<char> done((size_t)2 * S * M, 0);
-  std::vector<GenInter> g(P);
-  std::vector<int> pos(P, 0);
-  std::vector<size_t> now;
-  for (int c = 0; c < P; ++c) g[c].init(P, v, M, c, split, split ? c : 0);
-  int live = 0, left = P;
-  for (int round = 0; left > 0; ++round) {
-    if (round >= sc_round_cap(P, M, v)) return false;
-    now.clear();
-    for (int c = 0; c < P; ++c) {
-      if (pos[c] == n) continue;
-      const int kind = g[c].kind, m = g[c].m, s = c + g[c].k * P;
-      const int ps = kind == KF ? s - 1 : kind == KB ? s + 1 : -1;
-      const bool cross = ps >= 0 && ps < S;
-      if (cross && !done[((size_t)kind * S + ps) * M + m]) continue;
-      if (cross && P > 1) --live;  // read, and nobody else's
-      if (kind != KW) now.push_back(((size_t)kind * S + s) * M + m);
-      if (P > 1 && ((kind == KF && s < S - 1) || (kind == KB && s > 0))) ++live;
-      if (++pos[c] == n) --left;
-      g[c].advance(true);
-    }
-    if (live > neg) return false;
-    for (size_t x : now) done[x] = 1;
-  }
-  return true;
 }
 
 // Geometry of the static schedules for a problem (cached in the workspace).
@@ -5555,9 +5455,9 @@ int64_t qtab_offsets(const octo_problem* p, int64_t inter[2][2], int64_t merge[2
   return off + 3;
 }
 
-int build_qtab(const octo_problem* p, Workspace& ws, int lds_max, bool wide, hipStream_t stream) {
+int build_qtab(const octo_problem* p, Workspace& ws, int lds_max, hipStream_t stream) {
   const int P = p->P, M = p->M, vmax2 = std::min(p->v_max, 2);
-  TabGeom geo[2] = {tab_geom(p, lds_max, 1, wide), tab_geom(p, lds_max, 2, wide)};
+  TabGeom geo[2] = {tab_geom(p, lds_max, 1), tab_geom(p, lds_max, 2)};
   bool same = ws.qt_valid && ws.qt_P == P && ws.qt_vmax == p->v_max && ws.qt_M == M;
   for (int v = 1; v <= vmax2; ++v)
     same = same && ws.qt_R[v - 1] == geo[v - 1].ring.R && ws.qt_lg[v - 1] == geo[v - 1].lg;
@@ -5868,16 +5768,15 @@ int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, hipStream_t str
 // stage).
 template <int VC, int X>
 int launch_sim(const octo_problem* prob, const Setup& su, const int64_t* link, const void* cands,
-               int64_t n, int64_t* ms, int64_t* bub, int64_t* peak, int64_t* comm,
-               int64_t* bound, int s_cap, int ring_want, uint64_t mask, int work,
-               hipStream_t stream, bool any_ring = false) {
+               int64_t n, int64_t* ms, int64_t* bub, int s_cap, int ring_want, uint64_t mask,
+               int work, hipStream_t stream, bool any_ring = false) {
   const Ring ring = make_ring(prob->M, ring_want);
   // table-driven launches (v <= 2) keep 3 v {w, dur} streams per lane in LDS and need tables
   // encoded for exactly this geometry
   bool tab = false;
   Plan pl{};
-  if (VC <= 2 && X != XS && X != XR && su.ws->qt_valid) {
-    const TabGeom geo = tab_geom(prob, su.di.lds_max, VC, X != XP);
+  if (VC <= 2 && X == XP && su.ws->qt_valid) {
+    const TabGeom geo = tab_geom(prob, su.di.lds_max, VC);
     constexpr int vi = VC <= 2 ? VC - 1 : 0;
     tab = geo.plan.CPW >= 1 && geo.ring.R == ring.R && su.ws->qt_R[vi] == geo.ring.R &&
           su.ws->qt_lg[vi] == geo.lg && geo.plan.G * geo.plan.CPW <= WAVE;
@@ -5885,9 +5784,7 @@ int launch_sim(const octo_problem* prob, const Setup& su, const int64_t* link, c
   }
   if (!tab) pl = fast_plan(prob, su.di.lds_max, s_cap, ring.R, 0);
   if (pl.CPW < 1) return OCTO_EUNSUPPORTED;
-  SimArgs a = make_args(prob, pl, su, link, cands, n, ms, bub, peak);
-  a.out_comm = comm;
-  a.out_bound = bound;
+  SimArgs a = make_args(prob, pl, su, link, cands, n, ms, bub);
   if (tab) a.qtab = static_cast<const uint32_t*>(su.ws->qt);
   a.bin_mask = mask, a.work = work;
   a.ring = ring.R;
@@ -6163,30 +6060,34 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
     }
   }
   if ((rc = record_mark(1, stream))) return rc;
-  // what is left takes the generated-queue kernels
+  // What is left takes the generated-queue kernels: everything with blocking transfers, and in a
+  // no-allocation call whose scratch has no room for the schedules. Where they have room, every
+  // shape within the limits has them all (checked on every shape by the tests), so that the other variants leave
+  // nothing.
   const uint64_t left1 = bins_of(1, 1, false) & ~taken;
   const uint64_t left2 = prob->v_max >= 2 ? bins_of(2, 2, false) & ~taken : 0;
   const uint64_t left8 = prob->v_max >= 3 ? bins_of(3, prob->v_max, false) & ~taken : 0;
-  if (left1 | left2 | left8) compute_inflight(prob, *su.ws);
-  if (X != XS && X != XR && (left1 | left2) &&
-      (rc = build_qtab(prob, *su.ws, su.di.lds_max, X != XP, stream)))
-    return rc;
-  if (left2 &&
-      (rc = launch_sim<2, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
-                             2 * P, 2 * P, left2, CTL_WORK + 1, stream)))
-    return rc;
-  if ((rc = record_mark(2, stream))) return rc;
-  if (left1 &&
-      (rc = launch_sim<1, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm, bd,
-                             P, P, left1, CTL_WORK + 0, stream)))
-    return rc;
-  if ((rc = record_mark(3, stream))) return rc;
-  for (int v = 3; v <= prob->v_max; ++v)
-    if ((left8 & bins_of(v, v, false)) &&
-        (rc = launch_sim<8, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm,
-                               bd, P * v, P * v, left8 & bins_of(v, v, false),
-                               CTL_WORK_V + v - 3, stream)))
+  if constexpr (X == XP || X == XR) {
+    if (left1 | left2 | left8) compute_inflight(prob, *su.ws);
+    if (X == XP && (left1 | left2) && (rc = build_qtab(prob, *su.ws, su.di.lds_max, stream)))
       return rc;
+    if (left2 && (rc = launch_sim<2, X>(prob, su, link, candidates, n, out_makespan, out_bubble,
+                                        2 * P, 2 * P, left2, CTL_WORK + 1, stream)))
+      return rc;
+    if ((rc = record_mark(2, stream))) return rc;
+    if (left1 && (rc = launch_sim<1, X>(prob, su, link, candidates, n, out_makespan, out_bubble,
+                                        P, P, left1, CTL_WORK + 0, stream)))
+      return rc;
+    if ((rc = record_mark(3, stream))) return rc;
+    for (int v = 3; v <= prob->v_max; ++v)
+      if ((left8 & bins_of(v, v, false)) &&
+          (rc = launch_sim<8, X>(prob, su, link, candidates, n, out_makespan, out_bubble, P * v,
+                                 P * v, left8 & bins_of(v, v, false), CTL_WORK_V + v - 3, stream)))
+        return rc;
+  } else {
+    if (left1 | left2 | left8) return OCTO_EUNSUPPORTED;
+    if ((rc = record_mark(2, stream)) || (rc = record_mark(3, stream))) return rc;
+  }
   if ((rc = record_mark(4, stream))) return rc;
   if constexpr (X != XR) {
     if (ap.grid > 0 && (rc = launch_afab<X>(prob, su, a, ap, n, stream)))
@@ -6195,16 +6096,15 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
     // rendezvous: GPipe queues in the generated kernels, per v class, with one slot per stage
     // (the blocking sends keep at most one value of a stage row untaken; relax_rdv)
     if (prob->v_max >= 2 &&
-        (rc = launch_sim<2, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm,
-                               bd, 2 * P, 1, bins_of(2, 2, true), CTL_WORK + 4, stream, true)))
+        (rc = launch_sim<2, X>(prob, su, link, candidates, n, out_makespan, out_bubble, 2 * P, 1,
+                               bins_of(2, 2, true), CTL_WORK + 4, stream, true)))
       return rc;
-    if ((rc = launch_sim<1, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm,
-                               bd, P, 1, bins_of(1, 1, true), CTL_WORK + 5, stream, true)))
+    if ((rc = launch_sim<1, X>(prob, su, link, candidates, n, out_makespan, out_bubble, P, 1,
+                               bins_of(1, 1, true), CTL_WORK + 5, stream, true)))
       return rc;
     for (int v = 3; v <= prob->v_max; ++v)
-      if ((rc = launch_sim<8, X>(prob, su, link, candidates, n, out_makespan, out_bubble, pk, cm,
-                                 bd, P * v, 1, bins_of(v, v, true), CTL_WORK_V + 6 + v - 3,
-                                 stream, true)))
+      if ((rc = launch_sim<8, X>(prob, su, link, candidates, n, out_makespan, out_bubble, P * v, 1,
+                                 bins_of(v, v, true), CTL_WORK_V + 6 + v - 3, stream, true)))
         return rc;
   }
   if ((rc = record_mark(5, stream))) return rc;

@@ -804,8 +804,7 @@ __device__ __forceinline__ void rounds(Gen& gen, const Chunks<VMAX>& c, const Ri
 //   wanted values | 23-25 state bits written, parity included (0 = writes nothing) |
 //   26-28 stream e = kind * v + chunk.
 // The candidate's per-stream input weight and duration (32-bit) sit in LDS, 64 lanes
-// interleaved: the pair of lane l for stream e at byte e * 512 + l * 8 (memory-model variants:
-// 16-byte records {w, dur, activation delta} at e * 1024 + l * 16).
+// interleaved: the pair of lane l for stream e at byte e * 512 + l * 8.
 // ------------------------------------------------------------------------------------------
 // Rows are RS = R + 5 slots apart: with rows of R slots (R and the interleave are powers of
 // two) the same micro-batch of every stage falls in one LDS bank, and the lanes of a group
@@ -848,15 +847,10 @@ constexpr uint32_t QT_END = 1u << 20;
 // nothing: the slot is empty or holds the backward of micro-batch m - R, which this device has
 // already run, so its time never exceeds the device clock. Each round decodes its op first, so
 // the stream read and the slot read are in flight together, and loads the entry after next at
-// its start, to be taken at the end of the next round. Rl = RS << lg. XM: streams are 16-byte records
-// {w, dur, activation delta}; mem / peak track the activation bytes held. XC: 16-byte records
-// {w, dur, output transfer time, CX flags}; cm tallies the communication nodes.
-template <int X>
+// its start, to be taken at the end of the next round. Rl = RS << lg.
 __device__ __forceinline__ void relax_tab(const uint32_t* __restrict__ qt, uint32_t row, int Rl,
                                           const uint8_t* strm, int64_t& clock, const Table40& T,
-                                          int G, uint64_t gbit, uint64_t lsb, bool& dead,
-                                          int64_t& mem, int64_t& peak, CommTally& cm,
-                                          int64_t& fs) {
+                                          int G, uint64_t gbit, uint64_t lsb, bool& dead) {
   uint32_t cur = qt[row], nxt = qt[row + 1u];
   // byte offset of the entry after next (32 bits: the load takes the table's address as its
   // scalar base and this offset as its only per-lane address)
@@ -871,8 +865,7 @@ __device__ __forceinline__ void relax_tab(const uint32_t* __restrict__ qt, uint3
     const int rdj = (int)(cur & 0x7FFFu) | T.g;
     const int wrj = rdj + __mul24((int)((cur >> 15) & 3u), Rl) - Rl;
     const uint32_t mask = (cur >> 17) & 7u, want = (cur >> 20) & 7u, state = (cur >> 23) & 7u;
-    const uint32_t soff = X != XP ? ((cur >> 16) & 0x1C00u) : ((cur >> 17) & 0xE00u);
-    const uint2 wd = *reinterpret_cast<const uint2*>(strm + soff);
+    const uint2 wd = *reinterpret_cast<const uint2*>(strm + ((cur >> 17) & 0xE00u));
     const uint32_t plo = T.lo[rdj], phi = T.hi[rdj];
     const uint64_t p = (uint64_t)plo | ((uint64_t)phi << 32);
     const bool ok = (plo & mask) == want;
@@ -883,17 +876,7 @@ __device__ __forceinline__ void relax_tab(const uint32_t* __restrict__ qt, uint3
       T.lo[wrj] = (uint32_t)(((uint64_t)fin << 3) | state);
       T.hi[wrj] = (uint8_t)((uint64_t)fin >> 29);
     }
-    if constexpr (X == XC) {
-      const uint2 cc = *reinterpret_cast<const uint2*>(strm + soff + 8);
-      cm.op(ok, (int)cc.y, tin, (int64_t)wd.x, clock, st, fin, (int64_t)cc.x);
-    }
-    if constexpr (X == XB) fs = (ok && fs < 0) ? st : fs;
     clock = ok ? fin : clock;
-    if constexpr (X == XM) {
-      const int64_t dm = *reinterpret_cast<const int64_t*>(strm + soff + 8);
-      mem = ok ? mem + dm : mem;
-      peak = mem > peak ? mem : peak;
-    }
     __asm__ volatile("" : "+v"(prev));  // the previous load is used here, after this one issued
     const uint32_t n1 = okp ? prev : nxt;
     qb += ok ? 4u : 0u;

@@ -86,6 +86,55 @@ def test_stage_rows_rule(P, v_max, M, L):
     assert done > 5 or v_max * P == 2
 
 
+SHAPES = r"""
+#include <hip/hip_runtime.h>
+#include <cstdio>
+#include <thread>
+#include "octo_schedules.hpp"
+int main() {
+  std::vector<std::thread> t;
+  int bad[8] = {}, all[8] = {};
+  for (int w = 0; w < 8; ++w)
+    t.emplace_back([&, w] {
+      int i = 0;
+      for (int v = 1; v <= 8; ++v)
+        for (int P = 1; P * v <= 64; ++P)
+          for (int M = 1; M <= 2047 && P * v * M <= 20480; ++M) {
+            if (i++ % 8 != w) continue;
+            ++all[w];
+            for (int split = 0; split < 2; ++split)
+              if (!octo::inter_schedule_fits(P, M, v, split) ||
+                  (v >= 2 && octo::stage_steps(P * v, M, split) == 0)) {
+                ++bad[w];
+                std::printf("P=%d v=%d M=%d split=%d\n", P, v, M, split);
+              }
+          }
+    });
+  for (auto& x : t) x.join();
+  int a = 0, b = 0;
+  for (int w = 0; w < 8; ++w) a += all[w], b += bad[w];
+  std::printf("%d %d\n", a, b);
+}
+"""
+
+
+def test_every_shape_has_its_schedules(tmp_path):
+    """The host checks over every shape within the limits (the finish table of 8 P v M bytes has to
+    fit the LDS): no shape needs the generated-queue kernels."""
+    import shutil
+    import subprocess
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    src = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                       "paper_2509_23722_amd", "csrc")
+    (tmp_path / "shapes.cpp").write_text(SHAPES)
+    exe = str(tmp_path / "shapes")
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-O2", "-std=c++17", "-I", src,
+                    str(tmp_path / "shapes.cpp"), "-o", exe, "-lpthread"], check=True)
+    out = subprocess.run([exe], check=True, capture_output=True, text=True).stdout.splitlines()
+    n, bad = map(int, out[-1].split())
+    assert n > 150_000 and bad == 0, out[:5]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("P,v_max,M,L", [
     (1, 2, 1, 5), (1, 8, 3, 16), (2, 2, 1, 7), (2, 3, 9, 11), (3, 2, 15, 13), (6, 4, 6, 40),

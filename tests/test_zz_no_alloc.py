@@ -1,6 +1,6 @@
 """octo_sim_batch_noalloc (every buffer in the library's static device scratch) against
-octo_sim_batch, bit for bit, through the C ABI: two calls in a row, the second smaller, and a
-batch too large for the scratch rejected before any launch."""
+octo_sim_batch, bit for bit, through the C ABI: two calls in a row, the second smaller, batches that
+leave no room for the schedules, and a batch too large for the scratch rejected before any launch."""
 import numpy as np
 import pytest
 
@@ -83,6 +83,51 @@ def test_deeper_interleaving(gpu):
     out = both(gpu, L, P, v_max, M, 2, costs, link, recs)
     assert_same(*out, "v_max = 4 batch")
     assert (recs[:, 1] >= 3).sum() > 500
+
+
+SCRATCH = 32 << 20
+
+
+def tables(P, v_max, M):
+    """Bytes of the scratch that the queue rows and tables of a shape take, at least, and of its class
+    schedules alone."""
+    pairs = 2 * P * (2 * P - 1) // 2
+    rows = 2 * (2 * P) ** 2 * ((6 * M + 7) // 8 * 8) * 2
+    qtab = 4 * (P * 5 * 3 * M + pairs * 10 * M)
+    # (entries of a row: twice the largest op count and four times the stages)
+    length = lambda v: 6 * v * M + 4 * P * v  # noqa: E731
+    cls = 4 * (P + 1) * (9 * length(2) + sum(2 * length(v) for v in range(3, v_max + 1)))
+    return rows + qtab, cls
+
+
+def spread(rng, recs, n):
+    """n records, all zeros (invalid) but for the given ones at random places."""
+    out = np.zeros((n, recs.shape[1]), np.uint8)
+    out[np.sort(rng.choice(n, len(recs), replace=False))] = recs
+    return out
+
+
+@pytest.mark.parametrize("P,v_max,M,n,good", [
+    # no room for the schedules at any size; between the lists and the schedules
+    (32, 2, 172, 700, 700), (32, 2, 172, 9000, 500), (16, 4, 256, 1_500_000, 1500),
+    (16, 2, 256, 1_600_000, 1500),
+])
+def test_no_room_for_the_schedules(gpu, P, v_max, M, n, good):
+    """The schedules do not fit beside the lists: generated queues, with the same results; then a
+    batch of the same shape that leaves them room."""
+    base, cls = tables(P, v_max, M)
+    assert base + 13 * n < SCRATCH < base + 13 * n + cls
+    rng = np.random.default_rng(P + M + n)
+    log(f"noalloc without schedules: P={P} v_max={v_max} M={M} n={n}")
+    L = P * v_max + 11
+    costs = rng.integers(1, 3_000_000, size=(L, 3)).astype(np.int64)
+    link = rng.integers(0, 800_000, size=(P, P)).astype(np.int64)
+    recs = I.random_candidates(rng, L, P, v_max, M, good, max_pert=1, pert_rate=0.02)
+    some = spread(rng, recs, n)
+    for batch in (some, recs, some):
+        out = both(gpu, L, P, v_max, M, 1, costs, link, batch)
+        assert_same(*out, f"n = {len(batch)}")
+        assert (out[0] > 0).sum() > good // 2
 
 
 def test_too_large_for_the_scratch(gpu):
