@@ -5184,11 +5184,13 @@ Plan ring_plan(const octo_problem* p, int lds_max, int s_cap, int R) {
 Plan moves_plan(const octo_problem* p, int slot_bytes) {
   Plan pl;
   pl.G = WAVE, pl.CPW = 1;
-  pl.slots = (int)align_up((size_t)p->P * p->v_max * p->M, 16);
+  // (64-bit tables as in big_plan, so that no shape that fits there is refused here)
+  pl.slots = p->P * p->v_max * p->M;
+  if (slot_bytes == 5) pl.slots = (int)align_up(pl.slots, 16);
   pl.rec_bytes = pert_off(p->P * p->v_max);
   pl.rec_stride = (int)align_up(pl.rec_bytes, 16);
   // (at the end the table's memory holds the whole record)
-  pl.table_bytes = std::max(pl.slots * slot_bytes, p->cand_stride);
+  pl.table_bytes = std::max((int)align_up((size_t)pl.slots * slot_bytes, 16), p->cand_stride);
   pl.group_bytes = pl.table_bytes + pl.rec_stride;
   pl.strm_off = pl.group_bytes;
   pl.lds_bytes = pl.strm_off + (slot_bytes == 5 ? lean_streams(p) * WAVE * 8 : 0);

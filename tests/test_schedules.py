@@ -281,6 +281,34 @@ def test_alg1_moves(P, v_max, M, L, big):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("P,M,mp", [(28, 731, 1), (28, 731, 0), (45, 454, 1)])
+def test_alg1_largest_tables(P, M, mp):
+    """Shapes whose 64-bit finish tables fill the LDS to the last few bytes (20,468 and 20,430 slots of
+    eight bytes of the 163,840)."""
+    import torch
+    from oracle import alg1 as A
+    from paper_2509_23722_amd import _lib
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(P)
+    print(f"alg1 largest tables: P={P} M={M}", flush=True)
+    L = P + 4
+    costs = rng.integers(1, 3000, size=(L, 3)).astype(np.int64)
+    link = rng.integers(0, 900, size=(P, P)).astype(np.int64)
+    recs = I.random_candidates(rng, L, P, 1, M, 3, max_pert=mp)
+    rec = torch.from_numpy(recs.copy()).cuda()
+    ms, bub, stats, _ = _lib.alg1_tune_ex(_lib.problem(L, P, 1, M, recs.shape[1], mp),
+                                          torch.from_numpy(costs).cuda(),
+                                          torch.from_numpy(link).cuda(), rec, 1, 0, 5)
+    torch.cuda.synchronize()
+    r = A.tune(R.problem(L, P, 1, M, recs.shape[1], mp), costs, link, recs, 1, nthreads=NTHREADS,
+               insert=False, random_search=False, seed=5)
+    np.testing.assert_array_equal(rec.cpu().numpy(), r[0])
+    np.testing.assert_array_equal(ms.cpu().numpy(), r[1])
+    np.testing.assert_array_equal(bub.cpu().numpy(), r[2])
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("P,M,n", [
     (1, 1, 1), (1, 5, 40), (2, 1, 200), (2, 9, 200), (3, 2, 200), (3, 8, 300), (4, 3, 300),
     (5, 11, 300), (7, 6, 300), (8, 8, 300), (8, 7, 300), (8, 40, 300), (9, 17, 300), (11, 36, 300),
