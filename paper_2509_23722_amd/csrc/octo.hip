@@ -5,10 +5,11 @@
 //   k_merge_tab ideal stage-level start times for the MERGE order (cached per (P, v_max, M)).
 //   k_classify  one thread per candidate: validate, resolve the queue generator, write the
 //               sentinel of invalid candidates, count candidates per work bin.
-//   k_plan      start position of each bin.
+//   k_plan      start position of each bin; which kernel takes the v = 1 GPipe records.
 //   k_scatter   candidate indices grouped by bin (counting sort).
 //   k_front     the four above (k_merge_tab aside) in one block, for small batches.
-//   k_pipe      the v = 1 orders and the looped interleaved ones of v = 2 as systolic arrays.
+//   k_pipe      the v = 1 orders (GPipe where k_afab is the slower kernel) and the looped
+//               interleaved ones of v = 2 as systolic arrays.
 //   k_sched     persistent waves; each takes a chunk of CPW candidates of one bin and runs them
 //               together from precomputed entries (the hot kernel): the round schedules of the
 //               structure classes, the stage rows of the MERGE orders.
@@ -5812,7 +5813,11 @@ template <int X>
 int afab_plan(const octo_problem* prob, const Setup& su, AfabPlan* pl) {
   // rows as line envelopes (plain, memory and bounds variants); the communication and
   // serialised-link variants, which need every op, keep rows of exactly 32 or 64 micro-batches
-  // in registers and other lengths in LDS
+  // in registers, where the whole sweep is one straight run of code, and other lengths in LDS. us a
+  // call on 65,536 candidates at P = 8, v <= 2, a quarter of them GPipe: serialised links 296 at
+  // M = 64, 349 in LDS at M = 48; comm 329 and 295. Register rows of up to 64 whose sweeps end with M
+  // (a test per eight ops) are slower than LDS rows at most lengths: serialised links 356 at M = 48, 334
+  // for 317 at M = 40, 207 for 185 at M = 8; comm 302 at M = 48, 279 for 266 at M = 40.
   constexpr bool LINES = X == XP || X == XM || X == XB;
   const int mmax = LINES ? -1 : prob->M == 32 ? 32 : prob->M == 64 ? 64 : 0;
   // per device: the clock, the busy time (in registers for the plain variant at P <= 8), then
@@ -5958,7 +5963,7 @@ int classify_sort(const octo_problem* prob, const Setup& su, const SimArgs& a, i
 }
 
 // The batch evaluation behind octo_sim_batch (X = XP), octo_sim_batch_mem (XM),
-// octo_sim_batch_comm (XC), octo_sim_batch_serial (XS: generated queues, not tables) and
+// octo_sim_batch_comm (XC), octo_sim_batch_serial (XS), octo_sim_batch_rdv (XR) and
 // octo_sim_batch_bounds (XB). The caller has checked the arguments and holds g_mu.
 template <int X>
 int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const int64_t* layer_mem,
@@ -6007,13 +6012,15 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   // at 32,768 records, 48 / 45 at 65,536, 56 / 65 at 131,072; P = 16, M = 32: 184 / 95 at 131,072.
   // With serialised links k_afab runs every op, and k_pipe is the faster one up to 524,288 records
   // (P = 8: 232 / 217 at M = 64, 6,161 / 488 at M = 200). Beside rows of v >= 2, all of which k_afab
-  // runs at once: 131,072 records at P = 8, M = 64, half of them v = 1: 80 / 99.
+  // runs at once: 131,072 records at P = 8, M = 64, half of them v = 1: 80 / 99; but at P > 8 one v = 1
+  // candidate that passes the envelopes costs a pass of the 64-bit kernel (P = 16, M = 32, 8,192 records
+  // of every policy: 219 / 184; all GPipe, where others pass them anyway: 167 / 172).
   AfabPlan ap{};
   if constexpr (X != XR) {
     const int most = X == XS || M <= 2 * P ? INT32_MAX : ((P <= 8 ? 5 : 20) << 20) / (M + P);
     if ((!a.pipe || prob->v_max >= 2 || n > most) && (rc = afab_plan<X>(prob, su, &ap))) return rc;
     a.gpipe.most = a.pipe ? most : 0;
-    a.gpipe.room = (ap.grid - prob->v_max + 1) * ap.lanes;
+    a.gpipe.room = P <= 8 || X == XS ? (ap.grid - prob->v_max + 1) * ap.lanes : 0;
   }
   if (front) {
     char* base = static_cast<char*>(su.ws->base);
@@ -6028,9 +6035,10 @@ int sim_batch_run(const octo_problem* prob, const int64_t* layer_costs, const in
   } else if ((rc = classify_sort(prob, su, a, n, stream))) {
     return rc;
   }
-  // generated INTER / MERGE queues, one launch per v with finish tables sized for it (ring
-  // rows of the next power of two >= P v where the in-flight bound allows): v = 2, v = 1, then
-  // v = 3..8; then AFAB queues; then materialised queues (perturbations, 64-bit redo).
+  // systolic arrays and schedules; then the INTER / MERGE bins that they leave, one launch per v with
+  // finish tables sized for it (ring rows of the next power of two >= P v where the in-flight bound
+  // allows): v = 2, v = 1, then v = 3..8; then AFAB queues; then materialised queues (perturbations,
+  // 64-bit redo).
   if ((rc = record_mark(0, stream))) return rc;
   uint64_t taken = 0;  // bins that the schedules and k_pipe cover
   if constexpr (X != XR) {
