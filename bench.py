@@ -28,8 +28,9 @@ sys.path.insert(0, ROOT)
 # MI355X (gfx950): 256 CUs x 4 SIMD x 16 lanes at 2.4 GHz -> 32-bit integer VALU lane-ops/s.
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 HBM_PEAK_GBS = 8000.0
-# simulation kernels, in launch order, between the library's measurement boundaries
-SIM_KERNELS = ["k_sched", "k_sim<2>", "k_sim<1>", "k_sim<8>", "k_afab", "k_sim_mat<2>"]
+# simulation kernels, in launch order, between the library's measurement boundaries (the first interval
+# holds k_pipe and the launches of k_sched)
+SIM_KERNELS = ["k_pipe + k_sched", "k_sim<2>", "k_sim<1>", "k_sim<8>", "k_afab", "k_sim_mat<2>"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_nemotron-h-like-52L-P8-M64.json")
 
 
@@ -55,9 +56,9 @@ def algorithmic_work(recs, P, M):
 
 
 def scheduled_mask(recs):
-    """Candidates that the library evaluates from precomputed entries (k_sched): no moves, not
-    AFAB (the structure classes' round schedules and the MERGE orders' stage rows together cover
-    every generated queue)."""
+    """Candidates that the library evaluates as systolic arrays (k_pipe) or from precomputed entries
+    (k_sched): no moves, not AFAB (the structure classes' round schedules and the MERGE orders'
+    stage rows together cover every generated queue)."""
     return (recs[:, 0] != 0) & (recs[:, 2] == 0)
 
 

@@ -409,14 +409,15 @@ int octo_alg1_tune_ex(const octo_problem* prob, const int64_t* layer_costs, cons
 /*
  * Measurement hook. events[0..n_events-1] are hipEvent_t handles (n_events <= 8; entries may be
  * NULL). Each later octo_sim_batch call records them on its stream at fixed boundaries around
- * its simulation kernels: events[0] before the scheduled kernels (generated queues run from
- * precomputed entries: the structure classes and the MERGE orders of every v), [1] after them,
- * [2] after the v = 2 generated-queue kernel (1F1B, I1F1B, ZB queues that no schedule covers;
- * every one with rendezvous transfers), [3] after the v = 1 kernel, [4] after the v = 3..8
- * kernel, [5] after the AFAB kernel (every v), [6] after the materialised-queue kernel (a kernel
- * that a problem does not need is skipped, so its interval is empty). A caller can time each
- * kernel alone on the stream
- * it runs on. octo_profile_events(NULL, 0) turns it off. Process-wide.
+ * its simulation kernels: events[0] before the scheduled kernels (the orders that run as systolic
+ * arrays, among them the v = 1 AFAB records of batches in which that is the faster way, and those
+ * that run from precomputed entries: the structure classes and the MERGE orders of every v), [1]
+ * after them, [2] after the v = 2 generated-queue kernel (1F1B, I1F1B, ZB queues with rendezvous
+ * transfers, or without schedules in a no-allocation call), [3] after the v = 1 kernel, [4] after
+ * the v = 3..8 kernel, [5] after the AFAB kernel (the other AFAB records), [6] after the
+ * materialised-queue kernel (a kernel that a problem does not need is skipped, so its interval is
+ * empty). A caller can time each interval alone on the stream it runs on.
+ * octo_profile_events(NULL, 0) turns it off. Process-wide.
  */
 int octo_profile_events(void* const* events, int32_t n_events);
 
