@@ -5761,12 +5761,13 @@ int launch_pipe(const SimArgs& base, const Setup& su, int64_t n, hipStream_t str
   if (rc) return rc;
   // Waves for the batch's chunks and a last one for each further bin (a wave with two chunks would take
   // twice as long as the others). Blocks of several waves: one per chunk up to a block per CU, then
-  // as many on every CU; the blocks' first waves take the chunks first. us a call on looped v = 2
+  // as many on every CU (one block more than that costs its CU more than a second chunk its wave: 16,384
+  // candidates at P = 16, M = 64 87.0 us for 82.2); the blocks' first waves take the chunks first. us a call on looped v = 2
   // candidates at P = 8, M = 64, with blocks for the chunks alone / now: 79.7 / 63.3 on 4,096, 86.5 / 80.9
   // on 34,552.
   const int64_t chunks = (n + a.CPW - 1) / a.CPW, some = chunks + 4, cus = su.di.cus;
   const int64_t per_cu = (chunks + waves * cus - 1) / (waves * cus);
-  const int64_t need = std::max((some + waves - 1) / waves, std::min(some, per_cu * cus));
+  const int64_t need = std::min(some, per_cu * cus);
   grid = (int)std::min<int64_t>(grid, need);
   hipLaunchKernelGGL((k_pipe<X, TWO>), dim3(grid), dim3(waves * WAVE), lds, stream, a);
   return launch_ok();
